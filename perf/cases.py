@@ -344,3 +344,81 @@ def tolerance(case):
     # off (2^-7 of the value at most).  Predicted queries: seen 1e-4, the activations enter the
     # matrix cores as two bf16 numbers; projected keys: seen 1e-5.
     return {"rel": 5e-4 if case["kind"] == "predict" else 5e-5, "max": 0.02, "differ": 0.001}
+
+
+# ---- the same numbers in 64 bits --------------------------------------------------------------------
+def _exact_scores(q_imp, Kimp, n):
+    """One batch element: [Hq, d'] queries, [Hkv, N, d'] projected keys -> [Hq, n] and the size of the
+    sums' terms."""
+    hq, hkv = q_imp.shape[0], Kimp.shape[0]
+    q = q_imp.double().view(hkv, hq // hkv, -1)
+    k = Kimp[:, :n].double()
+    return torch.matmul(q, k.transpose(1, 2)).view(hq, n), torch.matmul(q.abs(), k.abs().transpose(1, 2)).view(hq, n)
+
+
+def _exact_lists(scores, size, c):
+    """[heads, N] scores -> the policy's lists [heads, count], or None where two scores at the budget's
+    edge are closer than 32-bit sums resolve (either list is right then)."""
+    n = scores.shape[1]
+    lo = min(c["sink"], n)
+    hi = max(lo, n - c["window"])
+    kk = min(c["k"], hi - lo)
+    pick = torch.topk(scores[:, lo:hi], min(kk + 1, hi - lo), dim=1)
+    if kk < hi - lo:
+        edge = lo + pick.indices[:, kk - 1:kk + 1]
+        if bool((pick.values[:, kk - 1] - pick.values[:, kk] < 1e-6 * size.gather(1, edge).amax(1)).any()):
+            return None
+    keep = torch.zeros_like(scores, dtype=torch.bool)
+    keep[:, :lo], keep[:, hi:] = True, True
+    keep[:, lo:hi].scatter_(1, pick.indices[:, :kk], True)
+    return keep.nonzero()[:, 1].view(scores.shape[0], -1)
+
+
+def _exact_attention(q, K, V, lists, sm):
+    """One batch element: [Hq, D] queries, [Hkv, N, D] rows, [Hq, count] lists."""
+    hq, g = q.shape[0], q.shape[0] // K.shape[0]
+    out, lse = [], []
+    for h in range(hq):
+        k, v = K[h // g][lists[h]].double(), V[h // g][lists[h]].double()
+        x = torch.mv(k, q[h].double()) * sm
+        lse.append(torch.logsumexp(x, 0))
+        out.append(torch.mv(v.t().contiguous(), torch.softmax(x, 0)))
+    return torch.stack(out), torch.stack(lse)
+
+
+def _exact_decode(c, s):
+    scores, outs, lses = [], [], []
+    for b in range(c["B"]):
+        sc, size = _exact_scores(s["q_imp"][b], s["Kimp"][b], c["N"])
+        lists = _exact_lists(sc, size, c) if outs is not None else None
+        full = torch.zeros(s["scores"].shape[1:], dtype=torch.float64, device=DEV)  # (the padding of a row stays 0)
+        full[:, :c["N"]] = sc
+        scores.append(full)
+        if lists is None:
+            outs = None
+            continue
+        o, l = _exact_attention(s["q"][b], s["K"][b], s["V"][b], lists.expand(c["Hq"], -1), s["sm"])
+        outs.append(o)
+        lses.append(l)
+    return torch.stack(scores), None, None, None if outs is None else torch.stack(outs), None if outs is None else torch.stack(lses)
+
+
+def exact(case, seed):
+    c, s = case, prepare(case, seed)
+    if c["kind"] in ("step", "headless"):
+        return _exact_decode(c, s)
+    if c["kind"] == "project":
+        return torch.stack([torch.matmul(s["K"][b].double(), s["W"].double()) for b in range(c["B"])])
+    if c["kind"] == "predict":
+        d = {name: s[name].double() for name in ("h", "gamma", "beta", "W1", "b1", "W2", "b2")}
+        x = torch.nn.functional.layer_norm(d["h"], (c["E"],), d["gamma"], d["beta"], 1e-5)
+        z = torch.nn.functional.gelu(x @ d["W1"].t() + d["b1"])
+        y = z @ d["W2"].t() + d["b2"]
+        return y.view(c["B"], c["G"], c["Hq"], c["Dimp"]).transpose(0, 1).contiguous(), z
+    # The loops' lists hang on scores of keys that were rounded to their storage type on the way, so
+    # one value either side of a rounding boundary changes what follows; their projected rows do not.
+    dec = s["dec"]
+    first, last = (c["N"] - c["P"], c["N"]) if c["kind"] == "interval" else (c["N"], c["N"] + c["ring"])
+    rows = torch.matmul(dec.K[:, :, first:last].double(), dec.W.double())
+    outs = [None] * (c["P"] if c["kind"] == "interval" else c["P"] + 1)
+    return (outs, None, None, None, None, None, None, rows) if c["kind"] == "interval" else (outs, None, None, None, None, None, None, None, rows)
