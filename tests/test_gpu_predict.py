@@ -53,6 +53,42 @@ def test_predict_queries(oracle, dtype, B, E, hidden, G, Hq, Dimp):
         assert np.abs(got - rq).max() <= 2e-4 * max(1.0, np.abs(rq).max())
 
 
+@pytest.mark.parametrize("dtype,B,E,hidden,G,Hq,Dimp", [
+    (torch.bfloat16, 1, 4096, 512, 1, 8, 16),    # eight slices, summed by the output kernel
+    (torch.bfloat16, 2, 4096, 264, 1, 3, 8),     # just past what it sums itself; ragged tiles on both sides
+    (torch.bfloat16, 3, 8192, 2048, 1, 4, 8),    # largest sizes: 16 waves, several chunks of steps
+    (torch.bfloat16, 17, 1000, 40, 1, 5, 8),     # a second M tile with one row; pieces past E in the last step
+    (torch.bfloat16, 33, 264, 520, 2, 4, 16),    # more hidden units than inputs: one slice
+    (torch.float32, 1, 5120, 512, 1, 8, 16),
+    (torch.float32, 7, 3000, 520, 2, 4, 16),     # ragged last step and slice
+    (torch.float32, 33, 64, 8, 3, 2, 8),         # two workgroup groups along the batch, sizes below one step
+])
+def test_predict_split_layers(oracle, dtype, B, E, hidden, G, Hq, Dimp):
+    """Edges of the tiles, steps and slices; z starts 4 bytes off a 16-byte boundary.  Bars of
+    test_predict_queries; LN(h) is an fp32 evaluation of a few operations on values of size <= 10."""
+    print(f"[case] predictor split dtype={dtype} B={B} E={E} hidden={hidden} G={G} Hq={Hq} Dimp={Dimp}", flush=True)
+    p = make(B, E, hidden, G, Hq, Dimp, dtype, 24)
+    z = torch.full((B * hidden + 1,), float("nan"), dtype=torch.float32, device=DEV)[1:].view(B, hidden)
+    q_imp = torch.zeros((G, B, Hq, Dimp), dtype=dtype, device=DEV)
+    xln = torch.full((B, E), float("nan"), dtype=torch.float32, device=DEV)
+    tb.tb_predict_queries(p["h"], p["gamma"], p["beta"], p["W1"], p["b1"], p["W2"], p["b2"], G, Hq, Dimp, z, xln, q_imp)
+    torch.cuda.synchronize()
+    dn = dtype_name(p["h"])
+    rq, rz = oracle.predict_queries(*(np_of(p[k]) for k in ("h", "gamma", "beta", "W1", "b1", "W2", "b2")), G, Hq, Dimp, dn)
+    # fp32 sums of E products, seen 2e-7 relative to the largest: an eighth of the general bar
+    assert np.abs(np_of(z) - rz).max() <= 2.5e-5 * max(1.0, np.abs(rz).max())
+    got = np_of(q_imp)
+    if dn == "bf16":
+        g64, r64 = oracle.bf16_to_f64(got), oracle.bf16_to_f64(rq)
+        assert np.all(np.abs(g64 - r64) <= 2.0 ** -7 * np.abs(r64) + 1e-4)
+        assert np.mean(got == rq) > 0.97
+    else:
+        assert np.abs(got - rq).max() <= 2.5e-5 * max(1.0, np.abs(rq).max())
+    if B > 2:
+        ln = torch.nn.functional.layer_norm(p["h"].double().cpu(), (E,), p["gamma"].double().cpu(), p["beta"].double().cpu(), 1e-5)
+        assert (xln.double().cpu() - ln).abs().max() <= 1e-5
+
+
 def test_predicted_slot_feeds_scoring(oracle):
     """Slot s of the predictor's output is laid out as tb_score's q_imp."""
     print("[case] predictor slot -> tb_score", flush=True)
