@@ -25,8 +25,9 @@
 //   select_kernel                      one 1024-thread workgroup per row, no global scratch;
 //   prefilter_kernel + stage_b_kernel  long rows: the row is cut into pieces, one workgroup per
 //                                      piece keeps the keys at or above the lower end of a bracket
-//                                      that every piece derives from the same sample of the row,
-//                                      and a second kernel selects among the kept keys.
+//                                      that every piece derives from the same sample of the row
+//                                      (or, for a small budget of a very long row, finds ready from
+//                                      bracket_kernel), and a second kernel selects among the kept keys.
 #include "tb_device.h"
 #include "tb_internal.h"
 
@@ -848,22 +849,83 @@ __global__ __launch_bounds__(kSelThreads, (NT >= 1 && NT <= 4) ? 8 : 4) void sel
   }
 }
 
-// ---- selection of a row by pieces, stage A.  The piece's scores are in registers (NT tiles per
-// wave).  Every piece of a row takes the same sample of the row's candidates (one 128-bit load
-// per thread at positions spread evenly over [lo, hi)) and so arrives at the same bracket as its
-// siblings.  The scores whose keys are at or above the bracket's lower end are kept, in position
-// order: collected per wave in LDS, then copied out behind the entries of the waves before.
-constexpr int kPieceCapPerTile = 56;  // a wave's region holds 22% of its span: several times what a piece keeps
-template <int W, int NT>
-struct PieceLds {
+template <int W>
+struct SampleLds {
   uint32_t hist[kHistBins];
   __attribute__((aligned(16))) Found found;
   uint32_t part[W], wsum[W];
+};
+
+// The sample of a row: four adjacent scores at each of THREADS * M positions spread evenly over the
+// candidates.
+template <int THREADS, int M>
+__device__ inline int64_t sample_pos(const SelectArgs& a, int i) {
+  const int64_t place = static_cast<int64_t>(i) * THREADS + threadIdx.x;
+  return (a.lo + place * (a.hi - a.lo) / (THREADS * M)) & ~int64_t{3};
+}
+template <int THREADS, int M>
+__device__ inline void sample_load(const SelectArgs& a, const float* row, float4 (&raw)[M]) {
+  const int64_t last4 = (a.N - 1) & ~int64_t{3};
+#pragma unroll
+  for (int i = 0; i < M; ++i) raw[i] = load_scores4(row, last4, sample_pos<THREADS, M>(a, i));
+}
+// The bracket of the sample, by the whole workgroup (starts with a barrier, ends with one).
+template <int W, int M, typename Lds>
+__device__ __forceinline__ void bracket_of_sample(const SelectArgs& a, const float4 (&raw)[M], int64_t span, Lds& sl, uint32_t& b_lo,
+                                                  uint32_t& b_hi, uint32_t& t_lo) {
+  constexpr int kThreads = W * kWave;
+  const int tid = threadIdx.x;
+  uint4* z = reinterpret_cast<uint4*>(sl.hist);
+  for (int i = tid; i < kHistBins / 4; i += kThreads) z[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (tid < kFoundWords) reinterpret_cast<uint32_t*>(&sl.found)[tid] = 0;
+  __syncthreads();
+  uint32_t n_valid = 0;
+#pragma unroll
+  for (int i = 0; i < M; ++i) {
+    uint32_t sk[4];
+    keys_of4(raw[i], a.lo, a.hi, sample_pos<kThreads, M>(a, i), sk);  // (the four may straddle an end of the candidate range)
+    // all four enter the histogram: a narrower bracket means fewer kept keys to store and to
+    // select among
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (sk[e]) {
+        atomicAdd(&sl.hist[sk[e] >> kTopShift], 1u);
+        ++n_valid;
+      }
+    }
+  }
+  sample_bracket<W>(sl.hist, n_valid, sl.part, sl.wsum, &sl.found, a.kk, span, b_lo, b_hi, &t_lo);
+}
+
+// The bracket of a row from one larger sample, taken once (one workgroup per row): b_lo, b_hi and the
+// cut go to the header of the row's first piece.  Bound by its chain of phases (7.6 us for 32 rows).
+__global__ __launch_bounds__(kSelThreads) void bracket_kernel(SelectArgs a) {
+  constexpr int M = kRowSample / (4 * kSelThreads);
+  __shared__ SampleLds<kSelWaves> sl;
+  const int u = blockIdx.x, tid = threadIdx.x;
+  float4 raw[M];
+  sample_load<kSelThreads, M>(a, a.scores + static_cast<int64_t>(u) * a.score_stride, raw);
+  __builtin_amdgcn_sched_barrier(0);
+  uint32_t b_lo, b_hi, t_lo;
+  bracket_of_sample<kSelWaves, M>(a, raw, a.hi - a.lo, sl, b_lo, b_hi, t_lo);
+  if (tid < 3) a.piece_hdr[static_cast<int64_t>(u) * a.pieces * 4 + 1 + tid] = tid == 0 ? b_lo : (tid == 1 ? b_hi : t_lo);
+}
+
+// ---- selection of a row by pieces, stage A.  The piece's scores are in registers (NT tiles per
+// wave).  Every piece of a row takes the same sample of the row's candidates (one 128-bit load
+// per thread at positions spread evenly over [lo, hi)) and so arrives at the same bracket as its
+// siblings (OWN), or reads the bracket that bracket_kernel has left in the header of the row's first
+// piece.  The scores whose keys are at or above the bracket's lower end are kept, in position
+// order: collected per wave in LDS, then copied out behind the entries of the waves before.
+constexpr int kPieceCapPerTile = 56;  // a wave's region holds 22% of its span: several times what a piece keeps
+template <int W, int NT, bool OWN>
+struct PieceLds {
+  SampleLds<OWN ? W : 1> sample[OWN ? 1 : 0];
   RegionLds<W, NT, kPieceCapPerTile> reg;
 };
 
-template <int W, int NT>
-__device__ __forceinline__ void piece_body(const SelectArgs& a, const int u, const int c, PieceLds<W, NT>& pl) {
+template <int W, int NT, bool OWN>
+__device__ __forceinline__ void piece_body(const SelectArgs& a, const int u, const int c, PieceLds<W, NT, OWN>& pl) {
   constexpr int kThreads = W * kWave;
   constexpr int kCap = RegionLds<W, NT, kPieceCapPerTile>::kCap;
   const int tid = threadIdx.x;
@@ -876,42 +938,28 @@ __device__ __forceinline__ void piece_body(const SelectArgs& a, const int u, con
   const float* s = row + base;
   const int last4 = n_c > 0 ? static_cast<int>((n_c - 1) & ~int64_t{3}) : 0;
   const int wspan0 = wave * NT * kWaveTile;  // the wave's span, as positions inside the piece
-  // the sample of the whole row: four adjacent scores at each of `kThreads` positions spread
-  // evenly over the candidates
-  const int64_t span = a.hi - a.lo;
-  const int64_t sp = (a.lo + (tid * span) / kThreads) & ~int64_t{3};
-  const int64_t row_last4 = (a.N - 1) & ~int64_t{3};
+  int32_t* out_idx = a.cand_idx + (static_cast<int64_t>(u) * a.pieces + c) * a.cap;
+  uint32_t* out_key = a.cand_key + (static_cast<int64_t>(u) * a.pieces + c) * a.cap;
+  uint32_t* row_hdr = a.piece_hdr + static_cast<int64_t>(u) * a.pieces * 4;
+  uint32_t* hdr = row_hdr + c * 4;
   float4 raw[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     const int n0 = wspan0 + j * kWaveTile + lane * 4;
     raw[j] = *reinterpret_cast<const float4*>(s + (n0 < last4 ? n0 : last4));  // (past the piece's end: excluded by position below)
   }
-  const float4 sraw = load_scores4(row, row_last4, sp);
-  __builtin_amdgcn_sched_barrier(0);
-
-  {
-    uint4* z = reinterpret_cast<uint4*>(pl.hist);
-    for (int i = tid; i < kHistBins / 4; i += kThreads) z[i] = make_uint4(0u, 0u, 0u, 0u);
+  uint32_t t_lo;  // keys from here up are kept (inside the bracket's bottom bin)
+  if constexpr (OWN) {
+    float4 sraw[1];
+    const int64_t span = a.hi - a.lo;
+    sample_load<kThreads, 1>(a, row, sraw);
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t b_lo, b_hi;
+    bracket_of_sample<W, 1>(a, sraw, span, pl.sample[0], b_lo, b_hi, t_lo);
+    if (tid < 2) hdr[1 + tid] = tid == 0 ? b_lo : b_hi;
+  } else {
+    t_lo = row_hdr[3];
   }
-  if (tid < kFoundWords) reinterpret_cast<uint32_t*>(&pl.found)[tid] = 0;
-  __syncthreads();
-  uint32_t n_valid = 0;
-  {
-    uint32_t sk[4];
-    keys_of4(sraw, a.lo, a.hi, sp, sk);  // (the four may straddle an end of the candidate range)
-    // all four enter the histogram: a narrower bracket means fewer kept keys to store and to
-    // select among
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (sk[i]) {
-        atomicAdd(&pl.hist[sk[i] >> kTopShift], 1u);
-        ++n_valid;
-      }
-    }
-  }
-  uint32_t b_lo, b_hi, t_lo;  // t_lo: keys from here up are kept (inside the bracket's bottom bin)
-  sample_bracket<W>(pl.hist, n_valid, pl.part, pl.wsum, &pl.found, a.kk, span, b_lo, b_hi, &t_lo);
   // a score is kept when it is at least f_lo; a lower end at or below the key of -inf keeps
   // every candidate (NaN, whose key is that of -inf, included)
   const bool all = t_lo <= kKeyOfMinusInf;
@@ -927,11 +975,8 @@ __device__ __forceinline__ void piece_body(const SelectArgs& a, const int u, con
   const uint32_t wave_base = wave_entries_scan<W>(pl.reg.cnt, total);
   const int l16 = lane & 15;
   const bool overflowed = __ballot(l16 < W && pl.reg.cnt[l16 < W ? l16 : 0] > static_cast<uint32_t>(kCap)) != 0ull;
-  int32_t* out_idx = a.cand_idx + (static_cast<int64_t>(u) * a.pieces + c) * a.cap;
-  uint32_t* out_key = a.cand_key + (static_cast<int64_t>(u) * a.pieces + c) * a.cap;
-  uint32_t* hdr = a.piece_hdr + (static_cast<int64_t>(u) * a.pieces + c) * 4;
+  if (tid == 0) hdr[0] = total;
   if (!overflowed) {
-    if (tid < 3) hdr[tid] = tid == 0 ? total : (tid == 1 ? b_lo : b_hi);
     const uint32_t* lkey = pl.reg.key + wave * kCap;
     const int32_t* lpos = pl.reg.pos + wave * kCap;
     for (uint32_t e = lane; e < run; e += kWave) {
@@ -974,7 +1019,6 @@ __device__ __forceinline__ void piece_body(const SelectArgs& a, const int u, con
     }
     at += popc64(m[0]) + popc64(m[1]) + popc64(m[2]) + popc64(m[3]);
   }
-  if (tid < 3) hdr[tid] = tid == 0 ? total : (tid == 1 ? b_lo : b_hi);
 }
 
 // ---- stage B.  One workgroup per row: builds the table of the pieces' kept keys and selects
@@ -1019,28 +1063,28 @@ __global__ __launch_bounds__(kSelThreads, 4) void stage_b_kernel(SelectArgs a) {
 // Stage A.  All pieces of a row run on one XCD (workgroups go to the eight XCDs round-robin by
 // their linear index), close together in time: the sample of the row that every piece takes is
 // then served by that XCD's L2, out of the lines that the row's pieces fetch anyway.
-template <int W, int NT>
+template <int W, int NT, bool OWN>
 __global__ __launch_bounds__(W * kWave) void prefilter_kernel(SelectArgs a) {
-  __shared__ PieceLds<W, NT> sl;
+  __shared__ PieceLds<W, NT, OWN> sl;
   const int64_t xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int64_t u = (slot / a.pieces) * 8 + xcd;
   if (u >= a.units) return;  // (the launch is padded to a multiple of eight rows)
   // the pieces of a row from its end backwards: with scores that favour recent positions the
   // last pieces keep the most and take the longest, so they should not be the last to start
-  piece_body<W, NT>(a, static_cast<int>(u), a.pieces - 1 - static_cast<int>(slot % a.pieces), sl);
+  piece_body<W, NT, OWN>(a, static_cast<int>(u), a.pieces - 1 - static_cast<int>(slot % a.pieces), sl);
 }
 
-template <int W>
+template <int W, bool OWN>
 tb_status launch_prefilter_w(const SelectArgs& a, int tiles, dim3 grid, hipStream_t st) {
   const dim3 block(W * kWave);
   if (tiles <= 2)
-    hipLaunchKernelGGL((prefilter_kernel<W, 2>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((prefilter_kernel<W, 2, OWN>), grid, block, 0, st, a);
   else if (tiles <= 4)
-    hipLaunchKernelGGL((prefilter_kernel<W, 4>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((prefilter_kernel<W, 4, OWN>), grid, block, 0, st, a);
   else if (tiles <= 8)
-    hipLaunchKernelGGL((prefilter_kernel<W, 8>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((prefilter_kernel<W, 8, OWN>), grid, block, 0, st, a);
   else
-    hipLaunchKernelGGL((prefilter_kernel<W, 16>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((prefilter_kernel<W, 16, OWN>), grid, block, 0, st, a);
   return hip_status(hipGetLastError());
 }
 
@@ -1134,13 +1178,16 @@ tb_status launch_select(const SelectLaunch& L, hipStream_t st) {
   a.piece_hdr = a.cand_key + L.units * per_unit;
   a.units = L.units;
   const dim3 grid(static_cast<unsigned>((L.units + 7) / 8 * 8 * plan.pieces));
+  const bool own = !plan.row_sample;
+  if (!own) {
+    hipLaunchKernelGGL(bracket_kernel, dim3(static_cast<unsigned>(L.units)), dim3(kSelThreads), 0, st, a);
+    if (hipGetLastError() != hipSuccess) return TB_ERR_HIP;
+  }
   tb_status rc;
   if (plan.piece_waves == 4)
-    rc = launch_prefilter_w<4>(a, plan.piece_tiles, grid, st);
-  else if (plan.piece_waves == 8)
-    rc = launch_prefilter_w<8>(a, plan.piece_tiles, grid, st);
+    rc = own ? launch_prefilter_w<4, true>(a, plan.piece_tiles, grid, st) : launch_prefilter_w<4, false>(a, plan.piece_tiles, grid, st);
   else
-    rc = launch_prefilter_w<16>(a, plan.piece_tiles, grid, st);
+    rc = own ? launch_prefilter_w<8, true>(a, plan.piece_tiles, grid, st) : launch_prefilter_w<8, false>(a, plan.piece_tiles, grid, st);
   if (rc != TB_OK) return rc;
   return launch_stage_b(L, plan, st);
 }

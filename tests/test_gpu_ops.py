@@ -213,6 +213,34 @@ def test_select_pieces_row_count_not_a_multiple_of_eight(oracle):
         check_select(oracle, scores, N, 2000, 64, 100)
 
 
+@pytest.mark.parametrize("N,rows,k,sink,window", [((1 << 20) - 3, 2, 8192, 0, 0), (1 << 20, 1, 6000, 128, 256), (900001, 3, 8000, 4, 0)])
+def test_select_pieces_row_sampled_once(oracle, N, rows, k, sink, window):
+    """A small budget of a very long row: the bracket comes from a kernel of its own.  Plain scores,
+    a ramp (the last pieces keep nearly all of their scores), few distinct values with NaN and -inf
+    among them, and scores that are large only where the sample looks (too little is kept: the whole
+    row is selected on) or only where it does not (too much is kept)."""
+    say(f"select by pieces, row sampled once, N={N} rows={rows}")
+    stride = (N + 3) // 4 * 4
+    scores = randn((1, rows, stride), torch.float32, 88)
+    check_select(oracle, scores, N, k, sink, window)
+    ramp = (scores + torch.arange(stride, dtype=torch.float32, device=DEV) * 1e-4).contiguous()
+    check_select(oracle, ramp, N, k, sink, window)
+    few = torch.round(scores * 4) / 4
+    few[:, :, ::7] = float("nan")
+    few[:, :, 3::7] = -float("inf")
+    check_select(oracle, few, N, k, sink, window)
+    lo, hi = sink, N - window
+    places = (lo + torch.arange(2048, device=DEV) * (hi - lo) // 2048) // 4 * 4
+    seen = scores.clone()
+    for c in range(4):
+        seen[:, :, (places + c).clamp(max=N - 1)] += 50.0
+    check_select(oracle, seen, N, k, sink, window)
+    unseen = scores.clone() + 50.0
+    for c in range(4):
+        unseen[:, :, (places + c).clamp(max=N - 1)] -= 50.0
+    check_select(oracle, unseen, N, k, sink, window)
+
+
 def test_select_pieces_many_rows(oracle):
     """Enough long rows that the pieces take their widest form (512 threads, 16384 scores)."""
     say("select by pieces, 128 rows")
