@@ -8,13 +8,10 @@
 namespace tb {
 
 constexpr int64_t kAttnTargetWgs = 512;   // workgroups a launch of the split attention aims at
+constexpr int64_t kAttnGroupTargetWgs = 256;
 constexpr int64_t kAttnMinTiles = 2;      // a workgroup is worth its hand-over from two tiles per wave on
 
-AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool grouped) {
-  // Aim for two workgroups per compute unit (256 CUs): the gathers of the whole chip are in
-  // flight together, and fewer, longer workgroups mean fewer partials to hand over (measured
-  // best across the five configurations; 1024 was 1 µs slower on the smallest and 2 µs on the
-  // largest).  A workgroup takes whole wave tiles.
+static AttnPlan split_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, int granule, int64_t target_wgs, int64_t min_tiles) {
   AttnPlan p;
   if (max_rows <= 0 || units <= 0) {
     p.rows_per_wg = tile_rows_per_wg;
@@ -22,16 +19,13 @@ AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool g
     p.max_split = 1;
     return p;
   }
-  const int64_t target_wgs = kAttnTargetWgs;  // (the same for one workgroup per KV group)
   int64_t want = (target_wgs + units - 1) / units;
-  (void)grouped;
-  const int64_t max_split = max_rows / (kAttnMinTiles * tile_rows_per_wg);
+  const int64_t max_split = max_rows / (min_tiles * tile_rows_per_wg);
   if (want > max_split) want = max_split;
   if (want < 1) want = 1;
   // equal shares, rounded up to whole wave instructions (4 rows x 4 waves for 256-byte rows) rather
   // than whole tiles: a ragged last tile per wave costs less than a last workgroup round that
   // only some compute units take part in
-  const int64_t granule = tile_rows_per_wg / kAttnLoadsPerTile;
   int64_t rows = (max_rows + want - 1) / want;
   rows = (rows + granule - 1) / granule * granule;
   p.rows_per_wg = static_cast<int>(rows);
@@ -40,13 +34,33 @@ AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool g
   return p;
 }
 
+AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg) {
+  // Aim for two workgroups per compute unit (256 CUs): the gathers of the whole chip are in
+  // flight together, and fewer, longer workgroups mean fewer partials to hand over (measured
+  // best across the five configurations; 1024 was 1 µs slower on the smallest and 2 µs on the
+  // largest).  A workgroup takes whole wave tiles.
+  return split_plan(units, max_rows, tile_rows_per_wg, tile_rows_per_wg / kAttnLoadsPerTile, kAttnTargetWgs, kAttnMinTiles);
+}
+
+AttnPlan attn_group_plan(const tb_cache_desc* d, int64_t max_rows) {
+  const int64_t groups = static_cast<int64_t>(d->B) * d->Hkv;
+  if (!attn_group_mfma(d)) return attn_plan(groups, max_rows, attn_tile_rows_per_wg(d->dtype, d->D));
+  // on the matrix cores: 8 waves of 32 rows a step, one such workgroup per compute unit (the same
+  // rows in flight as two of 4 waves, half the partials to combine)
+  return split_plan(groups, max_rows, 32 * kAttnGroupWaves, 4 * kAttnGroupWaves, kAttnGroupTargetWgs, 1);
+}
+
 // A shared list with grouped queries: one workgroup per (KV group, split) loads every row once
 // for all heads of the group.  That pays when there are enough KV groups to fill the chip with
 // few splits each (the last workgroup of a group combines heads x splits partials with
 // device-scope loads, about 0.1 us per split); with fewer groups the per-head kernel, whose
-// heads share rows through the L2 of their XCD, is faster (8 groups, 3277 rows: 10.9 against 18.7 us).
-bool attn_shared_list_grouped(const tb_cache_desc* d) {
-  return d->Hq > d->Hkv && static_cast<int64_t>(d->B) * d->Hkv >= 32;
+// heads share rows through the L2 of their XCD, is faster.  On the matrix cores: 16 groups from 3072 rows on (g = 4,
+// score to attention: 3661 rows 29.6 -> 28.4 us, 8576 rows 50.3 -> 44.1; g = 8, 1384 rows 34.3 -> 35.6),
+// 8 groups nowhere (3661 rows: 25.0 -> 26.8).
+bool attn_shared_list_grouped(const tb_cache_desc* d, int64_t max_rows) {
+  const int64_t groups = static_cast<int64_t>(d->B) * d->Hkv;
+  if (d->Hq <= d->Hkv) return false;
+  return groups >= 32 || (attn_group_mfma(d) && groups >= 16 && max_rows >= 3072);
 }
 
 SelectPlan select_plan(int64_t units, int64_t candidates, int64_t N, int64_t kk) {
@@ -294,9 +308,8 @@ tb_status sparse_attn(const tb_cache_desc* d, const void* q, const void* K, cons
   const int64_t units = static_cast<int64_t>(d->B) * d->Hq;
   if (units == 0) return TB_OK;
   const int64_t rows = max_count + (tail_end - tail_begin);
-  const bool grouped = shared_list && attn_shared_list_grouped(d);
-  const int64_t wg_units = grouped ? static_cast<int64_t>(d->B) * d->Hkv : units;
-  const AttnPlan plan = attn_plan(wg_units, rows, attn_tile_rows_per_wg(d->dtype, d->D), wg_units != units);
+  const bool grouped = shared_list && attn_shared_list_grouped(d, rows);
+  const AttnPlan plan = grouped ? attn_group_plan(d, rows) : attn_plan(units, rows, attn_tile_rows_per_wg(d->dtype, d->D));
   const WsLayout w = ws_layout(units, d->D, plan.nsplit);
   if (!ws || !aligned16(ws) || ws_bytes < w.total) return TB_ERR_WORKSPACE;
   AttnLaunch L{d,   q,   K,   V,
@@ -486,8 +499,8 @@ size_t tb_workspace_bytes(int32_t op, const tb_cache_desc* d, int64_t max_count)
     // sized for the largest split count a shorter list could get, so that one workspace serves
     // every call whose list is no longer than max_count
     size_t att = ws_layout(units, d->D, plan.max_split).total;
-    if (attn_shared_list_grouped(d)) {  // the head-less form splits per KV group, possibly finer
-      const AttnPlan gp = attn_plan(static_cast<int64_t>(d->B) * d->Hkv, max_count, attn_tile_rows_per_wg(d->dtype, d->D), true);
+    if (attn_shared_list_grouped(d, max_count)) {  // the head-less form splits per KV group, possibly finer
+      const AttnPlan gp = attn_group_plan(d, max_count);
       const size_t g_att = ws_layout(units, d->D, gp.max_split).total;
       if (g_att > att) att = g_att;
     }

@@ -27,6 +27,7 @@ namespace {
 constexpr int kAttnThreads = 256;
 constexpr int kXcds = 8;  // accelerator complex dies of the chip, each with its own L2
 constexpr int kAttnWaves = kAttnThreads / kWave;
+constexpr int kGroupWaves = kAttnGroupWaves;  // of a workgroup that serves a KV group on the matrix cores
 constexpr int kLoadsPerTile = kAttnLoadsPerTile;
 // occupancy the register allocation is held to: 4 waves per SIMD = 4 workgroups per CU, so that a
 // launch of up to 1024 workgroups is resident at once (no second round of workgroups)
@@ -380,8 +381,167 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   if (tid == 0) __hip_atomic_store(&a.counters[u * kCounterStrideWords], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Head-less lists with grouped queries: the GH query heads of a KV head read the same rows, so
-// one workgroup serves all of them: every listed row is loaded once and used GH times (the
+// What the workgroups of a KV group share once their rows are streamed: the waves' (max, sum) pairs
+// and accumulators per head.
+template <int D, int GH, int NW>
+struct GroupLds {
+  static constexpr int kThreads = NW * kWave;
+  static constexpr int kOutsPerThread = (GH * D + kThreads - 1) / kThreads;
+  static constexpr int kMaxCH = kOutsPerThread <= 2 ? 32 : 16;  // splits whose partials are in flight together
+  static_assert(GH * kMaxCH <= kThreads, "one thread per (head, split) pair of a chunk");
+  float m[NW][GH], l[NW][GH];
+  float acc[NW][GH][D];
+  float pm[GH][kMaxCH], pl[GH][kMaxCH];
+  uint32_t last;
+};
+
+// Merges the waves of the workgroup; with several workgroups per KV group publishes the partial, and
+// the last one to arrive combines.
+template <int D, int GH, int NW>
+__device__ __forceinline__ void group_finish(const AttnArgs& a, const int64_t u0, const int split, GroupLds<D, GH, NW>& gl) {
+  constexpr int kThreads = NW * kWave;
+  constexpr int OUTS = GH * D;                         // outputs of the workgroup
+  constexpr int R = GroupLds<D, GH, NW>::kOutsPerThread;   // outputs per thread in the merges
+  const int tid = threadIdx.x;
+  __syncthreads();
+  // merge the waves: thread owns outputs (head, element) number tid, tid + 256, ...
+  float M[R], L[R], o[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int e = tid + r * kThreads;
+    const int hh = (e < OUTS) ? e / D : 0, d = e % D;
+    M[r] = -INFINITY;
+    L[r] = 0.f;
+    o[r] = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) M[r] = fmaxf(M[r], gl.m[w][hh]);
+    if (M[r] > -INFINITY) {
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float wgt = exp2_safe(gl.m[w][hh] - M[r]);
+        L[r] += gl.l[w][hh] * wgt;
+        o[r] += gl.acc[w][hh][d] * wgt;
+      }
+    }
+  }
+
+  if (a.nsplit == 1) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int e = tid + r * kThreads;
+      if (e < OUTS) {
+        const int hh = e / D, d = e % D;
+        a.out[(u0 + hh) * D + d] = (L[r] > 0.f) ? o[r] / L[r] : 0.f;
+        if (d == 0 && a.lse) a.lse[u0 + hh] = (L[r] > 0.f) ? M[r] * kLn2 + logf(L[r]) : -INFINITY;
+      }
+    }
+    return;
+  }
+
+  // several workgroups per KV group: publish the partials (agent-scope accesses and the same
+  // ordering as in attn_kernel), take a ticket, the last to arrive combines in split order
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int e = tid + r * kThreads;
+    if (e < OUTS) {
+      const int hh = e / D, d = e % D;
+      float* part = a.partials + ((u0 + hh) * a.nsplit + split) * (D + 2);
+      __hip_atomic_store(&part[d], o[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (d == 0) {
+        __hip_atomic_store(&part[D], M[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&part[D + 1], L[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+  }
+  publish_fence();
+  __syncthreads();
+  if (tid == 0) {
+    const uint32_t ticket = __hip_atomic_fetch_add(&a.counters[u0 * kCounterStrideWords], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    gl.last = (ticket == static_cast<uint32_t>(a.nsplit - 1)) ? 1u : 0u;
+  }
+  __syncthreads();
+  if (!gl.last) return;
+  // Combine: the device-scope loads of a chunk are issued together: per thread its R outputs
+  // of CH splits; the (max, sum) pairs of those splits, the same for all elements of a head,
+  // are fetched once by GH * CH threads and passed through LDS.  Splits are merged in order.
+  // A device-scope load is paid per instruction even when its result is not needed, so the
+  // chunk is sized to the split count.
+  constexpr int kMaxCH = GroupLds<D, GH, NW>::kMaxCH;
+  float Mg[R], Lg[R], og[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    Mg[r] = -INFINITY;
+    Lg[r] = 0.f;
+    og[r] = 0.f;
+  }
+  auto walk = [&](auto ch_tag) {
+    constexpr int CH = decltype(ch_tag)::value < kMaxCH ? decltype(ch_tag)::value : kMaxCH;
+    for (int s0 = 0; s0 < a.nsplit; s0 += CH) {
+      float ov[R][CH];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int e = tid + r * kThreads;
+        const int hh = (e < OUTS) ? e / D : 0, d = e % D;
+        const float* p0 = a.partials + (u0 + hh) * a.nsplit * (D + 2);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+          const int sl = (s0 + c < a.nsplit) ? s0 + c : a.nsplit - 1;
+          ov[r][c] = __hip_atomic_load(&p0[sl * (D + 2) + d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+      if (tid < GH * CH) {
+        const int hh = tid / CH, c = tid % CH;
+        const float* p0 = a.partials + (u0 + hh) * a.nsplit * (D + 2);
+        const int sl = (s0 + c < a.nsplit) ? s0 + c : a.nsplit - 1;
+        const float pm = __hip_atomic_load(&p0[sl * (D + 2) + D], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const float pl = __hip_atomic_load(&p0[sl * (D + 2) + D + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        gl.pm[hh][c] = (s0 + c < a.nsplit) ? pm : -INFINITY;  // a slot past the last split weighs nothing
+        gl.pl[hh][c] = (s0 + c < a.nsplit) ? pl : 0.f;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int e = tid + r * kThreads;
+        const int hh = (e < OUTS) ? e / D : 0;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+          const float mv = gl.pm[hh][c];
+          const float Mn = fmaxf(Mg[r], mv);
+          if (Mn > -INFINITY) {
+            const float wa = exp2_safe(Mg[r] - Mn), wb = exp2_safe(mv - Mn);
+            Lg[r] = Lg[r] * wa + gl.pl[hh][c] * wb;
+            og[r] = og[r] * wa + ov[r][c] * wb;
+            Mg[r] = Mn;
+          }
+        }
+      }
+      __syncthreads();  // the pairs are overwritten by the next chunk
+    }
+  };
+  if (a.nsplit <= 2)
+    walk(std::integral_constant<int, 2>{});
+  else if (a.nsplit <= 4)
+    walk(std::integral_constant<int, 4>{});
+  else if (a.nsplit <= 8)
+    walk(std::integral_constant<int, 8>{});
+  else if (a.nsplit <= 16)
+    walk(std::integral_constant<int, 16>{});
+  else
+    walk(std::integral_constant<int, 32>{});
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int e = tid + r * kThreads;
+    if (e < OUTS) {
+      const int hh = e / D, d = e % D;
+      a.out[(u0 + hh) * D + d] = (Lg[r] > 0.f) ? og[r] / Lg[r] : 0.f;
+      if (d == 0 && a.lse) a.lse[u0 + hh] = (Lg[r] > 0.f) ? Mg[r] * kLn2 + logf(Lg[r]) : -INFINITY;
+    }
+  }
+  if (tid == 0) __hip_atomic_store(&a.counters[u0 * kCounterStrideWords], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Head-less lists with grouped queries (fp32, and groups of two): the GH query heads of a KV head read
+// the same rows, so one workgroup serves all of them: every listed row is loaded once and used GH times (the
 // loads, not the arithmetic, bound this kernel).  Work split and tiling as in attn_kernel, with
 // one workgroup per (b, kv head, split); every lane group keeps GH softmax states and GH
 // accumulator slices.  The partial hand-over uses the counter of the group's first head.
@@ -391,13 +551,9 @@ __global__ __launch_bounds__(kAttnThreads) void attn_group_kernel(AttnArgs a) {
   constexpr int LPR = D / EPL;
   constexpr int GPW = kWave / LPR;
   constexpr int TILE = kLoadsPerTile * GPW;
-  constexpr int OUTS = GH * D;                                     // outputs of the workgroup
-  constexpr int R = (OUTS + kAttnThreads - 1) / kAttnThreads;      // outputs per thread in the merges
   static_assert(LPR >= 4 && LPR <= 32, "row must span 4..32 lanes");
 
-  __shared__ float s_m[kAttnWaves][GH], s_l[kAttnWaves][GH];
-  __shared__ float s_acc[kAttnWaves][GH][D];
-  __shared__ uint32_t s_last;
+  __shared__ GroupLds<D, GH, kAttnWaves> gl;
 
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
@@ -526,157 +682,227 @@ __global__ __launch_bounds__(kAttnThreads) void attn_group_kernel(AttnArgs a) {
     }
     if (grp == 0) {
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) s_acc[wave][j][sub * EPL + e] = acc[j][e];
+      for (int e = 0; e < EPL; ++e) gl.acc[wave][j][sub * EPL + e] = acc[j][e];
       if (sub == 0) {
-        s_m[wave][j] = m[j];
-        s_l[wave][j] = l[j];
+        gl.m[wave][j] = m[j];
+        gl.l[wave][j] = l[j];
       }
     }
   }
-  __syncthreads();
+  group_finish<D, GH, kAttnWaves>(a, u0, split, gl);
+}
 
-  // merge the waves: thread owns outputs (head, element) number tid, tid + 256, ...
-  float M[R], L[R], o[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int e = tid + r * kAttnThreads;
-    const int hh = (e < OUTS) ? e / D : 0, d = e % D;
-    M[r] = -INFINITY;
-    L[r] = 0.f;
-    o[r] = 0.f;
-#pragma unroll
-    for (int w = 0; w < kAttnWaves; ++w) M[r] = fmaxf(M[r], s_m[w][hh]);
-    if (M[r] > -INFINITY) {
-#pragma unroll
-      for (int w = 0; w < kAttnWaves; ++w) {
-        const float wgt = exp2_safe(s_m[w][hh] - M[r]);
-        L[r] += s_l[w][hh] * wgt;
-        o[r] += s_acc[w][hh][d] * wgt;
-      }
-    }
-  }
+// The same for bf16 on the matrix cores.  GH heads that read the same rows make both halves
+// contractions, and on the vector ALUs their arithmetic (about 1760 clocks of a SIMD per 16 rows with
+// four heads) is as long as the stream of the rows itself.  A wave takes 32 rows a step:
+//
+//   scores   (16 rows x D) x (D x heads), v_mfma_f32_16x16x32_bf16: lane (i, kb) = (lane % 16, lane / 16)
+//            loads 16 bytes of row i, elements 32 c + 8 kb .. + 7 for slice c; the other operand is the
+//            same slice of query i (zero past the group's heads).  Accumulator v of lane (j, kb) is
+//            (row 4 kb + v, head j).
+//   weights  exp2 in fp32, each the exact sum of three bf16 numbers (its upper halves: all 24 bits),
+//            so that the products with V are exact and only the fp32 accumulation rounds.
+//   output   (heads x 32 rows) x (32 rows x D): lane (j, kb) already holds the weights of head j for
+//            the rows 4 kb + v of both 16-row tiles -- the k slots 8 kb .. + 7 of this operand, in an
+//            order of their own that the other operand follows: lane (n, kb) loads elements EV n .. of
+//            the same rows of V, and element e of them all is column EV n + e.
+//
+// Invalid slots repeat the wave's first row with weight 0 (a row that is attended anyway, so that an
+// infinite value in an unlisted row cannot reach the result).  Relative error against 64 bits on
+// 3661 rows 2.0e-7 (vector form: 2.4e-7).
+//
+// Eight waves a workgroup, one workgroup per compute unit as a rule: as many rows in flight as two
+// of four waves, and half the partials for the last workgroup to combine (512 workgroups of eight waves:
+// 40.6 us instead of 31.7 below).  Bound by its chain of latencies (list, two steps of gathers,
+// hand-over, combination) at 3661 rows, by the gathers beyond.  Score to attention, 32 groups of four
+// heads, 3661 rows: 36.8 -> 31.7 us; of eight heads, 8576 rows: 85.9 -> 64.3 us.  Two heads a group
+// leave 14 of 16 columns idle and stay on the vector form (8576 rows: 60.4 against 61.7 us).
+typedef short attn_bf16x8 __attribute__((ext_vector_type(8)));
+typedef float attn_f32x4 __attribute__((ext_vector_type(4)));
 
-  if (a.nsplit == 1) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int e = tid + r * kAttnThreads;
-      if (e < OUTS) {
-        const int hh = e / D, d = e % D;
-        a.out[(u0 + hh) * D + d] = (L[r] > 0.f) ? o[r] / L[r] : 0.f;
-        if (d == 0 && a.lse) a.lse[u0 + hh] = (L[r] > 0.f) ? M[r] * kLn2 + logf(L[r]) : -INFINITY;
-      }
-    }
-    return;
-  }
+template <int D, int GH>
+__global__ __launch_bounds__(kGroupWaves * kWave, 2) void attn_group_mfma_kernel(AttnArgs a) {
+  constexpr int KC = D / 32;  // slices of a row for the scores
+  constexpr int EV = D / 16;  // elements of a V row per lane
+  constexpr int VW = EV / 2;  // ... in 32-bit words
+  constexpr int STEP = 32;
+  typedef uint32_t vword __attribute__((ext_vector_type(VW)));
+  static_assert(GH <= 16, "one column per head of the group");
+  __shared__ GroupLds<D, GH, kGroupWaves> gl;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = wave_id();
+  const int i16 = lane & 15, kb = lane >> 4;
+  const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
+  const int64_t u0 = static_cast<int64_t>(b) * a.Hq + static_cast<int64_t>(hkv) * GH;  // first head of the group
 
-  // several workgroups per KV group: publish the partials (agent-scope accesses and the same
-  // ordering as in attn_kernel), take a ticket, the last to arrive combines in split order
+  const int rows_per_wave = a.rows_per_wg / kGroupWaves;
+  const int64_t w_beg = static_cast<int64_t>(split) * a.rows_per_wg + static_cast<int64_t>(wave) * rows_per_wave;
+  const char* kbase = reinterpret_cast<const char*>(static_cast<const bf16_t*>(a.K) + b * a.k_stride_b + hkv * a.k_stride_h) + kb * 16;
+  const char* vbase = reinterpret_cast<const char*>(static_cast<const bf16_t*>(a.V) + b * a.v_stride_b + hkv * a.v_stride_h) + i16 * (EV * 2);
+  const uint32_t k_row_bytes = static_cast<uint32_t>(a.k_stride_n * sizeof(bf16_t));
+  const uint32_t v_row_bytes = static_cast<uint32_t>(a.v_stride_n * sizeof(bf16_t));
+  const int32_t* list = a.idx + b * a.idx_cap;
+
+  attn_bf16x8 qop[KC];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int e = tid + r * kAttnThreads;
-    if (e < OUTS) {
-      const int hh = e / D, d = e % D;
-      float* part = a.partials + ((u0 + hh) * a.nsplit + split) * (D + 2);
-      __hip_atomic_store(&part[d], o[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (d == 0) {
-        __hip_atomic_store(&part[D], M[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&part[D + 1], L[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
+  for (int c = 0; c < KC; ++c) {
+    const bf16_t* qp = static_cast<const bf16_t*>(a.q) + (u0 + (i16 < GH ? i16 : 0)) * D + c * 32 + kb * 8;
+    uint4 t = *reinterpret_cast<const uint4*>(qp);
+    if (i16 >= GH) t = make_uint4(0u, 0u, 0u, 0u);
+    __builtin_memcpy(&qop[c], &t, 16);
   }
-  publish_fence();
-  __syncthreads();
-  if (tid == 0) {
-    const uint32_t ticket = __hip_atomic_fetch_add(&a.counters[u0 * kCounterStrideWords], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = (ticket == static_cast<uint32_t>(a.nsplit - 1)) ? 1u : 0u;
-  }
-  __syncthreads();
-  if (!s_last) return;
-  // Combine: the device-scope loads of a chunk are issued together: per thread its R outputs
-  // of CH splits; the (max, sum) pairs of those splits, the same for all elements of a head,
-  // are fetched once by GH * CH threads and passed through LDS.  Splits are merged in order.
-  // A device-scope load is paid per instruction even when its result is not needed, so the
-  // chunk is sized to the split count.
-  constexpr int kMaxCH = (R <= 2) ? 32 : 16;
-  static_assert(GH * kMaxCH <= kAttnThreads, "one thread per (head, split) pair of a chunk");
-  __shared__ float s_pm[GH][kMaxCH], s_pl[GH][kMaxCH];
-  float Mg[R], Lg[R], og[R];
+  float m = -INFINITY, l = 0.f;  // of head i16 (l: this lane's rows only)
+  // accumulator v: head 4 kb + v, column EV i16 + e; the weights' lower parts are summed apart (one
+  // rounding a step at the size of the result instead of three)
+  attn_f32x4 acc[EV], acc_low[EV];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    Mg[r] = -INFINITY;
-    Lg[r] = 0.f;
-    og[r] = 0.f;
-  }
-  auto walk = [&](auto ch_tag) {
-    constexpr int CH = decltype(ch_tag)::value < kMaxCH ? decltype(ch_tag)::value : kMaxCH;
-    for (int s0 = 0; s0 < a.nsplit; s0 += CH) {
-      float ov[R][CH];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int e = tid + r * kAttnThreads;
-        const int hh = (e < OUTS) ? e / D : 0, d = e % D;
-        const float* p0 = a.partials + (u0 + hh) * a.nsplit * (D + 2);
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-          const int sl = (s0 + c < a.nsplit) ? s0 + c : a.nsplit - 1;
-          ov[r][c] = __hip_atomic_load(&p0[sl * (D + 2) + d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-      }
-      if (tid < GH * CH) {
-        const int hh = tid / CH, c = tid % CH;
-        const float* p0 = a.partials + (u0 + hh) * a.nsplit * (D + 2);
-        const int sl = (s0 + c < a.nsplit) ? s0 + c : a.nsplit - 1;
-        const float pm = __hip_atomic_load(&p0[sl * (D + 2) + D], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const float pl = __hip_atomic_load(&p0[sl * (D + 2) + D + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_pm[hh][c] = (s0 + c < a.nsplit) ? pm : -INFINITY;  // a slot past the last split weighs nothing
-        s_pl[hh][c] = (s0 + c < a.nsplit) ? pl : 0.f;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int e = tid + r * kAttnThreads;
-        const int hh = (e < OUTS) ? e / D : 0;
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-          const float mv = s_pm[hh][c];
-          const float Mn = fmaxf(Mg[r], mv);
-          if (Mn > -INFINITY) {
-            const float wa = exp2_safe(Mg[r] - Mn), wb = exp2_safe(mv - Mn);
-            Lg[r] = Lg[r] * wa + s_pl[hh][c] * wb;
-            og[r] = og[r] * wa + ov[r][c] * wb;
-            Mg[r] = Mn;
-          }
-        }
-      }
-      __syncthreads();  // the pairs are overwritten by the next chunk
-    }
+  for (int e = 0; e < EV; ++e) acc[e] = acc_low[e] = attn_f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // row of slot i of the list (read as `raw`), or of the dense tail behind it
+  int64_t cnt, w_end;
+  auto row_of = [&](int64_t i, int32_t raw) -> int32_t {
+    int64_t n = (i < cnt) ? static_cast<int64_t>(raw) : a.tail_begin + (i - cnt);
+    n = n < 0 ? 0 : (n >= a.N ? a.N - 1 : n);  // keep the gather inside the cache whatever the list holds
+    return static_cast<int32_t>(n);
   };
-  if (a.nsplit <= 2)
-    walk(std::integral_constant<int, 2>{});
-  else if (a.nsplit <= 4)
-    walk(std::integral_constant<int, 4>{});
-  else if (a.nsplit <= 8)
-    walk(std::integral_constant<int, 8>{});
-  else if (a.nsplit <= 16)
-    walk(std::integral_constant<int, 16>{});
-  else
-    walk(std::integral_constant<int, 32>{});
+  // lane r (and r + 32) of a step: the row of its slot r.  The first step's entries are read without
+  // waiting for the count (the slots are inside the list's capacity whatever the count is).
+  int32_t n_next;
+  {
+    const int64_t i0 = w_beg + (lane & 31);
+    const int64_t cap1 = a.idx_cap > 0 ? a.idx_cap - 1 : 0;
+    const int32_t raw = a.idx_cap > 0 ? list[i0 < cap1 ? i0 : cap1] : 0;
+    const int32_t raw_first = a.idx_cap > 0 ? list[w_beg < cap1 ? w_beg : cap1] : 0;
+    const int64_t c = a.count[b];
+    cnt = c < 0 ? 0 : (c > a.max_count ? a.max_count : c);
+    const int64_t total = cnt + (a.tail_end - a.tail_begin);
+    w_end = (w_beg + rows_per_wave < total) ? w_beg + rows_per_wave : total;
+    n_next = i0 < w_end ? row_of(i0, raw) : row_of(w_beg, raw_first);
+  }
+  auto fetch_rows = [&](int64_t t0) -> int32_t {
+    int64_t i = t0 + (lane & 31);
+    i = i < w_end ? i : w_beg;
+    return row_of(i, i < cnt ? list[i] : 0);
+  };
+  for (int64_t t0 = w_beg; t0 < w_end; t0 += STEP) {
+    const int32_t n_mine = n_next;
+    attn_bf16x8 kraw[2][KC];
+    vword vraw[2][4];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int e = tid + r * kAttnThreads;
-    if (e < OUTS) {
-      const int hh = e / D, d = e % D;
-      a.out[(u0 + hh) * D + d] = (Lg[r] > 0.f) ? og[r] / Lg[r] : 0.f;
-      if (d == 0 && a.lse) a.lse[u0 + hh] = (Lg[r] > 0.f) ? Mg[r] * kLn2 + logf(Lg[r]) : -INFINITY;
+    for (int t = 0; t < 2; ++t) {
+      const uint32_t row = static_cast<uint32_t>(__shfl(n_mine, 16 * t + i16, kWave));
+#pragma unroll
+      for (int c = 0; c < KC; ++c) {
+        const uint4 x = *reinterpret_cast<const uint4*>(kbase + row * k_row_bytes + c * 64);
+        __builtin_memcpy(&kraw[t][c], &x, 16);
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const uint32_t row = static_cast<uint32_t>(__shfl(n_mine, 16 * t + 4 * kb + v, kWave));
+        vraw[t][v] = *reinterpret_cast<const vword*>(vbase + row * v_row_bytes);
+      }
+    if (t0 + STEP < w_end) n_next = fetch_rows(t0 + STEP);
+    __builtin_amdgcn_sched_barrier(0);  // every gather of the step is in flight before the first is consumed
+    float p[2][4];
+    float tmax = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      // every slice on its own, added pairwise: fewer roundings at the size of the whole sum
+      attn_f32x4 sc[KC];
+#pragma unroll
+      for (int c = 0; c < KC; ++c)
+        sc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kraw[t][c], qop[c], attn_f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+      const attn_f32x4 s = KC == 2 ? sc[0] + sc[1] : (sc[0] + sc[1]) + (sc[KC - 2] + sc[KC - 1]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const bool valid = t0 + 16 * t + 4 * kb + v < w_end;
+        p[t][v] = s[v];
+        tmax = fmaxf(tmax, valid ? s[v] * a.sm_scale_log2 : -INFINITY);
+      }
+    }
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 16, kWave));
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
+    const float m_new = fmaxf(m, tmax);
+    const float m_ref = (m_new > -INFINITY) ? m_new : 0.f;  // nothing seen yet: all weights 0
+    if (__any(m_new > m)) {
+      const float alpha = exp2_safe(m - m_ref);
+      l *= alpha;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float al = __shfl(alpha, 4 * kb + v, kWave);  // (lane j < 16 holds head j)
+#pragma unroll
+        for (int e = 0; e < EV; ++e) {
+          acc[e][v] *= al;
+          acc_low[e][v] *= al;
+        }
+      }
+      m = m_new;
+    }
+    uint32_t part[3][4];  // the weights of the eight rows as three bf16 numbers each, packed in pairs
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        uint32_t w[3][2];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+          // one rounding for the scaled score and its distance to the maximum
+          const bool valid = t0 + 16 * t + 4 * kb + 2 * h + o < w_end;
+          const float x = valid ? exp2_safe(fmaf(p[t][2 * h + o], a.sm_scale_log2, -m_ref)) : 0.f;
+          l += x;
+          w[0][o] = __float_as_uint(x) & 0xFFFF0000u;
+          const float r = x - __uint_as_float(w[0][o]);  // exact
+          w[1][o] = __float_as_uint(r) & 0xFFFF0000u;
+          w[2][o] = __float_as_uint(r - __uint_as_float(w[1][o]));  // at most 8 bits are left
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) part[k][2 * t + h] = __builtin_amdgcn_perm(w[k][1], w[k][0], 0x07060302u);
+      }
+    attn_bf16x8 pop[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) __builtin_memcpy(&pop[k], &part[k][0], 16);
+#pragma unroll
+    for (int e = 0; e < EV; ++e) {
+      const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;  // element e of two rows side by side
+      uint32_t w[4];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          w[2 * t + h] = __builtin_amdgcn_perm(vraw[t][2 * h + 1][e / 2], vraw[t][2 * h][e / 2], sel);
+      attn_bf16x8 vop;
+      __builtin_memcpy(&vop, &w[0], 16);
+#pragma unroll
+      for (int k = 2; k >= 1; --k) acc_low[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pop[k], vop, acc_low[e], 0, 0, 0);
+      acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pop[0], vop, acc[e], 0, 0, 0);
     }
   }
-  if (tid == 0) __hip_atomic_store(&a.counters[u0 * kCounterStrideWords], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  l += __shfl_xor(l, 16, kWave);
+  l += __shfl_xor(l, 32, kWave);
+  if (lane < GH) {
+    gl.m[wave][lane] = m;
+    gl.l[wave][lane] = l;
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+    if (4 * kb + v < GH) {
+#pragma unroll
+      for (int e = 0; e < EV; ++e) gl.acc[wave][4 * kb + v][EV * i16 + e] = acc[e][v] + acc_low[e][v];
+    }
+  group_finish<D, GH, kGroupWaves>(a, u0, split, gl);
 }
 
 template <typename T, int D, int GH>
 tb_status launch_group(const AttnArgs& a, const AttnLaunch& L, hipStream_t st) {
   const tb_cache_desc& d = *L.desc;
-  hipLaunchKernelGGL((attn_group_kernel<T, D, GH>), dim3(L.plan.nsplit, d.Hkv, d.B), dim3(kAttnThreads), 0, st, a);
+  const dim3 grid(L.plan.nsplit, d.Hkv, d.B);
+  if constexpr (std::is_same<T, bf16_t>::value && GH >= 4)
+    hipLaunchKernelGGL((attn_group_mfma_kernel<D, GH>), grid, dim3(kGroupWaves * kWave), 0, st, a);
+  else
+    hipLaunchKernelGGL((attn_group_kernel<T, D, GH>), grid, dim3(kAttnThreads), 0, st, a);
   return hip_status(hipGetLastError());
 }
 

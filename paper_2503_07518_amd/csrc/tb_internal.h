@@ -30,8 +30,11 @@ struct AttnPlan {
   int max_split;    // upper bound of nsplit for any list no longer than the one planned for
 };
 
-AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool grouped = false);
-bool attn_shared_list_grouped(const tb_cache_desc* d);
+AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg);
+// A shared list's KV groups of four heads and more, bf16, are served on the matrix cores.
+inline bool attn_group_mfma(const tb_cache_desc* d) { return d->dtype == TB_BF16 && d->Hq >= 4 * d->Hkv; }
+AttnPlan attn_group_plan(const tb_cache_desc* d, int64_t max_rows);
+bool attn_shared_list_grouped(const tb_cache_desc* d, int64_t max_rows);
 WsLayout ws_layout(int64_t units, int D, int nsplit);
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -121,6 +124,7 @@ struct GatherLaunch {
 };
 tb_status launch_gather(const GatherLaunch& a, hipStream_t st);
 int attn_tile_rows_per_wg(int dtype, int D);
+constexpr int kAttnGroupWaves = 8;    // waves of a workgroup that serves a KV group on the matrix cores
 constexpr int kAttnLoadsPerTile = 4;  // K (and V) gathers of a lane per tile
 tb_status launch_attn(const AttnLaunch& a, hipStream_t st);
 

@@ -107,6 +107,36 @@ def test_headless_tail_and_ragged_counts(oracle, B):
     assert_attention(np_of(out), r_out, "bf16", np_of(lse), r_lse)
 
 
+@pytest.mark.parametrize("g,D,Hkv,B", [(4, 64, 4, 8), (4, 128, 8, 4), (8, 128, 2, 16), (8, 64, 8, 2)])  # (16 groups: long lists only)
+@pytest.mark.parametrize("rows", [1, 31, 33, 255, 257, 3100])
+def test_headless_group_step_edges(oracle, g, D, Hkv, B, rows):
+    """bf16 groups on the matrix cores around the 32 rows of a wave's step and the 256 of a
+    workgroup's, with a tail; every row that is not attended is infinite, so a slot past the end that
+    read one would show.  Outputs are fp32 sums of exact products: 2e-6 of the result's size, four
+    times what 3661 rows show (the general bar is 2e-2)."""
+    say(f"head-less group step edges g={g} D={D} Hkv={Hkv} B={B} rows={rows}")
+    gen = torch.Generator().manual_seed(33 + rows)
+    N, tail = 2 * rows + 70, (2 * rows + 40, 2 * rows + 40 + rows % 5)
+    K = torch.randn((B, Hkv, N, D), generator=gen).to(torch.bfloat16)
+    V = torch.randn((B, Hkv, N, D), generator=gen).to(torch.bfloat16)
+    q = torch.randn((B, g * Hkv, D), generator=gen).to(torch.bfloat16).to(DEV)
+    idx = torch.stack([torch.randperm(2 * rows + 30, generator=gen)[:rows].sort().values for _ in range(B)]).to(torch.int32)
+    cnt = torch.full((B,), rows, dtype=torch.int32)
+    n_tail = tail[1] - tail[0]
+    full = torch.cat([idx, torch.arange(tail[0], tail[1], dtype=torch.int32).expand(B, n_tail)], 1)
+    for b in range(B if B * Hkv >= 32 or rows > 3072 else 0):
+        skip = torch.ones(N, dtype=torch.bool)
+        skip[full[b].long()] = False
+        K[b, :, skip] = float("inf")
+        V[b, :, skip] = float("inf")
+    K, V = K.to(DEV), V.to(DEV)
+    sm = 1.0 / math.sqrt(D)
+    out, lse = shared_attn(q, K, V, idx.to(DEV), cnt.to(DEV), N, sm, rows, tail)
+    r_out, r_lse = oracle.sparse_decode_attn_shared(np_of(q), np_of(K), np_of(V), full.numpy(), (cnt + n_tail).numpy(), "bf16", sm)
+    assert_attention(np_of(out), r_out, "bf16", np_of(lse), r_lse)
+    assert np.abs(np_of(out) - r_out).max() <= 2e-6 * max(1.0, np.abs(r_out).max())
+
+
 @pytest.mark.parametrize("name", ["C2_llama3_8b_32k", "C3_batched_depth", "C5_long_context"])
 def test_headless_full_size_configs(oracle, name):
     """The benchmark shapes with one importance head (the first KV head's projected keys):
