@@ -2,17 +2,26 @@
 // intermediate "important buffer" copy is made).
 //
 // Work split: nsplit workgroups per (b, h) (placed per XCD when heads share KV rows, see the
-// kernel).  A workgroup of 4 waves takes a contiguous slice of the
-// head's list; each wave walks its part in tiles of 4*GPW rows, where GPW = 64/LPR row groups
-// and LPR = D*sizeof(T)/16 lanes cover one row with a 128-bit load each (bf16, D=128: 16
-// lanes per 256 B row, 4 rows per wave instruction, 16-row tiles).  All K and V loads of a
-// tile are issued before the first one is consumed, so a wave keeps 8 KiB of gathers in
+// kernel).  The head's list is cut into tiles of 4*GPW rows that go round all its waves (tile t to
+// wave t % 4 of workgroup t / 4 % nsplit), where GPW = 64/LPR row groups and LPR = D*sizeof(T)/16
+// lanes cover one row with a 128-bit load each (bf16, D=128: 16 lanes per 256 B row, 4 rows per
+// wave instruction, 16-row tiles).  All K and V loads of a tile are issued before the first one is consumed, so a wave keeps 8 KiB of gathers in
 // flight (measured best: 32-row tiles were 3-5% slower on the batched configurations).  Every lane group runs its own online softmax (running max, running sum, fp32
 // accumulator slice of D/LPR elements) in the base-2 domain; groups are merged by wave
 // shuffles, waves through LDS, and workgroups through fp32 partials in the workspace: the
 // last workgroup of a head to arrive (device-scope counter) combines the partials in split
 // order, so the result does not depend on arrival order.  The counter is reset by that
 // workgroup, which leaves the workspace ready for the next call.
+//
+// Why the tiles go round: a head's waves then walk its ascending list together, and so do the heads
+// that share a KV head, so the rows of the cache that are being read at any time lie close
+// together and a row that several heads list is still in their XCD's L2 when the next one asks for
+// it.  With a contiguous slice per wave the heads' positions drift apart by sqrt(slot) / density
+// rows, in as many places as there are waves.  And a list shorter than max_count (a widened one)
+// still occupies every wave.  Interval of 8 steps, 4 x 32 heads, 65536 rows, widened lists: 908 -> 850 us;
+// 2 x 64 heads (eight to a group), 30001 rows: 477 -> 370; 16 x 32 heads, 2048 of 16384 rows, one
+// workgroup a head: unchanged.  More workgroups than two a compute unit still lose (768: 893 and 366,
+// 1024: 865 and 419 us on these two).
 //
 // Head-less lists (one list per batch element for all heads) go through the same kernel with
 // the list shared, or, when there are enough KV groups to fill the chip, through
@@ -49,7 +58,7 @@ struct AttnArgs {
   float* lse;
   float* partials;
   uint32_t* counters;
-  int32_t Hq, g, rows_per_wg, nsplit, n_kv_groups, xcd_map;
+  int32_t Hq, g, nsplit, n_kv_groups, xcd_map;
   int32_t shared_list;  // one list and count per batch element, read by all of its heads
   // buffered form: the listed rows have been copied to per-query-head buffers
   // [B][Hq][buf_cap][D] in list order (slot i of the list is buffer row i); idx is unused
@@ -107,11 +116,10 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   }
   const int64_t u = static_cast<int64_t>(b) * a.Hq + h;
 
-  const int64_t wg_beg = static_cast<int64_t>(split) * a.rows_per_wg;
-  const int rows_per_wave = a.rows_per_wg / kAttnWaves;
-  const int64_t w_beg0 = wg_beg + static_cast<int64_t>(wave) * rows_per_wave;
-  const int64_t w_beg = w_beg0;
-  int64_t cnt, total, w_end;  // set once the count has arrived (first-tile block below)
+  // The tiles of the list go round the head's waves (see the head of this file)
+  const int64_t w_beg = static_cast<int64_t>(split * kAttnWaves + wave) * TILE;
+  const int64_t stride = static_cast<int64_t>(a.nsplit) * kAttnWaves * TILE;
+  int64_t cnt, total;  // set once the count has arrived (first-tile block below)
 
   const char* kbase = reinterpret_cast<const char*>(static_cast<const T*>(a.K) + b * a.k_stride_b +
                                                    hkv * a.k_stride_h) + sub * 16;
@@ -143,7 +151,7 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   // current tile is being processed.
   auto fetch_rows = [&](int64_t t0) -> int32_t {
     const int64_t i = t0 + lane;
-    if (lane < TILE && i < w_end) {
+    if (lane < TILE && i < total) {
       if (BUF) {  // slot i of the list is row i of the buffer; the tail is read from the cache
         if (i < cnt) return static_cast<int32_t>(i);
         const int64_t n = a.tail_begin + (i - cnt);
@@ -161,24 +169,22 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
     cnt_now = cnt_now < 0 ? 0 : (cnt_now > a.max_count ? a.max_count : cnt_now);
     cnt = cnt_now;
     total = cnt + (a.tail_end - a.tail_begin);
-    w_end = (w_beg0 + rows_per_wave < total) ? w_beg0 + rows_per_wave : total;
-    n_next = fetch_rows(w_beg0);
+    n_next = fetch_rows(w_beg);
   } else {
     // first tile: the list entry is read without waiting for the count (the slot is inside
     // the list's capacity whatever the count is) and sorted out afterwards
-    const int64_t i = w_beg0 + lane;
+    const int64_t i = w_beg + lane;
     const int64_t i_safe = (i < a.idx_cap) ? i : (a.idx_cap > 0 ? a.idx_cap - 1 : 0);
     const int32_t raw = (lane < TILE && a.idx_cap > 0) ? list[i_safe] : 0;
     int64_t cnt_now = a.count[lu];
     cnt_now = cnt_now < 0 ? 0 : (cnt_now > a.max_count ? a.max_count : cnt_now);
     cnt = cnt_now;
     total = cnt + (a.tail_end - a.tail_begin);
-    w_end = (w_beg0 + rows_per_wave < total) ? w_beg0 + rows_per_wave : total;
     int64_t n = (i < cnt) ? static_cast<int64_t>(raw) : a.tail_begin + (i - cnt);
     n = n < 0 ? 0 : (n >= a.N ? a.N - 1 : n);
-    n_next = (lane < TILE && i < w_end) ? static_cast<int32_t>(n) : -1;
+    n_next = (lane < TILE && i < total) ? static_cast<int32_t>(n) : -1;
   }
-  for (int64_t t0 = w_beg; t0 < w_end; t0 += TILE) {
+  for (int64_t t0 = w_beg; t0 < total; t0 += stride) {
     const int32_t n_mine = n_next;
     typename Pack16<T>::Raw kraw[kLoadsPerTile], vraw[kLoadsPerTile];  // kept packed until used
     bool valid[kLoadsPerTile];
@@ -201,7 +207,7 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
         vraw[t] = Pack16<T>::load_raw(vbase + row * v_row_bytes);
       }
     }
-    n_next = fetch_rows(t0 + TILE);
+    n_next = fetch_rows(t0 + stride);
     // every gather of the tile is in flight before the first one is consumed
     __builtin_amdgcn_sched_barrier(0);
     float sc[kLoadsPerTile];
@@ -563,8 +569,8 @@ __global__ __launch_bounds__(kAttnThreads) void attn_group_kernel(AttnArgs a) {
   const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
   const int64_t u0 = static_cast<int64_t>(b) * a.Hq + static_cast<int64_t>(hkv) * GH;  // first head of the group
 
-  const int rows_per_wave = a.rows_per_wg / kAttnWaves;
-  const int64_t w_beg = static_cast<int64_t>(split) * a.rows_per_wg + static_cast<int64_t>(wave) * rows_per_wave;
+  const int64_t w_beg = static_cast<int64_t>(split * kAttnWaves + wave) * TILE;
+  const int64_t stride = static_cast<int64_t>(a.nsplit) * kAttnWaves * TILE;
 
   const char* kbase = reinterpret_cast<const char*>(static_cast<const T*>(a.K) + b * a.k_stride_b +
                                                    hkv * a.k_stride_h) + sub * 16;
@@ -593,11 +599,10 @@ __global__ __launch_bounds__(kAttnThreads) void attn_group_kernel(AttnArgs a) {
   int64_t cnt = a.count[b];
   cnt = cnt < 0 ? 0 : (cnt > a.max_count ? a.max_count : cnt);
   const int64_t total = cnt + (a.tail_end - a.tail_begin);
-  const int64_t w_end = (w_beg + rows_per_wave < total) ? w_beg + rows_per_wave : total;
   // row numbers of a tile: lanes 0..TILE-1 fetch one entry each (list, then the dense tail)
   auto fetch_rows = [&](int64_t t0) -> int32_t {
     const int64_t i = t0 + lane;
-    if (lane < TILE && i < w_end) {
+    if (lane < TILE && i < total) {
       int64_t n = (i < cnt) ? static_cast<int64_t>(list[i]) : a.tail_begin + (i - cnt);
       n = n < 0 ? 0 : (n >= a.N ? a.N - 1 : n);  // keep the gather inside the cache whatever the list holds
       return static_cast<int32_t>(n);
@@ -605,7 +610,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_group_kernel(AttnArgs a) {
     return -1;
   };
   int32_t n_next = fetch_rows(w_beg);
-  for (int64_t t0 = w_beg; t0 < w_end; t0 += TILE) {
+  for (int64_t t0 = w_beg; t0 < total; t0 += stride) {
     const int32_t n_mine = n_next;
     typename Pack16<T>::Raw kraw[kLoadsPerTile], vraw[kLoadsPerTile];
     bool valid[kLoadsPerTile];
@@ -617,7 +622,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_group_kernel(AttnArgs a) {
       kraw[t] = Pack16<T>::load_raw(kbase + row * k_row_bytes);
       vraw[t] = Pack16<T>::load_raw(vbase + row * v_row_bytes);
     }
-    n_next = fetch_rows(t0 + TILE);
+    n_next = fetch_rows(t0 + stride);
     __builtin_amdgcn_sched_barrier(0);  // every gather of the tile is in flight before the first is consumed
     float sc[GH][kLoadsPerTile];
 #pragma unroll
@@ -735,8 +740,8 @@ __global__ __launch_bounds__(kGroupWaves * kWave, 2) void attn_group_mfma_kernel
   const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
   const int64_t u0 = static_cast<int64_t>(b) * a.Hq + static_cast<int64_t>(hkv) * GH;  // first head of the group
 
-  const int rows_per_wave = a.rows_per_wg / kGroupWaves;
-  const int64_t w_beg = static_cast<int64_t>(split) * a.rows_per_wg + static_cast<int64_t>(wave) * rows_per_wave;
+  const int64_t w_beg = static_cast<int64_t>(split * kGroupWaves + wave) * STEP;
+  const int64_t stride = static_cast<int64_t>(a.nsplit) * kGroupWaves * STEP;
   const char* kbase = reinterpret_cast<const char*>(static_cast<const bf16_t*>(a.K) + b * a.k_stride_b + hkv * a.k_stride_h) + kb * 16;
   const char* vbase = reinterpret_cast<const char*>(static_cast<const bf16_t*>(a.V) + b * a.v_stride_b + hkv * a.v_stride_h) + i16 * (EV * 2);
   const uint32_t k_row_bytes = static_cast<uint32_t>(a.k_stride_n * sizeof(bf16_t));
@@ -759,7 +764,7 @@ __global__ __launch_bounds__(kGroupWaves * kWave, 2) void attn_group_mfma_kernel
   for (int e = 0; e < EV; ++e) acc[e] = acc_low[e] = attn_f32x4{0.f, 0.f, 0.f, 0.f};
 
   // row of slot i of the list (read as `raw`), or of the dense tail behind it
-  int64_t cnt, w_end;
+  int64_t cnt, total;
   auto row_of = [&](int64_t i, int32_t raw) -> int32_t {
     int64_t n = (i < cnt) ? static_cast<int64_t>(raw) : a.tail_begin + (i - cnt);
     n = n < 0 ? 0 : (n >= a.N ? a.N - 1 : n);  // keep the gather inside the cache whatever the list holds
@@ -775,16 +780,15 @@ __global__ __launch_bounds__(kGroupWaves * kWave, 2) void attn_group_mfma_kernel
     const int32_t raw_first = a.idx_cap > 0 ? list[w_beg < cap1 ? w_beg : cap1] : 0;
     const int64_t c = a.count[b];
     cnt = c < 0 ? 0 : (c > a.max_count ? a.max_count : c);
-    const int64_t total = cnt + (a.tail_end - a.tail_begin);
-    w_end = (w_beg + rows_per_wave < total) ? w_beg + rows_per_wave : total;
-    n_next = i0 < w_end ? row_of(i0, raw) : row_of(w_beg, raw_first);
+    total = cnt + (a.tail_end - a.tail_begin);
+    n_next = i0 < total ? row_of(i0, raw) : row_of(w_beg, raw_first);
   }
   auto fetch_rows = [&](int64_t t0) -> int32_t {
     int64_t i = t0 + (lane & 31);
-    i = i < w_end ? i : w_beg;
+    i = i < total ? i : w_beg;
     return row_of(i, i < cnt ? list[i] : 0);
   };
-  for (int64_t t0 = w_beg; t0 < w_end; t0 += STEP) {
+  for (int64_t t0 = w_beg; t0 < total; t0 += stride) {
     const int32_t n_mine = n_next;
     attn_bf16x8 kraw[2][KC];
     vword vraw[2][4];
@@ -804,7 +808,7 @@ __global__ __launch_bounds__(kGroupWaves * kWave, 2) void attn_group_mfma_kernel
         const uint32_t row = static_cast<uint32_t>(__shfl(n_mine, 16 * t + 4 * kb + v, kWave));
         vraw[t][v] = *reinterpret_cast<const vword*>(vbase + row * v_row_bytes);
       }
-    if (t0 + STEP < w_end) n_next = fetch_rows(t0 + STEP);
+    if (t0 + stride < total) n_next = fetch_rows(t0 + stride);
     __builtin_amdgcn_sched_barrier(0);  // every gather of the step is in flight before the first is consumed
     float p[2][4];
     float tmax = -INFINITY;
@@ -818,7 +822,7 @@ __global__ __launch_bounds__(kGroupWaves * kWave, 2) void attn_group_mfma_kernel
       const attn_f32x4 s = KC == 2 ? sc[0] + sc[1] : (sc[0] + sc[1]) + (sc[KC - 2] + sc[KC - 1]);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const bool valid = t0 + 16 * t + 4 * kb + v < w_end;
+        const bool valid = t0 + 16 * t + 4 * kb + v < total;
         p[t][v] = s[v];
         tmax = fmaxf(tmax, valid ? s[v] * a.sm_scale_log2 : -INFINITY);
       }
@@ -850,7 +854,7 @@ __global__ __launch_bounds__(kGroupWaves * kWave, 2) void attn_group_mfma_kernel
 #pragma unroll
         for (int o = 0; o < 2; ++o) {
           // one rounding for the scaled score and its distance to the maximum
-          const bool valid = t0 + 16 * t + 4 * kb + 2 * h + o < w_end;
+          const bool valid = t0 + 16 * t + 4 * kb + 2 * h + o < total;
           const float x = valid ? exp2_safe(fmaf(p[t][2 * h + o], a.sm_scale_log2, -m_ref)) : 0.f;
           l += x;
           w[0][o] = __float_as_uint(x) & 0xFFFF0000u;
@@ -933,7 +937,6 @@ tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
   a.counters = L.counters;
   a.Hq = d.Hq;
   a.g = d.Hq / d.Hkv;
-  a.rows_per_wg = L.plan.rows_per_wg;
   a.nsplit = L.plan.nsplit;
   a.Kbuf = L.Kbuf;
   a.Vbuf = L.Vbuf;
