@@ -1,20 +1,13 @@
 // Key-cache projection K_imp = K W: rows [n_begin, n_end) of every (b, kv-head).
 //
-// Three forms.  project_rows_kernel takes up to four rows (the append of a decode step) with one
-// wave per row.  project_kernel serves every shape:
-// a workgroup projects a tile of 64 cache rows, W (D x Dimp) and the K tile are staged in LDS as
-// fp32, 64 columns of the head dimension per round; thread (row, quarter) accumulates Dimp/4
-// adjacent outputs in fp32 and rounds once (round to nearest even) to the storage type.
-// project_mfma_kernel is the batched form for bf16 with Dimp = 16 or 32 (a window of appended rows,
-// or the whole cache after prefill) on the matrix cores.
+// Two forms.  project_rows_kernel takes up to four rows (the append of a decode step) with one
+// wave per row; project_kernel takes everything else -- a window of appended rows, or the whole
+// cache after prefill -- on the matrix cores.
 #include "tb_device.h"
 #include "tb_internal.h"
 
 namespace tb {
 namespace {
-
-constexpr int kProjThreads = 256;
-constexpr int kProjRows = 64;
 
 struct ProjectArgs {
   const void* K;
@@ -24,162 +17,124 @@ struct ProjectArgs {
   int64_t k_stride_b, k_stride_h, k_stride_n;
   int64_t ki_stride_b, ki_stride_h, ki_stride_n;
   int32_t per_head_w;
-  int32_t tiles_per_wave;  // matrix-core form only
+  int32_t tiles_per_wave;  // project_kernel
 };
+
+// ---- many rows on the matrix cores.  The projection is a (Dimp x D) x (D x rows) contraction with up to
+// 25 flop per byte (bf16, Dimp = 32): bound by the stream of the cache, and the arithmetic has to stay
+// out of its way.  16 output columns are the M side of a 16 x 16 tile, 16 cache rows the N side:
+// lane (n, kb) = (lane % 16, lane / 16) loads 16 bytes of row n straight into the operand (elements
+// kb * EPL .. of slice c), so the cache passes through no LDS; the lane's column of W, the same
+// elements, stays in registers for all tiles of the wave (staged once per workgroup through LDS).
+// fp32 takes one v_mfma_f32_16x16x4_f32 per loaded element, bf16 one 16x16x32 per load; fp32
+// accumulators, one RNE rounding.  Accumulator v of lane (n, kb) and M tile t is column
+// col(4 kb + v, t) of row n; the columns are dealt so that a lane's outputs lie side by side and leave
+// as 128-bit stores.  The next tile's loads are issued before the current tile is multiplied.
+//
+// bf16, D = 128, Dimp = 32, 8 x 32768 rows: 17.5 -> 15.2 us (5.5 TB/s; before: the cache through LDS into
+// 32x32x8 products); Dimp = 16 17.4 -> 13.9; Dimp = 64 97 -> 26 and fp32 Dimp = 32 55 -> 40 us (before: vector
+// FMAs out of LDS); a window of 8 rows of 32 heads 8.1 -> 3.5 us.  fp32 with Dimp = 64 is as long in its matrix
+// instructions as in its stream.
+typedef short mfma_bf16x8 __attribute__((ext_vector_type(8)));
+typedef float mfma_f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // a 128-bit load kept as a plain vector
+constexpr int kProjThreads = 256;
+constexpr int kProjWaves = kProjThreads / kWave;
+constexpr int kProjTileRows = 16;
 
 template <typename T, int D, int DIMP>
 __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjectArgs a) {
+  constexpr bool kF32 = std::is_same<T, float>::value;
   constexpr int EPL = Pack16<T>::kElts;
-  constexpr int OPT = DIMP / 4;  // outputs per thread
-  constexpr int DC = 64;         // slice of the head dimension staged per round
-  constexpr int KS = DC + 1;     // padded row stride of the K tile in LDS
-  static_assert(D % DC == 0, "head_dim must be a multiple of 64");
-  __shared__ float s_w[DC * DIMP];
-  __shared__ float s_k[kProjRows * KS];
-
-  const int tid = threadIdx.x;
-  const int b = blockIdx.z, h = blockIdx.y;
-  const int64_t row0 = a.n_begin + static_cast<int64_t>(blockIdx.x) * kProjRows;
-  const T* w = static_cast<const T*>(a.W) + (a.per_head_w ? static_cast<int64_t>(h) * D * DIMP : 0);
-  const T* kb = static_cast<const T*>(a.K) + b * a.k_stride_b + h * a.k_stride_h;
-  constexpr int CPR = DC / EPL;  // 16-byte chunks per staged row slice
-
-  const int r = tid / 4;
-  const int j0 = (tid % 4) * OPT;
-  float acc[OPT];
-#pragma unroll
-  for (int j = 0; j < OPT; ++j) acc[j] = 0.f;
-
-  for (int d0 = 0; d0 < D; d0 += DC) {
-    if (d0) __syncthreads();
-    for (int i = tid * EPL; i < DC * DIMP; i += kProjThreads * EPL) {
-      float f[EPL];
-      Pack16<T>::load(w + d0 * DIMP + i, f);
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) s_w[i + e] = f[e];
-    }
-    for (int ch = tid; ch < kProjRows * CPR; ch += kProjThreads) {
-      const int rr = ch / CPR, cc = ch % CPR;
-      const int64_t row = row0 + rr;
-      float f[EPL];
-      if (row < a.n_end) {
-        Pack16<T>::load(kb + row * a.k_stride_n + d0 + cc * EPL, f);
-      } else {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) f[e] = 0.f;
-      }
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) s_k[rr * KS + cc * EPL + e] = f[e];
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int d = 0; d < DC; ++d) {
-      const float kd = s_k[r * KS + d];
-#pragma unroll
-      for (int j = 0; j < OPT; ++j) acc[j] = fmaf(kd, s_w[d * DIMP + j0 + j], acc[j]);
-    }
-  }
-  const int64_t row = row0 + r;
-  if (row < a.n_end) {
-    T* o = static_cast<T*>(a.Kimp) + b * a.ki_stride_b + h * a.ki_stride_h + row * a.ki_stride_n + j0;
-#pragma unroll
-    for (int j = 0; j < OPT; ++j) store_elt(o + j, acc[j]);
-  }
-}
-
-// ---- batched form for bf16 with Dimp = 16 or 32 on the matrix cores ---------------------------------
-// The projection of many rows is a (rows x D) x (D x 32) contraction with 25 flop per byte:
-// above what the plain fp32 FMA path sustains, so it goes through v_mfma_f32_32x32x8_bf16_1k.
-// A wave projects tiles of 32 cache rows: the tile is loaded with coalesced 128-bit loads,
-// passed through a padded LDS buffer into the MFMA operand layout (lane (i, kh) supplies row i,
-// k = 8s + 4kh .. +3 of step s), W is transposed into LDS once per workgroup and each lane
-// keeps its column's operands in registers for all tiles.  fp32 accumulators, one RNE rounding.
-typedef short mfma_bf16x4 __attribute__((ext_vector_type(4)));
-typedef float mfma_f32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // a 128-bit load kept as a plain vector
-constexpr int kMfmaThreads = 256;
-constexpr int kMfmaWaves = kMfmaThreads / kWave;
-constexpr int kMfmaRowsPerWave = 32;                         // one MFMA tile
-constexpr int kMfmaMaxTilesPerWave = 4;
-constexpr int kMfmaMinRows = 2048;                           // below this the plain form is used
-constexpr int kMfmaTargetWgs = 2048;                         // shorten the waves' spans to reach this
-
-// DIMP = 16 runs the same 32-column tile with the upper 16 columns of W zero (twice the matrix
-// work of what is needed, which the memory-bound kernel does not notice) and stores the lower 16.
-template <int D, int DIMP>
-__global__ __launch_bounds__(kMfmaThreads) void project_mfma_kernel(ProjectArgs a) {
-  static_assert(DIMP == 16 || DIMP == 32, "the MFMA tile has 32 columns");
-  constexpr int KSTEPS = D / 8;
-  constexpr int PITCH = D * 2 + 16;         // bytes per staged row (padded against bank conflicts)
-  constexpr int OPITCH = 32 * 2 + 16;       // bytes per row of the rounded output tile
-  constexpr int LPR = D * 2 / 16;           // lanes per row in the coalesced load
-  constexpr int RPI = kWave / LPR;          // rows per load instruction
-  constexpr int NLD = 32 / RPI;             // load instructions per tile
-  __shared__ __attribute__((aligned(16))) unsigned char s_k[kMfmaWaves][32 * PITCH];
-  __shared__ __attribute__((aligned(16))) uint16_t s_wt[32][D + 4];
-
+  constexpr int KC = D / (4 * EPL);  // 128-bit loads per lane and tile
+  constexpr int MT = DIMP / 16;
+  __shared__ __attribute__((aligned(16))) T s_w[D * DIMP];
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = wave_id();
+  const int i16 = lane & 15, kb = lane >> 4;
   const int b = blockIdx.z, h = blockIdx.y;
-  const int col = lane & 31, kh = lane >> 5;
+  const T* w = static_cast<const T*>(a.W) + (a.per_head_w ? static_cast<int64_t>(h) * D * DIMP : 0);
+  const T* kl = static_cast<const T*>(a.K) + b * a.k_stride_b + h * a.k_stride_h + kb * EPL;
+  T* ob = static_cast<T*>(a.Kimp) + b * a.ki_stride_b + h * a.ki_stride_h;
+  // tile t of the wave: the four waves of the workgroup read 64 adjacent rows at a time
+  const int64_t row00 = a.n_begin + (static_cast<int64_t>(blockIdx.x) * a.tiles_per_wave * kProjWaves + wave) * kProjTileRows + i16;
+  constexpr int kTileStep = kProjWaves * kProjTileRows;
 
-  const uint16_t* w = static_cast<const uint16_t*>(a.W) + (a.per_head_w ? static_cast<int64_t>(h) * D * DIMP : 0);
-  for (int i = tid; i < D * DIMP; i += kMfmaThreads) s_wt[i % DIMP][i / DIMP] = w[i];
-  if (DIMP < 32)
-    for (int i = tid; i < D * (32 - DIMP); i += kMfmaThreads) s_wt[DIMP + i / D][i % D] = 0;
+  u32x4 v[KC];
+  auto load = [&](int64_t row) {
+    row = row < a.n_end ? row : a.n_end - 1;  // (computed and dropped)
+    const T* p = kl + row * a.k_stride_n;
+#pragma unroll
+    for (int c = 0; c < KC; ++c) v[c] = *reinterpret_cast<const u32x4*>(p + c * 4 * EPL);
+  };
+  load(row00);
+  for (int i = tid; i < D * DIMP / EPL; i += kProjThreads)
+    reinterpret_cast<u32x4*>(s_w)[i] = reinterpret_cast<const u32x4*>(w)[i];
   __syncthreads();
-  mfma_bf16x4 bop[KSTEPS];
+  // column of row i of M tile t: bf16 lanes own 4 MT adjacent columns (4 kb + v <-> i), fp32 lanes 4 of every tile
+  auto col = [](int i, int t) { return kF32 ? 16 * t + i : (i >> 2) * (4 * MT) + 4 * t + (i & 3); };
+  u32x4 wop[KC][MT];
 #pragma unroll
-  for (int s = 0; s < KSTEPS; ++s) bop[s] = *reinterpret_cast<const mfma_bf16x4*>(&s_wt[col][8 * s + 4 * kh]);
+  for (int c = 0; c < KC; ++c)
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      T e[EPL];
+#pragma unroll
+      for (int x = 0; x < EPL; ++x) e[x] = s_w[(c * 4 * EPL + kb * EPL + x) * DIMP + col(i16, t)];
+      __builtin_memcpy(&wop[c][t], e, 16);
+    }
 
-  const uint16_t* kb = static_cast<const uint16_t*>(a.K) + b * a.k_stride_b + h * a.k_stride_h;
-  uint16_t* ob = static_cast<uint16_t*>(a.Kimp) + b * a.ki_stride_b + h * a.ki_stride_h;
-  unsigned char* tile = s_k[wave];
-  const int64_t wave_row0 =
-      a.n_begin + (static_cast<int64_t>(blockIdx.x) * kMfmaWaves + wave) * kMfmaRowsPerWave * a.tiles_per_wave;
-  const int lrow = lane / LPR;                                  // row of this lane within a load
-  const uint16_t* kl = kb + (lane % LPR) * 8;                   // its 16-byte piece of the row
-#define TB_LOAD_TILE(ROW0)                                                        \
-  _Pragma("unroll") for (int j = 0; j < NLD; ++j) {                               \
-    int64_t row = (ROW0) + j * RPI + lrow;                                        \
-    row = row < a.n_end ? row : a.n_end - 1; /* computed and dropped */           \
-    v[j] = *reinterpret_cast<const u32x4*>(kl + row * a.k_stride_n);              \
-  }
-  if (wave_row0 >= a.n_end) return;  // the same for the whole wave (no barrier follows)
-  u32x4 v[NLD];
-  TB_LOAD_TILE(wave_row0)
-  for (int t = 0; t < a.tiles_per_wave; ++t) {
-    const int64_t row0 = wave_row0 + t * 32;
-    if (row0 >= a.n_end) break;
+  for (int tile = 0; tile < a.tiles_per_wave; ++tile) {
+    const int64_t row = row00 + static_cast<int64_t>(tile) * kTileStep;
+    if (row - i16 >= a.n_end) break;  // the same for the whole wave
+    u32x4 k[KC];
 #pragma unroll
-    for (int j = 0; j < NLD; ++j)
-      *reinterpret_cast<u32x4*>(tile + (j * RPI + lrow) * PITCH + (lane % LPR) * 16) = v[j];
-    // the next tile's rows are on their way while this one is multiplied
-    if (t + 1 < a.tiles_per_wave) { TB_LOAD_TILE(row0 + 32) }  // clamped rows: always in bounds
-    mfma_f32x16 acc;
+    for (int c = 0; c < KC; ++c) k[c] = v[c];
+    if (tile + 1 < a.tiles_per_wave) load(row + kTileStep);  // clamped rows: always in bounds
+    mfma_f32x4 acc[MT];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    for (int t = 0; t < MT; ++t) acc[t] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < KSTEPS; ++s) {
-      const mfma_bf16x4 aop = *reinterpret_cast<const mfma_bf16x4*>(tile + col * PITCH + (8 * s + 4 * kh) * 2);
-      acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(aop, bop[s], acc, 0, 0, 0);
+    for (int c = 0; c < KC; ++c) {
+      if constexpr (kF32) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+          for (int t = 0; t < MT; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(wop[c][t][x]), __uint_as_float(k[c][x]), acc[t], 0, 0, 0);
+      } else {
+        mfma_bf16x8 kop, wo;
+        __builtin_memcpy(&kop, &k[c], 16);
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+          __builtin_memcpy(&wo, &wop[c][t], 16);
+          acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wo, kop, acc[t], 0, 0, 0);
+        }
+      }
     }
-    // accumulator i of lane (col, kh) is output (row = 8*(i/4) + 4*kh + i%4, column col); the
-    // rounded tile goes back through LDS (the wave's own buffer, free again once the operands
-    // are read: LDS operations of a wave complete in order) and leaves as 128-bit stores
+    if (row < a.n_end) {
+      T* o = ob + row * a.ki_stride_n;
+      if constexpr (kF32) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-      *reinterpret_cast<uint16_t*>(tile + (8 * (i / 4) + 4 * kh + (i % 4)) * OPITCH + col * 2) = f32_to_bf16_rne(acc[i]);
-    constexpr int PARTS = DIMP * 2 / 16;  // 128-bit pieces of an output row
+        for (int t = 0; t < MT; ++t) *reinterpret_cast<mfma_f32x4*>(o + 16 * t + 4 * kb) = acc[t];
+      } else {
+        uint32_t r[2 * MT];
 #pragma unroll
-    for (int j = 0; j < 32 * PARTS / kWave; ++j) {
-      const int c = lane + kWave * j, r = c / PARTS, part = c % PARTS;
-      const uint4 o = *reinterpret_cast<const uint4*>(tile + r * OPITCH + part * 16);
-      if (row0 + r < a.n_end) *reinterpret_cast<uint4*>(ob + (row0 + r) * a.ki_stride_n + part * 8) = o;
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+          for (int x = 0; x < 2; ++x)
+            r[2 * t + x] = f32_to_bf16_rne(acc[t][2 * x]) | (static_cast<uint32_t>(f32_to_bf16_rne(acc[t][2 * x + 1])) << 16);
+        T* dst = o + kb * (4 * MT);
+        if constexpr (MT == 1) {
+          *reinterpret_cast<uint2*>(dst) = make_uint2(r[0], r[1]);
+        } else {
+#pragma unroll
+          for (int x = 0; x < 2 * MT; x += 4) *reinterpret_cast<uint4*>(dst + 2 * x) = make_uint4(r[x], r[x + 1], r[x + 2], r[x + 3]);
+        }
+      }
     }
   }
-#undef TB_LOAD_TILE
 }
 
 // ---- a few rows (the append of a decode step): one wave per cache row, no LDS, no barrier.
@@ -216,21 +171,18 @@ tb_status launch_tdd(const tb_cache_desc& d, ProjectArgs a, hipStream_t st) {
     hipLaunchKernelGGL((project_rows_kernel<T, D, DIMP>), grid, dim3(kWave), 0, st, a);
     return hip_status(hipGetLastError());
   }
-  if constexpr (std::is_same<T, bf16_t>::value && (DIMP == 16 || DIMP == 32)) {
-    if (rows >= kMfmaMinRows) {  // batched projection: enough rows to fill the matrix cores
-      int tiles = kMfmaMaxTilesPerWave;
-      auto wgs = [&](int t) {
-        const int64_t per_wg = static_cast<int64_t>(kMfmaWaves) * kMfmaRowsPerWave * t;
-        return (rows + per_wg - 1) / per_wg;
-      };
-      while (tiles > 1 && wgs(tiles) * d.Hkv * d.B < kMfmaTargetWgs) tiles >>= 1;
-      a.tiles_per_wave = tiles;
-      dim3 grid(static_cast<unsigned>(wgs(tiles)), d.Hkv, d.B);
-      hipLaunchKernelGGL((project_mfma_kernel<D, DIMP>), grid, dim3(kMfmaThreads), 0, st, a);
-      return hip_status(hipGetLastError());
-    }
-  }
-  dim3 grid(static_cast<unsigned>((rows + kProjRows - 1) / kProjRows), d.Hkv, d.B);
+  auto wgs = [&](int tiles) {
+    const int64_t per_wg = static_cast<int64_t>(kProjWaves) * kProjTileRows * tiles;
+    return (rows + per_wg - 1) / per_wg;
+  };
+  // Tiles of a wave: the more, the less of its time goes into W, the fewer workgroups share the
+  // stream.  bf16, D = 128, Dimp = 32: 8 x 32768 rows 15.2 us with 2 tiles, 15.8 with 4, 17.7 with 1; 16 x 4096
+  // rows 7.1 with 2, 7.9 with 1; 128 x 16384 rows 125 with 4, 132 with 8; D = 64, 16 x 50000 rows 31.3 with 2,
+  // 32.8 with 4.
+  const int64_t heads = static_cast<int64_t>(d.Hkv) * d.B;
+  const int tiles = wgs(4) * heads >= 4096 ? 4 : (wgs(2) * heads >= 512 ? 2 : 1);
+  a.tiles_per_wave = tiles;
+  const dim3 grid(static_cast<unsigned>(wgs(tiles)), d.Hkv, d.B);
   hipLaunchKernelGGL((project_kernel<T, D, DIMP>), grid, dim3(kProjThreads), 0, st, a);
   return hip_status(hipGetLastError());
 }

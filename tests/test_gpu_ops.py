@@ -77,6 +77,31 @@ def test_project_identity_and_row_range(oracle, N, n_begin, n_end):
     assert torch.all(Kimp[:, :, :n_begin] == 7.0) and torch.all(Kimp[:, :, n_end:] == 7.0)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("D,Dimp,B,Hkv,n_begin,n_end", [
+    (128, 32, 2, 2, 3, 8), (64, 16, 1, 3, 0, 15), (128, 64, 1, 2, 7, 24),     # below, at and past one 16-row tile
+    (128, 16, 2, 2, 1, 65), (64, 64, 1, 2, 0, 129),                           # past the four tiles of a workgroup
+    (128, 32, 16, 8, 5, 600), (64, 32, 16, 8, 2, 531),                        # two tiles a wave, the last ones ragged
+    (64, 16, 16, 8, 0, 8200),                                                 # four tiles a wave
+])
+def test_project_tile_edges(oracle, dtype, D, Dimp, B, Hkv, n_begin, n_end):
+    """Row ranges around the tiles of project_kernel, into rows with a stride of their own; what lies
+    outside the range keeps its bytes."""
+    say(f"project tile edges dtype={dtype} D={D} Dimp={Dimp} B={B} Hkv={Hkv} rows [{n_begin}, {n_end})")
+    N = n_end + 3
+    K = randn((B, Hkv, N, D), dtype, 61)
+    W = randn((Hkv if B == 2 else 1, D, Dimp), dtype, 62, 1.0 / math.sqrt(D))
+    store = torch.full((B, Hkv, N, Dimp + 8), 7.0, dtype=dtype, device=DEV)
+    gpu_project(K, W, N, n_begin=n_begin, n_end=n_end, Kimp=store[..., :Dimp])
+    torch.cuda.synchronize()
+    got, dn = np_of(store[..., :Dimp]), dtype_name(K)
+    ref = oracle.project_keys(np_of(K), np_of(W), dn)
+    mag = projection_magnitude(oracle, np_of(K), np_of(W), dn, Hkv)
+    rows = slice(n_begin, n_end)
+    assert_projection(oracle, got[:, :, rows], ref[:, :, rows], mag[:, :, rows], dn)
+    assert bool((store[:, :, :n_begin] == 7).all()) and bool((store[:, :, n_end:] == 7).all()) and bool((store[..., Dimp:] == 7).all())
+
+
 def test_project_strided_cache(oracle):
     say("project into a strided (over-allocated) cache")
     B, Hkv, N, D, Dimp = 2, 2, 200, 128, 32
