@@ -23,31 +23,58 @@ struct ProjectArgs {
 // ---- many rows on the matrix cores.  The projection is a (Dimp x D) x (D x rows) contraction with up to
 // 25 flop per byte (bf16, Dimp = 32): bound by the stream of the cache, and the arithmetic has to stay
 // out of its way.  16 output columns are the M side of a 16 x 16 tile, 16 cache rows the N side:
-// lane (n, kb) = (lane % 16, lane / 16) loads 16 bytes of row n straight into the operand (elements
-// kb * EPL .. of slice c), so the cache passes through no LDS; the lane's column of W, the same
-// elements, stays in registers for all tiles of the wave (staged once per workgroup through LDS).
-// fp32 takes one v_mfma_f32_16x16x4_f32 per loaded element, bf16 one 16x16x32 per load; fp32
-// accumulators, one RNE rounding.  Accumulator v of lane (n, kb) and M tile t is column
+// lane (n, kb) = (lane % 16, lane / 16) loads 16 bytes of row n (elements kb * EPL .. of slice c), so the
+// cache passes through no LDS; the lane's part of W stays in registers for all tiles of the wave
+// (staged once per workgroup through LDS).  Accumulator v of lane (n, kb) and M tile t is column
 // col(4 kb + v, t) of row n; the columns are dealt so that a lane's outputs lie side by side and leave
-// as 128-bit stores.  The next tile's loads are issued before the current tile is multiplied.
+// as 128-bit stores.  fp32 accumulators, one RNE rounding.  The next tile's loads are issued before
+// the current tile is multiplied.
 //
-// bf16, D = 128, Dimp = 32, 8 x 32768 rows: 17.5 -> 15.2 us (5.5 TB/s; before: the cache through LDS into
-// 32x32x8 products); Dimp = 16 17.4 -> 13.9; Dimp = 64 97 -> 26 and fp32 Dimp = 32 55 -> 40 us (before: vector
-// FMAs out of LDS); a window of 8 rows of 32 heads 8.1 -> 3.5 us.  fp32 with Dimp = 64 is as long in its matrix
-// instructions as in its stream.
+// Two forms.  From 2048 rows on, bf16 with Dimp = 16 or 32 takes one 16x16x32 product per load and M
+// tile.  Everything else (fp32, Dimp = 64, fewer rows) takes v_mfma_f32_16x16x4_f32, whose sum is the chain
+// of fused multiply-adds over its four inputs: with the elements in the order of the head dimension
+// (a 4 x 4 transposition over the lanes of a row) the results are those of a scalar chain, bit for bit,
+// which is what these shapes have always returned.  bf16 with Dimp = 64 would stream at 26 us instead
+// of 53 below in the other form, with other roundings of one value in 10^4.
+//
+// D = 128, 8 x 32768 rows: bf16 Dimp = 32 17.5 -> 15.2 us (5.5 TB/s; before: the cache through LDS into
+// 32x32x8 products), Dimp = 16 17.5 -> 14.0; before with vector FMAs out of LDS: Dimp = 64 97 -> 53, fp32
+// Dimp = 32 55 -> 41, fp32 Dimp = 64 (24 x 20001 rows) 166 -> 103 us, a window of 8 rows of 32 heads 8.1 -> 4.4 us.
+// The fp32 products bound the chain form with Dimp = 64, the stream the others.
 typedef short mfma_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float mfma_f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // a 128-bit load kept as a plain vector
 constexpr int kProjThreads = 256;
 constexpr int kProjWaves = kProjThreads / kWave;
 constexpr int kProjTileRows = 16;
+constexpr int kProjBf16Rows = 2048;  // bf16 products from here on
 
-template <typename T, int D, int DIMP>
+// 4 x 4 transposition of the registers f[0..3] over the four lanes (n, 0..3): afterwards register r of
+// lane (n, kb) is what register kb of lane (n, r) was.
+__device__ inline void lane_transpose4(uint32_t (&f)[4]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const auto x = __builtin_amdgcn_permlane32_swap(f[i], f[i + 2], false, false);
+    f[i] = x[0];
+    f[i + 2] = x[1];
+  }
+#pragma unroll
+  for (int i = 0; i < 4; i += 2) {
+    const auto x = __builtin_amdgcn_permlane16_swap(f[i], f[i + 1], false, false);
+    f[i] = x[0];
+    f[i + 1] = x[1];
+  }
+}
+
+// CHAIN: fp32 products in the order of the head dimension (v_mfma_f32_16x16x4_f32, the four lanes of
+// a row hold elements 4 s .. 4 s + 3 at step s); otherwise bf16 products.
+template <typename T, int D, int DIMP, bool CHAIN>
 __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjectArgs a) {
   constexpr bool kF32 = std::is_same<T, float>::value;
   constexpr int EPL = Pack16<T>::kElts;
   constexpr int KC = D / (4 * EPL);  // 128-bit loads per lane and tile
   constexpr int MT = DIMP / 16;
+  static_assert(CHAIN || !kF32, "fp32 has the chain only");
   __shared__ __attribute__((aligned(16))) T s_w[D * DIMP];
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
@@ -61,6 +88,7 @@ __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjectArgs a) {
   const int64_t row00 = a.n_begin + (static_cast<int64_t>(blockIdx.x) * a.tiles_per_wave * kProjWaves + wave) * kProjTileRows + i16;
   constexpr int kTileStep = kProjWaves * kProjTileRows;
 
+  using Raw = typename Pack16<T>::Raw;
   u32x4 v[KC];
   auto load = [&](int64_t row) {
     row = row < a.n_end ? row : a.n_end - 1;  // (computed and dropped)
@@ -74,16 +102,23 @@ __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjectArgs a) {
   __syncthreads();
   // column of row i of M tile t: bf16 lanes own 4 MT adjacent columns (4 kb + v <-> i), fp32 lanes 4 of every tile
   auto col = [](int i, int t) { return kF32 ? 16 * t + i : (i >> 2) * (4 * MT) + 4 * t + (i & 3); };
-  u32x4 wop[KC][MT];
+  u32x4 wop[CHAIN ? 1 : KC][MT];
+  float wst[CHAIN ? D / 4 : 1][MT];
 #pragma unroll
-  for (int c = 0; c < KC; ++c)
+  for (int t = 0; t < MT; ++t) {
+    if constexpr (CHAIN) {
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      T e[EPL];
+      for (int st = 0; st < D / 4; ++st) wst[st][t] = to_float(s_w[(4 * st + kb) * DIMP + col(i16, t)]);
+    } else {
 #pragma unroll
-      for (int x = 0; x < EPL; ++x) e[x] = s_w[(c * 4 * EPL + kb * EPL + x) * DIMP + col(i16, t)];
-      __builtin_memcpy(&wop[c][t], e, 16);
+      for (int c = 0; c < KC; ++c) {
+        T e[EPL];
+#pragma unroll
+        for (int x = 0; x < EPL; ++x) e[x] = s_w[(c * 4 * EPL + kb * EPL + x) * DIMP + col(i16, t)];
+        __builtin_memcpy(&wop[c][t], e, 16);
+      }
     }
+  }
 
   for (int tile = 0; tile < a.tiles_per_wave; ++tile) {
     const int64_t row = row00 + static_cast<int64_t>(tile) * kTileStep;
@@ -97,12 +132,26 @@ __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjectArgs a) {
     for (int t = 0; t < MT; ++t) acc[t] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
-      if constexpr (kF32) {
+      if constexpr (CHAIN) {
+        Raw raw;
+        __builtin_memcpy(&raw, &k[c], 16);
+        float f[EPL];
+        Pack16<T>::unpack(raw, f);
 #pragma unroll
-        for (int x = 0; x < 4; ++x)
+        for (int g = 0; g < EPL / 4; ++g) {  // elements EPL kb + 4 g .. + 3 of every lane
+          uint32_t x[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) x[i] = __float_as_uint(f[4 * g + i]);
+          lane_transpose4(x);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) f[4 * g + i] = __uint_as_float(x[i]);
+        }
+        // register i of group g now belongs to step (EPL i + 4 g) / 4 of this slice
+#pragma unroll
+        for (int st = 0; st < EPL; ++st)
 #pragma unroll
           for (int t = 0; t < MT; ++t)
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(wop[c][t][x]), __uint_as_float(k[c][x]), acc[t], 0, 0, 0);
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wst[c * EPL + st][t], f[4 * (st % (EPL / 4)) + st / (EPL / 4)], acc[t], 0, 0, 0);
       } else {
         mfma_bf16x8 kop, wo;
         __builtin_memcpy(&kop, &k[c], 16);
@@ -183,7 +232,13 @@ tb_status launch_tdd(const tb_cache_desc& d, ProjectArgs a, hipStream_t st) {
   const int tiles = wgs(4) * heads >= 4096 ? 4 : (wgs(2) * heads >= 512 ? 2 : 1);
   a.tiles_per_wave = tiles;
   const dim3 grid(static_cast<unsigned>(wgs(tiles)), d.Hkv, d.B);
-  hipLaunchKernelGGL((project_kernel<T, D, DIMP>), grid, dim3(kProjThreads), 0, st, a);
+  if constexpr (std::is_same<T, bf16_t>::value && DIMP <= 32) {
+    if (rows >= kProjBf16Rows) {
+      hipLaunchKernelGGL((project_kernel<T, D, DIMP, false>), grid, dim3(kProjThreads), 0, st, a);
+      return hip_status(hipGetLastError());
+    }
+  }
+  hipLaunchKernelGGL((project_kernel<T, D, DIMP, true>), grid, dim3(kProjThreads), 0, st, a);
   return hip_status(hipGetLastError());
 }
 
