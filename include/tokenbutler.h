@@ -166,6 +166,12 @@ tb_status tb_gather_important(const tb_cache_desc* desc, const void* K, const vo
                               int32_t skip_back, void* Kbuf, void* Vbuf, int64_t buf_cap, int32_t* count_out,
                               void* stream);
 
+/* Arrival of new rows in a buffer (the Local Window ring of Sec. 3.3): one launch for K and V of every
+ * KV head.  Kdst/Vdst[b,h,dst_row + i,:] = K/V[b,h,src_row + i,:] for 0 <= i < rows.  src and dst describe
+ * the two places (same B, Hkv, D and dtype; strides as everywhere, rows [0, desc->N)); they must not overlap. */
+tb_status tb_append_kv(const tb_cache_desc* src, const void* K, const void* V, int64_t src_row, const tb_cache_desc* dst,
+                       void* Kdst, void* Vdst, int64_t dst_row, int64_t rows, void* stream);
+
 /* tb_sparse_decode_attn over rows that tb_gather_kv has migrated: the rows 0 .. count[b,h]-1 of
  * the per-query-head buffers (no index list is read) followed by the dense range
  * [tail_begin, tail_end) of the cache K, V (the local window of tokens appended since the

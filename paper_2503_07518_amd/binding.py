@@ -23,7 +23,7 @@ TB_OP_SELECT, TB_OP_ATTN, TB_OP_DECODE_STEP = 1, 2, 3
 EXPORTS = (
     "tb_project_keys", "tb_score", "tb_select_topk", "tb_expand_neighbors", "tb_sparse_decode_attn",
     "tb_sparse_decode_attn_shared", "tb_sparse_decode_attn_static",
-    "tb_gather_kv", "tb_gather_important", "tb_buffered_decode_attn", "tb_predict_queries", "tb_decode_step", "tb_workspace_bytes", "tb_workspace_init", "tb_read_stream_probe", "tb_status_string", "tb_version",
+    "tb_gather_kv", "tb_gather_important", "tb_append_kv", "tb_buffered_decode_attn", "tb_predict_queries", "tb_decode_step", "tb_workspace_bytes", "tb_workspace_init", "tb_read_stream_probe", "tb_status_string", "tb_version",
 )
 
 
@@ -76,6 +76,7 @@ def load_library() -> ctypes.CDLL:
                                  vp, sz, vp]
     L.tb_gather_kv.argtypes = [dp, vp, vp, vp, vp, i64, i64, vp, vp, i64, vp]
     L.tb_gather_important.argtypes = [dp, vp, vp, vp, vp, i64, i64, i32, i32, vp, vp, i64, vp, vp]
+    L.tb_append_kv.argtypes = [dp, vp, vp, i64, dp, vp, vp, i64, i64, vp]
     L.tb_buffered_decode_attn.argtypes = [dp, vp, vp, vp, i64, vp, i64, vp, vp, i64, i64, f32, vp, vp, vp, sz, vp]
     L.tb_predict_queries.argtypes = [ctypes.POINTER(tb_predictor_desc), i32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
     L.tb_workspace_bytes.argtypes = [i32, dp, i64]
@@ -101,13 +102,14 @@ def _check(code: int, what: str) -> None:
         raise TbError(code, what)
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+# (plain integers: the argument types turn them into pointers, at a third of the cost of c_void_p objects)
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream=None):
+def _stream(stream=None) -> int:
     s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return s.cuda_stream
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -121,8 +123,9 @@ def _dtype_code(t: torch.Tensor) -> int:
 def _strides3(t: Optional[torch.Tensor], inner: int) -> Tuple[int, int, int]:
     if t is None:
         return (0, 0, inner)
-    assert t.dim() == 4 and t.stride(3) == 1, "cache tensors are [B, Hkv, N, D] with D contiguous"
-    return (t.stride(0), t.stride(1), t.stride(2))
+    st = t.stride()
+    assert len(st) == 4 and st[3] == 1, "cache tensors are [B, Hkv, N, D] with D contiguous"
+    return st[:3]
 
 
 def make_desc(N: int, Hq: int, K: Optional[torch.Tensor] = None, V: Optional[torch.Tensor] = None,
@@ -134,12 +137,8 @@ def make_desc(N: int, Hq: int, K: Optional[torch.Tensor] = None, V: Optional[tor
     B, Hkv = ref.shape[0], ref.shape[1]
     D = D if D is not None else (K.shape[3] if K is not None else (V.shape[3] if V is not None else 128))
     Dimp = Dimp if Dimp is not None else (Kimp.shape[3] if Kimp is not None else 32)
-    d = tb_cache_desc()
-    d.B, d.Hq, d.Hkv, d.D, d.Dimp, d.dtype, d.N = B, Hq, Hkv, D, Dimp, _dtype_code(ref), N
-    d.k_stride_b, d.k_stride_h, d.k_stride_n = _strides3(K, D)
-    d.v_stride_b, d.v_stride_h, d.v_stride_n = _strides3(V if V is not None else K, D)
-    d.ki_stride_b, d.ki_stride_h, d.ki_stride_n = _strides3(Kimp, Dimp)
-    return d
+    return tb_cache_desc(B, Hq, Hkv, D, Dimp, _dtype_code(ref), N, *_strides3(K, D), *_strides3(V if V is not None else K, D),
+                         *_strides3(Kimp, Dimp))
 
 
 def tb_version() -> int:
@@ -201,6 +200,12 @@ def tb_gather_important(desc, K, V, idx, count, max_count: int, skip_front: int,
     _check(load_library().tb_gather_important(ctypes.byref(desc), _ptr(K), _ptr(V), _ptr(idx), _ptr(count),
                                               idx.stride(-2), max_count, skip_front, skip_back, _ptr(Kbuf), _ptr(Vbuf),
                                               Kbuf.shape[2], _ptr(count_out), _stream(stream)), "tb_gather_important")
+
+
+def tb_append_kv(src, K, V, src_row: int, dst, Kdst, Vdst, dst_row: int, rows: int = 1, stream=None) -> None:
+    """Kdst/Vdst[b, h, dst_row + i] = K/V[b, h, src_row + i] for i < rows, every KV head of the batch."""
+    _check(load_library().tb_append_kv(ctypes.byref(src), _ptr(K), _ptr(V), src_row, ctypes.byref(dst), _ptr(Kdst), _ptr(Vdst), dst_row,
+                                       rows, _stream(stream)), "tb_append_kv")
 
 
 def tb_buffered_decode_attn(desc, q, Kbuf, Vbuf, count, max_count: int, K, V, sm_scale: float, out, lse, ws,

@@ -399,6 +399,22 @@ tb_status tb_gather_important(const tb_cache_desc* d, const void* K, const void*
   return launch_gather(L, static_cast<hipStream_t>(stream));
 }
 
+tb_status tb_append_kv(const tb_cache_desc* src, const void* K, const void* V, int64_t src_row, const tb_cache_desc* dst,
+                       void* Kdst, void* Vdst, int64_t dst_row, int64_t rows, void* stream) {
+  TB_TRY(check_desc(src));
+  TB_TRY(check_desc(dst));
+  if (!K || !V || !Kdst || !Vdst || rows < 0 || src_row < 0 || dst_row < 0) return TB_ERR_INVALID_ARG;
+  if (src->B != dst->B || src->Hkv != dst->Hkv || src->D != dst->D || src->dtype != dst->dtype) return TB_ERR_INVALID_ARG;
+  if (rows > src->N - src_row || rows > dst->N - dst_row) return TB_ERR_INVALID_ARG;
+  for (const tb_cache_desc* d : {src, dst}) {
+    TB_TRY(check_strides(d, d->k_stride_b, d->k_stride_h, d->k_stride_n, d->D));
+    TB_TRY(check_strides(d, d->v_stride_b, d->v_stride_h, d->v_stride_n, d->D));
+  }
+  if (!aligned16(K) || !aligned16(V) || !aligned16(Kdst) || !aligned16(Vdst)) return TB_ERR_UNSUPPORTED;
+  if (rows > (int64_t{1} << 20)) return TB_ERR_UNSUPPORTED;
+  return launch_append(*src, K, V, src_row, *dst, Kdst, Vdst, dst_row, rows, static_cast<hipStream_t>(stream));
+}
+
 tb_status tb_buffered_decode_attn(const tb_cache_desc* d, const void* q, const void* Kbuf, const void* Vbuf,
                                   int64_t buf_cap, const int32_t* count, int64_t max_count, const void* K,
                                   const void* V, int64_t tail_begin, int64_t tail_end, float sm_scale, float* out,

@@ -123,6 +123,8 @@ struct GatherLaunch {
   int32_t* count_out = nullptr;           // receives count - skip_front - skip_back (>= 0) per list
 };
 tb_status launch_gather(const GatherLaunch& a, hipStream_t st);
+tb_status launch_append(const tb_cache_desc& src, const void* K, const void* V, int64_t src_row, const tb_cache_desc& dst, void* Kdst,
+                        void* Vdst, int64_t dst_row, int64_t rows, hipStream_t st);
 int attn_tile_rows_per_wg(int dtype, int D);
 constexpr int kAttnGroupWaves = 8;    // waves of a workgroup that serves a KV group on the matrix cores
 constexpr int kAttnLoadsPerTile = 4;  // K (and V) gathers of a lane per tile

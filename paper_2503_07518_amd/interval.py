@@ -128,9 +128,8 @@ class RingLayoutDecoder:
     and appended to the projected-key cache.  Tokens in the ring are attended without a score,
     so the selection never needs a projected key that does not exist yet.
 
-    Moving the model's new K/V row into the ring (and the first ``sink`` rows into the Sink
-    Buffer) is data arrival, done here with a plain device copy; everything that computes is a
-    library call.
+    Moving the first ``sink`` rows into the Sink Buffer is data arrival, done here with a plain device
+    copy; the model's new K/V row reaches the ring through ``tb_append_kv`` (one launch for both).
     """
 
     def __init__(self, K, V, W, Kimp, Hq: int, k: int, P: int, radius: int, ring: int, sink: int = 0,
@@ -168,8 +167,8 @@ class RingLayoutDecoder:
         S, R = self.sink, self.ring
         if t > 0:  # the token appended before this step arrives in the ring
             slot = (t - 1) % R
-            self.aux_K[:, :, S + slot].copy_(self.K[:, :, N_t - 1])
-            self.aux_V[:, :, S + slot].copy_(self.V[:, :, N_t - 1])
+            tb.tb_append_kv(tb.make_desc(self.Ncap, self.Hq, K=self.K, V=self.V), self.K, self.V, N_t - 1,
+                            tb.make_desc(S + R, self.Hq, K=self.aux_K, V=self.aux_V), self.aux_K, self.aux_V, S + slot)
             if t % R == 0:
                 # the head is back at slot 0: slot i holds token N_t - R + i; project the R keys of
                 # the ring in one batch and append them to the projected-key cache

@@ -173,3 +173,23 @@ def test_ring_layout_interval_loop(oracle, mode):
         ro, rl = oracle.sparse_decode_attn(np_of(data["q"][t]), Kn[:, :, :N_t], Vn[:, :, :N_t], u_idx, u_cnt, cfg.dtype,
                                            cfg.sm_scale)
         assert_attention(np_of(recs[t][0]), ro, cfg.dtype, np_of(recs[t][1]), rl, what=f"step {t}")
+
+
+@pytest.mark.parametrize("dtype,D,rows", [(torch.bfloat16, 64, 1), (torch.bfloat16, 128, 1), (torch.float32, 128, 1), (torch.float32, 64, 37)])
+def test_append_kv(dtype, D, rows):
+    """Rows of strided caches into a buffer: the named rows change, byte for byte, and nothing else."""
+    say(f"append rows dtype={dtype} D={D} rows={rows}")
+    B, Hkv, N, R = 3, 2, 90, 50
+    g = torch.Generator().manual_seed(71)
+    K, V = (torch.randn((B, N, Hkv, D), generator=g).to(dtype).to(DEV).transpose(1, 2) for _ in range(2))  # strides of their own
+    dK, dV = (torch.randn((B, Hkv, R, D), generator=g).to(dtype).to(DEV) for _ in range(2))
+    rK, rV = dK.clone(), dV.clone()
+    rK[:, :, 5:5 + rows] = K[:, :, 40:40 + rows]
+    rV[:, :, 5:5 + rows] = V[:, :, 40:40 + rows]
+    src, dst = tb.make_desc(N, Hkv, K=K, V=V), tb.make_desc(R, Hkv, K=dK, V=dV)
+    tb.tb_append_kv(src, K, V, 40, dst, dK, dV, 5, rows)
+    torch.cuda.synchronize()
+    assert torch.equal(dK, rK) and torch.equal(dV, rV)
+    for bad in ((N - rows + 1, 0), (0, R - rows + 1), (-1, 0)):
+        with pytest.raises(tb.TbError):
+            tb.tb_append_kv(src, K, V, bad[0], dst, dK, dV, bad[1], rows)
