@@ -105,8 +105,8 @@ tb_status launch_td(const GatherLaunch& L, hipStream_t st) {
 }
 
 // Arrival of new rows: one 16-byte piece of K and one of V per thread, all KV heads of the batch in one
-// launch.  Bound by its launch (two elementwise copies of one row of 16 heads each: 2 x 2.3 us and the gap
-// between them; this: 2.6 us).
+// launch.  Bound by its launch (two elementwise copies of one row of 16 heads each: 2 x 3.0 us and the gap
+// between them; this: 4.4 us, the row cold).
 struct AppendArgs {
   const char* src[2];
   char* dst[2];
