@@ -512,7 +512,8 @@ tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
   if (hipGetLastError() != hipSuccess) return TB_ERR_HIP;
   const unsigned out_tiles = static_cast<unsigned>((a.G * a.Hq * a.Dimp + 15) / 16);
   if constexpr (MT == 1) {
-    if (slices > 1 && static_cast<int64_t>(a.B) * a.hidden <= kFoldElements) {
+    // (up to two sequences: the folding kernel has no workgroups that write LN(h))
+    if (slices > 1 && a.B <= 2 && a.B * a.hidden <= kFoldElements) {
       hipLaunchKernelGGL((output_kernel<T, 1, true>), dim3(out_tiles), dim3(kPredThreads), 0, st, a, slices);
       return hip_status(hipGetLastError());
     }

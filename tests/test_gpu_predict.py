@@ -62,6 +62,11 @@ def test_predict_queries(oracle, dtype, B, E, hidden, G, Hq, Dimp):
     (torch.float32, 1, 5120, 512, 1, 8, 16),
     (torch.float32, 7, 3000, 520, 2, 4, 16),     # ragged last step and slice
     (torch.float32, 33, 64, 8, 3, 2, 8),         # two workgroup groups along the batch, sizes below one step
+    # several slices and few hidden activations: more than two sequences still get LN(h)
+    (torch.bfloat16, 4, 4096, 128, 1, 4, 8),
+    (torch.float32, 3, 2048, 160, 1, 4, 8),
+    (torch.bfloat16, 16, 1024, 32, 1, 4, 8),
+    (torch.float32, 2, 4096, 128, 1, 4, 8),      # two sequences: summed by the output kernel
 ])
 def test_predict_split_layers(oracle, dtype, B, E, hidden, G, Hq, Dimp):
     """Edges of the tiles, steps and slices; z starts 4 bytes off a 16-byte boundary.  Bars of
