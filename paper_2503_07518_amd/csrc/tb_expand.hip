@@ -25,12 +25,13 @@ constexpr int kExpThreads = 1024;
 constexpr int kExpWaves = kExpThreads / kWave;
 
 constexpr int kExpStaged = 16384;  // entries of a list that are staged in LDS
+constexpr int64_t kExpMaxEntries = int64_t{1} << 30;  // N, and so an ascending list, is no longer
 
 struct ExpandArgs {
   int32_t N, radius;
   const int32_t* idx_in;
   const int32_t* count_in;
-  int64_t cap_in;
+  int64_t cap_in;  // also the distance between two lists
   int32_t* idx_out;
   int32_t* count_out;
   int64_t cap_out;
@@ -44,7 +45,8 @@ __device__ inline const int32_t* open_list(const ExpandArgs& a, int& c, int& j0,
   const int64_t u = blockIdx.x;
   const int32_t* in = a.idx_in + u * a.cap_in;
   const int64_t cnt = a.count_in[u];
-  c = static_cast<int>(cnt < 0 ? 0 : (cnt > a.cap_in ? a.cap_in : cnt));
+  const int64_t most = a.cap_in < kExpMaxEntries ? a.cap_in : kExpMaxEntries;
+  c = static_cast<int>(cnt < 0 ? 0 : (cnt > most ? most : cnt));
   const int per = (c + kExpThreads - 1) / kExpThreads;
   j0 = min(static_cast<int>(threadIdx.x) * per, c);
   j1 = min(j0 + per, c);
@@ -192,7 +194,6 @@ tb_status launch_expand(int64_t units, int64_t N, int32_t radius, int32_t mode, 
                         const int32_t* count_in, int64_t cap_in, int32_t* idx_out, int32_t* count_out,
                         int64_t cap_out, hipStream_t st) {
   if (units == 0) return TB_OK;
-  if (cap_in > (int64_t{1} << 30)) cap_in = int64_t{1} << 30;
   ExpandArgs a{static_cast<int32_t>(N), radius, idx_in, count_in, cap_in, idx_out, count_out, cap_out};
   const dim3 grid(static_cast<unsigned>(units)), block(kExpThreads);
   const bool staged = cap_in <= kExpStaged;

@@ -407,6 +407,27 @@ def test_expand_neighbors(oracle, N, count_max, radius, mode):
     assert np.all(go[~mask] == -7)
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+def test_expand_capacity_beyond_30_bits(oracle, mode):
+    """Lists that lie more than 2^30 entries apart: every unit reads its own."""
+    say(f"expand, lists 2^30 + 16 entries apart, mode={mode}")
+    cap, N = (1 << 30) + 16, 1000
+    idx = torch.zeros((1, 2, cap), dtype=torch.int32, device=DEV)
+    lists = [[3, 4, 500, 999], [7, 100, 101, 102, 640]]
+    cnt = torch.tensor([[len(l) for l in lists]], dtype=torch.int32, device=DEV)
+    for u, l in enumerate(lists):
+        idx[0, u, :len(l)] = torch.tensor(l, dtype=torch.int32)
+    small = np_of(idx[:, :, :8])
+    out, oc = gpu_expand(idx, cnt, N, 1, mode)
+    torch.cuda.synchronize()
+    del idx
+    torch.cuda.empty_cache()
+    ro, rc = oracle.expand_neighbors(small, np_of(cnt), N, 1, cap_out=N, mode=mode)
+    assert np.array_equal(np_of(oc), rc)
+    for u in range(2):
+        assert np.array_equal(np_of(out)[0, u, :rc[0, u]], ro[0, u, :rc[0, u]])
+
+
 # --------------------------------------------------------------------------- attention
 
 @pytest.mark.parametrize("dtype,B,Hq,Hkv,D,N,count_max", [
