@@ -24,7 +24,10 @@ namespace {
 constexpr int kExpThreads = 1024;
 constexpr int kExpWaves = kExpThreads / kWave;
 
-constexpr int kExpStaged = 16384;  // entries of a list that are staged in LDS
+// Entries of a list that are staged in LDS: what 64 KiB hold beside the kernels' own arrays, so that no
+// launch has to ask for a larger limit.
+constexpr int kExpOwnLds = 256;
+constexpr int kExpStaged = (64 * 1024 - kExpOwnLds) / 4;
 constexpr int64_t kExpMaxEntries = int64_t{1} << 30;  // N, and so an ascending list, is no longer
 
 struct ExpandArgs {
@@ -130,6 +133,7 @@ template <bool STAGED>
 __global__ __launch_bounds__(kExpThreads) void expand_cluster_kernel(ExpandArgs a) {
   __shared__ uint32_t s_wave[kExpWaves];
   __shared__ DebtMap s_map[kExpWaves];
+  static_assert(sizeof(s_wave) + sizeof(s_map) <= kExpOwnLds, "the staged list and these fit 64 KiB");
   const int lane = lane_id(), wave = wave_id();
   int c, j0, j1;
   const int32_t* in = open_list<STAGED>(a, c, j0, j1);

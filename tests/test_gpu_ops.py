@@ -428,6 +428,29 @@ def test_expand_capacity_beyond_30_bits(oracle, mode):
         assert np.array_equal(np_of(out)[0, u, :rc[0, u]], ro[0, u, :rc[0, u]])
 
 
+@pytest.mark.parametrize("N,cap,counts", [
+    (100000, 16319, (16319, 9000, 0)), (100000, 16320, (16320, 16319, 1)),   # the longest lists staged in LDS
+    (100000, 16321, (16321, 16320, 2)), (100000, 16384, (16384, 16383, 5)),  # and the shortest that are not
+    (70000, 60000, (60000, 59999, 1023)), (50000, 50000, (50000, 1025, 1)),  # several tens of entries a thread; every position
+])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_expand_long_lists(oracle, N, cap, counts, mode):
+    """Either side of the length up to which a list is staged, and well beyond it."""
+    say(f"expand long lists N={N} cap={cap} counts={counts} mode={mode}")
+    rng = np.random.default_rng(N + cap)
+    idx = np.full((1, len(counts), cap), -1, np.int32)
+    for u, c in enumerate(counts):
+        idx[0, u, :c] = np.sort(rng.choice(N, c, replace=False))
+    cnt = np.asarray([counts], np.int32)
+    out, oc = gpu_expand(torch.from_numpy(idx).to(DEV), torch.from_numpy(cnt).to(DEV), N, 1, mode)
+    torch.cuda.synchronize()
+    ro, rc = oracle.expand_neighbors(idx, cnt, N, 1, cap_out=out.shape[-1], mode=mode)
+    go = np_of(out)
+    assert np.array_equal(np_of(oc), rc)
+    mask = np.arange(go.shape[-1])[None, None, :] < rc[..., None]
+    assert np.array_equal(np.where(mask, go, -1), np.where(mask, ro, -1)) and np.all(go[~mask] == -7)
+
+
 # --------------------------------------------------------------------------- attention
 
 @pytest.mark.parametrize("dtype,B,Hq,Hkv,D,N,count_max", [
