@@ -78,6 +78,13 @@ __device__ inline uint16_t f32_to_bf16_rne(float f) {
   return static_cast<uint16_t>(b >> 16);
 }
 
+// Two packed bf16 numbers, the infinite and NaN ones among them replaced by 0.
+__device__ inline uint32_t bf16x2_finite_or_zero(uint32_t w) {
+  const uint32_t lo = (w & 0x7F80u) == 0x7F80u ? 0u : 0xFFFFu;
+  const uint32_t hi = (w & 0x7F800000u) == 0x7F800000u ? 0u : 0xFFFF0000u;
+  return w & (lo | hi);
+}
+
 __device__ inline void store_elt(float* p, float v) { *p = v; }
 __device__ inline void store_elt(bf16_t* p, float v) { p->bits = f32_to_bf16_rne(v); }
 

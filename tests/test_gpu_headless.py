@@ -137,6 +137,39 @@ def test_headless_group_step_edges(oracle, g, D, Hkv, B, rows):
     assert np.abs(np_of(out) - r_out).max() <= 2e-6 * max(1.0, np.abs(r_out).max())
 
 
+@pytest.mark.parametrize("g,D", [(4, 128), (8, 64), (2, 128)])
+@pytest.mark.parametrize("rows", [1, 33, 257, 700])
+def test_headless_infinite_values(oracle, g, D, rows):
+    """Infinite values in attended rows of V: the columns that hold them become infinite (NaN where both
+    signs or a NaN come together), all others stay as they are -- also where slots past the list's end
+    repeat such a row."""
+    say(f"head-less infinite values g={g} D={D} rows={rows}")
+    gen = torch.Generator().manual_seed(35 + rows)
+    B, Hkv, N, dt = 8, 4, 2 * rows + 20, torch.bfloat16
+    K = torch.randn((B, Hkv, N, D), generator=gen).to(dt)
+    V = torch.randn((B, Hkv, N, D), generator=gen).to(dt)
+    q = torch.randn((B, g * Hkv, D), generator=gen).to(dt)
+    idx = torch.stack([1 + torch.randperm(N - 1, generator=gen)[:rows].sort().values for _ in range(B)]).to(torch.int32)
+    cnt = torch.full((B,), rows, dtype=torch.int32)
+    inf = float("inf")
+    for b in range(B):
+        first, mid, last = (int(idx[b, j]) for j in (0, rows // 2, rows - 1))
+        V[b, :, first, 0] = inf
+        V[b, :, last, 1] = -inf
+        V[b, 1:, mid, D - 1] = inf
+        V[b, 2, first, 5], V[b, 2, last, 5] = inf, -inf if rows > 1 else inf
+        V[b, 3, last, 6] = float("nan")
+    sm = 1.0 / math.sqrt(D)
+    out, lse = shared_attn(q.to(DEV), K.to(DEV), V.to(DEV), idx.to(DEV), cnt.to(DEV), N, sm, rows)
+    ref, r_lse = oracle.sparse_decode_attn_shared(np_of(q), np_of(K), np_of(V), idx.numpy(), cnt.numpy(), "bf16", sm)
+    got = np_of(out)
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    fin = np.isfinite(ref)
+    assert 0 < fin.sum() < fin.size
+    assert_attention(np.where(fin, got, 0.0), np.where(fin, ref, 0.0), "bf16", np_of(lse), r_lse)
+
+
 @pytest.mark.parametrize("name", ["C2_llama3_8b_32k", "C3_batched_depth", "C5_long_context"])
 def test_headless_full_size_configs(oracle, name):
     """The benchmark shapes with one importance head (the first KV head's projected keys):
