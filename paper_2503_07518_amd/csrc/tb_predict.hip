@@ -158,6 +158,10 @@ template <>
 struct MfmaStep<bf16_t> {
   static constexpr int kInputs = 32;  // inputs that a wave covers: 4 lane groups x 8
   static constexpr int kAccs = 1;
+  static constexpr bool kSplit = true;  // activations enter in parts
+  // INF: infinite and NaN weights meet the upper parts only (a lower part may be 0, and 0 times infinity
+  // is NaN).
+  template <bool INF>
   __device__ static inline void run(const float (&x)[8], const uint4& w, mfma_f32x4 (&acc)[kAccs]) {
     uint32_t p[3][4];
 #pragma unroll
@@ -177,13 +181,17 @@ struct MfmaStep<bf16_t> {
 #pragma unroll
       for (int t = 0; t < 3; ++t) p[t][i] = __builtin_amdgcn_perm(part[t][1], part[t][0], 0x07060302u);
     }
-    mfma_bf16x8 wv;
+    mfma_bf16x8 wv, wv_low;
     __builtin_memcpy(&wv, &w, 16);
+    uint4 low = w;
+    if constexpr (INF)
+      low = make_uint4(bf16x2_finite_or_zero(w.x), bf16x2_finite_or_zero(w.y), bf16x2_finite_or_zero(w.z), bf16x2_finite_or_zero(w.w));
+    __builtin_memcpy(&wv_low, &low, 16);
 #pragma unroll
     for (int t = 2; t >= 0; --t) {  // the small parts first
       mfma_bf16x8 xv;
       __builtin_memcpy(&xv, &p[t][0], 16);
-      acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv, wv, acc[0], 0, 0, 0);
+      acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv, t > 0 ? wv_low : wv, acc[0], 0, 0, 0);
     }
   }
 };
@@ -192,6 +200,8 @@ template <>
 struct MfmaStep<float> {
   static constexpr int kInputs = 16;
   static constexpr int kAccs = 4;
+  static constexpr bool kSplit = false;
+  template <bool INF>
   __device__ static inline void run(const float (&x)[4], const float4& w, mfma_f32x4 (&acc)[kAccs]) {
     acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0], w.x, acc[0], 0, 0, 0);
     acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[1], w.y, acc[1], 0, 0, 0);
@@ -204,6 +214,18 @@ template <int NA>
 __device__ inline mfma_f32x4 total_of(const mfma_f32x4 (&acc)[NA]) {
   if constexpr (NA == 1) return acc[0];
   else return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+}
+
+// Whether a lane of the wave holds a NaN sum: it may come from an infinite weight and a lower part of an
+// activation that is 0, and the wave multiplies again with care.  (Infinities of both signs make a NaN, too.)
+template <int MT, int NA>
+__device__ inline bool any_nan(const mfma_f32x4 (&acc)[MT][NA]) {
+  float s = 0.f;
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int c = 0; c < NA; ++c) s += (acc[m][c][0] + acc[m][c][1]) + (acc[m][c][2] + acc[m][c][3]);
+  return __any(s != s);
 }
 
 // Partial sums over the inputs [slice * steps * NW waves * kInputs, ...) of 16 hidden units and MT * 16
@@ -303,29 +325,39 @@ __global__ __launch_bounds__(NW * kWave) void hidden_kernel(PredictArgs a, int n
     const int rr = b0 + m * 16 + r < a.B ? m * 16 + r : a.B - 1 - b0;  // (rows past the batch use the last one's)
     mean[m] = s_mean[rr];
     rstd[m] = s_rstd[rr];
-    for (int c = 0; c < Step::kAccs; ++c) acc[m][c] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  for (int s0 = 0; s0 < steps; s0 += CH) {
-    if (s0 > 0) load(s0);
+  auto multiply = [&](auto inf_tag) {
+    constexpr bool kInf = decltype(inf_tag)::value;
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      if (s0 + c < steps) {  // the same for the whole wave
-        const bool in = k_first + (s0 + c) * Step::kInputs < a.E;  // pieces past the row add nothing
-        float gm[EPL], bt[EPL];
-        Pack16<T>::unpack(gr[c], gm);
-        Pack16<T>::unpack(br[c], bt);
-        typename Pack16<T>::Raw w = wr[c];
-        if (!in) w = typename Pack16<T>::Raw{};
+    for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int m = 0; m < MT; ++m) {
-          float x[EPL];
-          Pack16<T>::unpack(hr[c][m], x);
+      for (int c = 0; c < Step::kAccs; ++c) acc[m][c] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < steps; s0 += CH) {
+      if (kInf || s0 > 0) load(s0);
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) x[e] = in ? (x[e] - mean[m]) * rstd[m] * gm[e] + bt[e] : 0.f;
-          Step::run(x, w, acc[m]);
+      for (int c = 0; c < CH; ++c) {
+        if (s0 + c < steps) {  // the same for the whole wave
+          const bool in = k_first + (s0 + c) * Step::kInputs < a.E;  // pieces past the row add nothing
+          float gm[EPL], bt[EPL];
+          Pack16<T>::unpack(gr[c], gm);
+          Pack16<T>::unpack(br[c], bt);
+          typename Pack16<T>::Raw w = wr[c];
+          if (!in) w = typename Pack16<T>::Raw{};
+#pragma unroll
+          for (int m = 0; m < MT; ++m) {
+            float x[EPL];
+            Pack16<T>::unpack(hr[c][m], x);
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) x[e] = in ? (x[e] - mean[m]) * rstd[m] * gm[e] + bt[e] : 0.f;
+            Step::template run<kInf>(x, w, acc[m]);
+          }
         }
       }
     }
+  };
+  multiply(std::false_type{});
+  if constexpr (Step::kSplit) {
+    if (__builtin_expect(any_nan(acc), 0)) multiply(std::true_type{});
   }
 #pragma unroll
   for (int m = 0; m < MT; ++m)
@@ -427,42 +459,50 @@ __global__ __launch_bounds__(kOutWaves * kWave) void output_kernel(PredictArgs a
     xrow[m] = (FOLD ? s_z : a.z) + static_cast<int64_t>(b < a.B ? b : a.B - 1) * a.hidden;
   }
   mfma_f32x4 acc[MT][Step::kAccs];
+  auto multiply = [&](auto inf_tag) {
+    constexpr bool kInf = decltype(inf_tag)::value;
+    if constexpr (kInf) load_w(wave * Step::kInputs);
 #pragma unroll
-  for (int m = 0; m < MT; ++m)
+    for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int c = 0; c < Step::kAccs; ++c) acc[m][c] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = wave * Step::kInputs; k0 < a.hidden; k0 += CH * kStride) {
-    float x[CH][MT][EPL];
+      for (int c = 0; c < Step::kAccs; ++c) acc[m][c] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = wave * Step::kInputs; k0 < a.hidden; k0 += CH * kStride) {
+      float x[CH][MT][EPL];
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int k = k0 + c * kStride + q * EPL;
-      const int ks = k < a.hidden ? k : 0;
+      for (int c = 0; c < CH; ++c) {
+        const int k = k0 + c * kStride + q * EPL;
+        const int ks = k < a.hidden ? k : 0;
 #pragma unroll
-      for (int m = 0; m < MT; ++m)
+        for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int e = 0; e < EPL; e += 4) {
-          const f32x4_u v = *reinterpret_cast<const f32x4_u*>(xrow[m] + ks + e);
+          for (int e = 0; e < EPL; e += 4) {
+            const f32x4_u v = *reinterpret_cast<const f32x4_u*>(xrow[m] + ks + e);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) x[c][m][e + i] = v[i];
-        }
-    }
-    __builtin_amdgcn_sched_barrier(0);
+            for (int i = 0; i < 4; ++i) x[c][m][e + i] = v[i];
+          }
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int kc = k0 + c * kStride;
-      if (kc < a.hidden) {  // the same for the whole wave
-        const bool in = kc + q * EPL < a.hidden;  // pieces past the row add nothing
-        typename Pack16<T>::Raw w = wr[c];
-        if (!in) w = typename Pack16<T>::Raw{};
+      for (int c = 0; c < CH; ++c) {
+        const int kc = k0 + c * kStride;
+        if (kc < a.hidden) {  // the same for the whole wave
+          const bool in = kc + q * EPL < a.hidden;  // pieces past the row add nothing
+          typename Pack16<T>::Raw w = wr[c];
+          if (!in) w = typename Pack16<T>::Raw{};
 #pragma unroll
-        for (int m = 0; m < MT; ++m) {
+          for (int m = 0; m < MT; ++m) {
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) x[c][m][e] = in ? x[c][m][e] : 0.f;
-          Step::run(x[c][m], w, acc[m]);
+            for (int e = 0; e < EPL; ++e) x[c][m][e] = in ? x[c][m][e] : 0.f;
+            Step::template run<kInf>(x[c][m], w, acc[m]);
+          }
         }
       }
+      if (k0 + CH * kStride < a.hidden) load_w(k0 + CH * kStride);
     }
-    if (k0 + CH * kStride < a.hidden) load_w(k0 + CH * kStride);
+  };
+  multiply(std::false_type{});
+  if constexpr (Step::kSplit) {
+    if (__builtin_expect(any_nan(acc), 0)) multiply(std::true_type{});
   }
 #pragma unroll
   for (int m = 0; m < MT; ++m)

@@ -94,6 +94,38 @@ def test_predict_split_layers(oracle, dtype, B, E, hidden, G, Hq, Dimp):
         assert (xln.double().cpu() - ln).abs().max() <= 1e-5
 
 
+@pytest.mark.parametrize("dtype,B", [(torch.bfloat16, 1), (torch.bfloat16, 3), (torch.bfloat16, 20), (torch.float32, 2)])
+def test_predict_infinite_weights(oracle, dtype, B):
+    """An infinite weight makes the sums it enters infinite (NaN where a hidden activation's argument is
+    -inf, by the oracle's formula) and no others.  Its inputs have few bits (beta alone; gelu(20) = 20), so
+    that the lower of the three bf16 parts they are split into are 0."""
+    print(f"[case] predictor infinite weights dtype={dtype} B={B}", flush=True)
+    E, hidden, G, Hq, Dimp = 2048, 64, 1, 4, 8
+    p = make(B, E, hidden, G, Hq, Dimp, dtype, 25)
+    inf, at = float("inf"), [5, 40, 62, 63]
+    p["gamma"][at] = 0.0
+    p["W1"][at], p["b1"][at] = 0.0, 20.0
+    for where in ("W1", "W2"):
+        w = dict(p)
+        w[where] = p[where].clone()
+        w[where][3, 5], w[where][7, 40], w[where][12, 63] = inf, -inf, inf
+        w[where][12, 62] = -inf  # both signs in one row: NaN or infinite, as the signs of the inputs have it
+        z = torch.zeros((B, hidden), dtype=torch.float32, device=DEV)
+        xln = torch.zeros((B, E), dtype=torch.float32, device=DEV)
+        q_imp = torch.zeros((G, B, Hq, Dimp), dtype=dtype, device=DEV)
+        tb.tb_predict_queries(w["h"], w["gamma"], w["beta"], w["W1"], w["b1"], w["W2"], w["b2"], G, Hq, Dimp, z, xln, q_imp)
+        torch.cuda.synchronize()
+        dn = dtype_name(w["h"])
+        rq, rz = oracle.predict_queries(*(np_of(w[k]) for k in ("h", "gamma", "beta", "W1", "b1", "W2", "b2")), G, Hq, Dimp, dn)
+        pairs = [(np_of(z).astype(np.float64), np.asarray(rz, np.float64))]
+        if where == "W2":
+            pairs.append(tuple(oracle.bf16_to_f64(x) if dn == "bf16" else np.asarray(x, np.float64) for x in (np_of(q_imp), rq)))
+        for got, ref in pairs:
+            assert np.array_equal(np.isnan(got), np.isnan(ref))
+            assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)]) and not np.isinf(got[~np.isinf(ref)]).any()
+        assert not np.isfinite(pairs[-1][1]).all() and np.isfinite(pairs[-1][1]).any()
+
+
 def test_predicted_slot_feeds_scoring(oracle):
     """Slot s of the predictor's output is laid out as tb_score's q_imp."""
     print("[case] predictor slot -> tb_score", flush=True)
