@@ -407,8 +407,8 @@ __global__ __launch_bounds__(kPredThreads) void hidden_sum_kernel(PredictArgs a,
 // to the storage type and scattered to q_imp[slot][b][head][j].  The four waves split the inputs
 // (one tile per workgroup: four times the workgroups of one tile per wave).
 // FOLD (one or two sequences, several slices): every workgroup sums the first layer's partial sums
-// itself, into LDS, instead of a launch of its own that would do it; otherwise the first a.B
-// workgroups write LN(h), whose buffer held the partial sums until now.
+// itself, into LDS, instead of a launch of its own that would do it; otherwise the first
+// workgroups of a group of sequences write LN(h), whose buffer held the partial sums until now.
 template <typename T, int MT, bool FOLD>
 __global__ __launch_bounds__(kOutWaves * kWave) void output_kernel(PredictArgs a, int n_slices) {
   static_assert(kOutWaves * kWave == kPredThreads, "ln_row and sum_slices run on kPredThreads threads");
@@ -420,12 +420,14 @@ __global__ __launch_bounds__(kOutWaves * kWave) void output_kernel(PredictArgs a
   __shared__ float s_red[kOutWaves][MT][256];
   __shared__ float s_z[FOLD ? kFoldElements : 4];
   int tile = blockIdx.x;
-  if constexpr (!FOLD) {
-    if (tile < a.B) {
-      if (blockIdx.y == 0) ln_row<T>(a, tile);
+  if constexpr (!FOLD) {  // the first workgroups of every group of sequences write its LN(h)
+    const int n_ln = min(a.B, 16 * MT);
+    if (tile < n_ln) {
+      const int b = blockIdx.y * (16 * MT) + tile;
+      if (b < a.B) ln_row<T>(a, b);
       return;
     }
-    tile -= a.B;
+    tile -= n_ln;
   }
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = wave_id();
   const int r = lane % 16, q = lane / 16;
@@ -564,7 +566,7 @@ tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((hidden_sum_kernel<T>), sgrid, dim3(kPredThreads), 0, st, a, slices);
     if (hipGetLastError() != hipSuccess) return TB_ERR_HIP;
   }
-  hipLaunchKernelGGL((output_kernel<T, MT, false>), dim3(a.B + out_tiles, groups), dim3(kPredThreads), 0, st, a, slices);
+  hipLaunchKernelGGL((output_kernel<T, MT, false>), dim3((a.B < 16 * MT ? a.B : 16 * MT) + out_tiles, groups), dim3(kPredThreads), 0, st, a, slices);
   return hip_status(hipGetLastError());
 }
 
