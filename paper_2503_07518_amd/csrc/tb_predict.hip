@@ -139,6 +139,7 @@ __device__ inline void ln_row(const PredictArgs& a, int b) {
 // statistics of its rows itself (one pass over bytes that sit in the L2, against a launch of its
 // own); the partial sums wait in the LN(h) buffer, are added in slice order by a small second
 // kernel, and the third kernel's first workgroups write LN(h) there beside the output tiles.
+// From some hundred sequences on it is the arithmetic that prepares the activations (launch_tiles).
 // bf16, E = 4096, hidden 512, 4096 outputs, in a graph of such calls: B = 16 23.8 -> 15.4 us (before: 32
 // workgroups that each converted all activations, LN in a launch of its own), B = 6 34.7 -> 12.8 and
 // B = 1 11.3 -> 10.5 us (before: vector FMAs); fp32 B = 16 39.4 -> 19.9, B = 1 17.3 -> 13.1 us.
@@ -149,8 +150,8 @@ constexpr int kOutWaves = 4;          // waves of an output-layer workgroup: the
 constexpr int kFoldElements = 512;    // up to so many hidden activations the output kernel sums the slices itself
 constexpr int kHidTargetWgs = 256;    // one hidden-layer workgroup per compute unit
 
-// acc[0] + ... += x . w over one step: 8 inputs of a lane (bf16 weights) or 4 (fp32 weights; these
-// are summed in kAccs chains, so that no chain is longer than the bf16 form's).
+// acc(n)[0] + ... += x . w[n] over one step, n < NT: 8 inputs of a lane (bf16 weights) or 4 (fp32 weights;
+// these are summed in kAccs chains, so that no chain is longer than the bf16 form's).
 template <typename T>
 struct MfmaStep;
 
@@ -161,8 +162,8 @@ struct MfmaStep<bf16_t> {
   static constexpr bool kSplit = true;  // activations enter in parts
   // INF: infinite and NaN weights meet the upper parts only (a lower part may be 0, and 0 times infinity
   // is NaN).
-  template <bool INF>
-  __device__ static inline void run(const float (&x)[8], const uint4& w, mfma_f32x4 (&acc)[kAccs]) {
+  template <bool INF, int NT, typename Acc>
+  __device__ static inline void run(const float (&x)[8], const uint4 (&w)[NT], Acc&& acc) {
     uint32_t p[3][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -181,17 +182,21 @@ struct MfmaStep<bf16_t> {
 #pragma unroll
       for (int t = 0; t < 3; ++t) p[t][i] = __builtin_amdgcn_perm(part[t][1], part[t][0], 0x07060302u);
     }
-    mfma_bf16x8 wv, wv_low;
-    __builtin_memcpy(&wv, &w, 16);
-    uint4 low = w;
-    if constexpr (INF)
-      low = make_uint4(bf16x2_finite_or_zero(w.x), bf16x2_finite_or_zero(w.y), bf16x2_finite_or_zero(w.z), bf16x2_finite_or_zero(w.w));
-    __builtin_memcpy(&wv_low, &low, 16);
+    mfma_bf16x8 xv[3];
 #pragma unroll
-    for (int t = 2; t >= 0; --t) {  // the small parts first
-      mfma_bf16x8 xv;
-      __builtin_memcpy(&xv, &p[t][0], 16);
-      acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv, t > 0 ? wv_low : wv, acc[0], 0, 0, 0);
+    for (int t = 0; t < 3; ++t) __builtin_memcpy(&xv[t], &p[t][0], 16);
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      mfma_bf16x8 wv, wv_low;
+      __builtin_memcpy(&wv, &w[n], 16);
+      uint4 low = w[n];
+      if constexpr (INF)
+        low = make_uint4(bf16x2_finite_or_zero(low.x), bf16x2_finite_or_zero(low.y), bf16x2_finite_or_zero(low.z), bf16x2_finite_or_zero(low.w));
+      __builtin_memcpy(&wv_low, &low, 16);
+      mfma_f32x4& sum = acc(n)[0];
+#pragma unroll
+      for (int t = 2; t >= 0; --t)  // the small parts first
+        sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[t], t > 0 ? wv_low : wv, sum, 0, 0, 0);
     }
   }
 };
@@ -201,12 +206,16 @@ struct MfmaStep<float> {
   static constexpr int kInputs = 16;
   static constexpr int kAccs = 4;
   static constexpr bool kSplit = false;
-  template <bool INF>
-  __device__ static inline void run(const float (&x)[4], const float4& w, mfma_f32x4 (&acc)[kAccs]) {
-    acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0], w.x, acc[0], 0, 0, 0);
-    acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[1], w.y, acc[1], 0, 0, 0);
-    acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[2], w.z, acc[2], 0, 0, 0);
-    acc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[3], w.w, acc[3], 0, 0, 0);
+  template <bool INF, int NT, typename Acc>
+  __device__ static inline void run(const float (&x)[4], const float4 (&w)[NT], Acc&& acc) {
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      mfma_f32x4(&sum)[kAccs] = acc(n);
+      sum[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0], w[n].x, sum[0], 0, 0, 0);
+      sum[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[1], w[n].y, sum[1], 0, 0, 0);
+      sum[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[2], w[n].z, sum[2], 0, 0, 0);
+      sum[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[3], w[n].w, sum[3], 0, 0, 0);
+    }
   }
 };
 
@@ -228,10 +237,10 @@ __device__ inline bool any_nan(const mfma_f32x4 (&acc)[MT][NA]) {
   return __any(s != s);
 }
 
-// Partial sums over the inputs [slice * steps * NW waves * kInputs, ...) of 16 hidden units and MT * 16
-// sequences.  n_slices == 1: the sums are whole and leave as z = gelu(sum + b1); otherwise they go to
+// Partial sums over the inputs [slice * steps * NW waves * kInputs, ...) of NT * 16 hidden units and
+// MT * 16 sequences.  n_slices == 1: the sums are whole and leave as z = gelu(sum + b1); otherwise they go to
 // part[slice][b][unit].
-template <typename T, int MT, int NW>
+template <typename T, int MT, int NT, int NW>
 __global__ __launch_bounds__(NW * kWave) void hidden_kernel(PredictArgs a, int n_slices, int steps) {
   using Step = MfmaStep<T>;
   constexpr int EPL = Pack16<T>::kElts;
@@ -241,9 +250,11 @@ __global__ __launch_bounds__(NW * kWave) void hidden_kernel(PredictArgs a, int n
   __shared__ float s_mean[MT * 16], s_rstd[MT * 16];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = wave_id();
   const int r = lane % 16, q = lane / 16;
-  const int n0 = blockIdx.x * 16, slice = blockIdx.y, b0 = blockIdx.z * (16 * MT);
-  const int unit = n0 + r < a.hidden ? n0 + r : a.hidden - 1;
-  const T* wrow = static_cast<const T*>(a.W1) + static_cast<int64_t>(unit) * a.E;
+  const int n0 = blockIdx.x * (16 * NT), slice = blockIdx.y, b0 = blockIdx.z * (16 * MT);
+  const T* wrow[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+    wrow[t] = static_cast<const T*>(a.W1) + static_cast<int64_t>(min(n0 + 16 * t + r, a.hidden - 1)) * a.E;
   const T* hrow[MT];
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
@@ -253,13 +264,14 @@ __global__ __launch_bounds__(NW * kWave) void hidden_kernel(PredictArgs a, int n
   // the wave's steps lie next to each other: lane (r, q) takes pieces of row r, 64 bytes a step
   const int k_first = (slice * NW + wave) * steps * Step::kInputs + q * EPL;
 
-  typename Pack16<T>::Raw wr[CH], gr[CH], br[CH], hr[CH][MT];
+  typename Pack16<T>::Raw wr[CH][NT], gr[CH], br[CH], hr[CH][MT];
   auto load = [&](int s0) {
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
       const int k = k_first + (s0 + c) * Step::kInputs;
       const int ks = (s0 + c < steps && k < a.E) ? k : 0;
-      wr[c] = Pack16<T>::load_raw(wrow + ks);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) wr[c][t] = Pack16<T>::load_raw(wrow[t] + ks);
       gr[c] = Pack16<T>::load_raw(static_cast<const T*>(a.gamma) + ks);
       br[c] = Pack16<T>::load_raw(static_cast<const T*>(a.beta) + ks);
 #pragma unroll
@@ -319,7 +331,7 @@ __global__ __launch_bounds__(NW * kWave) void hidden_kernel(PredictArgs a, int n
   __syncthreads();
 
   float mean[MT], rstd[MT];
-  mfma_f32x4 acc[MT][Step::kAccs];
+  mfma_f32x4 acc[NT][MT][Step::kAccs];
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
     const int rr = b0 + m * 16 + r < a.B ? m * 16 + r : a.B - 1 - b0;  // (rows past the batch use the last one's)
@@ -329,9 +341,11 @@ __global__ __launch_bounds__(NW * kWave) void hidden_kernel(PredictArgs a, int n
   auto multiply = [&](auto inf_tag) {
     constexpr bool kInf = decltype(inf_tag)::value;
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int c = 0; c < Step::kAccs; ++c) acc[m][c] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int c = 0; c < Step::kAccs; ++c) acc[t][m][c] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
     for (int s0 = 0; s0 < steps; s0 += CH) {
       if (kInf || s0 > 0) load(s0);
 #pragma unroll
@@ -341,15 +355,19 @@ __global__ __launch_bounds__(NW * kWave) void hidden_kernel(PredictArgs a, int n
           float gm[EPL], bt[EPL];
           Pack16<T>::unpack(gr[c], gm);
           Pack16<T>::unpack(br[c], bt);
-          typename Pack16<T>::Raw w = wr[c];
-          if (!in) w = typename Pack16<T>::Raw{};
+          typename Pack16<T>::Raw w[NT];
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            w[t] = wr[c][t];
+            if (!in) w[t] = typename Pack16<T>::Raw{};
+          }
 #pragma unroll
           for (int m = 0; m < MT; ++m) {
             float x[EPL];
             Pack16<T>::unpack(hr[c][m], x);
 #pragma unroll
             for (int e = 0; e < EPL; ++e) x[e] = in ? (x[e] - mean[m]) * rstd[m] * gm[e] + bt[e] : 0.f;
-            Step::template run<kInf>(x, w, acc[m]);
+            Step::template run<kInf, NT>(x, w, [&](int t) -> mfma_f32x4(&)[Step::kAccs] { return acc[t][m]; });
           }
         }
       }
@@ -357,25 +375,32 @@ __global__ __launch_bounds__(NW * kWave) void hidden_kernel(PredictArgs a, int n
   };
   multiply(std::false_type{});
   if constexpr (Step::kSplit) {
-    if (__builtin_expect(any_nan(acc), 0)) multiply(std::true_type{});
+    bool nan = false;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) nan |= any_nan(acc[t]);
+    if (__builtin_expect(nan, 0)) multiply(std::true_type{});
   }
 #pragma unroll
-  for (int m = 0; m < MT; ++m)
-    *reinterpret_cast<mfma_f32x4*>(&s_red[wave][m][lane * 4]) = total_of(acc[m]);
-  __syncthreads();
-  // accumulator v of lane l is (sequence 4 * (l / 16) + v, unit l % 16); the waves are summed in order
-  for (int t = tid; t < MT * 256; t += NW * kWave) {
-    const int m = t / 256, row = t % 256 / 16, n = n0 + t % 16;
-    const int e = (16 * (row / 4) + t % 16) * 4 + row % 4;
-    float sum = 0.f;
+  for (int nt = 0; nt < NT; ++nt) {
+    if (nt > 0) __syncthreads();  // the sums of the tile before have been read
 #pragma unroll
-    for (int w = 0; w < NW; ++w) sum += s_red[w][m][e];
-    const int b = b0 + m * 16 + row;
-    if (b < a.B && n < a.hidden) {
-      if (n_slices == 1)
-        a.z[static_cast<int64_t>(b) * a.hidden + n] = gelu_erf(sum + to_float(static_cast<const T*>(a.b1)[n]));
-      else
-        a.xln[(static_cast<int64_t>(slice) * a.B + b) * a.hidden + n] = sum;
+    for (int m = 0; m < MT; ++m)
+      *reinterpret_cast<mfma_f32x4*>(&s_red[wave][m][lane * 4]) = total_of(acc[nt][m]);
+    __syncthreads();
+    // accumulator v of lane l is (sequence 4 * (l / 16) + v, unit l % 16); the waves are summed in order
+    for (int t = tid; t < MT * 256; t += NW * kWave) {
+      const int m = t / 256, row = t % 256 / 16, n = n0 + 16 * nt + t % 16;
+      const int e = (16 * (row / 4) + t % 16) * 4 + row % 4;
+      float sum = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) sum += s_red[w][m][e];
+      const int b = b0 + m * 16 + row;
+      if (b < a.B && n < a.hidden) {
+        if (n_slices == 1)
+          a.z[static_cast<int64_t>(b) * a.hidden + n] = gelu_erf(sum + to_float(static_cast<const T*>(a.b1)[n]));
+        else
+          a.xln[(static_cast<int64_t>(slice) * a.B + b) * a.hidden + n] = sum;
+      }
     }
   }
 }
@@ -403,13 +428,13 @@ __global__ __launch_bounds__(kPredThreads) void hidden_sum_kernel(PredictArgs a,
   a.z[i] = gelu_erf(sum_slices(a, i, n_slices) + bias);
 }
 
-// y[b][o] = W2[o] . z[b] + b2[o] for 16 output rows o and MT * 16 sequences per workgroup, rounded
+// y[b][o] = W2[o] . z[b] + b2[o] for NT * 16 output rows o and MT * 16 sequences per workgroup, rounded
 // to the storage type and scattered to q_imp[slot][b][head][j].  The four waves split the inputs
 // (one tile per workgroup: four times the workgroups of one tile per wave).
 // FOLD (one or two sequences, several slices): every workgroup sums the first layer's partial sums
 // itself, into LDS, instead of a launch of its own that would do it; otherwise the first
 // workgroups of a group of sequences write LN(h), whose buffer held the partial sums until now.
-template <typename T, int MT, bool FOLD>
+template <typename T, int MT, int NT, bool FOLD>
 __global__ __launch_bounds__(kOutWaves * kWave) void output_kernel(PredictArgs a, int n_slices) {
   static_assert(kOutWaves * kWave == kPredThreads, "ln_row and sum_slices run on kPredThreads threads");
   using Step = MfmaStep<T>;
@@ -432,20 +457,24 @@ __global__ __launch_bounds__(kOutWaves * kWave) void output_kernel(PredictArgs a
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = wave_id();
   const int r = lane % 16, q = lane / 16;
   const int n_out = a.G * a.Hq * a.Dimp;
-  const int n0 = tile * 16, b0 = blockIdx.y * (16 * MT);
-  const int o_row = n0 + r < n_out ? n0 + r : n_out - 1;
-  const T* wrow = static_cast<const T*>(a.W2) + static_cast<int64_t>(o_row) * a.hidden;
-  typename Pack16<T>::Raw wr[CH];
+  const int n0 = tile * (16 * NT), b0 = blockIdx.y * (16 * MT);
+  const T* wrow[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+    wrow[t] = static_cast<const T*>(a.W2) + static_cast<int64_t>(min(n0 + 16 * t + r, n_out - 1)) * a.hidden;
+  typename Pack16<T>::Raw wr[CH][NT];
   auto load_w = [&](int k0) {
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
       const int k = k0 + c * kStride + q * EPL;
-      wr[c] = Pack16<T>::load_raw(wrow + (k < a.hidden ? k : 0));
+#pragma unroll
+      for (int t = 0; t < NT; ++t) wr[c][t] = Pack16<T>::load_raw(wrow[t] + (k < a.hidden ? k : 0));
     }
   };
   load_w(wave * Step::kInputs);
-  const int o_mine = n0 + tid % 16;
-  const float bias = to_float(static_cast<const T*>(a.b2)[o_mine < n_out ? o_mine : n_out - 1]);
+  float bias[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) bias[t] = to_float(static_cast<const T*>(a.b2)[min(n0 + 16 * t + tid % 16, n_out - 1)]);
   if constexpr (FOLD) {
     for (int i = tid; i < a.B * a.hidden; i += kPredThreads) {
       const float z = gelu_erf(sum_slices(a, i, n_slices) + to_float(static_cast<const T*>(a.b1)[i % a.hidden]));
@@ -460,14 +489,16 @@ __global__ __launch_bounds__(kOutWaves * kWave) void output_kernel(PredictArgs a
     const int b = b0 + m * 16 + r;
     xrow[m] = (FOLD ? s_z : a.z) + static_cast<int64_t>(b < a.B ? b : a.B - 1) * a.hidden;
   }
-  mfma_f32x4 acc[MT][Step::kAccs];
+  mfma_f32x4 acc[NT][MT][Step::kAccs];
   auto multiply = [&](auto inf_tag) {
     constexpr bool kInf = decltype(inf_tag)::value;
     if constexpr (kInf) load_w(wave * Step::kInputs);
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int c = 0; c < Step::kAccs; ++c) acc[m][c] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int c = 0; c < Step::kAccs; ++c) acc[t][m][c] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
     for (int k0 = wave * Step::kInputs; k0 < a.hidden; k0 += CH * kStride) {
       float x[CH][MT][EPL];
 #pragma unroll
@@ -489,13 +520,17 @@ __global__ __launch_bounds__(kOutWaves * kWave) void output_kernel(PredictArgs a
         const int kc = k0 + c * kStride;
         if (kc < a.hidden) {  // the same for the whole wave
           const bool in = kc + q * EPL < a.hidden;  // pieces past the row add nothing
-          typename Pack16<T>::Raw w = wr[c];
-          if (!in) w = typename Pack16<T>::Raw{};
+          typename Pack16<T>::Raw w[NT];
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            w[t] = wr[c][t];
+            if (!in) w[t] = typename Pack16<T>::Raw{};
+          }
 #pragma unroll
           for (int m = 0; m < MT; ++m) {
 #pragma unroll
             for (int e = 0; e < EPL; ++e) x[c][m][e] = in ? x[c][m][e] : 0.f;
-            Step::template run<kInf>(x[c][m], w, acc[m]);
+            Step::template run<kInf, NT>(x[c][m], w, [&](int t) -> mfma_f32x4(&)[Step::kAccs] { return acc[t][m]; });
           }
         }
       }
@@ -504,24 +539,32 @@ __global__ __launch_bounds__(kOutWaves * kWave) void output_kernel(PredictArgs a
   };
   multiply(std::false_type{});
   if constexpr (Step::kSplit) {
-    if (__builtin_expect(any_nan(acc), 0)) multiply(std::true_type{});
-  }
+    bool nan = false;
 #pragma unroll
-  for (int m = 0; m < MT; ++m)
-    *reinterpret_cast<mfma_f32x4*>(&s_red[wave][m][lane * 4]) = total_of(acc[m]);
-  __syncthreads();
+    for (int t = 0; t < NT; ++t) nan |= any_nan(acc[t]);
+    if (__builtin_expect(nan, 0)) multiply(std::true_type{});
+  }
   const int per_slot = a.Hq * a.Dimp;
-  const int slot = o_mine / per_slot, rest = o_mine % per_slot;
   const int row = tid / 16;
   const int e = (16 * (row / 4) + tid % 16) * 4 + row % 4;
 #pragma unroll
-  for (int m = 0; m < MT; ++m) {
-    float sum = 0.f;
+  for (int nt = 0; nt < NT; ++nt) {
+    if (nt > 0) __syncthreads();  // the sums of the tile before have been read
 #pragma unroll
-    for (int w = 0; w < kOutWaves; ++w) sum += s_red[w][m][e];
-    const int b = b0 + m * 16 + row;
-    if (b < a.B && o_mine < n_out)
-      store_elt(static_cast<T*>(a.q_imp) + (static_cast<int64_t>(slot) * a.B + b) * per_slot + rest, sum + bias);
+    for (int m = 0; m < MT; ++m)
+      *reinterpret_cast<mfma_f32x4*>(&s_red[wave][m][lane * 4]) = total_of(acc[nt][m]);
+    __syncthreads();
+    const int o_mine = n0 + 16 * nt + tid % 16;
+    const int slot = o_mine / per_slot, rest = o_mine % per_slot;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      float sum = 0.f;
+#pragma unroll
+      for (int w = 0; w < kOutWaves; ++w) sum += s_red[w][m][e];
+      const int b = b0 + m * 16 + row;
+      if (b < a.B && o_mine < n_out)
+        store_elt(static_cast<T*>(a.q_imp) + (static_cast<int64_t>(slot) * a.B + b) * per_slot + rest, sum + bias[nt]);
+    }
   }
 }
 
@@ -529,6 +572,13 @@ template <typename T, int MT>
 tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
   constexpr int kInputs = MfmaStep<T>::kInputs;
   const int tiles = (a.hidden + 15) / 16, groups = (a.B + 16 * MT - 1) / (16 * MT);
+  const int out_tiles = (a.G * a.Hq * a.Dimp + 15) / 16;
+  // Batches that fill the chip several times over: up to four tiles of a layer per workgroup, as long as
+  // one workgroup per compute unit is left, share the LayerNorm and the splitting of their activations
+  // (bf16, 2048 sequences: E = 4096, hidden 512, 4096 outputs 340 -> 170 us, hidden 128, 128 outputs 71.7 -> 45.8,
+  // E = 8192, hidden 1024, 1024 outputs 813 -> 369; 256 sequences of the first 51.6 -> 42.3).
+  auto tiles_of = [&](int n) { return MT == 1 || n * groups < 2 * kHidTargetWgs ? 1 : (n * groups < 4 * kHidTargetWgs ? 2 : 4); };
+  const int hidden_nt = tiles_of(tiles), out_nt = tiles_of(out_tiles);
   // slices of E: until about one workgroup per compute unit is there, while every wave has a step of
   // its own and the partial sums fit the LN(h) buffer
   int waves = 8, steps = 0, slices = 0;
@@ -544,19 +594,41 @@ tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
     slices = (all_steps + steps - 1) / steps;
     // 8 waves while their steps are in flight together, more waves otherwise (B = 16: 15.4 against
     // 16.5 us at E = 4096, hidden 512; B = 24: 41.7 against 37.6 us at E = 8192, hidden 1024)
-    if (steps <= 4 || waves == 16) break;
+    if (steps <= 4 || waves == 16 || hidden_nt > 1) break;
   }
-  const dim3 hgrid(tiles, slices, groups);
-  if (waves == 8)
-    hipLaunchKernelGGL((hidden_kernel<T, MT, 8>), hgrid, dim3(8 * kWave), 0, st, a, slices, steps);
-  else
-    hipLaunchKernelGGL((hidden_kernel<T, MT, 16>), hgrid, dim3(16 * kWave), 0, st, a, slices, steps);
+  auto launch_hidden = [&](auto nt, auto nw) {
+    constexpr int NT = decltype(nt)::value, NW = decltype(nw)::value;
+    hipLaunchKernelGGL((hidden_kernel<T, MT, NT, NW>), dim3((tiles + NT - 1) / NT, slices, groups), dim3(NW * kWave), 0, st, a, slices, steps);
+  };
+  auto launch_output = [&](auto nt, auto fold) {
+    constexpr int NT = decltype(nt)::value;
+    constexpr bool FOLD = decltype(fold)::value;
+    const int n_ln = FOLD ? 0 : (a.B < 16 * MT ? a.B : 16 * MT);
+    hipLaunchKernelGGL((output_kernel<T, MT, NT, FOLD>), dim3(n_ln + (out_tiles + NT - 1) / NT, groups), dim3(kPredThreads), 0, st, a, slices);
+  };
+  using std::integral_constant;
+  const integral_constant<int, 1> one;
+  const integral_constant<int, 8> w8;
+  const integral_constant<int, 16> w16;
+  if constexpr (MT == 2) {
+    const integral_constant<int, 2> two;
+    const integral_constant<int, 4> four;
+    if (hidden_nt == 4)
+      launch_hidden(four, w8);
+    else if (hidden_nt == 2)
+      launch_hidden(two, w8);
+  }
+  if (hidden_nt == 1) {
+    if (waves == 8)
+      launch_hidden(one, w8);
+    else
+      launch_hidden(one, w16);
+  }
   if (hipGetLastError() != hipSuccess) return TB_ERR_HIP;
-  const unsigned out_tiles = static_cast<unsigned>((a.G * a.Hq * a.Dimp + 15) / 16);
   if constexpr (MT == 1) {
     // (up to two sequences: the folding kernel has no workgroups that write LN(h))
     if (slices > 1 && a.B <= 2 && a.B * a.hidden <= kFoldElements) {
-      hipLaunchKernelGGL((output_kernel<T, 1, true>), dim3(out_tiles), dim3(kPredThreads), 0, st, a, slices);
+      launch_output(one, std::true_type{});
       return hip_status(hipGetLastError());
     }
   }
@@ -566,7 +638,15 @@ tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((hidden_sum_kernel<T>), sgrid, dim3(kPredThreads), 0, st, a, slices);
     if (hipGetLastError() != hipSuccess) return TB_ERR_HIP;
   }
-  hipLaunchKernelGGL((output_kernel<T, MT, false>), dim3((a.B < 16 * MT ? a.B : 16 * MT) + out_tiles, groups), dim3(kPredThreads), 0, st, a, slices);
+  if constexpr (MT == 2) {
+    const integral_constant<int, 2> two;
+    const integral_constant<int, 4> four;
+    if (out_nt == 4)
+      launch_output(four, std::false_type{});
+    else if (out_nt == 2)
+      launch_output(two, std::false_type{});
+  }
+  if (out_nt == 1) launch_output(one, std::false_type{});
   return hip_status(hipGetLastError());
 }
 

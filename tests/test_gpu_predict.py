@@ -67,6 +67,11 @@ def test_predict_queries(oracle, dtype, B, E, hidden, G, Hq, Dimp):
     (torch.float32, 3, 2048, 160, 1, 4, 8),
     (torch.bfloat16, 16, 1024, 32, 1, 4, 8),
     (torch.float32, 2, 4096, 128, 1, 4, 8),      # two sequences: summed by the output kernel
+    # large batches: two and four tiles of a layer per workgroup, the last ones ragged
+    (torch.bfloat16, 520, 264, 520, 1, 67, 8),
+    (torch.bfloat16, 1030, 264, 520, 1, 67, 8),
+    (torch.float32, 1030, 264, 520, 1, 67, 8),
+    (torch.float32, 520, 264, 520, 1, 67, 8),
 ])
 def test_predict_split_layers(oracle, dtype, B, E, hidden, G, Hq, Dimp):
     """Edges of the tiles, steps and slices; z starts 4 bytes off a 16-byte boundary.  Bars of
