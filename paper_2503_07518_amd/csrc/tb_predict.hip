@@ -147,7 +147,8 @@ typedef short mfma_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float mfma_f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kOutWaves = 4;          // waves of an output-layer workgroup: they split the inputs
-constexpr int kFoldElements = 512;    // up to so many hidden activations the output kernel sums the slices itself
+constexpr int kFoldSums = 4096;       // up to so many partial sums the output kernel adds the slices itself
+constexpr int kFoldElements = kFoldSums / 2;  // ... which are at least two per hidden activation
 constexpr int kHidTargetWgs = 256;    // one hidden-layer workgroup per compute unit
 
 // acc(n)[0] + ... += x . w[n] over one step, n < NT: 8 inputs of a lane (bf16 weights) or 4 (fp32 weights;
@@ -405,18 +406,25 @@ __global__ __launch_bounds__(NW * kWave) void hidden_kernel(PredictArgs a, int n
   }
 }
 
-// Element i of [B][hidden] of the first layer: the slices in order, eight loads in flight.
-__device__ inline float sum_slices(const PredictArgs& a, int64_t i, int n_slices) {
+// Elements i, i + stride, ... of [B][hidden] of the first layer, J of them: the slices in order, S of
+// them (8 / J) in flight for every element.
+template <int J>
+__device__ inline void sum_slices(const PredictArgs& a, int64_t i, int64_t stride, int n_slices, float (&sum)[J]) {
+  constexpr int S = 8 / J;
   const int64_t n = static_cast<int64_t>(a.B) * a.hidden;
-  float sum = 0.f;
-  for (int s0 = 0; s0 < n_slices; s0 += 8) {
-    float v[8];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) v[s] = a.xln[(s0 + s < n_slices ? s0 + s : s0) * n + i];
+  for (int j = 0; j < J; ++j) sum[j] = 0.f;
+  for (int s0 = 0; s0 < n_slices; s0 += S) {
+    float v[J][S];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) sum += s0 + s < n_slices ? v[s] : 0.f;
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int s = 0; s < S; ++s) v[j][s] = a.xln[(s0 + s < n_slices ? s0 + s : s0) * n + (i + j * stride < n ? i + j * stride : i)];
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int s = 0; s < S; ++s) sum[j] += s0 + s < n_slices ? v[j][s] : 0.f;
   }
-  return sum;
 }
 
 // z = gelu(sum over the slices + b1), one element per thread.
@@ -425,7 +433,9 @@ __global__ __launch_bounds__(kPredThreads) void hidden_sum_kernel(PredictArgs a,
   const int64_t i = static_cast<int64_t>(blockIdx.x) * kPredThreads + threadIdx.x;
   if (i >= static_cast<int64_t>(a.B) * a.hidden) return;
   const float bias = to_float(static_cast<const T*>(a.b1)[i % a.hidden]);
-  a.z[i] = gelu_erf(sum_slices(a, i, n_slices) + bias);
+  float sum[1];
+  sum_slices<1>(a, i, 0, n_slices, sum);
+  a.z[i] = gelu_erf(sum[0] + bias);
 }
 
 // y[b][o] = W2[o] . z[b] + b2[o] for NT * 16 output rows o and MT * 16 sequences per workgroup, rounded
@@ -476,11 +486,31 @@ __global__ __launch_bounds__(kOutWaves * kWave) void output_kernel(PredictArgs a
 #pragma unroll
   for (int t = 0; t < NT; ++t) bias[t] = to_float(static_cast<const T*>(a.b2)[min(n0 + 16 * t + tid % 16, n_out - 1)]);
   if constexpr (FOLD) {
-    for (int i = tid; i < a.B * a.hidden; i += kPredThreads) {
-      const float z = gelu_erf(sum_slices(a, i, n_slices) + to_float(static_cast<const T*>(a.b1)[i % a.hidden]));
-      s_z[i] = z;
-      if (tile == 0) a.z[i] = z;
-    }
+    auto fold = [&](auto per_thread) {
+      constexpr int J = decltype(per_thread)::value;
+      const int n = a.B * a.hidden;
+      for (int i = tid; i < n; i += J * kPredThreads) {
+        float b1[J], sum[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) b1[j] = to_float(static_cast<const T*>(a.b1)[(i + j * kPredThreads) % a.hidden]);
+        sum_slices<J>(a, i, kPredThreads, n_slices, sum);
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+          const int at = i + j * kPredThreads;
+          if (at < n) {
+            const float z = gelu_erf(sum[j] + b1[j]);
+            s_z[at] = z;
+            if (tile == 0) a.z[at] = z;
+          }
+        }
+      }
+    };
+    if (n_slices <= 2)
+      fold(std::integral_constant<int, 4>{});
+    else if (n_slices <= 4)
+      fold(std::integral_constant<int, 2>{});
+    else
+      fold(std::integral_constant<int, 1>{});
     __syncthreads();
   }
   const float* xrow[MT];
@@ -579,6 +609,11 @@ tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
   // E = 8192, hidden 1024, 1024 outputs 813 -> 369; 256 sequences of the first 51.6 -> 42.3).
   auto tiles_of = [&](int n) { return MT == 1 || n * groups < 2 * kHidTargetWgs ? 1 : (n * groups < 4 * kHidTargetWgs ? 2 : 4); };
   const int hidden_nt = tiles_of(tiles), out_nt = tiles_of(out_tiles);
+  // One or two sequences with few partial sums: the output kernel adds the slices itself (it has no
+  // workgroups that write LN(h) then).  B = 1: bf16, E = 2048, hidden 520, 128 outputs 10.2 us against 11.2 with a launch
+  // of its own for the sums, E = 4096, hidden 1024 12.0 against 12.6; fp32, E = 2048, hidden 1024 12.7 against 14.2; more
+  // partial sums (B = 2, hidden 512, eight slices) gain nothing.
+  auto folds = [&](int n_slices) { return MT == 1 && a.B <= 2 && n_slices > 1 && n_slices * a.B * a.hidden <= kFoldSums; };
   // slices of E: as many as give up to one workgroup per compute unit (one more round for a few of them
   // would cost the most: a compute unit holds one; bf16, E = 5120, hidden 640, 5120 outputs, B = 1: 17.4 us with
   // 280 workgroups, 13.7 with 200), while every wave has a step of its own and the partial sums fit the
@@ -588,10 +623,12 @@ tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
     const int all_steps = (a.E + waves * kInputs - 1) / (waves * kInputs);
     int want = kHidTargetWgs / (tiles * groups);
     if (want > all_steps) want = all_steps;
+    if (a.B <= 2 && want > 16) want = 16;  // (two round trips for their sum; fp32, E = 4096, hidden 128, B = 1: 11.4 us with 32, 10.5)
     if (want > a.E / a.hidden) want = a.E / a.hidden;
     // two slices save less than the launch that sums them costs where a whole tile is 64 KiB of weights
-    // at most (B = 1, bf16, E = 2048, hidden 1024: 11.4 against 12.0 us; fp32, twice the bytes: 16.7 against 15.4)
-    if (want < 2 || (want == 2 && 16 * a.E * sizeof(T) <= 64 * 1024)) want = 1;
+    // at most (measured at B = 1 with that launch: bf16, E = 2048, hidden 1024 11.4 us without slices, 12.0 with
+    // two; fp32, twice the bytes, 16.7 and 15.4)
+    if (want < 2 || (want == 2 && !folds(2) && 16 * a.E * sizeof(T) <= 64 * 1024)) want = 1;
     steps = (all_steps + want - 1) / want;
     slices = (all_steps + steps - 1) / steps;
     // 8 waves while their steps are in flight together, more waves otherwise (B = 16: 15.4 against
@@ -628,8 +665,7 @@ tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
   }
   if (hipGetLastError() != hipSuccess) return TB_ERR_HIP;
   if constexpr (MT == 1) {
-    // (up to two sequences: the folding kernel has no workgroups that write LN(h))
-    if (slices > 1 && a.B <= 2 && a.B * a.hidden <= kFoldElements) {
+    if (folds(slices)) {
       launch_output(one, std::true_type{});
       return hip_status(hipGetLastError());
     }

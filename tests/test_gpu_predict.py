@@ -67,6 +67,9 @@ def test_predict_queries(oracle, dtype, B, E, hidden, G, Hq, Dimp):
     (torch.float32, 3, 2048, 160, 1, 4, 8),
     (torch.bfloat16, 16, 1024, 32, 1, 4, 8),
     (torch.float32, 2, 4096, 128, 1, 4, 8),      # two sequences: summed by the output kernel
+    (torch.bfloat16, 1, 2048, 520, 1, 4, 8),     # ... two elements a thread
+    (torch.bfloat16, 1, 2048, 1024, 1, 5, 8),    # ... four elements a thread
+    (torch.float32, 2, 2304, 1000, 1, 5, 8),     # ... as many as it takes, the last round ragged
     # large batches: two and four tiles of a layer per workgroup, the last ones ragged
     (torch.bfloat16, 520, 264, 520, 1, 67, 8),
     (torch.bfloat16, 1030, 264, 520, 1, 67, 8),
