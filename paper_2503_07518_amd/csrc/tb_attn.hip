@@ -23,6 +23,13 @@
 // workgroup a head: unchanged.  More workgroups than two a compute unit still lose (768: 893 and 366,
 // 1024: 865 and 419 us on these two).
 //
+// Few KV groups (one, two or four: no placement per XCD, below): the splits of a head lie on the XCDs
+// split % 8, and with the tiles going round all of them every XCD fetches the rows of all heads.  There
+// (where the splits divide by eight) the list is cut into eight shares, one per XCD, and its tiles go round the
+// waves of that XCD.  The first list entry then waits for the count: 0.07 us.  4 groups of eight heads, fp32,
+// 2839 of 11356 rows: 15.5 us without shares, 13.2 with them, 6000 of 18000 rows: 24.3 and 18.7; 4 groups of four,
+// bf16, 6000 of 18000 rows: 11.7 and 10.9.
+//
 // Head-less lists (one list per batch element for all heads) go through the same kernel with
 // the list shared, or, when there are enough KV groups to fill the chip, through
 // attn_group_kernel: one workgroup per (b, kv head, split) that serves all query heads of the
@@ -75,7 +82,8 @@ __device__ inline float exp2_safe(float d) { return __builtin_amdgcn_exp2f(d); }
 // acknowledged (s_waitcnt with all counters at zero).
 __device__ inline void publish_fence() { __builtin_amdgcn_s_waitcnt(0); }
 
-template <typename T, int D, bool BUF>
+// SHARES: the list is cut into one share per XCD (nsplit divides by their number)
+template <typename T, int D, bool BUF, bool SHARES>
 __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(AttnArgs a) {
   constexpr int EPL = Pack16<T>::kElts;    // elements per lane
   constexpr int LPR = D / EPL;             // lanes per row
@@ -116,10 +124,10 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   }
   const int64_t u = static_cast<int64_t>(b) * a.Hq + h;
 
-  // The tiles of the list go round the head's waves (see the head of this file)
-  const int64_t w_beg = static_cast<int64_t>(split * kAttnWaves + wave) * TILE;
-  const int64_t stride = static_cast<int64_t>(a.nsplit) * kAttnWaves * TILE;
-  int64_t cnt, total;  // set once the count has arrived (first-tile block below)
+  // The tiles of the list, or of an XCD's share of it, go round the waves (see the head of this file)
+  int64_t w_beg = static_cast<int64_t>(split * kAttnWaves + wave) * TILE;
+  int64_t stride = static_cast<int64_t>(a.nsplit) * kAttnWaves * TILE;
+  int64_t cnt, total;  // set once the count has arrived (first-tile block below); total: this wave's end
 
   const char* kbase = reinterpret_cast<const char*>(static_cast<const T*>(a.K) + b * a.k_stride_b +
                                                    hkv * a.k_stride_h) + sub * 16;
@@ -164,11 +172,17 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
     return -1;
   };
   int32_t n_next;
-  if (BUF) {
-    int64_t cnt_now = a.count[u];
+  if (BUF || SHARES) {
+    int64_t cnt_now = a.count[lu];
     cnt_now = cnt_now < 0 ? 0 : (cnt_now > a.max_count ? a.max_count : cnt_now);
     cnt = cnt_now;
     total = cnt + (a.tail_end - a.tail_begin);
+    if (SHARES) {  // whole tiles per XCD
+      const int64_t share = (total + kXcds * TILE - 1) / (kXcds * TILE) * TILE, beg = (split % kXcds) * share;
+      w_beg = beg + static_cast<int64_t>(split / kXcds * kAttnWaves + wave) * TILE;
+      stride = static_cast<int64_t>(a.nsplit / kXcds) * kAttnWaves * TILE;
+      total = min(total, beg + share);
+    }
     n_next = fetch_rows(w_beg);
   } else {
     // first tile: the list entry is read without waiting for the count (the slot is inside
@@ -987,10 +1001,15 @@ tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
   }
   dim3 grid(L.plan.nsplit, d.Hq, d.B);
   if (a.xcd_map) grid = dim3(static_cast<unsigned>(kXcds * ((a.n_kv_groups + kXcds - 1) / kXcds) * a.g * a.nsplit));
-  if (L.Kbuf)
-    hipLaunchKernelGGL((attn_kernel<T, D, true>), grid, dim3(kAttnThreads), 0, st, a);
+  const bool shares = a.g > 1 && !a.xcd_map && a.nsplit % kXcds == 0;
+  if (L.Kbuf && shares)
+    hipLaunchKernelGGL((attn_kernel<T, D, true, true>), grid, dim3(kAttnThreads), 0, st, a);
+  else if (L.Kbuf)
+    hipLaunchKernelGGL((attn_kernel<T, D, true, false>), grid, dim3(kAttnThreads), 0, st, a);
+  else if (shares)
+    hipLaunchKernelGGL((attn_kernel<T, D, false, true>), grid, dim3(kAttnThreads), 0, st, a);
   else
-    hipLaunchKernelGGL((attn_kernel<T, D, false>), grid, dim3(kAttnThreads), 0, st, a);
+    hipLaunchKernelGGL((attn_kernel<T, D, false, false>), grid, dim3(kAttnThreads), 0, st, a);
   return hip_status(hipGetLastError());
 }
 

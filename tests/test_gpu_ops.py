@@ -506,6 +506,40 @@ def test_attn_full_budget_equals_dense_and_tail(oracle):
     assert_attention(np_of(out_t), ro, "bf16", np_of(lse_t), rl)
 
 
+@pytest.mark.parametrize("dtype,g,Hkv,D", [(torch.bfloat16, 8, 1, 128), (torch.bfloat16, 4, 2, 64), (torch.float32, 2, 4, 128)])
+@pytest.mark.parametrize("cap,counts", [(1500, (1500, 1, 127)), (3000, (129, 2999, 0)), (3000, (1023, 1025, 2048))])
+def test_attn_few_groups_shares(oracle, dtype, g, Hkv, D, cap, counts):
+    """Few KV groups, whose lists are cut into one share per XCD: lists of every length below their
+    capacity, with a tail, and the buffered form the same bit for bit."""
+    from paper_2503_07518_amd import binding as tb
+    say(f"attn shares dtype={dtype} g={g} Hkv={Hkv} D={D} counts={counts}")
+    B, Hq, N = 1, g * Hkv, 2 * cap + 9
+    q, K, V = randn((B, Hq, D), dtype, 26), randn((B, Hkv, N, D), dtype, 27), randn((B, Hkv, N, D), dtype, 28)
+    tail, sm = (N - 9, N - 2), 1 / math.sqrt(D)
+    idx, cnt = random_lists(B, Hq, N - 9, cap, seed=29)
+    for h in range(Hq):
+        c = counts[h % 3]
+        idx[0, h, :c] = np.sort(np.random.default_rng(h).choice(N - 9, c, replace=False))
+        cnt[0, h] = c
+    ti, tc = torch.from_numpy(idx).to(DEV), torch.from_numpy(cnt).to(DEV)
+    out, lse = gpu_attn(q, K, V, ti, tc, N, sm, tail=tail)
+    Kbuf, Vbuf = (torch.zeros((B, Hq, cap, D), dtype=dtype, device=DEV) for _ in range(2))
+    d = tb.make_desc(N, Hq, K=K, V=V)
+    ws = tb.new_workspace(tb.TB_OP_ATTN, d, cap + 7)
+    out_b, lse_b = torch.empty_like(out), torch.empty_like(lse)
+    tb.tb_gather_kv(d, K, V, ti, tc, cap, Kbuf, Vbuf)
+    tb.tb_buffered_decode_attn(d, q, Kbuf, Vbuf, tc, cap, K, V, sm, out_b, lse_b, ws, tail_begin=tail[0], tail_end=tail[1])
+    torch.cuda.synchronize()
+    joined = np.full((B, Hq, cap + 7), -1, np.int32)
+    for h in range(Hq):
+        joined[0, h, :cnt[0, h]] = idx[0, h, :cnt[0, h]]
+        joined[0, h, cnt[0, h]:cnt[0, h] + 7] = np.arange(*tail)
+    dn = dtype_name(K)
+    ro, rl = oracle.sparse_decode_attn(np_of(q), np_of(K), np_of(V), joined, cnt + 7, dn, sm)
+    assert_attention(np_of(out), ro, dn, np_of(lse), rl)
+    assert torch.equal(out, out_b) and torch.equal(lse, lse_b)
+
+
 def test_attn_strided_cache_and_max_count_truncation(oracle):
     say("attn on a strided cache view; max_count truncates longer lists")
     B, Hq, Hkv, D, N = 2, 4, 2, 128, 1200
