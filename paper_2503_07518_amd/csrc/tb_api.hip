@@ -11,56 +11,66 @@ constexpr int64_t kAttnTargetWgs = 512;   // workgroups a launch of the split at
 constexpr int64_t kAttnGroupTargetWgs = 256;
 constexpr int64_t kAttnMinTiles = 2;      // a workgroup is worth its hand-over from two tiles per wave on
 
-static AttnPlan split_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, int granule, int64_t target_wgs, int64_t min_tiles) {
-  AttnPlan p;
-  if (max_rows <= 0 || units <= 0) {
-    p.rows_per_wg = tile_rows_per_wg;
-    p.nsplit = 1;
-    p.max_split = 1;
-    return p;
-  }
-  int64_t want = (target_wgs + units - 1) / units;
-  const int64_t max_split = max_rows / (min_tiles * tile_rows_per_wg);
-  if (want > max_split) want = max_split;
-  if (want < 1) want = 1;
-  // equal shares, rounded up to whole wave instructions (4 rows x 4 waves for 256-byte rows) rather
-  // than whole tiles: a ragged last tile per wave costs less than a last workgroup round that
-  // only some compute units take part in
+// `want` splits or a few less: as many as equal shares of whole granules make
+static AttnPlan split_plan(int64_t max_rows, int64_t want, int granule) {
+  AttnPlan p{1, static_cast<int>(want)};
   int64_t rows = (max_rows + want - 1) / want;
   rows = (rows + granule - 1) / granule * granule;
-  p.rows_per_wg = static_cast<int>(rows);
   p.nsplit = static_cast<int>((max_rows + rows - 1) / rows);
-  p.max_split = static_cast<int>(want);
   return p;
 }
 
 AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg) {
+  if (max_rows <= 0 || units <= 0) return AttnPlan{1, 1};
   // Aim for two workgroups per compute unit (256 CUs): the gathers of the whole chip are in
   // flight together, and fewer, longer workgroups mean fewer partials to hand over (measured
   // best across the five configurations; 1024 was 1 µs slower on the smallest and 2 µs on the
-  // largest).  A workgroup takes whole wave tiles.
-  return split_plan(units, max_rows, tile_rows_per_wg, tile_rows_per_wg / kAttnLoadsPerTile, kAttnTargetWgs, kAttnMinTiles);
+  // largest).
+  int64_t want = (kAttnTargetWgs + units - 1) / units;
+  const int64_t most = max_rows / (kAttnMinTiles * tile_rows_per_wg);
+  if (want > most) want = most;
+  if (want < 1) want = 1;
+  return split_plan(max_rows, want, tile_rows_per_wg / kAttnLoadsPerTile);
 }
 
 AttnPlan attn_group_plan(const tb_cache_desc* d, int64_t max_rows) {
   const int64_t groups = static_cast<int64_t>(d->B) * d->Hkv;
-  if (!attn_group_mfma(d)) return attn_plan(groups, max_rows, attn_tile_rows_per_wg(d->dtype, d->D));
-  // on the matrix cores: 8 waves of 32 rows a step, one such workgroup per compute unit (the same
-  // rows in flight as two of 4 waves, half the partials to combine)
-  return split_plan(groups, max_rows, 32 * kAttnGroupWaves, 4 * kAttnGroupWaves, kAttnGroupTargetWgs, 1);
+  if (max_rows <= 0 || groups <= 0 || !attn_group_mfma(d)) return attn_plan(groups, max_rows, attn_tile_rows_per_wg(d->dtype, d->D));
+  // On the matrix cores: 8 waves of 32 rows a step, up to one such workgroup per compute unit (the same
+  // rows in flight as two of 4 waves, half the partials to combine).  A compute unit holds one of them at D = 128,
+  // so a few more than compute units would take a second round (g = 4, D = 128, 3300 rows, attention alone:
+  // 24 groups 18.4 us with 11 splits, 15.9 with 10; 72 groups 37.4 with 4, 27.0 with 3).  More groups than
+  // compute units take several rounds anyway: as many splits as make the rounds shortest in all, a round
+  // costing its rows and about two steps (304 groups, 3000 rows: 112.5 us with one split, 102.7 with three; 1500
+  // rows 53.5 and 52.6).
+  const int64_t step = 32 * kAttnGroupWaves, most = max_rows > step ? max_rows / step : 1;
+  int64_t want = kAttnGroupTargetWgs / groups, cap = want;
+  if (groups > kAttnGroupTargetWgs) {
+    auto cost = [&](int64_t n) { return (groups * n + kAttnGroupTargetWgs - 1) / kAttnGroupTargetWgs * (max_rows / n + 2 * step); };
+    want = 1;
+    cap = 4;
+    for (int64_t n = 2; n <= cap && n <= most; ++n)
+      if (cost(n) < cost(want)) want = n;
+  }
+  AttnPlan p = split_plan(max_rows, want < most ? want : most, 4 * kAttnGroupWaves);
+  p.max_split = static_cast<int>(cap < most ? cap : most);
+  return p;
 }
 
 // A shared list with grouped queries: one workgroup per (KV group, split) loads every row once
 // for all heads of the group.  That pays when there are enough KV groups to fill the chip with
 // few splits each (the last workgroup of a group combines heads x splits partials with
 // device-scope loads, about 0.1 us per split); with fewer groups the per-head kernel, whose
-// heads share rows through the L2 of their XCD, is faster.  On the matrix cores: 16 groups from 3072 rows on (g = 4,
-// score to attention: 3661 rows 29.6 -> 28.4 us, 8576 rows 50.3 -> 44.1; g = 8, 1384 rows 34.3 -> 35.6),
-// 8 groups nowhere (3661 rows: 25.0 -> 26.8).
+// heads share rows through the L2 of their XCD, is faster.  On the matrix cores: 16 groups from 3072 rows on
+// (attention alone, per head and grouped, us: 16 groups of four, D = 128: 2500 rows 11.3 and 12.6, 3400 rows 13.6 and
+// 13.5, 4200 rows 16.1 and 14.3; 24 groups: 3300 rows 17.5 and 15.9; groups of eight gain from 2000 rows on), the
+// narrowest shape from 4096 on (16 groups of four, D = 64: 3300 rows 9.4 and 10.3, 4200 10.7 and 10.9, 6000 12.2 and
+// 11.4; from 20 groups on 17.1 and 10.8 at 3300); 8 groups nowhere (score to attention, 3661 rows: 25.0 and 26.8).
 bool attn_shared_list_grouped(const tb_cache_desc* d, int64_t max_rows) {
   const int64_t groups = static_cast<int64_t>(d->B) * d->Hkv;
   if (d->Hq <= d->Hkv) return false;
-  return groups >= 32 || (attn_group_mfma(d) && groups >= 16 && max_rows >= 3072);
+  const int64_t enough = groups < 20 && d->Hq / d->Hkv * d->D <= 256 ? 4096 : 3072;
+  return groups >= 32 || (attn_group_mfma(d) && groups >= 16 && max_rows >= enough);
 }
 
 SelectPlan select_plan(int64_t units, int64_t candidates, int64_t N, int64_t kk) {

@@ -25,9 +25,8 @@ struct WsLayout {
 };
 
 struct AttnPlan {
-  int rows_per_wg;  // list entries handled by one workgroup
-  int nsplit;       // workgroups per (b,h)
-  int max_split;    // upper bound of nsplit for any list no longer than the one planned for
+  int nsplit;     // workgroups per (b,h): the tiles of its list go round them
+  int max_split;  // upper bound of nsplit for any list no longer than the one planned for
 };
 
 AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg);

@@ -170,6 +170,37 @@ def test_headless_infinite_values(oracle, g, D, rows):
     assert_attention(np.where(fin, got, 0.0), np.where(fin, ref, 0.0), "bf16", np_of(lse), r_lse)
 
 
+@pytest.mark.parametrize("B,Hkv,g,D,rows", [(33, 8, 4, 64, 2100), (38, 8, 4, 128, 1100), (5, 8, 8, 128, 1900), (3, 8, 4, 128, 3100),
+                                            (2, 8, 4, 64, 4095), (2, 8, 4, 64, 4100)])
+def test_headless_group_counts(oracle, B, Hkv, g, D, rows):
+    """Numbers of KV groups that do not divide the compute units, more groups than compute units (several
+    splits), and either side of the list length from which sixteen narrow groups are served together;
+    the workspace is sized for the longest list and shorter lists use it, too."""
+    say(f"head-less group counts B={B} Hkv={Hkv} g={g} D={D} rows={rows}")
+    gen = torch.Generator().manual_seed(37)
+    N, dt = rows + 50, torch.bfloat16
+    K = torch.randn((B, Hkv, N, D), generator=gen).to(dt)
+    V = torch.randn((B, Hkv, N, D), generator=gen).to(dt)
+    q = torch.randn((B, g * Hkv, D), generator=gen).to(dt)
+    idx = torch.stack([torch.randperm(N, generator=gen)[:rows].sort().values for _ in range(B)]).to(torch.int32)
+    sm, pick = 1.0 / math.sqrt(D), [0, B - 1]
+    Kd, Vd, qd, idxd = K.to(DEV), V.to(DEV), q.to(DEV), idx.to(DEV)
+    d = tb.make_desc(N, g * Hkv, K=Kd, V=Vd)
+    ws = tb.new_workspace(tb.TB_OP_ATTN, d, rows)
+    for n in (rows, 700, 257, rows):
+        cnt = torch.full((B,), n, dtype=torch.int32)
+        cnt[B // 2] = n // 2
+        out = torch.full((B, g * Hkv, D), float("nan"), dtype=torch.float32, device=DEV)
+        lse = torch.full((B, g * Hkv), float("nan"), dtype=torch.float32, device=DEV)
+        tb.tb_sparse_decode_attn_shared(d, qd, Kd, Vd, idxd, cnt.to(DEV), n, sm, out, lse, ws)
+        torch.cuda.synchronize()
+        for b in sorted({*pick, B // 2}):
+            ref, r_lse = oracle.sparse_decode_attn_shared(np_of(q[b:b + 1]), np_of(K[b:b + 1]), np_of(V[b:b + 1]), idx[b:b + 1].numpy(),
+                                                          cnt[b:b + 1].numpy(), "bf16", sm)
+            assert_attention(np_of(out[b:b + 1]), ref, "bf16", np_of(lse[b:b + 1]), r_lse)
+        assert bool(torch.isfinite(out).all())
+
+
 @pytest.mark.parametrize("name", ["C2_llama3_8b_32k", "C3_batched_depth", "C5_long_context"])
 def test_headless_full_size_configs(oracle, name):
     """The benchmark shapes with one importance head (the first KV head's projected keys):
