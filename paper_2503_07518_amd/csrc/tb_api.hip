@@ -97,26 +97,32 @@ SelectPlan select_plan(int64_t units, int64_t candidates, int64_t N, int64_t kk)
   p.piece_tiles = tiles;
   const int64_t cap = 2 * kk + 4096;                      // the budget, the bracket's slack, a coarse top bin
   p.cap = ((cap < len ? cap : len) + 3) / 4 * 4;
-  // what the pieces keep together: the share of the row above the cut, whose rank in the sample is that
-  // of the threshold plus the bracket's slack, five standard deviations of that rank more, and every
-  // piece padded to a multiple of 4
+  // what the pieces keep together, give or take: the share of the row above the cut (the rank of the
+  // threshold in the sample plus twice the bracket's slack: the cut lies one slack below the expected rank, and
+  // the other one allows for the sample's own spread), every piece padded to a multiple of 4
   const double frac = static_cast<double>(kk) / static_cast<double>(candidates);
   auto kept_of = [&](double n_s) {
-    const double ks = frac * n_s, rank = ks + 6.0 * sqrt(ks * (1.0 - frac)) + 4.0;
-    const double kept = (rank + 5.0 * sqrt(rank)) / n_s * static_cast<double>(candidates) + 3.0 * static_cast<double>(pieces);
+    const double ks = frac * n_s, slack = 6.0 * sqrt(ks * (1.0 - frac)) + 4.0;
+    const double kept = (ks + 2.0 * slack) / n_s * static_cast<double>(candidates) + 3.0 * static_cast<double>(pieces);
     return kept < static_cast<double>(pieces * p.cap) ? kept : static_cast<double>(pieces * p.cap);
   };
-  double kept = kept_of(4.0 * 64 * waves);
+  // 4096-key tiles that stage B holds (32: more than it can hold, it reads them again in every phase)
+  auto tiles_of = [](double kept) {
+    const int64_t t4k = (static_cast<int64_t>(kept) + 4095) / 4096;
+    return t4k <= 2 ? 2 : (t4k <= 4 ? 4 : (t4k <= 8 ? 8 : (t4k <= 16 ? 16 : 32)));
+  };
   // A small budget of a very long row is a small rank in a piece's own sample, and the pieces keep
   // several budgets' worth of keys.  Where these would need more than 8 tiles of stage B, one larger
-  // sample of the row, taken once, is worth its launch (32 rows of 1M scores, 8192 kept: the selection
-  // 73 -> 50 us, stage B 38.8 -> 15.2 of them); elsewhere it is not (256 rows of 131072: 48 us either way, 32 rows: 2 us slower).
-  if (kept > 8 * 4096) {
+  // sample of the row, taken once, is worth its launch if fewer tiles do then (32 rows of 1M scores, 8192 kept:
+  // the selection 73 -> 50 us, stage B 38.8 -> 15.2 of them; 32 rows of 500000, 15625 kept: 53 -> 36); elsewhere it is
+  // not (256 rows of 131072: 48 us either way, 32 rows: 2 us slower; 64 rows of 262144, 30840 kept, sixteen tiles
+  // either way: 70 -> 72).
+  int stage_b = tiles_of(kept_of(4.0 * 64 * waves));
+  if (stage_b > 8 && tiles_of(kept_of(kRowSample)) < stage_b) {
     p.row_sample = true;
-    kept = kept_of(kRowSample);
+    stage_b = tiles_of(kept_of(kRowSample));
   }
-  const int64_t t4k = (static_cast<int64_t>(kept) + 4095) / 4096;
-  p.stage_b_tiles = t4k <= 2 ? 2 : (t4k <= 4 ? 4 : (t4k <= 8 ? 8 : 16));
+  p.stage_b_tiles = stage_b < 16 ? stage_b : 16;
   return p;
 }
 
