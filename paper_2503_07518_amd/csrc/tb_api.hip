@@ -325,9 +325,18 @@ tb_status sparse_attn(const tb_cache_desc* d, const void* q, const void* K, cons
   if (units == 0) return TB_OK;
   const int64_t rows = max_count + (tail_end - tail_begin);
   const bool grouped = shared_list && attn_shared_list_grouped(d, rows);
-  const AttnPlan plan = grouped ? attn_group_plan(d, rows) : attn_plan(units, rows, attn_tile_rows_per_wg(d->dtype, d->D));
+  const AttnPlan by_head = attn_plan(units, rows, attn_tile_rows_per_wg(d->dtype, d->D));
+  AttnPlan plan = grouped ? attn_group_plan(d, rows) : by_head;
+  if (!ws || !aligned16(ws)) return TB_ERR_WORKSPACE;
+  if (grouped && attn_group_mfma(d)) {
+    // where a workgroup per KV group splits finer than the forms that such a shape asked room for before it
+    // (per head, or one split a group), a workspace of that size still serves, with fewer splits
+    const int64_t groups = static_cast<int64_t>(d->B) * d->Hkv;
+    const int least = groups > kAttnGroupTargetWgs ? 1 : (groups < 32 ? by_head.nsplit : plan.nsplit);
+    while (plan.nsplit > least && ws_bytes < ws_layout(units, d->D, plan.nsplit).total) --plan.nsplit;
+  }
   const WsLayout w = ws_layout(units, d->D, plan.nsplit);
-  if (!ws || !aligned16(ws) || ws_bytes < w.total) return TB_ERR_WORKSPACE;
+  if (ws_bytes < w.total) return TB_ERR_WORKSPACE;
   AttnLaunch L{d,   q,   K,   V,
                idx, count, idx_cap, max_count, tail_begin, tail_end,
                sm_scale, out, lse,

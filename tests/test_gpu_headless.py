@@ -201,6 +201,39 @@ def test_headless_group_counts(oracle, B, Hkv, g, D, rows):
         assert bool(torch.isfinite(out).all())
 
 
+@pytest.mark.parametrize("B,Hkv,D,rows,fits", [(38, 8, 64, 2100, 200), (2, 8, 64, 4200, None)])
+def test_headless_workspace_of_fewer_splits(oracle, B, Hkv, D, rows, fits):
+    """A workspace with room for one split a group (more groups than compute units), or for the per-head
+    form (16 groups), serves the grouped form with fewer splits; a smaller one is refused."""
+    say(f"head-less, workspace of fewer splits, B={B} Hkv={Hkv} rows={rows}")
+    gen = torch.Generator().manual_seed(38)
+    g, N = 4, rows + 20
+    K = torch.randn((B, Hkv, N, D), generator=gen).to(torch.bfloat16)
+    V = torch.randn((B, Hkv, N, D), generator=gen).to(torch.bfloat16)
+    q = torch.randn((B, g * Hkv, D), generator=gen).to(torch.bfloat16)
+    idx = torch.stack([torch.randperm(N, generator=gen)[:rows].sort().values for _ in range(B)]).to(torch.int32)
+    cnt, sm = torch.full((B,), rows, dtype=torch.int32), 1.0 / math.sqrt(D)
+    Kd, Vd, qd, idxd, cntd = (t.to(DEV) for t in (K, V, q, idx, cnt))
+    d = tb.make_desc(N, g * Hkv, K=Kd, V=Vd)
+    units = B * g * Hkv
+    if fits:  # one split
+        need = tb.tb_workspace_bytes(tb.TB_OP_ATTN, d, fits)
+    else:     # 512 workgroups over the heads
+        one = tb.tb_workspace_bytes(tb.TB_OP_ATTN, d, 100)
+        need = one + (512 // units - 1) * units * (D + 2) * 4
+    assert need < tb.tb_workspace_bytes(tb.TB_OP_ATTN, d, rows)
+    out, lse = torch.empty((B, g * Hkv, D), dtype=torch.float32, device=DEV), torch.empty((B, g * Hkv), dtype=torch.float32, device=DEV)
+    ws = torch.zeros(need, dtype=torch.uint8, device=DEV)
+    tb.tb_sparse_decode_attn_shared(d, qd, Kd, Vd, idxd, cntd, rows, sm, out, lse, ws)
+    torch.cuda.synchronize()
+    for b in (0, B - 1):
+        ref, r_lse = oracle.sparse_decode_attn_shared(np_of(q[b:b + 1]), np_of(K[b:b + 1]), np_of(V[b:b + 1]), idx[b:b + 1].numpy(),
+                                                      cnt[b:b + 1].numpy(), "bf16", sm)
+        assert_attention(np_of(out[b:b + 1]), ref, "bf16", np_of(lse[b:b + 1]), r_lse)
+    with pytest.raises(tb.TbError):
+        tb.tb_sparse_decode_attn_shared(d, qd, Kd, Vd, idxd, cntd, rows, sm, out, lse, ws[:need - 256])
+
+
 @pytest.mark.parametrize("name", ["C2_llama3_8b_32k", "C3_batched_depth", "C5_long_context"])
 def test_headless_full_size_configs(oracle, name):
     """The benchmark shapes with one importance head (the first KV head's projected keys):
