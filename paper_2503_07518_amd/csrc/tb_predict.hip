@@ -160,10 +160,8 @@ template <>
 struct MfmaStep<bf16_t> {
   static constexpr int kInputs = 32;  // inputs that a wave covers: 4 lane groups x 8
   static constexpr int kAccs = 1;
-  static constexpr bool kSplit = true;  // activations enter in parts
-  // INF: infinite and NaN weights meet the upper parts only (a lower part may be 0, and 0 times infinity
-  // is NaN).
-  template <bool INF, int NT, typename Acc>
+  static constexpr bool kSplit = true;  // activations enter in parts: see sum_of_products()
+  template <int NT, typename Acc>
   __device__ static inline void run(const float (&x)[8], const uint4 (&w)[NT], Acc&& acc) {
     uint32_t p[3][4];
 #pragma unroll
@@ -188,16 +186,12 @@ struct MfmaStep<bf16_t> {
     for (int t = 0; t < 3; ++t) __builtin_memcpy(&xv[t], &p[t][0], 16);
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
-      mfma_bf16x8 wv, wv_low;
+      mfma_bf16x8 wv;
       __builtin_memcpy(&wv, &w[n], 16);
-      uint4 low = w[n];
-      if constexpr (INF)
-        low = make_uint4(bf16x2_finite_or_zero(low.x), bf16x2_finite_or_zero(low.y), bf16x2_finite_or_zero(low.z), bf16x2_finite_or_zero(low.w));
-      __builtin_memcpy(&wv_low, &low, 16);
       mfma_f32x4& sum = acc(n)[0];
 #pragma unroll
       for (int t = 2; t >= 0; --t)  // the small parts first
-        sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[t], t > 0 ? wv_low : wv, sum, 0, 0, 0);
+        sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[t], wv, sum, 0, 0, 0);
     }
   }
 };
@@ -207,7 +201,7 @@ struct MfmaStep<float> {
   static constexpr int kInputs = 16;
   static constexpr int kAccs = 4;
   static constexpr bool kSplit = false;
-  template <bool INF, int NT, typename Acc>
+  template <int NT, typename Acc>
   __device__ static inline void run(const float (&x)[4], const float4 (&w)[NT], Acc&& acc) {
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
@@ -226,16 +220,16 @@ __device__ inline mfma_f32x4 total_of(const mfma_f32x4 (&acc)[NA]) {
   else return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
-// Whether a lane of the wave holds a NaN sum: it may come from an infinite weight and a lower part of an
-// activation that is 0, and the wave multiplies again with care.  (Infinities of both signs make a NaN, too.)
-template <int MT, int NA>
-__device__ inline bool any_nan(const mfma_f32x4 (&acc)[MT][NA]) {
-  float s = 0.f;
-#pragma unroll
-  for (int m = 0; m < MT; ++m)
-#pragma unroll
-    for (int c = 0; c < NA; ++c) s += (acc[m][c][0] + acc[m][c][1]) + (acc[m][c][2] + acc[m][c][3]);
-  return __any(s != s);
+// `sum` as the matrix cores have it, or, where that is NaN, the plain chain of multiply-adds: a lower part of an
+// activation may be 0, and 0 times an infinite weight is NaN, where the product itself is infinite.
+template <typename T, typename X>
+__device__ inline float sum_of_products(float sum, const T* w, int k0, int k1, X&& x) {
+  if (MfmaStep<T>::kSplit && __builtin_expect(sum != sum, 0)) {
+    sum = 0.f;
+#pragma nounroll
+    for (int k = k0; k < k1; ++k) sum = fmaf(x(k), to_float(w[k]), sum);
+  }
+  return sum;
 }
 
 // Partial sums over the inputs [slice * steps * NW waves * kInputs, ...) of NT * 16 hidden units and
@@ -339,47 +333,37 @@ __global__ __launch_bounds__(NW * kWave) void hidden_kernel(PredictArgs a, int n
     mean[m] = s_mean[rr];
     rstd[m] = s_rstd[rr];
   }
-  auto multiply = [&](auto inf_tag) {
-    constexpr bool kInf = decltype(inf_tag)::value;
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int m = 0; m < MT; ++m)
+    for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int c = 0; c < Step::kAccs; ++c) acc[t][m][c] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < steps; s0 += CH) {
-      if (kInf || s0 > 0) load(s0);
+      for (int c = 0; c < Step::kAccs; ++c) acc[t][m][c] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < steps; s0 += CH) {
+    if (s0 > 0) load(s0);
 #pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        if (s0 + c < steps) {  // the same for the whole wave
-          const bool in = k_first + (s0 + c) * Step::kInputs < a.E;  // pieces past the row add nothing
-          float gm[EPL], bt[EPL];
-          Pack16<T>::unpack(gr[c], gm);
-          Pack16<T>::unpack(br[c], bt);
-          typename Pack16<T>::Raw w[NT];
+    for (int c = 0; c < CH; ++c) {
+      if (s0 + c < steps) {  // the same for the whole wave
+        const bool in = k_first + (s0 + c) * Step::kInputs < a.E;  // pieces past the row add nothing
+        float gm[EPL], bt[EPL];
+        Pack16<T>::unpack(gr[c], gm);
+        Pack16<T>::unpack(br[c], bt);
+        typename Pack16<T>::Raw w[NT];
 #pragma unroll
-          for (int t = 0; t < NT; ++t) {
-            w[t] = wr[c][t];
-            if (!in) w[t] = typename Pack16<T>::Raw{};
-          }
+        for (int t = 0; t < NT; ++t) {
+          w[t] = wr[c][t];
+          if (!in) w[t] = typename Pack16<T>::Raw{};
+        }
 #pragma unroll
-          for (int m = 0; m < MT; ++m) {
-            float x[EPL];
-            Pack16<T>::unpack(hr[c][m], x);
+        for (int m = 0; m < MT; ++m) {
+          float x[EPL];
+          Pack16<T>::unpack(hr[c][m], x);
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) x[e] = in ? (x[e] - mean[m]) * rstd[m] * gm[e] + bt[e] : 0.f;
-            Step::template run<kInf, NT>(x, w, [&](int t) -> mfma_f32x4(&)[Step::kAccs] { return acc[t][m]; });
-          }
+          for (int e = 0; e < EPL; ++e) x[e] = in ? (x[e] - mean[m]) * rstd[m] * gm[e] + bt[e] : 0.f;
+          Step::template run<NT>(x, w, [&](int t) -> mfma_f32x4(&)[Step::kAccs] { return acc[t][m]; });
         }
       }
     }
-  };
-  multiply(std::false_type{});
-  if constexpr (Step::kSplit) {
-    bool nan = false;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) nan |= any_nan(acc[t]);
-    if (__builtin_expect(nan, 0)) multiply(std::true_type{});
   }
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
@@ -397,6 +381,12 @@ __global__ __launch_bounds__(NW * kWave) void hidden_kernel(PredictArgs a, int n
       for (int w = 0; w < NW; ++w) sum += s_red[w][m][e];
       const int b = b0 + m * 16 + row;
       if (b < a.B && n < a.hidden) {
+        const T* h = static_cast<const T*>(a.h) + static_cast<int64_t>(b) * a.E;
+        const int span = NW * steps * Step::kInputs, k0 = slice * span;
+        sum = sum_of_products(sum, static_cast<const T*>(a.W1) + static_cast<int64_t>(n) * a.E, k0, min(k0 + span, a.E), [&](int k) {
+          return (to_float(h[k]) - s_mean[m * 16 + row]) * s_rstd[m * 16 + row] * to_float(static_cast<const T*>(a.gamma)[k]) +
+                 to_float(static_cast<const T*>(a.beta)[k]);
+        });
         if (n_slices == 1)
           a.z[static_cast<int64_t>(b) * a.hidden + n] = gelu_erf(sum + to_float(static_cast<const T*>(a.b1)[n]));
         else
@@ -520,59 +510,48 @@ __global__ __launch_bounds__(kOutWaves * kWave) void output_kernel(PredictArgs a
     xrow[m] = (FOLD ? s_z : a.z) + static_cast<int64_t>(b < a.B ? b : a.B - 1) * a.hidden;
   }
   mfma_f32x4 acc[NT][MT][Step::kAccs];
-  auto multiply = [&](auto inf_tag) {
-    constexpr bool kInf = decltype(inf_tag)::value;
-    if constexpr (kInf) load_w(wave * Step::kInputs);
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int c = 0; c < Step::kAccs; ++c) acc[t][m][c] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int k0 = wave * Step::kInputs; k0 < a.hidden; k0 += CH * kStride) {
+    float x[CH][MT][EPL];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int k = k0 + c * kStride + q * EPL;
+      const int ks = k < a.hidden ? k : 0;
 #pragma unroll
       for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int c = 0; c < Step::kAccs; ++c) acc[t][m][c] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = wave * Step::kInputs; k0 < a.hidden; k0 += CH * kStride) {
-      float x[CH][MT][EPL];
+        for (int e = 0; e < EPL; e += 4) {
+          const f32x4_u v = *reinterpret_cast<const f32x4_u*>(xrow[m] + ks + e);
 #pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const int k = k0 + c * kStride + q * EPL;
-        const int ks = k < a.hidden ? k : 0;
+          for (int i = 0; i < 4; ++i) x[c][m][e + i] = v[i];
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int m = 0; m < MT; ++m)
+    for (int c = 0; c < CH; ++c) {
+      const int kc = k0 + c * kStride;
+      if (kc < a.hidden) {  // the same for the whole wave
+        const bool in = kc + q * EPL < a.hidden;  // pieces past the row add nothing
+        typename Pack16<T>::Raw w[NT];
 #pragma unroll
-          for (int e = 0; e < EPL; e += 4) {
-            const f32x4_u v = *reinterpret_cast<const f32x4_u*>(xrow[m] + ks + e);
+        for (int t = 0; t < NT; ++t) {
+          w[t] = wr[c][t];
+          if (!in) w[t] = typename Pack16<T>::Raw{};
+        }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) x[c][m][e + i] = v[i];
-          }
-      }
-      __builtin_amdgcn_sched_barrier(0);
+        for (int m = 0; m < MT; ++m) {
 #pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const int kc = k0 + c * kStride;
-        if (kc < a.hidden) {  // the same for the whole wave
-          const bool in = kc + q * EPL < a.hidden;  // pieces past the row add nothing
-          typename Pack16<T>::Raw w[NT];
-#pragma unroll
-          for (int t = 0; t < NT; ++t) {
-            w[t] = wr[c][t];
-            if (!in) w[t] = typename Pack16<T>::Raw{};
-          }
-#pragma unroll
-          for (int m = 0; m < MT; ++m) {
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) x[c][m][e] = in ? x[c][m][e] : 0.f;
-            Step::template run<kInf, NT>(x[c][m], w, [&](int t) -> mfma_f32x4(&)[Step::kAccs] { return acc[t][m]; });
-          }
+          for (int e = 0; e < EPL; ++e) x[c][m][e] = in ? x[c][m][e] : 0.f;
+          Step::template run<NT>(x[c][m], w, [&](int t) -> mfma_f32x4(&)[Step::kAccs] { return acc[t][m]; });
         }
       }
-      if (k0 + CH * kStride < a.hidden) load_w(k0 + CH * kStride);
     }
-  };
-  multiply(std::false_type{});
-  if constexpr (Step::kSplit) {
-    bool nan = false;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) nan |= any_nan(acc[t]);
-    if (__builtin_expect(nan, 0)) multiply(std::true_type{});
+    if (k0 + CH * kStride < a.hidden) load_w(k0 + CH * kStride);
   }
   const int per_slot = a.Hq * a.Dimp;
   const int row = tid / 16;
@@ -592,8 +571,11 @@ __global__ __launch_bounds__(kOutWaves * kWave) void output_kernel(PredictArgs a
 #pragma unroll
       for (int w = 0; w < kOutWaves; ++w) sum += s_red[w][m][e];
       const int b = b0 + m * 16 + row;
-      if (b < a.B && o_mine < n_out)
+      if (b < a.B && o_mine < n_out) {
+        const float* z = (FOLD ? s_z : a.z) + static_cast<int64_t>(b) * a.hidden;
+        sum = sum_of_products(sum, static_cast<const T*>(a.W2) + static_cast<int64_t>(o_mine) * a.hidden, 0, a.hidden, [&](int k) { return z[k]; });
         store_elt(static_cast<T*>(a.q_imp) + (static_cast<int64_t>(slot) * a.B + b) * per_slot + rest, sum + bias[nt]);
+      }
     }
   }
 }
