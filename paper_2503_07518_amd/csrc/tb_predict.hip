@@ -432,8 +432,8 @@ __global__ __launch_bounds__(kPredThreads) void hidden_sum_kernel(PredictArgs a,
 // to the storage type and scattered to q_imp[slot][b][head][j].  The four waves split the inputs
 // (one tile per workgroup: four times the workgroups of one tile per wave).
 // FOLD (one or two sequences, several slices): every workgroup sums the first layer's partial sums
-// itself, into LDS, instead of a launch of its own that would do it; otherwise the first
-// workgroups of a group of sequences write LN(h), whose buffer held the partial sums until now.
+// itself, into LDS, instead of a launch of its own that would do it; otherwise workgroups
+// ahead of those of the tiles write LN(h), whose buffer held the partial sums until now.
 template <typename T, int MT, int NT, bool FOLD>
 __global__ __launch_bounds__(kOutWaves * kWave) void output_kernel(PredictArgs a, int n_slices) {
   static_assert(kOutWaves * kWave == kPredThreads, "ln_row and sum_slices run on kPredThreads threads");
@@ -444,20 +444,22 @@ __global__ __launch_bounds__(kOutWaves * kWave) void output_kernel(PredictArgs a
   typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));  // (z need not be 16-byte aligned)
   __shared__ float s_red[kOutWaves][MT][256];
   __shared__ float s_z[FOLD ? kFoldElements : 4];
-  int tile = blockIdx.x;
-  if constexpr (!FOLD) {  // the first workgroups of every group of sequences write its LN(h)
-    const int n_ln = min(a.B, 16 * MT);
-    if (tile < n_ln) {
-      const int b = blockIdx.y * (16 * MT) + tile;
+  int tile = blockIdx.x, group = blockIdx.y;
+  if constexpr (!FOLD) {  // LN(h): one group of sequences: by the first workgroups of its row, more: by rows of workgroups ahead of theirs
+    const int ahead = a.B <= 16 * MT ? 0 : (a.B + static_cast<int>(gridDim.x) - 1) / static_cast<int>(gridDim.x);
+    const int b = group * static_cast<int>(gridDim.x) + tile;
+    if (ahead == 0 ? tile < a.B : group < ahead) {
       if (b < a.B) ln_row<T>(a, b);
       return;
     }
-    tile -= n_ln;
+    if (ahead == 0) tile -= a.B;
+    group -= ahead;
   }
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = wave_id();
   const int r = lane % 16, q = lane / 16;
   const int n_out = a.G * a.Hq * a.Dimp;
-  const int n0 = tile * (16 * NT), b0 = blockIdx.y * (16 * MT);
+  const int n0 = tile * (16 * NT), b0 = group * (16 * MT);
+  if (n0 >= n_out) return;
   const T* wrow[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -624,8 +626,10 @@ tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
   auto launch_output = [&](auto nt, auto fold) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool FOLD = decltype(fold)::value;
-    const int n_ln = FOLD ? 0 : (a.B < 16 * MT ? a.B : 16 * MT);
-    hipLaunchKernelGGL((output_kernel<T, MT, NT, FOLD>), dim3(n_ln + (out_tiles + NT - 1) / NT, groups), dim3(kPredThreads), 0, st, a, slices);
+    // (at least 16 workgroups a row, so that the rows of LN(h) stay a few thousand)
+    const int wgs = (out_tiles + NT - 1) / NT, row = groups > 1 && wgs < 16 ? 16 : wgs;
+    const dim3 grid(groups > 1 || FOLD ? row : a.B + row, groups > 1 ? groups + (a.B + row - 1) / row : 1);
+    hipLaunchKernelGGL((output_kernel<T, MT, NT, FOLD>), grid, dim3(kPredThreads), 0, st, a, slices);
   };
   using std::integral_constant;
   const integral_constant<int, 1> one;
