@@ -588,11 +588,13 @@ tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
   const int tiles = (a.hidden + 15) / 16, groups = (a.B + 16 * MT - 1) / (16 * MT);
   const int out_tiles = (a.G * a.Hq * a.Dimp + 15) / 16;
   // Batches that fill the chip several times over: up to four tiles of a layer per workgroup, as long as
-  // one workgroup per compute unit is left, share the LayerNorm and the splitting of their activations
+  // one workgroup per compute unit is left, share the LayerNorm and the splitting of their activations (fp32
+  // activations are not split: nothing gained)
   // (bf16, 2048 sequences: E = 4096, hidden 512, 4096 outputs 340 -> 170 us, hidden 128, 128 outputs 71.7 -> 45.8,
-  // E = 8192, hidden 1024, 1024 outputs 813 -> 369; 256 sequences of the first 51.6 -> 42.3).
-  auto tiles_of = [&](int n) { return MT == 1 || n * groups < 2 * kHidTargetWgs ? 1 : (n * groups < 4 * kHidTargetWgs ? 2 : 4); };
-  const int hidden_nt = tiles_of(tiles), out_nt = tiles_of(out_tiles);
+  // E = 8192, hidden 1024, 1024 outputs 813 -> 369; 256 sequences of the first 51.6 -> 42.3)
+  // (an output workgroup is half as large: twice as many of them).
+  auto tiles_of = [&](int n, int wgs) { return !MfmaStep<T>::kSplit || MT == 1 || n * groups < 2 * wgs ? 1 : (n * groups < 4 * wgs ? 2 : 4); };
+  const int hidden_nt = tiles_of(tiles, kHidTargetWgs), out_nt = tiles_of(out_tiles, 2 * kHidTargetWgs);
   // One or two sequences with few partial sums: the output kernel adds the slices itself (it has no
   // workgroups that write LN(h) then).  B = 1: bf16, E = 2048, hidden 520, 128 outputs 10.2 us against 11.2 with a launch
   // of its own for the sums, E = 4096, hidden 1024 12.0 against 12.6; fp32, E = 2048, hidden 1024 12.7 against 14.2; more
@@ -635,7 +637,7 @@ tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
   const integral_constant<int, 1> one;
   const integral_constant<int, 8> w8;
   const integral_constant<int, 16> w16;
-  if constexpr (MT == 2) {
+  if constexpr (MT == 2 && MfmaStep<T>::kSplit) {
     const integral_constant<int, 2> two;
     const integral_constant<int, 4> four;
     if (hidden_nt == 4)
@@ -662,7 +664,7 @@ tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((hidden_sum_kernel<T>), sgrid, dim3(kPredThreads), 0, st, a, slices);
     if (hipGetLastError() != hipSuccess) return TB_ERR_HIP;
   }
-  if constexpr (MT == 2) {
+  if constexpr (MT == 2 && MfmaStep<T>::kSplit) {
     const integral_constant<int, 2> two;
     const integral_constant<int, 4> four;
     if (out_nt == 4)
