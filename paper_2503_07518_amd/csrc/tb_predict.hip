@@ -147,8 +147,8 @@ typedef short mfma_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float mfma_f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kOutWaves = 4;          // waves of an output-layer workgroup: they split the inputs
-constexpr int kFoldSums = 4096;       // up to so many partial sums the output kernel adds the slices itself
-constexpr int kFoldElements = kFoldSums / 2;  // ... which are at least two per hidden activation
+constexpr int kFoldElements = 512;    // up to so many hidden activations, or
+constexpr int kFoldSums = 4096;       // so many partial sums, the output kernel adds the slices itself
 constexpr int kHidTargetWgs = 256;    // one hidden-layer workgroup per compute unit
 
 // acc(n)[0] + ... += x . w[n] over one step, n < NT: 8 inputs of a lane (bf16 weights) or 4 (fp32 weights;
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(kOutWaves * kWave) void output_kernel(PredictArgs a
   constexpr int kStride = kOutWaves * Step::kInputs;
   typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));  // (z need not be 16-byte aligned)
   __shared__ float s_red[kOutWaves][MT][256];
-  __shared__ float s_z[FOLD ? kFoldElements : 4];
+  __shared__ float s_z[FOLD ? kFoldSums / 2 : 4];  // (at least two partial sums per activation)
   int tile = blockIdx.x, group = blockIdx.y;
   if constexpr (!FOLD) {  // LN(h): one group of sequences: by the first workgroups of its row, more: by rows of workgroups ahead of theirs
     const int ahead = a.B <= 16 * MT ? 0 : (a.B + static_cast<int>(gridDim.x) - 1) / static_cast<int>(gridDim.x);
@@ -595,11 +595,15 @@ tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
   // (an output workgroup is half as large: twice as many of them).
   auto tiles_of = [&](int n, int wgs) { return !MfmaStep<T>::kSplit || MT == 1 || n * groups < 2 * wgs ? 1 : (n * groups < 4 * wgs ? 2 : 4); };
   const int hidden_nt = tiles_of(tiles, kHidTargetWgs), out_nt = tiles_of(out_tiles, 2 * kHidTargetWgs);
-  // One or two sequences with few partial sums: the output kernel adds the slices itself (it has no
-  // workgroups that write LN(h) then).  B = 1: bf16, E = 2048, hidden 520, 128 outputs 10.2 us against 11.2 with a launch
-  // of its own for the sums, E = 4096, hidden 1024 12.0 against 12.6; fp32, E = 2048, hidden 1024 12.7 against 14.2; more
-  // partial sums (B = 2, hidden 512, eight slices) gain nothing.
-  auto folds = [&](int n_slices) { return MT == 1 && a.B <= 2 && n_slices > 1 && n_slices * a.B * a.hidden <= kFoldSums; };
+  // One or two sequences with few activations or partial sums: the output kernel adds the slices itself (it has
+  // no workgroups that write LN(h) then).  Against a launch of its own for the sums: B = 1, bf16, E = 2048, hidden 520,
+  // 128 outputs 10.2 and 11.2 us, E = 4096, hidden 1024 12.0 and 12.6; fp32, E = 2048, hidden 1024 12.7 and 14.2; B = 2, E = 3072,
+  // hidden 256 (512 activations, twelve slices) 12.8 and 15.7; B = 2, E = 2048, hidden 512, four
+  // slices: no difference in a graph, 12.5 and 15.0 launched one by one.
+  auto folds = [&](int n_slices) {
+    const int n = a.B * a.hidden;
+    return MT == 1 && a.B <= 2 && n_slices > 1 && (n <= kFoldElements || n_slices * n <= kFoldSums);
+  };
   // slices of E: as many as give up to one workgroup per compute unit (one more round for a few of them
   // would cost the most: a compute unit holds one; bf16, E = 5120, hidden 640, 5120 outputs, B = 1: 17.4 us with
   // 280 workgroups, 13.7 with 200), while every wave has a step of its own and the partial sums fit the
@@ -613,8 +617,8 @@ tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
     if (want > a.E / a.hidden) want = a.E / a.hidden;
     // two slices save less than the launch that sums them costs where a whole tile is 64 KiB of weights
     // at most (measured at B = 1 with that launch: bf16, E = 2048, hidden 1024 11.4 us without slices, 12.0 with
-    // two; fp32, twice the bytes, 16.7 and 15.4)
-    if (want < 2 || (want == 2 && !folds(2) && 16 * a.E * sizeof(T) <= 64 * 1024)) want = 1;
+    // two; fp32, twice the bytes, 16.7 and 15.4); the same for two sequences that fold (12.2 and 13.1)
+    if (want < 2 || (want == 2 && !(a.B == 1 && folds(2)) && 16 * a.E * sizeof(T) <= 64 * 1024)) want = 1;
     steps = (all_steps + want - 1) / want;
     slices = (all_steps + steps - 1) / steps;
     // 8 waves while their steps are in flight together, more waves otherwise (B = 16: 15.4 against
