@@ -591,7 +591,7 @@ tb_status launch_tiles(const PredictArgs& a, hipStream_t st) {
   // one workgroup per compute unit is left, share the LayerNorm and the splitting of their activations (fp32
   // activations are not split: nothing gained)
   // (bf16, 2048 sequences: E = 4096, hidden 512, 4096 outputs 340 -> 170 us, hidden 128, 128 outputs 71.7 -> 45.8,
-  // E = 8192, hidden 1024, 1024 outputs 813 -> 369; 256 sequences of the first 51.6 -> 42.3)
+  // E = 8192, hidden 1024, 1024 outputs 813 -> 369; 256 sequences of the first 49.5 -> 39.6)
   // (an output workgroup is half as large: twice as many of them).
   auto tiles_of = [&](int n, int wgs) { return !MfmaStep<T>::kSplit || MT == 1 || n * groups < 2 * wgs ? 1 : (n * groups < 4 * wgs ? 2 : 4); };
   const int hidden_nt = tiles_of(tiles, kHidTargetWgs), out_nt = tiles_of(out_tiles, 2 * kHidTargetWgs);
