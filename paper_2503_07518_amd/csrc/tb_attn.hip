@@ -728,7 +728,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_group_kernel(AttnArgs a) {
 //
 // Invalid slots repeat the wave's first row with weight 0 (a row that is attended anyway, so that an
 // infinite value in an unlisted row cannot reach the result).  Infinite and NaN values in attended rows
-// of V give what a sum of products gives (see walk() below): a wave whose result holds a NaN goes over
+// of V give what a sum of products gives (see below): a wave whose result holds a NaN goes over
 // its rows a second time, all others pay one test.  Relative error against 64 bits on 3661 rows 2.0e-7
 // (vector form: 2.4e-7).
 //
@@ -786,7 +786,7 @@ __global__ __launch_bounds__(kGroupWaves * kWave, 2) void attn_group_mfma_kernel
   };
   // lane r (and r + 32) of a step: the row of its slot r.  The first step's entries are read without
   // waiting for the count (the slots are inside the list's capacity whatever the count is).
-  int32_t n_first;
+  int32_t n_next;
   {
     const int64_t i0 = w_beg + (lane & 31);
     const int64_t cap1 = a.idx_cap > 0 ? a.idx_cap - 1 : 0;
@@ -795,132 +795,132 @@ __global__ __launch_bounds__(kGroupWaves * kWave, 2) void attn_group_mfma_kernel
     const int64_t c = a.count[b];
     cnt = c < 0 ? 0 : (c > a.max_count ? a.max_count : c);
     total = cnt + (a.tail_end - a.tail_begin);
-    n_first = i0 < total ? row_of(i0, raw) : row_of(w_beg, raw_first);
+    n_next = i0 < total ? row_of(i0, raw) : row_of(w_beg, raw_first);
   }
   auto fetch_rows = [&](int64_t t0) -> int32_t {
     int64_t i = t0 + (lane & 31);
     i = i < total ? i : w_beg;
     return row_of(i, i < cnt ? list[i] : 0);
   };
-  // kInf: elements of V that are infinite or NaN meet the weights' upper parts only (a lower part may be 0,
-  // and 0 times infinity is NaN), and the slots past the list's end count as rows of zeros.
-  auto walk = [&](auto inf_tag) {
-    constexpr bool kInf = decltype(inf_tag)::value;
+  auto clear = [&]() {
     m = -INFINITY;
     l = 0.f;
 #pragma unroll
     for (int e = 0; e < EV; ++e) acc[e] = acc_low[e] = attn_f32x4{0.f, 0.f, 0.f, 0.f};
-    int32_t n_next = n_first;
-    for (int64_t t0 = w_beg; t0 < total; t0 += stride) {
-      const int32_t n_mine = n_next;
-      attn_bf16x8 kraw[2][KC];
-      vword vraw[2][4];
+  };
+  // kInf: elements of V that are infinite or NaN meet the weights' upper parts only (a lower part may be 0,
+  // and 0 times infinity is NaN), and the slots past the list's end count as rows of zeros.
+  auto step = [&](const int64_t t0, auto inf_tag) {
+    constexpr bool kInf = decltype(inf_tag)::value;
+    const int32_t n_mine = n_next;
+    attn_bf16x8 kraw[2][KC];
+    vword vraw[2][4];
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const uint32_t row = static_cast<uint32_t>(__shfl(n_mine, 16 * t + i16, kWave));
+    for (int t = 0; t < 2; ++t) {
+      const uint32_t row = static_cast<uint32_t>(__shfl(n_mine, 16 * t + i16, kWave));
 #pragma unroll
-        for (int c = 0; c < KC; ++c) {
-          const uint4 x = *reinterpret_cast<const uint4*>(kbase + row * k_row_bytes + c * 64);
-          __builtin_memcpy(&kraw[t][c], &x, 16);
-        }
-      }
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const uint32_t row = static_cast<uint32_t>(__shfl(n_mine, 16 * t + 4 * kb + v, kWave));
-          vraw[t][v] = *reinterpret_cast<const vword*>(vbase + row * v_row_bytes);
-        }
-      if (t0 + stride < total) n_next = fetch_rows(t0 + stride);
-      __builtin_amdgcn_sched_barrier(0);  // every gather of the step is in flight before the first is consumed
-      if constexpr (kInf) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            if (t0 + 16 * t + 4 * kb + v >= total) vraw[t][v] = vword{};
-      }
-      float p[2][4];
-      float tmax = -INFINITY;
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        // every slice on its own, added pairwise: fewer roundings at the size of the whole sum
-        attn_f32x4 sc[KC];
-#pragma unroll
-        for (int c = 0; c < KC; ++c)
-          sc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kraw[t][c], qop[c], attn_f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        const attn_f32x4 s = KC == 2 ? sc[0] + sc[1] : (sc[0] + sc[1]) + (sc[KC - 2] + sc[KC - 1]);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const bool valid = t0 + 16 * t + 4 * kb + v < total;
-          p[t][v] = s[v];
-          tmax = fmaxf(tmax, valid ? s[v] * a.sm_scale_log2 : -INFINITY);
-        }
-      }
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 16, kWave));
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
-      const float m_new = fmaxf(m, tmax);
-      const float m_ref = (m_new > -INFINITY) ? m_new : 0.f;  // nothing seen yet: all weights 0
-      if (__any(m_new > m)) {
-        const float alpha = exp2_safe(m - m_ref);
-        l *= alpha;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const float al = __shfl(alpha, 4 * kb + v, kWave);  // (lane j < 16 holds head j)
-#pragma unroll
-          for (int e = 0; e < EV; ++e) {
-            acc[e][v] *= al;
-            acc_low[e][v] *= al;
-          }
-        }
-        m = m_new;
-      }
-      uint32_t part[3][4];  // the weights of the eight rows as three bf16 numbers each, packed in pairs
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          uint32_t w[3][2];
-#pragma unroll
-          for (int o = 0; o < 2; ++o) {
-            // one rounding for the scaled score and its distance to the maximum
-            const bool valid = t0 + 16 * t + 4 * kb + 2 * h + o < total;
-            const float x = valid ? exp2_safe(fmaf(p[t][2 * h + o], a.sm_scale_log2, -m_ref)) : 0.f;
-            l += x;
-            w[0][o] = __float_as_uint(x) & 0xFFFF0000u;
-            const float r = x - __uint_as_float(w[0][o]);  // exact
-            w[1][o] = __float_as_uint(r) & 0xFFFF0000u;
-            w[2][o] = __float_as_uint(r - __uint_as_float(w[1][o]));  // at most 8 bits are left
-          }
-#pragma unroll
-          for (int k = 0; k < 3; ++k) part[k][2 * t + h] = __builtin_amdgcn_perm(w[k][1], w[k][0], 0x07060302u);
-        }
-      attn_bf16x8 pop[3];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) __builtin_memcpy(&pop[k], &part[k][0], 16);
-#pragma unroll
-      for (int e = 0; e < EV; ++e) {
-        const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;  // element e of two rows side by side
-        uint32_t w[4];
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-            w[2 * t + h] = __builtin_amdgcn_perm(vraw[t][2 * h + 1][e / 2], vraw[t][2 * h][e / 2], sel);
-        attn_bf16x8 vop, vop_low;
-        __builtin_memcpy(&vop, &w[0], 16);
-        if constexpr (kInf) {
-#pragma unroll
-          for (int x = 0; x < 4; ++x) w[x] = bf16x2_finite_or_zero(w[x]);
-        }
-        __builtin_memcpy(&vop_low, &w[0], 16);
-#pragma unroll
-        for (int k = 2; k >= 1; --k) acc_low[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pop[k], vop_low, acc_low[e], 0, 0, 0);
-        acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pop[0], vop, acc[e], 0, 0, 0);
+      for (int c = 0; c < KC; ++c) {
+        const uint4 x = *reinterpret_cast<const uint4*>(kbase + row * k_row_bytes + c * 64);
+        __builtin_memcpy(&kraw[t][c], &x, 16);
       }
     }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const uint32_t row = static_cast<uint32_t>(__shfl(n_mine, 16 * t + 4 * kb + v, kWave));
+        vraw[t][v] = *reinterpret_cast<const vword*>(vbase + row * v_row_bytes);
+      }
+    if (t0 + stride < total) n_next = fetch_rows(t0 + stride);
+    __builtin_amdgcn_sched_barrier(0);  // every gather of the step is in flight before the first is consumed
+    if constexpr (kInf) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (t0 + 16 * t + 4 * kb + v >= total) vraw[t][v] = vword{};
+    }
+    float p[2][4];
+    float tmax = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      // every slice on its own, added pairwise: fewer roundings at the size of the whole sum
+      attn_f32x4 sc[KC];
+#pragma unroll
+      for (int c = 0; c < KC; ++c)
+        sc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kraw[t][c], qop[c], attn_f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+      const attn_f32x4 s = KC == 2 ? sc[0] + sc[1] : (sc[0] + sc[1]) + (sc[KC - 2] + sc[KC - 1]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const bool valid = t0 + 16 * t + 4 * kb + v < total;
+        p[t][v] = s[v];
+        tmax = fmaxf(tmax, valid ? s[v] * a.sm_scale_log2 : -INFINITY);
+      }
+    }
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 16, kWave));
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
+    const float m_new = fmaxf(m, tmax);
+    const float m_ref = (m_new > -INFINITY) ? m_new : 0.f;  // nothing seen yet: all weights 0
+    if (__any(m_new > m)) {
+      const float alpha = exp2_safe(m - m_ref);
+      l *= alpha;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float al = __shfl(alpha, 4 * kb + v, kWave);  // (lane j < 16 holds head j)
+#pragma unroll
+        for (int e = 0; e < EV; ++e) {
+          acc[e][v] *= al;
+          acc_low[e][v] *= al;
+        }
+      }
+      m = m_new;
+    }
+    uint32_t part[3][4];  // the weights of the eight rows as three bf16 numbers each, packed in pairs
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        uint32_t w[3][2];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+          // one rounding for the scaled score and its distance to the maximum
+          const bool valid = t0 + 16 * t + 4 * kb + 2 * h + o < total;
+          const float x = valid ? exp2_safe(fmaf(p[t][2 * h + o], a.sm_scale_log2, -m_ref)) : 0.f;
+          l += x;
+          w[0][o] = __float_as_uint(x) & 0xFFFF0000u;
+          const float r = x - __uint_as_float(w[0][o]);  // exact
+          w[1][o] = __float_as_uint(r) & 0xFFFF0000u;
+          w[2][o] = __float_as_uint(r - __uint_as_float(w[1][o]));  // at most 8 bits are left
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) part[k][2 * t + h] = __builtin_amdgcn_perm(w[k][1], w[k][0], 0x07060302u);
+      }
+    attn_bf16x8 pop[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) __builtin_memcpy(&pop[k], &part[k][0], 16);
+#pragma unroll
+    for (int e = 0; e < EV; ++e) {
+      const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;  // element e of two rows side by side
+      uint32_t w[4];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          w[2 * t + h] = __builtin_amdgcn_perm(vraw[t][2 * h + 1][e / 2], vraw[t][2 * h][e / 2], sel);
+      attn_bf16x8 vop, vop_low;
+      __builtin_memcpy(&vop, &w[0], 16);
+      if constexpr (kInf) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) w[x] = bf16x2_finite_or_zero(w[x]);
+      }
+      __builtin_memcpy(&vop_low, &w[0], 16);
+#pragma unroll
+      for (int k = 2; k >= 1; --k) acc_low[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pop[k], vop_low, acc_low[e], 0, 0, 0);
+      acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pop[0], vop, acc[e], 0, 0, 0);
+    }
   };
-  walk(std::false_type{});
+  clear();
+  for (int64_t t0 = w_beg; t0 < total; t0 += stride) step(t0, std::false_type{});
   // A NaN in the result may come from such an element: the wave goes over its rows again with care.
   // (The sum of the results is NaN where one of them is; infinities of both signs make it one, too.)
   float sum[4] = {0.f, 0.f, 0.f, 0.f};
@@ -931,7 +931,11 @@ __global__ __launch_bounds__(kGroupWaves * kWave, 2) void attn_group_mfma_kernel
   bool nan = false;
 #pragma unroll
   for (int v = 0; v < 4; ++v) nan |= (4 * kb + v < GH) & (sum[v] != sum[v]);
-  if (__builtin_expect(__any(nan), 0)) walk(std::true_type{});
+  if (__builtin_expect(__any(nan), 0)) {
+    clear();
+    n_next = fetch_rows(w_beg);
+    for (int64_t t0 = w_beg; t0 < total; t0 += stride) step(t0, std::true_type{});
+  }
   l += __shfl_xor(l, 16, kWave);
   l += __shfl_xor(l, 32, kWave);
   if (lane < GH) {
