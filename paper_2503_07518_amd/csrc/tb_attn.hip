@@ -63,7 +63,8 @@ struct AttnArgs {
   float sm_scale_log2;
   float* out;
   float* lse;
-  float* partials;
+  float* partials;  // of the splits: accumulators [units][nsplit][D], then (max, sum) pairs [units][nsplit]
+  int64_t pairs_off;  // floats before the pairs
   uint32_t* counters;
   int32_t Hq, g, nsplit, n_kv_groups, xcd_map;
   int32_t shared_list;  // one list and count per batch element, read by all of its heads
@@ -82,6 +83,112 @@ __device__ inline float exp2_safe(float d) { return __builtin_amdgcn_exp2f(d); }
 // acknowledged (s_waitcnt with all counters at zero).
 __device__ inline void publish_fence() { __builtin_amdgcn_s_waitcnt(0); }
 
+// A workgroup's (max, sum) of a split, handed over as one 64-bit word.
+__device__ inline void store_pair(float* p, float m, float l) {
+  const unsigned long long x = __float_as_uint(m) | static_cast<unsigned long long>(__float_as_uint(l)) << 32;
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Adds up the splits of GH heads (partials `po`, pairs `pp` of the first of them) and writes their outputs: the
+// work of the last workgroup to arrive, whose time is added to the whole launch.  A quad of outputs per
+// thread, 128 bits of an accumulator and its pair per load, the splits dealt round the J thread groups that
+// cover the outputs.  All loads of a thread are in flight together: a chain of device-scope loads would cost
+// a memory round trip per split, and such a load is paid per instruction even when its result is not needed,
+// so the chunk is sized to the split count.  With a scalar load each for value, max and sum (24 instructions
+// a thread for 16 splits instead of 4) the kernel took 15.0 us instead of 14.6 (32 heads, 3277 of 32768 rows, cold);
+// of these the ticket costs 0.7 and the combination 1.1.  The order of combination is fixed.
+constexpr int kAgentScope = 16;  // cache policy of a buffer load that agent-scope stores are visible to (sc1)
+template <int D, int GH, int NW>
+__device__ __forceinline__ void combine_splits(const float* po, const float* pp, const int nsplit, float* out, float* lse,
+                                               float (&s_m)[NW][GH], float (&s_l)[NW][GH], float (&s_acc)[NW][GH][D]) {
+  constexpr int kThreads = NW * kWave;
+  constexpr int QUADS = GH * D / 4;       // threads that cover the outputs
+  constexpr int J = kThreads / QUADS;     // thread groups, each taking every J-th split
+  constexpr int ROWS = QUADS < kWave ? NW : J;  // partial sums left for LDS
+  static_assert(QUADS <= kThreads && ROWS <= NW, "every output has a thread, the sums fit the waves' LDS");
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  const int tid = threadIdx.x;
+  const int quad = tid % QUADS, j = tid / QUADS;
+  const int hh = quad / (D / 4), d = quad % (D / 4) * 4;
+  const __amdgpu_buffer_rsrc_t rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(po), 0, GH * nsplit * D * static_cast<int>(sizeof(float)), 0x00027000);
+  float M = -INFINITY, L = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
+  auto add = [&](const float m_o, const float l_o, const float (&o_o)[4]) {
+    const float m_n = fmaxf(M, m_o);
+    if (m_n > -INFINITY) {
+      const float wa = exp2_safe(M - m_n), wb = exp2_safe(m_o - m_n);
+      L = L * wa + l_o * wb;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = o[e] * wa + o_o[e] * wb;
+      M = m_n;
+    }
+  };
+  auto walk = [&](auto ch_tag) {
+    constexpr int CH = decltype(ch_tag)::value;
+    for (int s0 = j; s0 < nsplit; s0 += J * CH) {
+      u32x4 ov[CH];
+      unsigned long long pv[CH];
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        const int sp = s0 + c * J < nsplit ? s0 + c * J : nsplit - 1;
+        pv[c] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(pp) + hh * nsplit + sp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ov[c] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, ((hh * nsplit + sp) * D + d) * static_cast<int>(sizeof(float)), 0, kAgentScope);
+      }
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        const bool real = s0 + c * J < nsplit;  // (a repeated last split weighs nothing)
+        const float oc[4] = {__uint_as_float(ov[c].x), __uint_as_float(ov[c].y), __uint_as_float(ov[c].z), __uint_as_float(ov[c].w)};
+        add(real ? __uint_as_float(static_cast<uint32_t>(pv[c])) : -INFINITY, __uint_as_float(static_cast<uint32_t>(pv[c] >> 32)), oc);
+      }
+    }
+  };
+  if (nsplit <= J)
+    walk(std::integral_constant<int, 1>{});
+  else if (nsplit <= 2 * J)
+    walk(std::integral_constant<int, 2>{});
+  else if (nsplit <= 4 * J)
+    walk(std::integral_constant<int, 4>{});
+  else
+    walk(std::integral_constant<int, 8>{});
+#pragma unroll
+  for (int off = QUADS; off < kWave; off <<= 1) {
+    const float m_o = __shfl_xor(M, off, kWave), l_o = __shfl_xor(L, off, kWave);
+    float o_o[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o_o[e] = __shfl_xor(o[e], off, kWave);
+    add(m_o, l_o, o_o);
+  }
+  // (the LDS arrays were last read before the partial was published)
+  const int row = QUADS < kWave ? tid / kWave : j;
+  if (QUADS >= kWave || tid % kWave < QUADS) {
+    *reinterpret_cast<float4*>(&s_acc[row][hh][d]) = make_float4(o[0], o[1], o[2], o[3]);
+    if (d == 0) {
+      s_m[row][hh] = M;
+      s_l[row][hh] = L;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e0 = 0; e0 < GH * D; e0 += kThreads) {
+    const int e = e0 + tid, eh = e / D, ed = e % D;
+    if (e < GH * D) {
+      float Mt = -INFINITY, Lt = 0.f, ot = 0.f;
+#pragma unroll
+      for (int r = 0; r < ROWS; ++r) Mt = fmaxf(Mt, s_m[r][eh]);
+      if (Mt > -INFINITY) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+          const float wgt = exp2_safe(s_m[r][eh] - Mt);
+          Lt += s_l[r][eh] * wgt;
+          ot += s_acc[r][eh][ed] * wgt;
+        }
+      }
+      out[e] = (Lt > 0.f) ? ot / Lt : 0.f;
+      if (ed == 0 && lse) lse[eh] = (Lt > 0.f) ? Mt * kLn2 + logf(Lt) : -INFINITY;
+    }
+  }
+}
+
 // SHARES: the list is cut into one share per XCD (nsplit divides by their number)
 template <typename T, int D, bool BUF, bool SHARES>
 __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(AttnArgs a) {
@@ -91,8 +198,8 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   constexpr int TILE = kLoadsPerTile * GPW;  // rows per wave tile
   static_assert(LPR >= 4 && LPR <= 32, "row must span 4..32 lanes");
 
-  __shared__ float s_m[kAttnWaves], s_l[kAttnWaves];
-  __shared__ float s_acc[kAttnWaves][D];
+  __shared__ float s_m[kAttnWaves][1], s_l[kAttnWaves][1];
+  __shared__ __attribute__((aligned(16))) float s_acc[kAttnWaves][1][D];
   __shared__ uint32_t s_last;
 
   const int tid = threadIdx.x;
@@ -273,10 +380,10 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   }
   if (grp == 0) {
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) s_acc[wave][sub * EPL + e] = acc[e];
+    for (int e = 0; e < EPL; ++e) s_acc[wave][0][sub * EPL + e] = acc[e];
     if (sub == 0) {
-      s_m[wave] = m;
-      s_l[wave] = l;
+      s_m[wave][0] = m;
+      s_l[wave][0] = l;
     }
   }
   __syncthreads();
@@ -285,13 +392,13 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   float M = -INFINITY, L = 0.f, o = 0.f;
   if (tid < D) {
 #pragma unroll
-    for (int w = 0; w < kAttnWaves; ++w) M = fmaxf(M, s_m[w]);
+    for (int w = 0; w < kAttnWaves; ++w) M = fmaxf(M, s_m[w][0]);
     if (M > -INFINITY) {
 #pragma unroll
       for (int w = 0; w < kAttnWaves; ++w) {
-        const float wgt = exp2_safe(s_m[w] - M);
-        L += s_l[w] * wgt;
-        o += s_acc[w][tid] * wgt;
+        const float wgt = exp2_safe(s_m[w][0] - M);
+        L += s_l[w][0] * wgt;
+        o += s_acc[w][0][tid] * wgt;
       }
     }
   }
@@ -312,12 +419,8 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   // memory side.  The drawer of the last ticket issues its agent-scope loads after the ticket
   // has returned (branch on its value behind a barrier), so they find every partial whose
   // ticket preceded its own.
-  float* part = a.partials + (u * a.nsplit + split) * (D + 2);
-  if (tid < D) __hip_atomic_store(&part[tid], o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (tid == 0) {
-    __hip_atomic_store(&part[D], M, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&part[D + 1], L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (tid < D) __hip_atomic_store(&a.partials[(u * a.nsplit + split) * D + tid], o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0) store_pair(a.partials + a.pairs_off + (u * a.nsplit + split) * 2, M, L);
   publish_fence();
   __syncthreads();
   if (tid == 0) {
@@ -326,78 +429,8 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   }
   __syncthreads();
   if (!s_last) return;
-  // Combine the partials: thread (d, lane-group j) walks splits j, j+G, ... in chunks whose
-  // loads are all issued before the first is used (a dependent chain of device-scope loads
-  // would cost one memory round trip per split); the G groups are then merged through LDS in
-  // group order.  The order of combination is fixed, so the result is reproducible.
-  {
-    constexpr int G = kAttnThreads / D;  // split groups: 2 for D=128, 4 for D=64
-    const int d = tid % D, j = tid / D;
-    const float* p0 = a.partials + u * a.nsplit * (D + 2);
-    float Mg = -INFINITY, Lg = 0.f, og = 0.f;
-    // CH loads in flight per thread and field.  A device-scope load is paid per instruction
-    // even when its result is not needed, so the chunk is sized to the split count.
-    auto walk = [&](auto ch_tag) {
-      constexpr int CH = decltype(ch_tag)::value;
-      for (int s0 = j; s0 < a.nsplit; s0 += G * CH) {
-        float mv[CH], lv[CH], ov[CH];
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-          const int sp = s0 + c * G;
-          const int sl = sp < a.nsplit ? sp : a.nsplit - 1;
-          mv[c] = __hip_atomic_load(&p0[sl * (D + 2) + D], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          lv[c] = __hip_atomic_load(&p0[sl * (D + 2) + D + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          ov[c] = __hip_atomic_load(&p0[sl * (D + 2) + d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (sp >= a.nsplit) {
-            mv[c] = -INFINITY;
-            lv[c] = 0.f;
-            ov[c] = 0.f;
-          }
-        }
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-          const float Mn = fmaxf(Mg, mv[c]);
-          if (Mn > -INFINITY) {
-            const float wa = exp2_safe(Mg - Mn), wb = exp2_safe(mv[c] - Mn);
-            Lg = Lg * wa + lv[c] * wb;
-            og = og * wa + ov[c] * wb;
-            Mg = Mn;
-          }
-        }
-      }
-    };
-    if (a.nsplit <= G)
-      walk(std::integral_constant<int, 1>{});
-    else if (a.nsplit <= 2 * G)
-      walk(std::integral_constant<int, 2>{});
-    else if (a.nsplit <= 4 * G)
-      walk(std::integral_constant<int, 4>{});
-    else
-      walk(std::integral_constant<int, 8>{});
-    __syncthreads();  // s_acc / s_m / s_l were last read before the partial was published
-    s_acc[j][d] = og;
-    if (d == 0) {
-      s_m[j] = Mg;
-      s_l[j] = Lg;
-    }
-    __syncthreads();
-    if (tid < D) {
-      float Mt = -INFINITY;
-#pragma unroll
-      for (int jj = 0; jj < G; ++jj) Mt = fmaxf(Mt, s_m[jj]);
-      float Lt = 0.f, ot = 0.f;
-      if (Mt > -INFINITY) {
-#pragma unroll
-        for (int jj = 0; jj < G; ++jj) {
-          const float wgt = exp2_safe(s_m[jj] - Mt);
-          Lt += s_l[jj] * wgt;
-          ot += s_acc[jj][tid] * wgt;
-        }
-      }
-      a.out[u * D + tid] = (Lt > 0.f) ? ot / Lt : 0.f;
-      if (tid == 0 && a.lse) a.lse[u] = (Lt > 0.f) ? Mt * kLn2 + logf(Lt) : -INFINITY;
-    }
-  }
+  combine_splits<D, 1, kAttnWaves>(a.partials + u * a.nsplit * D, a.partials + a.pairs_off + u * a.nsplit * 2, a.nsplit, a.out + u * D,
+                                   a.lse ? a.lse + u : nullptr, s_m, s_l, s_acc);
   if (tid == 0) __hip_atomic_store(&a.counters[u * kCounterStrideWords], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -407,11 +440,8 @@ template <int D, int GH, int NW>
 struct GroupLds {
   static constexpr int kThreads = NW * kWave;
   static constexpr int kOutsPerThread = (GH * D + kThreads - 1) / kThreads;
-  static constexpr int kMaxCH = kOutsPerThread <= 2 ? 32 : 16;  // splits whose partials are in flight together
-  static_assert(GH * kMaxCH <= kThreads, "one thread per (head, split) pair of a chunk");
   float m[NW][GH], l[NW][GH];
-  float acc[NW][GH][D];
-  float pm[GH][kMaxCH], pl[GH][kMaxCH];
+  __attribute__((aligned(16))) float acc[NW][GH][D];
   uint32_t last;
 };
 
@@ -465,12 +495,9 @@ __device__ __forceinline__ void group_finish(const AttnArgs& a, const int64_t u0
     const int e = tid + r * kThreads;
     if (e < OUTS) {
       const int hh = e / D, d = e % D;
-      float* part = a.partials + ((u0 + hh) * a.nsplit + split) * (D + 2);
-      __hip_atomic_store(&part[d], o[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (d == 0) {
-        __hip_atomic_store(&part[D], M[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&part[D + 1], L[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
+      const int64_t at = (u0 + hh) * a.nsplit + split;
+      __hip_atomic_store(&a.partials[at * D + d], o[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (d == 0) store_pair(a.partials + a.pairs_off + at * 2, M[r], L[r]);
     }
   }
   publish_fence();
@@ -481,82 +508,8 @@ __device__ __forceinline__ void group_finish(const AttnArgs& a, const int64_t u0
   }
   __syncthreads();
   if (!gl.last) return;
-  // Combine: the device-scope loads of a chunk are issued together: per thread its R outputs
-  // of CH splits; the (max, sum) pairs of those splits, the same for all elements of a head,
-  // are fetched once by GH * CH threads and passed through LDS.  Splits are merged in order.
-  // A device-scope load is paid per instruction even when its result is not needed, so the
-  // chunk is sized to the split count.
-  constexpr int kMaxCH = GroupLds<D, GH, NW>::kMaxCH;
-  float Mg[R], Lg[R], og[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    Mg[r] = -INFINITY;
-    Lg[r] = 0.f;
-    og[r] = 0.f;
-  }
-  auto walk = [&](auto ch_tag) {
-    constexpr int CH = decltype(ch_tag)::value < kMaxCH ? decltype(ch_tag)::value : kMaxCH;
-    for (int s0 = 0; s0 < a.nsplit; s0 += CH) {
-      float ov[R][CH];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int e = tid + r * kThreads;
-        const int hh = (e < OUTS) ? e / D : 0, d = e % D;
-        const float* p0 = a.partials + (u0 + hh) * a.nsplit * (D + 2);
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-          const int sl = (s0 + c < a.nsplit) ? s0 + c : a.nsplit - 1;
-          ov[r][c] = __hip_atomic_load(&p0[sl * (D + 2) + d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-      }
-      if (tid < GH * CH) {
-        const int hh = tid / CH, c = tid % CH;
-        const float* p0 = a.partials + (u0 + hh) * a.nsplit * (D + 2);
-        const int sl = (s0 + c < a.nsplit) ? s0 + c : a.nsplit - 1;
-        const float pm = __hip_atomic_load(&p0[sl * (D + 2) + D], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const float pl = __hip_atomic_load(&p0[sl * (D + 2) + D + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        gl.pm[hh][c] = (s0 + c < a.nsplit) ? pm : -INFINITY;  // a slot past the last split weighs nothing
-        gl.pl[hh][c] = (s0 + c < a.nsplit) ? pl : 0.f;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int e = tid + r * kThreads;
-        const int hh = (e < OUTS) ? e / D : 0;
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-          const float mv = gl.pm[hh][c];
-          const float Mn = fmaxf(Mg[r], mv);
-          if (Mn > -INFINITY) {
-            const float wa = exp2_safe(Mg[r] - Mn), wb = exp2_safe(mv - Mn);
-            Lg[r] = Lg[r] * wa + gl.pl[hh][c] * wb;
-            og[r] = og[r] * wa + ov[r][c] * wb;
-            Mg[r] = Mn;
-          }
-        }
-      }
-      __syncthreads();  // the pairs are overwritten by the next chunk
-    }
-  };
-  if (a.nsplit <= 2)
-    walk(std::integral_constant<int, 2>{});
-  else if (a.nsplit <= 4)
-    walk(std::integral_constant<int, 4>{});
-  else if (a.nsplit <= 8)
-    walk(std::integral_constant<int, 8>{});
-  else if (a.nsplit <= 16)
-    walk(std::integral_constant<int, 16>{});
-  else
-    walk(std::integral_constant<int, 32>{});
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int e = tid + r * kThreads;
-    if (e < OUTS) {
-      const int hh = e / D, d = e % D;
-      a.out[(u0 + hh) * D + d] = (Lg[r] > 0.f) ? og[r] / Lg[r] : 0.f;
-      if (d == 0 && a.lse) a.lse[u0 + hh] = (Lg[r] > 0.f) ? Mg[r] * kLn2 + logf(Lg[r]) : -INFINITY;
-    }
-  }
+  combine_splits<D, GH, NW>(a.partials + u0 * a.nsplit * D, a.partials + a.pairs_off + u0 * a.nsplit * 2, a.nsplit, a.out + u0 * D,
+                            a.lse ? a.lse + u0 : nullptr, gl.m, gl.l, gl.acc);
   if (tid == 0) __hip_atomic_store(&a.counters[u0 * kCounterStrideWords], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -986,6 +939,7 @@ tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
   a.out = L.out;
   a.lse = L.lse;
   a.partials = L.partials;
+  a.pairs_off = static_cast<int64_t>(d.B) * d.Hq * L.plan.nsplit * D;
   a.counters = L.counters;
   a.Hq = d.Hq;
   a.g = d.Hq / d.Hkv;

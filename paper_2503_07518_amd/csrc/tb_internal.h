@@ -17,7 +17,8 @@ constexpr int kCounterStrideWords = 64;
 
 // Workspace layout (byte offsets), fixed by B*Hq so that all operations agree on it:
 //   [0, part_off)              uint32 arrival counters, one per (b,h), 256 B apart -- zero between calls
-//   [part_off, ...)            fp32 split-attention partials [B*Hq][nsplit][D+2]; the two-stage
+//   [part_off, ...)            fp32 split-attention partials, accumulators [B*Hq][nsplit][D] and
+//                              (max, sum) pairs [B*Hq][nsplit][2]; the two-stage
 //                              selection of long rows keeps its candidates in the same region
 //                              (it has finished before the attention of the same stream starts)
 struct WsLayout {
