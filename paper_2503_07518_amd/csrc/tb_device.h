@@ -92,9 +92,9 @@ __device__ inline void store_elt(bf16_t* p, float v) { p->bits = f32_to_bf16_rne
 // NaN ranks with -inf and -0 equals +0 (selection policy).  The smallest key a real score can
 // produce is 0x007FFFFF (-inf), so key 0 is free to mark "not a candidate".
 __device__ inline uint32_t score_key(float s) {
-  // IEEE maxNum returns the operand that is a number, so NaN becomes -inf; adding +0 turns -0
-  // into +0 and changes nothing else (subnormals are kept: fp32 denormal mode is "preserve")
-  const uint32_t b = __float_as_uint(fmaxf(s, -__builtin_inff()) + 0.0f);
+  // adding +0 turns -0 into +0 and changes no other number (subnormals are kept: fp32 denormal mode is
+  // "preserve"), and it quiets a NaN; IEEE maxNum returns the operand that is a number, so NaN becomes -inf
+  const uint32_t b = __float_as_uint(fmaxf(s + 0.0f, -__builtin_inff()));
   // flip all bits of negatives, only the sign bit of non-negatives
   return b ^ (static_cast<uint32_t>(static_cast<int32_t>(b) >> 31) | 0x80000000u);
 }
@@ -104,6 +104,10 @@ __device__ inline int lane_id() { return threadIdx.x & (kWave - 1); }
 // lane: what is derived from it (the wave's span of a row, its LDS region, branches on them)
 // stays in scalar registers and scalar branches.
 __device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave); }
+
+// Lane mask of a predicate.  (The builtin leaves a compare's mask in its scalar registers; HIP's __ballot turns the
+// predicate into a number and compares that again.)
+__device__ inline unsigned long long ballot64(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
 // Inclusive prefix sum across the 64 lanes of a wave (generic: LDS-crossbar shuffles).
 template <typename T>

@@ -114,6 +114,27 @@ __device__ inline uint32_t mbcnt64(unsigned long long m, uint32_t acc) {
 }
 __device__ inline uint32_t popc64(unsigned long long m) { return static_cast<uint32_t>(__popcll(m)); }
 
+// A wave-uniform bound as a value of its own, so that a second pass over the scores compares again: the masks of the
+// first pass would otherwise be kept for it, two scalar registers per score, most of them spilled.
+__device__ inline float compared_anew(float bound) {
+  uint32_t b = __builtin_amdgcn_readfirstlane(__float_as_uint(bound));
+  asm volatile("" : "+s"(b));
+  return __uint_as_float(b);
+}
+
+// A count of lane masks, added up at this point (left alone, the compiler keeps the masks of a whole pass and counts at
+// its end, again with most of them spilled).
+__device__ inline void settle(uint32_t& count) {
+  asm volatile("" : "+s"(count));
+}
+
+// Smallest score whose key is `key` (a key that a real score produces).
+__device__ inline float score_of_key(uint32_t key) {
+  return __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key);
+}
+constexpr uint32_t kKeyOfMinusInf = 0x007FFFFFu;
+constexpr uint32_t kNoScore = 0x7FC00000u;  // a NaN, in the place of what is no candidate: no compare holds for it
+
 // Result of a histogram walk, published in LDS for the whole workgroup.
 struct Found {
   uint32_t bin_a, above_a;  // bin in which the running count (from the top bin down) reaches target a, count above it
@@ -132,7 +153,8 @@ constexpr int kFoundWords = sizeof(Found) / 4;
 // bin down and find, for each of two targets, the bin in which the running count reaches it
 // and the count in strictly higher bins.  A target of 0 or beyond the total finds nothing and
 // leaves the preset {0, 0}.  The targets may depend on a second block-wide sum: every wave
-// reduces `extra`, and `targets(extra_total, need_a, need_b)` turns the total into the targets.
+// brings its `extra` (the same in every lane), and `targets(extra_total, need_a, need_b)` turns the total into
+// the targets.
 //
 // All W waves take part: wave w owns the 4096/W bins below 4096 - (4096/W) w, lane l a run of
 // BL = 64/W adjacent bins (128-bit reads), so that (wave, lane, slot) ascending is bin
@@ -149,8 +171,7 @@ __device__ inline Found find_bins(const uint32_t* s_hist, uint32_t extra, uint32
   static_assert(BL >= 4 && BL % 4 == 0, "whole 128-bit reads per lane");
   const int lane = lane_id();
   const int wave = wave_id();
-  const uint32_t extra_incl = wave_incl_scan_u32(extra);
-  if (lane == kWave - 1) s_extra[wave] = extra_incl;
+  if (lane == 0) s_extra[wave] = extra;
   __syncthreads();  // the histogram and s_extra are complete
   const uint32_t bin0 = static_cast<uint32_t>(kHistBins - BW * (wave + 1) + BL * (kWave - 1 - lane));
   uint32_t c[BL];  // ascending bins bin0 .. bin0 + BL - 1
@@ -243,31 +264,30 @@ __device__ inline void sample_bracket(const uint32_t* s_hist, uint32_t n_valid, 
   }
 }
 
-// Streamed rows (NT == 0) may keep the keys that fall inside the bracket in LDS, so that only
-// two passes read the scores: the bracketed level and the final write-out.
-constexpr int kListCap = 16384;
+constexpr int kListCap = 16384;  // keys inside the bracket that a streamed row keeps in LDS
 constexpr int kStreamBatch = 8;  // tiles in flight per wave while streaming
 constexpr int kMaxLevels = 4;    // bracketed level (possibly repeated once over all bins) + up to 2 levels of low bits
 
 // LDS of one selection (shared by the bodies that run one after the other in a kernel).
 template <int W>
 struct SelLds {
-  uint32_t hist[2][kHistBins];  // alternating: one in use, the other being cleared
+  __attribute__((aligned(16))) uint32_t hist[2][kHistBins];  // of alternating levels
   __attribute__((aligned(16))) Found found[kMaxLevels + 1];
   uint32_t part[2][W];
   uint32_t wsum[W];
   uint32_t wgt[W], weq[W];
-  uint32_t wabove[W];  // streamed rows: every wave's count of keys above the bracket
-  uint32_t nlist;      // streamed rows: keys appended to the list (unusable when beyond its capacity)
-  uint32_t ntiny;      // keys gathered from a sparsely populated sub-bin
+  uint32_t ntiny;  // keys gathered from a sparsely populated sub-bin
   uint32_t tiny[kWave];
+  uint32_t spare[kWave];  // where lanes without an entry store
 };
-// Streamed rows that keep a list: keys inside the bracket (with the wave whose span they come
-// from) and per-(counting wave, owning wave) tallies of kept / tied keys.
+// Streamed rows: keys inside the bracket (with the wave whose span they come from), every wave's count of keys
+// above it, and per-(counting wave, owning wave) tallies of kept / tied keys.
 template <int W>
 struct ListLds {
   uint32_t ckey[kListCap];
   uint8_t cwave[kListCap];
+  uint32_t n;  // keys appended (the list is unusable when beyond its capacity)
+  uint32_t wabove[W];
   uint32_t lcnt[W][W][2];
 };
 // Stage B: where the pieces' kept keys lie in the row that stage B selects on.
@@ -279,137 +299,526 @@ struct PieceTab {
   uint32_t ok;                 // the row of kept keys can be selected on
 };
 
-// STAGE 0: the selection of a row of scores; 2: stage B of a selection by pieces (the row is
-// what the pieces kept, read through the piece table).
-// W: waves of the workgroup.  NT > 0: the wave's tiles are cached in registers (NT >= tiles per
-// wave); NT == 0: the row is streamed again in every phase; with LIST the keys inside the
-// bracket are kept in LDS and only two passes read the scores.
-// u: the row (b*Hq + h) this workgroup selects for.
-template <int W, int NT, int STAGE, bool LIST>
-__device__ __forceinline__ void select_body(const SelectArgs& a, const int u, const PieceTab* tab, SelLds<W>& sl,
-                                            ListLds<W>* ll) {
-  static_assert(!LIST || NT == 0, "only streamed rows keep a list");
+// The always-kept ranges, sink prefix [0, lo) and local window [hi, N), and the list's length.  Written last: a
+// global store that is still on its way would hold up whatever waits for memory after it.
+template <int W>
+__device__ __forceinline__ void write_fixed_ranges(const SelectArgs& a, const int u, int32_t* out) {
+  constexpr int kThreads = W * kWave;
+  const int tid = threadIdx.x;
+  for (int64_t n = tid; n < a.lo; n += kThreads) out[n] = static_cast<int32_t>(n);
+  for (int64_t n = a.hi + tid; n < a.N; n += kThreads) out[a.lo + a.kk + (n - a.hi)] = static_cast<int32_t>(n);
+  if (tid == 0) a.count[u] = static_cast<int32_t>(a.lo + a.kk + (a.N - a.hi));
+}
+
+// Level state of the radix descent: candidates are the keys with lo_key <= key < lo_key + span, histogrammed by
+// (key - lo_key) >> shift; keys above `above_key` (only on the first, bracketed level) are counted instead.
+struct Level {
+  uint32_t lo_key, span, above_key, need;
+  int shift;
+};
+__device__ inline Level bracketed_level(uint32_t b_lo, uint32_t b_hi, int kk) {
+  const uint32_t nb = b_hi - b_lo + 1;                         // 12-bit bins in the bracket
+  const int e = 31 - __clz(static_cast<int>(kHistBins / nb));  // extra bits of resolution
+  return Level{b_lo << kTopShift, nb << kTopShift, (b_hi == kHistBins - 1) ? 0xFFFFFFFFu : ((b_hi + 1) << kTopShift) - 1u,
+               static_cast<uint32_t>(kk), kTopShift - e};
+}
+// the sample misled us (possible on the bracketed level only): every real bin (bin 0 holds only "not a candidate")
+__device__ inline void widen_level(Level& v) {
+  v.lo_key = 1u << kTopShift;
+  v.span = static_cast<uint32_t>(kHistBins - 1) << kTopShift;
+  v.shift = kTopShift;
+  v.above_key = 0xFFFFFFFFu;
+}
+// the low bits of the chosen sub-bin
+__device__ inline void next_level(Level& v) {
+  v.span = 1u << v.shift;
+  v.shift = v.shift > 12 ? v.shift - 12 : 0;
+  v.above_key = 0xFFFFFFFFu;
+}
+
+// The selection of one row whose keys fit the workgroup's registers (NT tiles of 256 per wave).
+// STAGE 0: a row of scores; 2: stage B of a selection by pieces (the row is what the pieces kept, read through
+// the piece table).  u: the row (b*Hq + h) this workgroup selects for.  region: LDS, CAP words per wave, in
+// which a wave collects its part of the list (STAGE 0: the histograms, which are done with by then).
+//
+// One compute unit per row, so what counts is the instructions per score and what a phase waits for:
+//  * the sample is loaded first, and its histogram and walk run while the row itself is on its way;
+//  * where the bracket lies above zero (a budget below about half of the candidates) no keys are made: the scores' own
+//    bits are ordered there; what is no candidate is a NaN that no compare holds for;
+//  * histogram adds of scores outside the bracket go to a spare word of the lane instead of being branched around (the
+//    exec-mask bookkeeping of a branch per score cost more than the adds: 10.4 -> 9.6 us on a row of 32768);
+//  * the output is one pass: a compare per score, the lane masks (scalar registers) give every kept score its place in
+//    the wave's LDS region, and after the one barrier that tells the waves where their parts begin the region is copied out 64
+//    entries a store (counting first and storing from the registers, 32 stores of a few lanes each: 10.6 -> 10.0);
+//  * nothing derived from a score is kept in registers for a later pass (lane_pos, compared_anew, settle): 59 registers
+//    for 8 tiles, so that two workgroups share a compute unit, and none is spilled.
+// Selection alone, 32 rows, a tenth kept, us before and now: 1024 scores 6.4 and 4.2, 4096 5.3 and 4.9, 16384 7.7 and 6.9, 32768
+// 11.2 and 9.4, 65536 19.8 and 14.8; 512 rows of 16384 14.6 and 12.4, of 32768 27.4 and 19.3.  (1000 vector instructions a
+// wave for 32768 scores, now 650; half of a wave's time is waiting for barriers and LDS.)
+template <int W, int NT, int STAGE, int CAP>
+__device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, const PieceTab* tab, SelLds<W>& sl, uint32_t* region) {
   constexpr int kThreads = W * kWave;
   constexpr int kTileElts = W * kWaveTile;  // scores per workgroup-wide tile
-  constexpr bool kStream = LIST;
   constexpr bool kStageB = STAGE == 2;
-  uint32_t (&s_hist)[2][kHistBins] = sl.hist;
-  Found (&s_found)[kMaxLevels + 1] = sl.found;
-  uint32_t (&s_part)[2][W] = sl.part;
-  uint32_t (&s_wgt)[W] = sl.wgt;
-  uint32_t (&s_weq)[W] = sl.weq;
-  uint32_t (&s_wabove)[W] = sl.wabove;
-  uint32_t& s_nlist = sl.nlist;
-  uint32_t* s_ckey = kStream ? ll->ckey : nullptr;
-  uint8_t* s_cwave = kStream ? ll->cwave : nullptr;
-  uint32_t (*s_lcnt)[W][2] = kStream ? ll->lcnt : nullptr;
-
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = wave_id();
   const int kk = a.kk;
   // stage B: the row is the concatenation of the pieces' kept keys, every piece padded to a
   // multiple of 4; every key of it is a candidate
-  const int64_t N = kStageB ? static_cast<int64_t>(tab->len) : a.N;
-  const int lo = kStageB ? 0 : a.lo, hi = kStageB ? static_cast<int>(N) : a.hi;
-  const float* s = a.scores + static_cast<int64_t>(u) * a.score_stride;
+  const int N = kStageB ? static_cast<int>(tab->len) : static_cast<int>(a.N);
+  const int lo = kStageB ? 0 : a.lo, hi = kStageB ? N : a.hi;
   int32_t* out = a.idx + static_cast<int64_t>(u) * a.idx_cap;
-  // stage B: as many tiles per wave as the row needs (its length is not known at launch)
-  const int tpw_b = static_cast<int>((N + kTileElts - 1) / kTileElts);
-  const int tpw = (NT > 0) ? (kStageB ? (tpw_b < 1 ? 1 : (tpw_b < NT ? tpw_b : NT)) : NT) : a.tiles_per_wave;
-  const int64_t wbase = static_cast<int64_t>(wave) * tpw * kWaveTile + lane * 4;
-  const bool refine = kk > 0 && kk < hi - lo;
-  const int64_t last4 = N > 0 ? ((N - 1) & ~int64_t{3}) : 0;  // the vector that holds the last score
-  uint32_t keys[NT > 0 ? NT : 1][4];
-  int32_t cidx[(kStageB && NT > 0) ? NT : 1][4];  // stage B: positions in the original row
-  if (NT > 0 && kk > 0) {
-    if constexpr (kStageB) {
-      // where position n (a multiple of 4) of the row lies in the [piece][cap] arrays, and how
-      // many of the four keys from there on are real (the rest is padding)
-      const uint32_t* ckeys = a.cand_key + static_cast<int64_t>(u) * a.pieces * a.cap;
-      const int32_t* cpos = a.cand_idx + static_cast<int64_t>(u) * a.pieces * a.cap;
-      uint4 rk[NT], ri[NT];
-      int valid[NT];
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        const int64_t n0 = wbase + j * kWaveTile;
-        valid[j] = 0;
-        int64_t phys = 0;
-        if (j < tpw && n0 < N) {
-          int c = 0;  // the last piece that starts at or before n0 (binary search over the starts)
-#pragma unroll
-          for (int step = kMaxPieces / 2; step >= 1; step >>= 1)
-            if (c + step < a.pieces && static_cast<int64_t>(tab->start[c + step]) <= n0) c += step;
-          const int64_t off = n0 - tab->start[c];
-          valid[j] = static_cast<int>(tab->n[c]) - static_cast<int>(off);
-          phys = c * a.cap + off;
-        }
-        rk[j] = *reinterpret_cast<const uint4*>(ckeys + phys);
-        ri[j] = *reinterpret_cast<const uint4*>(cpos + phys);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        const uint32_t kv[4] = {rk[j].x, rk[j].y, rk[j].z, rk[j].w};
-        const uint32_t iv[4] = {ri[j].x, ri[j].y, ri[j].z, ri[j].w};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          keys[j][c] = c < valid[j] ? kv[c] : 0u;
-          cidx[(kStageB && NT > 0) ? j : 0][c] = static_cast<int32_t>(iv[c]);
-        }
-      }
-    } else {
-      float4 raw[NT > 0 ? NT : 1];  // every load of the thread is issued before the first is used
-#pragma unroll
-      for (int j = 0; j < NT; ++j) raw[j] = load_scores4(s, last4, wbase + j * kWaveTile);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int j = 0; j < NT; ++j) keys_of4(raw[j], lo, hi, wbase + j * kWaveTile, keys[j]);
-    }
-  }
-  for (int i = tid; i < 2 * kHistBins; i += kThreads) (&s_hist[0][0])[i] = 0;
-  for (int i = tid; i < (kMaxLevels + 1) * kFoundWords; i += kThreads) reinterpret_cast<uint32_t*>(&s_found[0])[i] = 0;
-  if (tid == 0) {
-    s_nlist = 0;
-    sl.ntiny = 0;
-  }
-
-  // always-kept ranges: sink prefix [0, lo) and local window [hi, N) of the original row (in
-  // stage B these are the ranges of the original row: a.lo, a.hi, a.N).  Written last: a global
-  // store that is still on its way would hold up the first barrier of the selection.
-  auto write_fixed_ranges = [&]() {
-    for (int64_t n = tid; n < a.lo; n += kThreads) out[n] = static_cast<int32_t>(n);
-    for (int64_t n = a.hi + tid; n < a.N; n += kThreads) out[a.lo + kk + (n - a.hi)] = static_cast<int32_t>(n);
-    if (tid == 0) a.count[u] = static_cast<int32_t>(a.lo + kk + (a.N - a.hi));
-  };
-  int32_t* sel_out = out + a.lo;
   if (kk == 0) {
-    write_fixed_ranges();
+    write_fixed_ranges<W>(a, u, out);
     return;
   }
-
-  // visit every tile of this wave's span: body(j, keys of the tile)
+  // stage B: as many tiles per wave as the row needs (its length is not known at launch)
+  const int tpw_b = (N + kTileElts - 1) / kTileElts;
+  const int tpw = kStageB ? (tpw_b < 1 ? 1 : (tpw_b < NT ? tpw_b : NT)) : NT;
+  const int wspan = wave * tpw * kWaveTile;  // first position of the wave's span (the same in every lane)
+  const bool refine = kk < hi - lo;
+  auto init_lds = [&]() {
+    uint4* z = reinterpret_cast<uint4*>(&sl.hist[0][0]);
+    for (int i = tid; i < 2 * kHistBins / 4; i += kThreads) z[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int i = tid; i < (kMaxLevels + 1) * kFoundWords; i += kThreads) reinterpret_cast<uint32_t*>(&sl.found[0])[i] = 0;
+    if (tid == 0) sl.ntiny = 0;
+    __syncthreads();
+  };
+  float s4[NT][4];                    // the scores
+  int32_t cidx[kStageB ? NT : 1][4];  // stage B: positions in the original row, -1 where there is no entry
+  float sample = 0.f;
+  int sample_pos = 0;
+  if constexpr (kStageB) {
+    // where position n (a multiple of 4) of the row lies in the [piece][cap] arrays, and how
+    // many of the four entries from there on are real (the rest is padding)
+    const uint32_t* ckeys = a.cand_key + static_cast<int64_t>(u) * a.pieces * a.cap;
+    const int32_t* cpos = a.cand_idx + static_cast<int64_t>(u) * a.pieces * a.cap;
+    uint4 rk[NT], ri[NT];
+    int valid[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int n0 = wspan + j * kWaveTile + lane * 4;
+      valid[j] = 0;
+      int64_t phys = 0;
+      if (j < tpw && n0 < N) {
+        int c = 0;  // the last piece that starts at or before n0 (binary search over the starts)
+#pragma unroll
+        for (int step = kMaxPieces / 2; step >= 1; step >>= 1)
+          if (c + step < a.pieces && static_cast<int>(tab->start[c + step]) <= n0) c += step;
+        const int off = n0 - static_cast<int>(tab->start[c]);
+        valid[j] = static_cast<int>(tab->n[c]) - off;
+        phys = c * a.cap + off;
+      }
+      rk[j] = *reinterpret_cast<const uint4*>(ckeys + phys);
+      ri[j] = *reinterpret_cast<const uint4*>(cpos + phys);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const uint32_t kv[4] = {rk[j].x, rk[j].y, rk[j].z, rk[j].w};
+      const uint32_t iv[4] = {ri[j].x, ri[j].y, ri[j].z, ri[j].w};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        s4[j][c] = __uint_as_float(c < valid[j] ? kv[c] : kNoScore);
+        cidx[kStageB ? j : 0][c] = c < valid[j] ? static_cast<int32_t>(iv[c]) : -1;
+      }
+    }
+  } else {
+    const float* s = a.scores + static_cast<int64_t>(u) * a.score_stride;
+    const char* s_bytes = reinterpret_cast<const char*>(s);
+    // the sample: four adjacent scores at each of kThreads / 4 places spread evenly over the candidates (the
+    // lanes of a place share its cache line), one score per thread
+    sample_pos = ((lo + (tid >> 2) * (hi - lo) / (kThreads / 4)) & ~3) + (tid & 3);
+    sample = s[sample_pos < N ? sample_pos : N - 1];
+    __builtin_amdgcn_sched_barrier(0);
+    init_lds();
+    __builtin_amdgcn_sched_barrier(0);
+    // A row's allocation covers score_stride >= N entries and score_stride is a multiple of 4, so the vector that
+    // holds the last score lies inside it; positions past it are clamped to it (and are no candidates)
+    const uint32_t last = static_cast<uint32_t>((N - 1) & ~3) * 4u;
+    float4 raw[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const uint32_t off = static_cast<uint32_t>(wspan + j * kWaveTile + lane * 4) * 4u;
+      raw[j] = *reinterpret_cast<const float4*>(s_bytes + (off < last ? off : last));
+    }
+    __builtin_amdgcn_sched_barrier(0);  // every load of the thread is issued before the first is used
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      s4[j][0] = raw[j].x;
+      s4[j][1] = raw[j].y;
+      s4[j][2] = raw[j].z;
+      s4[j][3] = raw[j].w;
+    }
+  }
+  // The lane's first position, relative to lo, as a value of its own for every pass over the scores: what is derived from it
+  // (a position per score, a test per score) would otherwise be kept in registers from one pass for the next.
+  auto lane_pos = [&]() -> int {
+    int p = wspan + lane * 4 - lo;
+    asm volatile("" : "+v"(p));
+    return p;
+  };
+  auto candidate = [&](int p, int j, int c) -> bool {
+    if constexpr (kStageB) return cidx[kStageB ? j : 0][c] >= 0;
+    return static_cast<uint32_t>(p + j * kWaveTile + c) < static_cast<uint32_t>(hi - lo);
+  };
+  // (the same for the keys of the scores: `zero` is +0)
+  auto fresh_zero = []() -> float {
+    float z = 0.f;
+    asm volatile("" : "+v"(z));
+    return z;
+  };
+  if constexpr (kStageB) init_lds();
   auto for_each_tile = [&](auto&& body) {
-    if constexpr (NT > 0) {
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+      if (!kStageB || j < tpw) body(j, s4[j]);
+  };
+
+  // The kept scores: all that are at least T (ties: scores equal to T are cut), or every candidate (all).
+  uint32_t T_key = 0;  // key of T
+  uint32_t r_eq = 0;   // with ties: how many scores equal to T are kept (lowest indices first)
+  bool all = true;
+  if (refine) {
+    uint32_t b_lo, b_hi;
+    if constexpr (kStageB) {
+      // the pieces have already derived the bracket from their sample of the row
+      b_lo = tab->b_lo;
+      b_hi = tab->b_hi;
+    } else {
+      const bool valid = sample_pos >= lo && sample_pos < hi;
+      if (valid) atomicAdd(&sl.hist[0][score_key(sample) >> kTopShift], 1u);
+      sample_bracket<W>(sl.hist[0], popc64(ballot64(valid)), sl.part[0], sl.wsum, &sl.found[0], kk, hi - lo, b_lo, b_hi);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // (the row's scores are waited for from here on)
+    if constexpr (!kStageB) {
+      if (!(wspan >= lo && wspan + NT * kWaveTile <= hi)) {  // (scalar)
+        const int p = lane_pos();
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) s4[j][c] = candidate(p, j, c) ? s4[j][c] : __uint_as_float(kNoScore);
+      }
+    }
+    Level v = bracketed_level(b_lo, b_hi, kk);
+    auto targets = [&](uint32_t c_above, uint32_t& na, uint32_t& nb) {
+      na = (c_above < v.need) ? v.need - c_above : 0u;
+      nb = 0u;
+    };
+    // A handful of scores share the chosen sub-bin (the usual case after the bracketed level: its
+    // sub-bins are a few thousand key values wide): instead of another histogram level,
+    // they have been gathered, one lane each (x: something that is ordered like them), and are ranked against each
+    // other in every wave.  Returns the threshold's x and reduces v.need to how many equal to it are needed.
+    auto rank_tiny = [&](uint32_t count, bool& whole) -> uint32_t {
+      __syncthreads();
+      const int n_tiny = static_cast<int>(count);
+      const uint32_t mine = lane < n_tiny ? sl.tiny[lane] : 0u;
+      uint32_t greater = 0, equal = 0;
+      for (int j = 0; j < n_tiny; ++j) {
+        const uint32_t other = __builtin_amdgcn_readlane(mine, j);
+        greater += other > mine ? 1u : 0u;
+        equal += other == mine ? 1u : 0u;
+      }
+      // the one whose ranks (greater, greater + equal] contain `need` is the threshold
+      const unsigned long long hit = ballot64(lane < n_tiny && greater < v.need && v.need <= greater + equal);
+      const int L = __ffsll(hit) - 1;  // (several lanes when the threshold value repeats: they agree)
+      v.need -= static_cast<uint32_t>(__builtin_amdgcn_readlane(greater, L));
+      whole = v.need == static_cast<uint32_t>(__builtin_amdgcn_readlane(equal, L));
+      return static_cast<uint32_t>(__builtin_amdgcn_readlane(mine, L));
+    };
+    bool found = false, whole = false;  // whole: every score from lo_key up is kept, none is cut
+    int call = 1;
+    bool dense = true;
+    constexpr uint32_t kSign = 0x80000000u, kPastInf = 0x7F800001u;
+    if (v.lo_key > kSign) {
+      // The bracket lies above zero (a budget below about half of the candidates): the bits of the scores
+      // themselves are ordered there, and those of what is negative, NaN or no candidate lie outside every range that
+      // ends at +inf, so no key has to be made (four instructions a score).
+      const uint32_t lo_bits = v.lo_key ^ kSign;
+      const uint32_t span = min(v.span, kPastInf - lo_bits);
+      const float f_above = __uint_as_float(v.above_key ^ kSign);  // (past +inf: a NaN, nothing is above)
+      uint32_t n_above = 0;
+      for_each_tile([&](int, const float(&f4)[4]) {
+        uint32_t* w[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const uint32_t d = __float_as_uint(f4[c]) - lo_bits;
+          n_above += popc64(ballot64(f4[c] > f_above));
+          w[c] = d < span ? &sl.hist[1][d >> v.shift] : &sl.spare[lane];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) atomicAdd(w[c], 1u);
+        settle(n_above);
+      });
+      const Found f = find_bins<W>(sl.hist[1], n_above, sl.part[1], sl.wsum, &sl.found[1], targets);
+      call = 2;
+      if (f.need_a >= 1u && f.need_a <= f.total) {
+        v.lo_key += f.bin_a << v.shift;
+        v.need = f.need_a - f.above_a;
+        if (v.need == f.count_a) {
+          found = whole = true;  // every score of this sub-bin is needed: no reason to look at its low bits
+        } else if (v.shift == 0) {
+          found = true;
+        } else if (f.count_a <= static_cast<uint32_t>(kWave)) {
+          const uint32_t bin_bits = v.lo_key ^ kSign;
+          const uint32_t sub = min(1u << v.shift, kPastInf - bin_bits);
+          for_each_tile([&](int, const float(&f4)[4]) {
+            const uint32_t d0 = __float_as_uint(f4[0]) - bin_bits, d1 = __float_as_uint(f4[1]) - bin_bits;
+            const uint32_t d2 = __float_as_uint(f4[2]) - bin_bits, d3 = __float_as_uint(f4[3]) - bin_bits;
+            const uint32_t dmin = min(min(d0, d1), min(d2, d3));
+            if (ballot64(dmin < sub) != 0ull) {
+              const uint32_t d[4] = {d0, d1, d2, d3};
+#pragma unroll
+              for (int c = 0; c < 4; ++c)
+                if (d[c] < sub) sl.tiny[atomicAdd(&sl.ntiny, 1u)] = d[c];
+            }
+          });
+          v.lo_key += rank_tiny(f.count_a, whole);
+          found = true;
+        } else {
+          next_level(v);
+          dense = false;
+        }
+      } else {
+        widen_level(v);
+      }
+    }
+    if (!found) {
+      // the general form, over keys (0: not a candidate; no real score has a key below 0x007FFFFF)
+      auto key4 = [&](int p, float zero, int j, const float(&f4)[4], uint32_t(&k4)[4]) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) k4[c] = candidate(p, j, c) ? score_key(f4[c] + zero) : 0u;
+      };
+#pragma nounroll
+      for (; call <= kMaxLevels; ++call) {
+        uint32_t* h = sl.hist[call & 1];
+        if (call > 1) {  // (it held an earlier level, or the sample)
+          uint4* z = reinterpret_cast<uint4*>(h);
+          for (int i = tid; i < kHistBins / 4; i += kThreads) z[i] = make_uint4(0u, 0u, 0u, 0u);
+          __syncthreads();
+        }
+        uint32_t n_above = 0;
+        const int p = lane_pos();
+        const float zero = fresh_zero();
+        if (dense) {
+          // a sizeable share of the keys falls into the range: test every key on its own.
+          // (key > above_key implies key - lo_key >= span, so the two cases are disjoint.)
+          for_each_tile([&](int j, const float(&f4)[4]) {
+            uint32_t k4[4];
+            key4(p, zero, j, f4, k4);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const uint32_t d = k4[c] - v.lo_key;  // wraps to a large value for keys below lo_key
+              n_above += popc64(ballot64(k4[c] > v.above_key));
+              if (d < v.span) atomicAdd(&h[d >> v.shift], 1u);
+            }
+            settle(n_above);
+          });
+        } else {
+          // only the keys of one sub-bin take part: skip wave-uniformly
+          for_each_tile([&](int j, const float(&f4)[4]) {
+            uint32_t k4[4];
+            key4(p, zero, j, f4, k4);
+            const uint32_t d0 = k4[0] - v.lo_key, d1 = k4[1] - v.lo_key, d2 = k4[2] - v.lo_key, d3 = k4[3] - v.lo_key;
+            const uint32_t dmin = min(min(d0, d1), min(d2, d3));
+            if (ballot64(dmin < v.span) != 0ull) {
+              if (d0 < v.span) atomicAdd(&h[d0 >> v.shift], 1u);
+              if (d1 < v.span) atomicAdd(&h[d1 >> v.shift], 1u);
+              if (d2 < v.span) atomicAdd(&h[d2 >> v.shift], 1u);
+              if (d3 < v.span) atomicAdd(&h[d3 >> v.shift], 1u);
+            }
+          });
+        }
+        const Found f = find_bins<W>(h, n_above, sl.part[call & 1], sl.wsum, &sl.found[call], targets);
+        if (f.need_a >= 1u && f.need_a <= f.total) {  // T lies inside this level's range: descend
+          v.lo_key += f.bin_a << v.shift;
+          v.need = f.need_a - f.above_a;
+          if (v.need == f.count_a) {
+            whole = true;
+            break;
+          }
+          if (v.shift == 0) break;
+          if (f.count_a <= static_cast<uint32_t>(kWave)) {
+            const uint32_t sub = 1u << v.shift;
+            const int p = lane_pos();
+            const float zero = fresh_zero();
+            for_each_tile([&](int j, const float(&f4)[4]) {
+              uint32_t k4[4];
+              key4(p, zero, j, f4, k4);
+#pragma unroll
+              for (int c = 0; c < 4; ++c) {
+                const uint32_t d = k4[c] - v.lo_key;
+                if (d < sub) sl.tiny[atomicAdd(&sl.ntiny, 1u)] = d;
+              }
+            });
+            v.lo_key += rank_tiny(f.count_a, whole);
+            break;
+          }
+          next_level(v);
+          dense = false;
+        } else {
+          widen_level(v);
+          dense = true;
+        }
+      }
+    }
+    T_key = v.lo_key;
+    r_eq = whole ? 0u : v.need;
+    all = whole && T_key <= kKeyOfMinusInf;
+  }
+
+  int32_t* sel_out = out + a.lo;
+  auto value = [&](int p, int j, int c) -> int32_t {  // what the list holds for score c of tile j (p: lane_pos() + lo)
+    return kStageB ? cidx[kStageB ? j : 0][c] : p + j * kWaveTile + c;
+  };
+  if (r_eq == 0u) {
+    // ---- ordered output, no score equal to T to cut (the usual case)
+    float T = score_of_key(T_key);
+    if (all) {  // every candidate, NaN included
+      T = 0.f;
+      const int p = lane_pos();
 #pragma unroll
       for (int j = 0; j < NT; ++j)
-        if (!kStageB || j < tpw) body(j, keys[j]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s4[j][c] = candidate(p, j, c) ? 0.f : __uint_as_float(kNoScore);
+    }
+    uint32_t* const part = region + wave * CAP;
+    const int p = lane_pos() + lo;
+    uint32_t run = 0;  // kept scores of the wave so far (the same in every lane)
+    for_each_tile([&](int j, const float(&f4)[4]) {
+      const bool t0 = f4[0] >= T, t1 = f4[1] >= T, t2 = f4[2] >= T, t3 = f4[3] >= T;
+      const unsigned long long m0 = ballot64(t0), m1 = ballot64(t1), m2 = ballot64(t2), m3 = ballot64(t3);
+      const uint32_t tot = popc64(m0) + popc64(m1) + popc64(m2) + popc64(m3);
+      if (run + tot <= static_cast<uint32_t>(CAP)) {
+        uint32_t* w = part + run + mbcnt64(m3, mbcnt64(m2, mbcnt64(m1, mbcnt64(m0, 0u))));  // after the entries of lower lanes and earlier tiles
+        if (t0) *w++ = static_cast<uint32_t>(value(p, j, 0));
+        if (t1) *w++ = static_cast<uint32_t>(value(p, j, 1));
+        if (t2) *w++ = static_cast<uint32_t>(value(p, j, 2));
+        if (t3) *w = static_cast<uint32_t>(value(p, j, 3));
+      }
+      run += tot;
+      settle(run);
+    });
+    if (lane == 0) sl.wgt[wave] = run;
+    __syncthreads();
+    uint32_t total;
+    uint32_t at = wave_entries_scan<W>(sl.wgt, total);  // kept scores of the waves before
+    if (run <= static_cast<uint32_t>(CAP)) {
+      if (at + run <= static_cast<uint32_t>(kk))  // (always, when the counts add up)
+        for (uint32_t e = lane; e < run; e += kWave) sel_out[at + e] = static_cast<int32_t>(part[e]);
     } else {
-      // streamed: the loads of kStreamBatch tiles are issued before the first tile is used (one
-      // load per iteration would leave a wave with 1 KiB in flight and the pass latency-bound)
-      for (int j0 = 0; j0 < tpw; j0 += kStreamBatch) {
-        float4 raw[kStreamBatch];
+      // more than the wave's region holds (large scores crowded into its span): from the registers
+      const float T2 = compared_anew(T);
+      const int p = lane_pos() + lo;
+      for_each_tile([&](int j, const float(&f4)[4]) {
+        const unsigned long long m0 = ballot64(f4[0] >= T2), m1 = ballot64(f4[1] >= T2), m2 = ballot64(f4[2] >= T2), m3 = ballot64(f4[3] >= T2);
+        uint32_t o = mbcnt64(m3, mbcnt64(m2, mbcnt64(m1, mbcnt64(m0, at))));
 #pragma unroll
-        for (int t = 0; t < kStreamBatch; ++t)  // tiles past the wave's span read a clamped address and are dropped
-          raw[t] = load_scores4(s, last4, wbase + static_cast<int64_t>(j0 + t) * kWaveTile);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int t = 0; t < kStreamBatch; ++t) {
-          if (j0 + t < tpw) {
-            uint32_t k4[4];
-            keys_of4(raw[t], lo, hi, wbase + static_cast<int64_t>(j0 + t) * kWaveTile, k4);
-            body(j0 + t, k4);
+        for (int c = 0; c < 4; ++c) {
+          if (f4[c] >= T2) {
+            if (o < static_cast<uint32_t>(kk)) sel_out[o] = value(p, j, c);
+            ++o;
           }
+        }
+        at += popc64(m0) + popc64(m1) + popc64(m2) + popc64(m3);
+      });
+    }
+  } else {
+    // ---- ordered output with ties at the threshold: {key > T} and the first r_eq of {key == T}.
+    // Pass A: the wave's totals of both.
+    auto key = [&](int p, float zero, int j, int c) { return candidate(p, j, c) ? score_key(s4[j][c] + zero) : 0u; };
+    const int p_a = lane_pos();
+    const float zero_a = fresh_zero();
+    uint32_t run_gt = 0, run_eq = 0;
+    for_each_tile([&](int j, const float(&)[4]) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const uint32_t k = key(p_a, zero_a, j, c);
+        run_gt += popc64(ballot64(k > T_key));
+        run_eq += popc64(ballot64(k == T_key));
+      }
+      settle(run_gt);
+      settle(run_eq);
+    });
+    if (lane == 0) {
+      sl.wgt[wave] = run_gt;
+      sl.weq[wave] = run_eq;
+    }
+    __syncthreads();
+    uint32_t unused;
+    uint32_t base_gt = wave_entries_scan<W>(sl.wgt, unused);
+    uint32_t base_eq = wave_entries_scan<W>(sl.weq, unused);
+    // Pass B: position of a kept score = (#greater before it) + min(#equal before it, r_eq)
+    const uint32_t T2 = __float_as_uint(compared_anew(__uint_as_float(T_key)));
+    const int p_b = lane_pos(), p = p_b + lo;
+    const float zero_b = fresh_zero();
+    for_each_tile([&](int j, const float(&)[4]) {
+      uint32_t gt = base_gt, eq = base_eq, k4[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        k4[c] = key(p_b, zero_b, j, c);
+        const unsigned long long mg = ballot64(k4[c] > T2), me = ballot64(k4[c] == T2);
+        gt = mbcnt64(mg, gt);
+        eq = mbcnt64(me, eq);
+        base_gt += popc64(mg);
+        base_eq += popc64(me);
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const bool is_gt = k4[c] > T2, is_eq = k4[c] == T2;
+        const uint32_t pos = gt + (eq < r_eq ? eq : r_eq);
+        if ((is_gt || (is_eq && eq < r_eq)) && pos < static_cast<uint32_t>(kk)) sel_out[pos] = value(p, j, c);
+        gt += is_gt ? 1u : 0u;
+        eq += is_eq ? 1u : 0u;
+      }
+    });
+  }
+  write_fixed_ranges<W>(a, u, out);
+}
+
+// The selection of one row by a workgroup that streams it again in every phase (rows too long for the registers, and
+// the fall-back of a selection by pieces); the keys inside the bracket are kept in LDS, so that only two passes read
+// the scores.
+template <int W>
+__device__ __forceinline__ void select_stream(const SelectArgs& a, const int u, SelLds<W>& sl, ListLds<W>& ll) {
+  constexpr int kThreads = W * kWave;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = wave_id();
+  const int kk = a.kk;
+  const int64_t N = a.N;
+  const int lo = a.lo, hi = a.hi;
+  const float* s = a.scores + static_cast<int64_t>(u) * a.score_stride;
+  int32_t* out = a.idx + static_cast<int64_t>(u) * a.idx_cap;
+  if (kk == 0) {
+    write_fixed_ranges<W>(a, u, out);
+    return;
+  }
+  const int tpw = a.tiles_per_wave;
+  const int64_t wbase = static_cast<int64_t>(wave) * tpw * kWaveTile + lane * 4;
+  const bool refine = kk < hi - lo;
+  const int64_t last4 = N > 0 ? ((N - 1) & ~int64_t{3}) : 0;  // the vector that holds the last score
+  for (int i = tid; i < 2 * kHistBins; i += kThreads) (&sl.hist[0][0])[i] = 0;
+  for (int i = tid; i < (kMaxLevels + 1) * kFoundWords; i += kThreads) reinterpret_cast<uint32_t*>(&sl.found[0])[i] = 0;
+  if (tid == 0) ll.n = 0;
+
+  // visit every tile of this wave's span: body(j, keys of the tile).  The loads of kStreamBatch tiles are issued
+  // before the first tile is used (one load per iteration would leave a wave with 1 KiB in flight and the pass
+  // latency-bound)
+  auto for_each_tile = [&](auto&& body) {
+    for (int j0 = 0; j0 < tpw; j0 += kStreamBatch) {
+      float4 raw[kStreamBatch];
+#pragma unroll
+      for (int t = 0; t < kStreamBatch; ++t)  // tiles past the wave's span read a clamped address and are dropped
+        raw[t] = load_scores4(s, last4, wbase + static_cast<int64_t>(j0 + t) * kWaveTile);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < kStreamBatch; ++t) {
+        if (j0 + t < tpw) {
+          uint32_t k4[4];
+          keys_of4(raw[t], lo, hi, wbase + static_cast<int64_t>(j0 + t) * kWaveTile, k4);
+          body(j0 + t, k4);
         }
       }
     }
@@ -417,71 +826,39 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int u, co
 
   uint32_t T = 0;        // threshold key: everything above is kept
   uint32_t r_eq = 0;     // how many keys equal to T are kept (lowest indices first)
-  bool list_ok = false;  // streamed rows: the LDS list holds every key inside the bracket
+  bool list_ok = false;  // the LDS list holds every key inside the bracket
   if (refine) {
     __syncthreads();  // LDS initialised
+    // bracket from a sample: one key per thread, the first key of a tile that varies with the lane so that the sample
+    // is spread over the wave's span.  (More keys would narrow the bracket a little, but they land in a handful of
+    // exponent bins and their LDS atomics serialise.)
     uint32_t b_lo, b_hi;
-    if constexpr (kStageB) {
-      // the pieces have already derived the bracket from their sample of the row
-      b_lo = tab->b_lo;
-      b_hi = tab->b_hi;
-    } else {
-      // ---- bracket from a sample: one key per thread, the first key of a tile that varies with
-      // the lane so that the sample is spread over the wave's span.  (More keys would narrow the
-      // bracket a little, but they land in a handful of exponent bins and their LDS atomics
-      // serialise.)
-      uint32_t n_valid = 0;
-      const int st = lane % tpw;  // tile sampled by this lane
-      uint32_t ks;
-      if constexpr (NT > 0) {
-        ks = keys[0][0];
-#pragma unroll
-        for (int j = 1; j < NT; ++j) ks = (j == st) ? keys[j][0] : ks;
-      } else {
-        const int64_t n0 = wbase + static_cast<int64_t>(st) * kWaveTile;
-        uint32_t k4[4];
-        keys_of4(load_scores4(s, last4, n0), lo, hi, n0, k4);
-        ks = k4[0];
-      }
-      if (ks) {
-        atomicAdd(&s_hist[0][ks >> kTopShift], 1u);
-        n_valid = 1;
-      }
-      sample_bracket<W>(s_hist[0], n_valid, s_part[0], sl.wsum, &s_found[0], kk, hi - lo, b_lo, b_hi);
-    }
-
-    // ---- radix descent.  Level state: candidates are the keys with lo_key <= key < lo_key +
-    // span, histogrammed by (key - lo_key) >> shift; keys above `above_key` (only on the
-    // first, bracketed level) are counted instead.  If the exact counts of the first level
-    // show that T is not inside the bracket, the level is repeated over every real bin.
-    uint32_t lo_key, span, above_key, need = static_cast<uint32_t>(kk);
-    int shift;
+    uint32_t k4[4];
     {
-      const uint32_t nb = b_hi - b_lo + 1;                         // 12-bit bins in the bracket
-      const int e = 31 - __clz(static_cast<int>(kHistBins / nb));  // extra bits of resolution
-      shift = kTopShift - e;
-      lo_key = b_lo << kTopShift;
-      span = nb << kTopShift;
-      above_key = (b_hi == kHistBins - 1) ? 0xFFFFFFFFu : ((b_hi + 1) << kTopShift) - 1u;
+      const int64_t n0 = wbase + static_cast<int64_t>(lane % tpw) * kWaveTile;
+      keys_of4(load_scores4(s, last4, n0), lo, hi, n0, k4);
+      if (k4[0]) atomicAdd(&sl.hist[0][k4[0] >> kTopShift], 1u);
     }
-    int cur = 1;  // s_hist[cur] is clear and becomes this level's histogram
-    bool dense_level = true;
-    bool take_whole_bin = false;
+    sample_bracket<W>(sl.hist[0], popc64(ballot64(k4[0] != 0u)), sl.part[0], sl.wsum, &sl.found[0], kk, hi - lo, b_lo, b_hi);
+
+    Level v = bracketed_level(b_lo, b_hi, kk);
+    int cur = 1;  // sl.hist[cur] is clear and becomes this level's histogram
+    bool dense = true, take_whole_bin = false;
 #pragma nounroll
     for (int call = 1; call <= kMaxLevels; ++call) {
-      uint32_t* h = s_hist[cur];
+      uint32_t* h = sl.hist[cur];
       uint32_t n_above = 0;
-      if (kStream && call == 1) {
-        // the bracketed level of a streamed row: as the dense level below, and the keys inside
-        // the bracket are appended to the LDS list (one slot reservation per wave tile)
+      if (call == 1) {
+        // the bracketed level: the keys inside the bracket are also appended to the LDS list (one slot reservation
+        // per wave tile)
         for_each_tile([&](int, const uint32_t(&k4)[4]) {
           uint32_t d[4], nin = 0;
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            d[c] = k4[c] - lo_key;
-            n_above += (k4[c] > above_key) ? 1u : 0u;
-            if (d[c] < span) {
-              atomicAdd(&h[d[c] >> shift], 1u);
+            d[c] = k4[c] - v.lo_key;  // wraps to a large value for keys below lo_key
+            n_above += (k4[c] > v.above_key) ? 1u : 0u;
+            if (d[c] < v.span) {
+              atomicAdd(&h[d[c] >> v.shift], 1u);
               ++nin;
             }
           }
@@ -489,267 +866,176 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int u, co
           const uint32_t tot = __builtin_amdgcn_readlane(incl, kWave - 1);
           if (tot) {
             uint32_t base = 0;
-            if (lane == kWave - 1) base = atomicAdd(&s_nlist, tot);
+            if (lane == kWave - 1) base = atomicAdd(&ll.n, tot);
             uint32_t pos = __builtin_amdgcn_readlane(base, kWave - 1) + incl - nin;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-              if (d[c] < span) {
+              if (d[c] < v.span) {
                 if (pos < static_cast<uint32_t>(kListCap)) {
-                  s_ckey[kStream ? pos : 0] = k4[c];
-                  s_cwave[kStream ? pos : 0] = static_cast<uint8_t>(wave);
+                  ll.ckey[pos] = k4[c];
+                  ll.cwave[pos] = static_cast<uint8_t>(wave);
                 }
                 ++pos;
               }
             }
           }
         });
-      } else if (dense_level) {
-        // a sizeable share of the keys falls into the range: test every key on its own.
-        // (key > above_key implies key - lo_key >= span, so the two cases are disjoint.)
+      } else if (dense) {
         for_each_tile([&](int, const uint32_t(&k4)[4]) {
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            const uint32_t d = k4[c] - lo_key;  // wraps to a large value for keys below lo_key
-            n_above += (k4[c] > above_key) ? 1u : 0u;
-            if (d < span) atomicAdd(&h[d >> shift], 1u);
+            const uint32_t d = k4[c] - v.lo_key;
+            n_above += (k4[c] > v.above_key) ? 1u : 0u;
+            if (d < v.span) atomicAdd(&h[d >> v.shift], 1u);
           }
         });
-      } else if (kStream && list_ok) {
-        // streamed row: the keys of the chosen sub-bin are all in the LDS list
-        const uint32_t nl = s_nlist;
+      } else if (list_ok) {
+        // the keys of the chosen sub-bin are all in the LDS list
+        const uint32_t nl = ll.n;
         for (uint32_t i = tid; i < nl; i += kThreads) {
-          const uint32_t d = s_ckey[kStream ? i : 0] - lo_key;
-          if (d < span) atomicAdd(&h[d >> shift], 1u);
+          const uint32_t d = ll.ckey[i] - v.lo_key;
+          if (d < v.span) atomicAdd(&h[d >> v.shift], 1u);
         }
       } else {
         // only the handful of keys of one sub-bin take part: skip wave-uniformly
         for_each_tile([&](int, const uint32_t(&k4)[4]) {
-          const uint32_t d0 = k4[0] - lo_key, d1 = k4[1] - lo_key, d2 = k4[2] - lo_key, d3 = k4[3] - lo_key;
+          const uint32_t d0 = k4[0] - v.lo_key, d1 = k4[1] - v.lo_key, d2 = k4[2] - v.lo_key, d3 = k4[3] - v.lo_key;
           const uint32_t dmin = min(min(d0, d1), min(d2, d3));
-          if (__any(dmin < span)) {
-            if (d0 < span) atomicAdd(&h[d0 >> shift], 1u);
-            if (d1 < span) atomicAdd(&h[d1 >> shift], 1u);
-            if (d2 < span) atomicAdd(&h[d2 >> shift], 1u);
-            if (d3 < span) atomicAdd(&h[d3 >> shift], 1u);
+          if (ballot64(dmin < v.span) != 0ull) {
+            if (d0 < v.span) atomicAdd(&h[d0 >> v.shift], 1u);
+            if (d1 < v.span) atomicAdd(&h[d1 >> v.shift], 1u);
+            if (d2 < v.span) atomicAdd(&h[d2 >> v.shift], 1u);
+            if (d3 < v.span) atomicAdd(&h[d3 >> v.shift], 1u);
           }
         });
       }
       // clear the other histogram for the next level while this one is being filled
-      for (int i = tid; i < kHistBins; i += kThreads) s_hist[cur ^ 1][i] = 0;
-      const Found f = find_bins<W>(h, n_above, s_part[call & 1], sl.wsum, &s_found[call],
+      for (int i = tid; i < kHistBins; i += kThreads) sl.hist[cur ^ 1][i] = 0;
+      const uint32_t n_above_wave = __builtin_amdgcn_readlane(wave_incl_scan_u32(n_above), kWave - 1);
+      const Found f = find_bins<W>(h, n_above_wave, sl.part[call & 1], sl.wsum, &sl.found[call],
                                    [&](uint32_t c_above, uint32_t& na, uint32_t& nb) {
-                                     na = (c_above < need) ? need - c_above : 0u;
+                                     na = (c_above < v.need) ? v.need - c_above : 0u;
                                      nb = 0u;
                                    });
-      const uint32_t want = f.need_a, total_in = f.total;
-      if (kStream && call == 1) {
-        list_ok = s_nlist <= static_cast<uint32_t>(kListCap);
-        if (tid < W) s_wabove[tid] = s_part[1][tid];  // per-wave counts of keys above the bracket
+      if (call == 1) {
+        list_ok = ll.n <= static_cast<uint32_t>(kListCap);
+        if (tid < W) ll.wabove[tid] = sl.part[1][tid];  // per-wave counts of keys above the bracket
       }
       cur ^= 1;
-      if (want >= 1u && want <= total_in) {  // T lies inside this level's range: descend
-        lo_key += f.bin_a << shift;
-        need = want - f.above_a;
-        if (need == f.count_a) {
+      if (f.need_a >= 1u && f.need_a <= f.total) {  // T lies inside this level's range: descend
+        v.lo_key += f.bin_a << v.shift;
+        v.need = f.need_a - f.above_a;
+        if (v.need == f.count_a) {
           // every key of this sub-bin is needed: no reason to look at its low bits
           take_whole_bin = true;
           break;
         }
-        if (shift == 0) break;
-        if (NT > 0 && f.count_a <= static_cast<uint32_t>(kWave)) {
-          // A handful of keys share the sub-bin (the usual case after the bracketed level: its
-          // sub-bins are a few thousand key values wide): instead of another histogram level,
-          // gather them -- one lane each -- and rank them against each other in every wave.
-          const uint32_t sub = 1u << shift;
-          for_each_tile([&](int, const uint32_t(&k4)[4]) {
-            const uint32_t d0 = k4[0] - lo_key, d1 = k4[1] - lo_key, d2 = k4[2] - lo_key, d3 = k4[3] - lo_key;
-            const uint32_t dmin = min(min(d0, d1), min(d2, d3));
-            if (__any(dmin < sub)) {
-#pragma unroll
-              for (int c = 0; c < 4; ++c)
-                if (k4[c] - lo_key < sub) sl.tiny[atomicAdd(&sl.ntiny, 1u)] = k4[c];
-            }
-          });
-          __syncthreads();
-          const int n_tiny = static_cast<int>(f.count_a);
-          const uint32_t mine = lane < n_tiny ? sl.tiny[lane] : 0u;
-          uint32_t greater = 0, equal = 0;
-          for (int j = 0; j < n_tiny; ++j) {
-            const uint32_t other = __builtin_amdgcn_readlane(mine, j);
-            greater += other > mine ? 1u : 0u;
-            equal += other == mine ? 1u : 0u;
-          }
-          // the key whose ranks (greater, greater + equal] contain `need` is the threshold
-          const unsigned long long hit = __ballot(lane < n_tiny && greater < need && need <= greater + equal);
-          const int L = __ffsll(hit) - 1;  // (several lanes when the threshold value repeats: they agree)
-          lo_key = static_cast<uint32_t>(__builtin_amdgcn_readlane(mine, L));
-          need -= static_cast<uint32_t>(__builtin_amdgcn_readlane(greater, L));
-          if (need == static_cast<uint32_t>(__builtin_amdgcn_readlane(equal, L))) take_whole_bin = true;  // every key equal to it is kept
-          break;
-        }
-        const int nshift = shift > 12 ? shift - 12 : 0;
-        span = 1u << shift;
-        shift = nshift;
-        above_key = 0xFFFFFFFFu;
-        dense_level = false;
+        if (v.shift == 0) break;
+        next_level(v);
+        dense = false;
       } else {
-        // the sample misled us (possible on the bracketed level only): widen to every real
-        // bin and count again.  Bin 0 holds only "not a candidate".
-        lo_key = 1u << kTopShift;
-        span = static_cast<uint32_t>(kHistBins - 1) << kTopShift;
-        shift = kTopShift;
-        above_key = 0xFFFFFFFFu;
+        widen_level(v);
         list_ok = false;
       }
     }
-    T = lo_key;
-    r_eq = need;
+    T = v.lo_key;
+    r_eq = v.need;
     if (take_whole_bin) {  // keep everything from the start of the sub-bin upwards
-      T = lo_key - 1u;
+      T = v.lo_key - 1u;
       r_eq = 0u;
     }
   }
   // kk == hi - lo: T = 0 keeps every candidate (all real keys are > 0)
 
-  // ---- ordered compaction.  Pass A: prefix of {key > T} (low half) and {key == T} (high
-  // half) inside each wave tile, and the wave's totals.  TIES == false: no key equal to T has
-  // to be cut (r_eq == 0: every kept key is > T), so the equal-to-T bookkeeping is left out.
-  auto compact = [&](auto ties_tag) {
-    constexpr bool TIES = decltype(ties_tag)::value;
-    auto tile_count = [&](const uint32_t(&k4)[4]) {
-      uint32_t cnt = 0;
+  // ---- ordered output.  Pass A: the wave's totals of {key > T} and {key == T} (packed: low and high half per tile)
+  int32_t* sel_out = out + a.lo;
+  auto tile_count = [&](const uint32_t(&k4)[4]) {
+    uint32_t cnt = 0;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        cnt += k4[c] > T ? 1u : 0u;
-        if (TIES) cnt += (k4[c] == T) ? 0x10000u : 0u;
-      }
-      return cnt;
-    };
-    if constexpr (!TIES && NT > 0) {
-      // Keys in registers and no tie to cut: the lane masks of the compares (scalar registers)
-      // give the counts (bit counts, scalar) and the positions (mask counts below the lane).
-      uint32_t run = 0;
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        if (kStageB && j >= tpw) break;
-        run += popc64(__ballot(keys[j][0] > T)) + popc64(__ballot(keys[j][1] > T)) + popc64(__ballot(keys[j][2] > T)) +
-               popc64(__ballot(keys[j][3] > T));
-      }
-      if (lane == 0) s_wgt[wave] = run;
-      __syncthreads();
-      uint32_t unused;
-      uint32_t at = wave_entries_scan<W>(s_wgt, unused);  // kept keys of the waves and tiles before
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        if (kStageB && j >= tpw) break;
-        const bool t0 = keys[j][0] > T, t1 = keys[j][1] > T, t2 = keys[j][2] > T, t3 = keys[j][3] > T;
-        const unsigned long long m0 = __ballot(t0), m1 = __ballot(t1), m2 = __ballot(t2), m3 = __ballot(t3);
-        const uint32_t tot = popc64(m0) + popc64(m1) + popc64(m2) + popc64(m3);
-        if (at + tot <= static_cast<uint32_t>(kk)) {  // (always, when the counts above add up)
-          int32_t* o = sel_out + at + mbcnt64(m3, mbcnt64(m2, mbcnt64(m1, mbcnt64(m0, 0u))));
-          const int32_t nn = static_cast<int32_t>(wbase) + j * kWaveTile;
-          if (t0) *o++ = kStageB ? cidx[(kStageB && NT > 0) ? j : 0][0] : nn;
-          if (t1) *o++ = kStageB ? cidx[(kStageB && NT > 0) ? j : 0][1] : nn + 1;
-          if (t2) *o++ = kStageB ? cidx[(kStageB && NT > 0) ? j : 0][2] : nn + 2;
-          if (t3) *o = kStageB ? cidx[(kStageB && NT > 0) ? j : 0][3] : nn + 3;
-        }
-        at += tot;
-      }
-      return;
+    for (int c = 0; c < 4; ++c) {
+      cnt += k4[c] > T ? 1u : 0u;
+      cnt += (k4[c] == T && r_eq != 0u) ? 0x10000u : 0u;
     }
-    constexpr bool kKeepPre = NT > 0 && NT <= 8;  // keep the in-tile prefixes when registers allow
-    uint32_t pre[kKeepPre ? NT : 1];
-    if (kStream && list_ok) {
-      // streamed row: the per-wave totals come from the list instead of another pass over the
-      // scores (a key above the bracket is kept for sure; a key below it never is)
-      for (int i = tid; i < (kStream ? W : 1) * W * 2; i += kThreads) (&s_lcnt[0][0][0])[i] = 0;
-      __syncthreads();
-      const uint32_t nl = s_nlist;
-      for (uint32_t i = tid; i < nl; i += kThreads) {
-        const uint32_t key = s_ckey[kStream ? i : 0];
-        const uint32_t w = s_cwave[kStream ? i : 0];
-        if (key > T) {
-          atomicAdd(&s_lcnt[kStream ? wave : 0][w][0], 1u);
-        } else if (key == T) {
-          atomicAdd(&s_lcnt[kStream ? wave : 0][w][1], 1u);
-        }
-      }
-      __syncthreads();
-      if (tid < W) {
-        uint32_t gt = s_wabove[tid], eq = 0;
-        for (int cw = 0; cw < (kStream ? W : 1); ++cw) {
-          gt += s_lcnt[cw][tid][0];
-          eq += s_lcnt[cw][tid][1];
-        }
-        s_wgt[tid] = gt;
-        s_weq[tid] = eq;
-      }
-    } else {
-      uint32_t run_gt = 0, run_eq = 0;
-      for_each_tile([&](int j, const uint32_t(&k4)[4]) {
-        const uint32_t cnt = tile_count(k4);
-        const uint32_t incl = wave_incl_scan_u32(cnt);
-        if (kKeepPre) pre[kKeepPre ? j : 0] = incl - cnt;
-        const uint32_t tot = __builtin_amdgcn_readlane(incl, kWave - 1);
-        run_gt += tot & 0xFFFFu;
-        run_eq += tot >> 16;
-      });
-      if (lane == 0) {
-        s_wgt[wave] = run_gt;
-        s_weq[wave] = run_eq;
+    return cnt;
+  };
+  if (list_ok) {
+    // the per-wave totals come from the list instead of another pass over the scores (a key above the bracket is kept
+    // for sure; a key below it never is)
+    for (int i = tid; i < W * W * 2; i += kThreads) (&ll.lcnt[0][0][0])[i] = 0;
+    __syncthreads();
+    const uint32_t nl = ll.n;
+    for (uint32_t i = tid; i < nl; i += kThreads) {
+      const uint32_t key = ll.ckey[i];
+      const uint32_t w = ll.cwave[i];
+      if (key > T) {
+        atomicAdd(&ll.lcnt[wave][w][0], 1u);
+      } else if (key == T) {
+        atomicAdd(&ll.lcnt[wave][w][1], 1u);
       }
     }
     __syncthreads();
-    // kept / tied keys in the spans of the waves before this one
-    uint32_t unused_total;
-    uint32_t base_gt = wave_entries_scan<W>(s_wgt, unused_total);
-    uint32_t base_eq = TIES ? wave_entries_scan<W>(s_weq, unused_total) : 0u;
-
-    // Pass B: position of a kept key = (#greater before it) + min(#equal before it, r_eq)
-    for_each_tile([&](int j, const uint32_t(&k4)[4]) {
-      const uint32_t cnt = tile_count(k4);
-      uint32_t excl;
-      if (kKeepPre) {
-        excl = pre[kKeepPre ? j : 0];
-      } else {
-        excl = wave_incl_scan_u32(cnt) - cnt;
+    if (tid < W) {
+      uint32_t gt = ll.wabove[tid], eq = 0;
+      for (int cw = 0; cw < W; ++cw) {
+        gt += ll.lcnt[cw][tid][0];
+        eq += ll.lcnt[cw][tid][1];
       }
-      const uint32_t tot = __builtin_amdgcn_readlane(excl + cnt, kWave - 1);
-      uint32_t gt_before = base_gt + (excl & 0xFFFFu);
-      uint32_t eq_before = base_eq + (excl >> 16);
-      const int32_t nn = static_cast<int32_t>(wbase + static_cast<int64_t>(j) * kWaveTile);
-      auto emit = [&](uint32_t pos, int c) {
-        if (pos < static_cast<uint32_t>(kk)) sel_out[pos] = kStageB ? cidx[(kStageB && NT > 0) ? j : 0][c] : nn + c;
-      };
-      if (!TIES || (tot >> 16) == 0) {
-        // no key of this wave tile equals T: the tie count is the same for every slot
-        uint32_t pos = gt_before + (TIES ? (eq_before < r_eq ? eq_before : r_eq) : 0u);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          if (k4[c] > T) {
-            emit(pos, c);
-            ++pos;
-          }
-        }
-      } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const bool gt = k4[c] > T;
-          const bool eq = k4[c] == T;
-          if (gt || (eq && eq_before < r_eq)) emit(gt_before + (eq_before < r_eq ? eq_before : r_eq), c);
-          gt_before += gt ? 1u : 0u;
-          eq_before += eq ? 1u : 0u;
-        }
-      }
-      base_gt += tot & 0xFFFFu;
-      base_eq += tot >> 16;
+      sl.wgt[tid] = gt;
+      sl.weq[tid] = eq;
+    }
+  } else {
+    uint32_t run_gt = 0, run_eq = 0;
+    for_each_tile([&](int, const uint32_t(&k4)[4]) {
+      const uint32_t tot = __builtin_amdgcn_readlane(wave_incl_scan_u32(tile_count(k4)), kWave - 1);
+      run_gt += tot & 0xFFFFu;
+      run_eq += tot >> 16;
     });
-  };
-  if (r_eq != 0)
-    compact(std::true_type{});
-  else
-    compact(std::false_type{});
-  write_fixed_ranges();
+    if (lane == 0) {
+      sl.wgt[wave] = run_gt;
+      sl.weq[wave] = run_eq;
+    }
+  }
+  __syncthreads();
+  // kept / tied keys in the spans of the waves before this one
+  uint32_t unused_total;
+  uint32_t base_gt = wave_entries_scan<W>(sl.wgt, unused_total);
+  uint32_t base_eq = r_eq != 0u ? wave_entries_scan<W>(sl.weq, unused_total) : 0u;
+
+  // Pass B: position of a kept key = (#greater before it) + min(#equal before it, r_eq)
+  for_each_tile([&](int j, const uint32_t(&k4)[4]) {
+    const uint32_t cnt = tile_count(k4);
+    const uint32_t excl = wave_incl_scan_u32(cnt) - cnt;
+    const uint32_t tot = __builtin_amdgcn_readlane(excl + cnt, kWave - 1);
+    uint32_t gt_before = base_gt + (excl & 0xFFFFu);
+    uint32_t eq_before = base_eq + (excl >> 16);
+    const int32_t nn = static_cast<int32_t>(wbase + static_cast<int64_t>(j) * kWaveTile);
+    auto emit = [&](uint32_t pos, int c) {
+      if (pos < static_cast<uint32_t>(kk)) sel_out[pos] = nn + c;
+    };
+    if ((tot >> 16) == 0) {
+      // no key of this wave tile equals T: the tie count is the same for every slot
+      uint32_t pos = gt_before + (eq_before < r_eq ? eq_before : r_eq);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if (k4[c] > T) {
+          emit(pos, c);
+          ++pos;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const bool gt = k4[c] > T;
+        const bool eq = k4[c] == T;
+        if (gt || (eq && eq_before < r_eq)) emit(gt_before + (eq_before < r_eq ? eq_before : r_eq), c);
+        gt_before += gt ? 1u : 0u;
+        eq_before += eq ? 1u : 0u;
+      }
+    }
+    base_gt += tot & 0xFFFFu;
+    base_eq += tot >> 16;
+  });
+  write_fixed_ranges<W>(a, u, out);
 }
 
 // ---- moving the scores at or above a bound into a list, with few instructions per score ----------
@@ -774,11 +1060,6 @@ struct RegionLds {
   uint32_t cnt[W];
 };
 
-// Smallest score whose key is `key` (a key that a real score produces).
-__device__ inline float score_of_key(uint32_t key) {
-  return __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key);
-}
-constexpr uint32_t kKeyOfMinusInf = 0x007FFFFFu;
 
 // Appends the candidates (positions in [lo, hi)) among the wave's NT tiles `raw` -- tile j holds
 // the positions pos0 + 256 j + 4 lane .. + 3 -- whose score is at least f_lo (`all`: every
@@ -799,7 +1080,7 @@ __device__ __forceinline__ uint32_t append_at_least(const float4 (&raw)[NT], con
   auto append = [&](int j, bool t0, bool t1, bool t2, bool t3) {
     const float v0 = raw[j].x, v1 = raw[j].y, v2 = raw[j].z, v3 = raw[j].w;
     const int p0 = pos0 + j * kWaveTile + lane * 4;
-    const unsigned long long m0 = __ballot(t0), m1 = __ballot(t1), m2 = __ballot(t2), m3 = __ballot(t3);
+    const unsigned long long m0 = ballot64(t0), m1 = ballot64(t1), m2 = ballot64(t2), m3 = ballot64(t3);
     uint32_t* w = lkey + run + mbcnt64(m3, mbcnt64(m2, mbcnt64(m1, mbcnt64(m0, 0u))));  // after the entries of lower lanes and earlier tiles
     uint32_t* d;
     d = t0 ? w : spare;
@@ -838,14 +1119,15 @@ __device__ __forceinline__ uint32_t append_at_least(const float4 (&raw)[NT], con
 constexpr int kSelWaves = 16;  // one workgroup per row
 constexpr int kSelThreads = kSelWaves * kWave;
 
-template <int NT>
-__global__ __launch_bounds__(kSelThreads, (NT >= 1 && NT <= 4) ? 8 : 4) void select_kernel(SelectArgs a) {
-  __shared__ SelLds<kSelWaves> sl;
+template <int NT, int W = kSelWaves>
+__global__ __launch_bounds__(W * kWave, (NT >= 1 && NT <= 8) ? 8 : 4)  // up to 8 tiles: two workgroups to a compute unit
+void select_kernel(SelectArgs a) {
+  __shared__ SelLds<W> sl;
   if constexpr (NT == 0) {
     __shared__ ListLds<kSelWaves> ll;
-    select_body<kSelWaves, 0, 0, true>(a, blockIdx.x, nullptr, sl, &ll);
+    select_stream<kSelWaves>(a, blockIdx.x, sl, ll);
   } else {
-    select_body<kSelWaves, NT, 0, false>(a, blockIdx.x, nullptr, sl, nullptr);
+    select_regs<W, NT, 0, 2 * kHistBins / W>(a, blockIdx.x, nullptr, sl, &sl.hist[0][0]);
   }
 }
 
@@ -888,10 +1170,8 @@ __device__ __forceinline__ void bracket_of_sample(const SelectArgs& a, const flo
     // select among
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      if (sk[e]) {
-        atomicAdd(&sl.hist[sk[e] >> kTopShift], 1u);
-        ++n_valid;
-      }
+      if (sk[e]) atomicAdd(&sl.hist[sk[e] >> kTopShift], 1u);
+      n_valid += popc64(ballot64(sk[e] != 0u));
     }
   }
   sample_bracket<W>(sl.hist, n_valid, sl.part, sl.wsum, &sl.found, a.kk, span, b_lo, b_hi, &t_lo);
@@ -974,7 +1254,7 @@ __device__ __forceinline__ void piece_body(const SelectArgs& a, const int u, con
   uint32_t total;
   const uint32_t wave_base = wave_entries_scan<W>(pl.reg.cnt, total);
   const int l16 = lane & 15;
-  const bool overflowed = __ballot(l16 < W && pl.reg.cnt[l16 < W ? l16 : 0] > static_cast<uint32_t>(kCap)) != 0ull;
+  const bool overflowed = ballot64(l16 < W && pl.reg.cnt[l16 < W ? l16 : 0] > static_cast<uint32_t>(kCap)) != 0ull;
   if (tid == 0) hdr[0] = total;
   if (!overflowed) {
     const uint32_t* lkey = pl.reg.key + wave * kCap;
@@ -983,7 +1263,7 @@ __device__ __forceinline__ void piece_body(const SelectArgs& a, const int u, con
       const uint32_t at = wave_base + e;
       if (at < static_cast<uint32_t>(a.cap)) {
         out_idx[at] = lpos[e];
-        out_key[at] = score_key(__uint_as_float(lkey[e]));
+        out_key[at] = lkey[e];
       }
     }
     return;
@@ -1004,7 +1284,7 @@ __device__ __forceinline__ void piece_body(const SelectArgs& a, const int u, con
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       t[e] = (all || v[e] >= f_lo) && p0 + e >= a.lo && p0 + e < a.hi;  // (the test of the pass above)
-      m[e] = __ballot(t[e]);
+      m[e] = ballot64(t[e]);
     }
     uint32_t o = mbcnt64(m[3], mbcnt64(m[2], mbcnt64(m[1], mbcnt64(m[0], at))));
 #pragma unroll
@@ -1012,7 +1292,7 @@ __device__ __forceinline__ void piece_body(const SelectArgs& a, const int u, con
       if (t[e]) {
         if (o < static_cast<uint32_t>(a.cap)) {
           out_idx[o] = p0 + e;
-          out_key[o] = score_key(v[e]);
+          out_key[o] = __float_as_uint(v[e]);
         }
         ++o;
       }
@@ -1054,9 +1334,9 @@ __global__ __launch_bounds__(kSelThreads, 4) void stage_b_kernel(SelectArgs a) {
   }
   __syncthreads();
   if (tab.ok) {
-    select_body<W, NT, 2, false>(a, u, &tab, sl, nullptr);
+    select_regs<W, NT, 2, kListCap / W>(a, u, &tab, sl, ll.ckey);
   } else {
-    select_body<W, 0, 0, true>(a, u, nullptr, sl, &ll);
+    select_stream<W>(a, u, sl, ll);
   }
 }
 
@@ -1094,14 +1374,31 @@ tb_status launch_whole(const SelectArgs& a, int64_t units, hipStream_t st) {
   b.tiles_per_wave = tiles;
   dim3 grid(static_cast<unsigned>(units));
   dim3 block(kSelThreads);
-  if (tiles <= 1)
-    hipLaunchKernelGGL(select_kernel<1>, grid, block, 0, st, b);
+  // A workgroup costs what its tiles per wave cost, so there is an instance for (almost) every number (20011 scores, five
+  // tiles: 10.3 us as eight, 8.1 now).  Up to 4096 scores eight waves do: their barriers are cheaper than what the
+  // other eight would take off them (1024 scores: 4.9 us with sixteen, 4.2; 4096: 5.0 and 4.8; 8192: 5.5 and 6.1).
+  constexpr int kFewWaves = 8;
+  const dim3 few(kFewWaves * kWave);
+  if (a.N <= kFewWaves * kWaveTile)
+    hipLaunchKernelGGL((select_kernel<1, kFewWaves>), grid, few, 0, st, b);
+  else if (a.N <= 2 * kFewWaves * kWaveTile)
+    hipLaunchKernelGGL((select_kernel<2, kFewWaves>), grid, few, 0, st, b);
   else if (tiles <= 2)
     hipLaunchKernelGGL(select_kernel<2>, grid, block, 0, st, b);
+  else if (tiles <= 3)
+    hipLaunchKernelGGL(select_kernel<3>, grid, block, 0, st, b);
   else if (tiles <= 4)
     hipLaunchKernelGGL(select_kernel<4>, grid, block, 0, st, b);
+  else if (tiles <= 5)
+    hipLaunchKernelGGL(select_kernel<5>, grid, block, 0, st, b);
+  else if (tiles <= 6)
+    hipLaunchKernelGGL(select_kernel<6>, grid, block, 0, st, b);
   else if (tiles <= 8)
     hipLaunchKernelGGL(select_kernel<8>, grid, block, 0, st, b);
+  else if (tiles <= 10)
+    hipLaunchKernelGGL(select_kernel<10>, grid, block, 0, st, b);
+  else if (tiles <= 12)
+    hipLaunchKernelGGL(select_kernel<12>, grid, block, 0, st, b);
   else if (tiles <= 16)
     hipLaunchKernelGGL(select_kernel<16>, grid, block, 0, st, b);
   else

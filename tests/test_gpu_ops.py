@@ -174,6 +174,30 @@ def test_select_sizes_random_scores(oracle, N):
         check_select(oracle, scores, N, 0, 3, 4)
 
 
+@pytest.mark.parametrize("N", [700, 2047, 2049, 4095, 4097, 8193, 12289, 16385, 20481, 24577, 32769, 40961, 49153, 65535])
+def test_select_register_forms(oracle, N):
+    """Either side of every size at which the one-workgroup selection takes another number of waves or of tiles per
+    wave, with scores that lead it through each of its paths: thresholds above and below zero, a wave's span that keeps
+    (almost) everything, ties, NaN and infinities, and a sample that misleads."""
+    say(f"select register forms N={N}")
+    s = randn((1, 9, (N + 3) // 4 * 4), torch.float32, 300 + N)
+    inf, nan = float("inf"), float("nan")
+    s[0, 1] -= 100.0                                                    # thresholds below zero
+    s[0, 2] = torch.arange(s.shape[-1], dtype=torch.float32).to(DEV)     # the kept scores crowd into the last waves
+    s[0, 3] = (s[0, 3] * 4).round() / 4                                   # ties (and both zeros) at the threshold
+    s[0, 4, ::3], s[0, 4, 1::3], s[0, 4, 2::97] = nan, -inf, inf          # thresholds at +-inf, NaN among what ties with -inf
+    s[0, 5] = torch.where(s[0, 5] > 1.0, torch.full_like(s[0, 5], -0.0), s[0, 5].abs() * 1e-42)  # denormals and -0
+    s[0, 6, ::5] = -nan
+    threads = 512 if N <= 4096 else 1024
+    pos = (torch.arange(threads // 4) * N // (threads // 4) // 4 * 4).view(-1, 1) + torch.arange(4)
+    pos = pos.view(-1)[pos.view(-1) < N].unique().to(DEV)
+    s[0, 7, pos], s[0, 8, pos] = 1e30, -1e30                              # the sample sees nothing but these
+    for k in sorted({1, N // 40, N // 10, N // 2 - 3, N - 1}):
+        check_select(oracle, s, N, k, 0, 0)
+    check_select(oracle, s, N, N // 7, 5, 9)
+    check_select(oracle, s, N, N // 9, N // 3, 70)
+
+
 @pytest.mark.parametrize("N,ks", [
     (65537, (1, 4096, 8192)),            # one score more than a workgroup holds in registers
     (70001, (4096, 8000, 35000)),        # a short last piece
