@@ -1,5 +1,6 @@
 // C ABI of libtokenbutler: argument validation on the host, workspace layout, launch plans.
 // Every entry point only enqueues kernels on the caller's stream.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -9,6 +10,10 @@ namespace tb {
 
 constexpr int64_t kAttnTargetWgs = 512;   // workgroups a launch of the split attention aims at
 constexpr int64_t kAttnGroupTargetWgs = 256;
+// Workgroups that the scoring kernel that filters aims at: several rounds of short ones follow the plain kernel's order
+// through the cache (4 x 8 KV heads, 131072 rows: 2048 workgroups 72.5 us, 4096 69.7, 8192 67.2, one block each 71.9), but
+// every piece costs the second stage some padding.
+constexpr int64_t kScoreFilterWgs = 8192;
 constexpr int64_t kAttnMinTiles = 2;      // a workgroup is worth its hand-over from two tiles per wave on
 
 // `want` splits or a few less: as many as equal shares of whole granules make
@@ -73,6 +78,29 @@ bool attn_shared_list_grouped(const tb_cache_desc* d, int64_t max_rows) {
   return groups >= 32 || (attn_group_mfma(d) && groups >= 16 && max_rows >= enough);
 }
 
+// 4096-key tiles of the second stage for the keys that the pieces keep together, give or take: the share of the row above
+// the cut (the rank of the threshold in a sample of n_s plus twice the bracket's slack: the cut lies one slack below the
+// expected rank, and the other one allows for the sample's own spread), every piece padded to a multiple of 4.
+// (32: more than the second stage can hold, it reads them again in every phase.)
+static int stage_b_tiles(const SelectPlan& p, int64_t candidates, int64_t kk, double n_s) {
+  const double frac = static_cast<double>(kk) / static_cast<double>(candidates);
+  const double ks = frac * n_s, slack = 6.0 * sqrt(ks * (1.0 - frac)) + 4.0;
+  double kept = (ks + 2.0 * slack) / n_s * static_cast<double>(candidates) + 3.0 * static_cast<double>(p.pieces);
+  if (kept > static_cast<double>(p.pieces * p.cap)) kept = static_cast<double>(p.pieces * p.cap);
+  const int64_t t4k = (static_cast<int64_t>(kept) + 4095) / 4096;
+  return t4k <= 2 ? 2 : (t4k <= 4 ? 4 : (t4k <= 8 ? 8 : (t4k <= 16 ? 16 : 32)));
+}
+// The larger sample where it saves tiles of a second stage with more than eight.
+static void choose_sample(SelectPlan& p, int64_t candidates, int64_t kk, double n_s, double n_large) {
+  int tiles = stage_b_tiles(p, candidates, kk, n_s);
+  p.row_sample = false;
+  if (tiles > 8 && stage_b_tiles(p, candidates, kk, n_large) < tiles) {
+    p.row_sample = true;
+    tiles = stage_b_tiles(p, candidates, kk, n_large);
+  }
+  p.stage_b_tiles = tiles < 16 ? tiles : 16;
+}
+
 SelectPlan select_plan(int64_t units, int64_t candidates, int64_t N, int64_t kk) {
   SelectPlan p{1, 0, 0, 2, 8, 16, false};
   // worth it when the budget is a small share of the candidates (the kept keys are then a small
@@ -97,32 +125,38 @@ SelectPlan select_plan(int64_t units, int64_t candidates, int64_t N, int64_t kk)
   p.piece_tiles = tiles;
   const int64_t cap = 2 * kk + 4096;                      // the budget, the bracket's slack, a coarse top bin
   p.cap = ((cap < len ? cap : len) + 3) / 4 * 4;
-  // what the pieces keep together, give or take: the share of the row above the cut (the rank of the
-  // threshold in the sample plus twice the bracket's slack: the cut lies one slack below the expected rank, and
-  // the other one allows for the sample's own spread), every piece padded to a multiple of 4
-  const double frac = static_cast<double>(kk) / static_cast<double>(candidates);
-  auto kept_of = [&](double n_s) {
-    const double ks = frac * n_s, slack = 6.0 * sqrt(ks * (1.0 - frac)) + 4.0;
-    const double kept = (ks + 2.0 * slack) / n_s * static_cast<double>(candidates) + 3.0 * static_cast<double>(pieces);
-    return kept < static_cast<double>(pieces * p.cap) ? kept : static_cast<double>(pieces * p.cap);
-  };
-  // 4096-key tiles that stage B holds (32: more than it can hold, it reads them again in every phase)
-  auto tiles_of = [](double kept) {
-    const int64_t t4k = (static_cast<int64_t>(kept) + 4095) / 4096;
-    return t4k <= 2 ? 2 : (t4k <= 4 ? 4 : (t4k <= 8 ? 8 : (t4k <= 16 ? 16 : 32)));
-  };
   // A small budget of a very long row is a small rank in a piece's own sample, and the pieces keep
   // several budgets' worth of keys.  Where these would need more than 8 tiles of stage B, one larger
   // sample of the row, taken once, is worth its launch if fewer tiles do then (32 rows of 1M scores, 8192 kept:
   // the selection 73 -> 50 us, stage B 38.8 -> 15.2 of them; 32 rows of 500000, 15625 kept: 53 -> 36); elsewhere it is
   // not (256 rows of 131072: 48 us either way, 32 rows: 2 us slower; 64 rows of 262144, 30840 kept, sixteen tiles
   // either way: 70 -> 72).
-  int stage_b = tiles_of(kept_of(4.0 * 64 * waves));
-  if (stage_b > 8 && tiles_of(kept_of(kRowSample)) < stage_b) {
-    p.row_sample = true;
-    stage_b = tiles_of(kept_of(kRowSample));
+  choose_sample(p, candidates, kk, 4.0 * 64 * waves, kRowSample);
+  return p;
+}
+
+// The first stage inside the scoring kernel pays where a row of the projected cache is short next to the g scores made
+// from it: the looped kernel streams that cache at 4.0 TB/s where the plain one reaches 4.3, and a sample of rows is read at
+// random by one compute unit, against a pass over the scores that falls away.  Steps in us, separate and together: 32 heads
+// on 8, d' = 32 bf16, 131072 rows 51.4 and 46.4, 1M rows 186 and 173; 4 x 64 on 8, 131072 rows 169 and 151; 8 x 16 on 8, 66001 rows
+// 86.7 and 82.6; one head a group: d' = 16, 4 x 8, 131072 rows 55.4 and 50.3, d' = 32, 16 x 8, 66001 rows 127 and 132; rows of 128
+// bytes: 8 x 8 on 1, 70000 rows 76.4 and 79.5, of 256 bytes: 8 heads, 131072 rows 69.0 and 78.5.
+SelectPlan score_select_plan(const tb_cache_desc* d, int64_t candidates, int64_t kk) {
+  const int64_t groups = static_cast<int64_t>(d->B) * d->Hkv, N = d->N;
+  SelectPlan p = select_plan(static_cast<int64_t>(d->B) * d->Hq, candidates, N, kk);
+  if (p.pieces < 2) return p;
+  const int row_bytes = d->Dimp * (d->dtype == TB_F32 ? 4 : 2);
+  if (row_bytes > 64 || row_bytes > 32 * (d->Hq / d->Hkv)) {
+    p.pieces = 1;
+    return p;
   }
-  p.stage_b_tiles = stage_b < 16 ? stage_b : 16;
+  int64_t blocks = (groups * N + 256 * kScoreFilterWgs - 1) / (256 * kScoreFilterWgs);  // per piece
+  const int64_t fewest = (N + 256 * 256 - 1) / (256 * 256);  // (the table of the second stage has 256 entries)
+  if (blocks < fewest) blocks = fewest;
+  p.piece_len = blocks * 256;
+  p.pieces = static_cast<int>((N + p.piece_len - 1) / p.piece_len);
+  p.cap = p.piece_len;
+  choose_sample(p, candidates, kk, kScoredSample, kScoredSampleLarge);
   return p;
 }
 
@@ -515,8 +549,13 @@ tb_status tb_decode_step(const tb_cache_desc* d, const void* q_imp, const void* 
   L.idx_cap = idx_cap;
   L.scratch = static_cast<char*>(ws) + w.part_off;
   L.scratch_bytes = ws_bytes - w.part_off;
-  TB_TRY(launch_score(S, st));
-  TB_TRY(launch_select(L, st));
+  const SelectPlan both = score_select_plan(d, p.hi - p.lo, p.kk);
+  if (both.pieces > 1 && L.scratch_bytes >= select_scratch_bytes(units, both)) {
+    TB_TRY(launch_score_select(S, L, both, st));
+  } else {
+    TB_TRY(launch_score(S, st));
+    TB_TRY(launch_select(L, st));
+  }
 
   AttnLaunch A{d,   q,   K,   V,
                idx, count, idx_cap, p.count, 0, 0,
@@ -545,7 +584,10 @@ size_t tb_workspace_bytes(int32_t op, const tb_cache_desc* d, int64_t max_count)
       const size_t g_att = ws_layout(units, d->D, gp.max_split).total;
       if (g_att > att) att = g_att;
     }
-    return (op == TB_OP_DECODE_STEP && sel_total > att) ? sel_total : att;
+    if (op == TB_OP_ATTN) return att;
+    const size_t both = select_scratch_bytes(units, score_select_plan(d, d->N, kk_bound));
+    const size_t step = both ? ws_layout(units, d->D, 1).part_off + align_up(both, 256) : 0;
+    return std::max(std::max(step, sel_total), att);
   }
   return 0;
 }

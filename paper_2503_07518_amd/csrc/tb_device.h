@@ -109,6 +109,18 @@ __device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane(static_c
 // predicate into a number and compares that again.)
 __device__ inline unsigned long long ballot64(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
+// Number of set bits of a lane mask below this lane, added to acc; number of set bits.
+__device__ inline uint32_t mbcnt64(unsigned long long m, uint32_t acc) {
+  return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), acc));
+}
+__device__ inline uint32_t popc64(unsigned long long m) { return static_cast<uint32_t>(__popcll(m)); }
+
+// Smallest score whose key is `key` (a key that a real score produces).
+__device__ inline float score_of_key(uint32_t key) {
+  return __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key);
+}
+constexpr uint32_t kKeyOfMinusInf = 0x007FFFFFu;
+
 // Inclusive prefix sum across the 64 lanes of a wave (generic: LDS-crossbar shuffles).
 template <typename T>
 __device__ inline T wave_incl_scan(T v) {

@@ -65,7 +65,11 @@ struct SelectPlan {
 };
 constexpr int kRowSample = 8192;  // scores of a row that the kernel before stage A looks at
 SelectPlan select_plan(int64_t units, int64_t candidates, int64_t N, int64_t kk);
-// kept positions int32 and keys uint32, [units][pieces][cap] each, then 4 words of header per piece
+// The plan of a selection whose first stage is part of the scoring kernel: pieces of whole 256-row blocks with
+// room for all of their rows.  pieces == 1: scores and selection are separate.
+constexpr int kScoredSample = 2048, kScoredSampleLarge = 8192;  // rows that the kernel before it scores for the bracket
+SelectPlan score_select_plan(const tb_cache_desc* d, int64_t candidates, int64_t kk);
+// kept (score, position) pairs [units][pieces][cap], then 4 words of header per piece
 inline size_t select_scratch_bytes(int64_t units, const SelectPlan& p) {
   return p.pieces > 1 ? static_cast<size_t>(units) * p.pieces * (p.cap * 8 + 16) : 0;
 }
@@ -81,9 +85,20 @@ struct SelectLaunch {
   int64_t idx_cap;
   void* scratch;         // 16-byte aligned, or NULL
   size_t scratch_bytes;  // below select_scratch_bytes(): one workgroup per row is used instead
-  const SelectPlan* plan = nullptr;  // NULL: select_plan() decides
 };
 tb_status launch_select(const SelectLaunch& a, hipStream_t st);
+// Scores and selects: a bracket from a sample, then one kernel that stores the scores and keeps what the bracket does not
+// rule out, then the selection among the kept (score_select_plan; the scratch has to hold it).
+tb_status launch_score_select(const ScoreLaunch& S, const SelectLaunch& L, const SelectPlan& plan, hipStream_t st);
+// What the scoring kernel keeps and where: candidates [lo, hi) at or above the cut in the header of a row's first piece.
+struct FilterOut {
+  uint2* cand;    // [units][pieces][cap] (score bits, position)
+  uint32_t* hdr;  // [units][pieces][4]; word 0 receives the number kept, word 3 of piece 0 holds the cut
+  int32_t pieces;
+  int64_t piece_len, cap;
+  int32_t lo, hi;
+};
+tb_status launch_score_filter(const ScoreLaunch& S, const FilterOut& f, hipStream_t st);
 
 struct AttnLaunch {
   const tb_cache_desc* desc;

@@ -17,6 +17,7 @@ typedef uint32_t nt_u32x4 __attribute__((ext_vector_type(4)));
 constexpr int64_t kScoreNtStoreBytes = 16 << 20;  // score arrays from this size on bypass the caches
 constexpr int kScoreThreads = 256;
 constexpr int kLoadsPerThread = 4;
+constexpr int kFilterBlock = kWave * 4;  // rows a step of the scoring kernel that filters: one float4 of scores per lane
 
 struct ScoreArgs {
   const void* q_imp;
@@ -181,11 +182,161 @@ __global__ __launch_bounds__(kScoreThreads) void score_mfma_kernel(ScoreArgs a) 
   }
 }
 
+// ---- scores of long rows, with the first stage of the selection ----------------------------------
+// One workgroup per piece of a row (all heads of its KV group): blocks of 256 rows one after the other, the next
+// block's loads in flight while the current one is multiplied and its scores go through LDS.  A wave owns a head (or
+// two of eight), so the scores at or above the head's cut go from the registers that store them straight to the
+// piece's list, in position order, behind the wave's running count: a compare, a mask count and (for a few lanes) an
+// 8-byte store per score, which the stream of projected keys hides (without the filter the kernel is no faster).  Bound
+// by the stream, which many workgroups looping over their own pieces cut into more places than one block each does:
+// 4 x 8 KV heads, 131072 rows, 8 heads each 67.2 us and 62.5 for the scores alone, whose pass by the selection's first
+// stage took 34.4; 8 KV heads, 1M rows, 4 heads each 120 and 108, the pass and its bracket 36.
 template <typename T, int DIMP, int G>
-tb_status launch_tdg(const ScoreLaunch& L, hipStream_t st) {
-  const tb_cache_desc& d = *L.desc;
+__global__ __launch_bounds__(kScoreThreads) void score_filter_kernel(ScoreArgs a, FilterOut f) {
+  constexpr bool kMfma = std::is_same<T, bf16_t>::value && DIMP == 32;
   constexpr int EPL = Pack16<T>::kElts;
-  constexpr int RW = kScoreThreads / (DIMP / EPL) * kLoadsPerThread;
+  constexpr int LPR = DIMP / EPL;           // lanes per projected row
+  constexpr int RPP = kScoreThreads / LPR;  // rows per pass of the workgroup
+  constexpr int NL = kFilterBlock / RPP;    // loads per lane and block
+  constexpr int kWaves = kScoreThreads / kWave;
+  constexpr int HPW = (G + kWaves - 1) / kWaves;  // heads per wave
+  constexpr int kPitch = kFilterBlock + 16;       // (the heads of a wave's stores start in different banks)
+  static_assert(!kMfma || LPR == 4, "a wave's 16 rows a pass");
+  __shared__ __attribute__((aligned(16))) float s_out[2][G][kPitch];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = wave_id();
+  const int b = blockIdx.z;
+  const int hkv = blockIdx.y;
+  const int piece = blockIdx.x;
+  const int64_t base = static_cast<int64_t>(piece) * f.piece_len;
+  const int rows = static_cast<int>(a.N - base < f.piece_len ? a.N - base : f.piece_len);  // (a piece has rows: pieces = ceil(N / piece_len))
+  // lane's place in a pass: on the matrix cores lane (i, kb) = (lane % 16, lane / 16) holds elements 8 kb .. 8 kb + 7 of row i
+  const int i16 = lane & 15, kb = lane >> 4;
+  const int part = kMfma ? kb : tid % LPR;
+  const int rsub = kMfma ? wave * 16 + i16 : tid / LPR;
+  const T* kbase = static_cast<const T*>(a.Kimp) + b * a.ki_stride_b + hkv * a.ki_stride_h + base * a.ki_stride_n + part * EPL;
+
+  nt_u32x4 raw[NL];
+  auto load = [&](int r0) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      int row = r0 + i * RPP + rsub;
+      row = row < rows ? row : rows - 1;  // clamp: the result of a clamped row is not used
+      raw[i] = __builtin_nontemporal_load(reinterpret_cast<const nt_u32x4*>(kbase + row * a.ki_stride_n));
+    }
+  };
+  load(0);
+
+  mfma_bf16x8 qop = {0, 0, 0, 0, 0, 0, 0, 0};
+  float qv[kMfma ? 1 : G][EPL];
+  const T* qbase = static_cast<const T*>(a.q_imp) + (static_cast<int64_t>(b) * a.Hq + hkv * G) * DIMP + part * EPL;
+  if constexpr (kMfma) {
+    if (i16 < G) {
+      const uint4 t = *reinterpret_cast<const uint4*>(qbase + i16 * DIMP);
+      __builtin_memcpy(&qop, &t, 16);
+    }
+  } else {
+#pragma unroll
+    for (int hh = 0; hh < G; ++hh) Pack16<T>::load(qbase + hh * DIMP, qv[hh]);
+  }
+
+  // the wave's heads: cut, list and running count
+  const int64_t u0 = static_cast<int64_t>(b) * a.Hq + hkv * G;
+  float f_lo[HPW];
+  bool all[HPW];  // a cut at or below the key of -inf keeps every candidate (NaN, whose key is that of -inf, included)
+  uint32_t run[HPW];
+#pragma unroll
+  for (int k = 0; k < HPW; ++k) {
+    const int hh = wave + k * kWaves;
+    const uint32_t cut = hh < G ? f.hdr[(u0 + hh) * f.pieces * 4 + 3] : 0xFFFFFFFFu;
+    all[k] = cut <= kKeyOfMinusInf;
+    f_lo[k] = all[k] ? 0.f : score_of_key(cut);
+    run[k] = 0;
+  }
+
+  for (int r0 = 0, buf = 0; r0 < rows; r0 += kFilterBlock, buf ^= 1) {
+    float (&out)[G][kPitch] = s_out[buf];
+    nt_u32x4 cur[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) cur[i] = raw[i];
+    if (r0 + kFilterBlock < rows) load(r0 + kFilterBlock);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      if constexpr (kMfma) {
+        mfma_bf16x8 kop;
+        __builtin_memcpy(&kop, &cur[i], 16);
+        mfma_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop, qop, acc, 0, 0, 0);
+        if (i16 < G)
+          *reinterpret_cast<float4*>(&out[i16 < G ? i16 : 0][i * RPP + wave * 16 + 4 * kb]) =
+              make_float4(acc[0] * a.scale, acc[1] * a.scale, acc[2] * a.scale, acc[3] * a.scale);
+      } else {
+        typename Pack16<T>::Raw kr;
+        __builtin_memcpy(&kr, &cur[i], 16);
+        float kf[EPL];
+        Pack16<T>::unpack(kr, kf);
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) {
+          float s = 0.f;
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) s = fmaf(qv[kMfma ? 0 : hh][e], kf[e], s);
+          s = group_allreduce_sum<LPR>(s) * a.scale;
+          if ((hh % LPR) == part) out[hh][i * RPP + rsub] = s;
+        }
+      }
+    }
+    __syncthreads();  // (the other buffer's readers are done: they are past the barrier before)
+#pragma unroll
+    for (int k = 0; k < HPW; ++k) {
+      const int hh = wave + k * kWaves;
+      if (hh >= G) break;  // (scalar)
+      const float4 v = *reinterpret_cast<const float4*>(&out[hh][lane * 4]);
+      const int r = r0 + lane * 4;
+      const int p = static_cast<int>(base) + r;
+      float* dst = a.scores + (u0 + hh) * a.score_stride + base + r;
+      if (r + 3 < rows) {
+        if (a.nt_store) {
+          typedef float nt_f32x4 __attribute__((ext_vector_type(4)));
+          const nt_f32x4 o = {v.x, v.y, v.z, v.w};
+          __builtin_nontemporal_store(o, reinterpret_cast<nt_f32x4*>(dst));
+        } else {
+          *reinterpret_cast<float4*>(dst) = v;
+        }
+      } else {
+        const float o[4] = {v.x, v.y, v.z, v.w};
+        for (int c = 0; c < 4; ++c)
+          if (r + c < rows) dst[c] = o[c];
+      }
+      bool t0 = v.x >= f_lo[k], t1 = v.y >= f_lo[k], t2 = v.z >= f_lo[k], t3 = v.w >= f_lo[k];
+      const int blk = static_cast<int>(base) + r0;
+      if (all[k] || blk < f.lo || blk + kFilterBlock > f.hi) {  // (scalar; a block past the row's end is past hi)
+        const uint32_t d = static_cast<uint32_t>(p - f.lo), n = static_cast<uint32_t>(f.hi - f.lo);
+        t0 = (t0 || all[k]) && d < n;
+        t1 = (t1 || all[k]) && d + 1u < n;
+        t2 = (t2 || all[k]) && d + 2u < n;
+        t3 = (t3 || all[k]) && d + 3u < n;
+      }
+      const unsigned long long m0 = ballot64(t0), m1 = ballot64(t1), m2 = ballot64(t2), m3 = ballot64(t3);
+      uint2* w = f.cand + ((u0 + hh) * f.pieces + piece) * f.cap + run[k] + mbcnt64(m3, mbcnt64(m2, mbcnt64(m1, mbcnt64(m0, 0u))));
+      if (t0) *w++ = make_uint2(__float_as_uint(v.x), static_cast<uint32_t>(p));
+      if (t1) *w++ = make_uint2(__float_as_uint(v.y), static_cast<uint32_t>(p + 1));
+      if (t2) *w++ = make_uint2(__float_as_uint(v.z), static_cast<uint32_t>(p + 2));
+      if (t3) *w = make_uint2(__float_as_uint(v.w), static_cast<uint32_t>(p + 3));
+      run[k] += popc64(m0) + popc64(m1) + popc64(m2) + popc64(m3);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < HPW; ++k) {
+    const int hh = wave + k * kWaves;
+    if (hh < G && lane == 0) f.hdr[((u0 + hh) * f.pieces + piece) * 4] = run[k];
+  }
+}
+
+ScoreArgs score_args(const ScoreLaunch& L) {
+  const tb_cache_desc& d = *L.desc;
   ScoreArgs a;
   a.q_imp = L.q_imp;
   a.Kimp = L.Kimp;
@@ -198,7 +349,23 @@ tb_status launch_tdg(const ScoreLaunch& L, hipStream_t st) {
   a.Hq = d.Hq;
   a.scale = L.scale;
   a.nt_store = static_cast<int64_t>(d.B) * d.Hq * d.N * 4 >= kScoreNtStoreBytes ? 1 : 0;
+  return a;
+}
+
+template <typename T, int DIMP, int G>
+tb_status launch_tdg(const ScoreLaunch& L, const FilterOut* f, hipStream_t st) {
+  const tb_cache_desc& d = *L.desc;
+  constexpr int EPL = Pack16<T>::kElts;
+  constexpr int RW = kScoreThreads / (DIMP / EPL) * kLoadsPerThread;
+  const ScoreArgs a = score_args(L);
   if (d.N == 0) return TB_OK;
+  if (f) {
+    if constexpr (DIMP * sizeof(T) <= 64) {  // (score_select_plan's rule)
+      hipLaunchKernelGGL((score_filter_kernel<T, DIMP, G>), dim3(f->pieces, d.Hkv, d.B), dim3(kScoreThreads), 0, st, a, *f);
+      return hip_status(hipGetLastError());
+    }
+    return TB_ERR_UNSUPPORTED;
+  }
   dim3 grid(static_cast<unsigned>((d.N + RW - 1) / RW), d.Hkv, d.B);
   if constexpr (std::is_same<T, bf16_t>::value && DIMP == 32) {
     static_assert(RW == kScoreThreads / 4 * kLoadsPerThread, "both kernels cut the rows alike");
@@ -210,22 +377,22 @@ tb_status launch_tdg(const ScoreLaunch& L, hipStream_t st) {
 }
 
 template <typename T, int DIMP>
-tb_status launch_td(const ScoreLaunch& L, hipStream_t st) {
+tb_status launch_td(const ScoreLaunch& L, const FilterOut* f, hipStream_t st) {
   switch (L.desc->Hq / L.desc->Hkv) {
-    case 1: return launch_tdg<T, DIMP, 1>(L, st);
-    case 2: return launch_tdg<T, DIMP, 2>(L, st);
-    case 4: return launch_tdg<T, DIMP, 4>(L, st);
-    case 8: return launch_tdg<T, DIMP, 8>(L, st);
+    case 1: return launch_tdg<T, DIMP, 1>(L, f, st);
+    case 2: return launch_tdg<T, DIMP, 2>(L, f, st);
+    case 4: return launch_tdg<T, DIMP, 4>(L, f, st);
+    case 8: return launch_tdg<T, DIMP, 8>(L, f, st);
     default: return TB_ERR_UNSUPPORTED;
   }
 }
 
 template <typename T>
-tb_status launch_t(const ScoreLaunch& L, hipStream_t st) {
+tb_status launch_t(const ScoreLaunch& L, const FilterOut* f, hipStream_t st) {
   switch (L.desc->Dimp) {
-    case 16: return launch_td<T, 16>(L, st);
-    case 32: return launch_td<T, 32>(L, st);
-    case 64: return launch_td<T, 64>(L, st);
+    case 16: return launch_td<T, 16>(L, f, st);
+    case 32: return launch_td<T, 32>(L, f, st);
+    case 64: return launch_td<T, 64>(L, f, st);
     default: return TB_ERR_UNSUPPORTED;
   }
 }
@@ -233,7 +400,11 @@ tb_status launch_t(const ScoreLaunch& L, hipStream_t st) {
 }  // namespace
 
 tb_status launch_score(const ScoreLaunch& L, hipStream_t st) {
-  return L.desc->dtype == TB_F32 ? launch_t<float>(L, st) : launch_t<bf16_t>(L, st);
+  return L.desc->dtype == TB_F32 ? launch_t<float>(L, nullptr, st) : launch_t<bf16_t>(L, nullptr, st);
+}
+
+tb_status launch_score_filter(const ScoreLaunch& L, const FilterOut& f, hipStream_t st) {
+  return L.desc->dtype == TB_F32 ? launch_t<float>(L, &f, st) : launch_t<bf16_t>(L, &f, st);
 }
 
 }  // namespace tb

@@ -27,7 +27,9 @@
 //                                      piece keeps the keys at or above the lower end of a bracket
 //                                      that every piece derives from the same sample of the row
 //                                      (or, for a small budget of a very long row, finds ready from
-//                                      bracket_kernel), and a second kernel selects among the kept keys.
+//                                      bracket_kernel), and a second kernel selects among the kept keys;
+//   score_bracket_kernel + scoring     long rows of a whole step: the bracket comes from a sample that is scored for it, the
+//   kernel + stage_b_kernel            scoring kernel keeps what lies above its lower end.
 #include "tb_device.h"
 #include "tb_internal.h"
 
@@ -50,8 +52,8 @@ struct SelectArgs {
   int32_t tiles_per_wave;  // of a workgroup that takes the whole row
   // Selection by pieces.  Stage A cuts the row into `pieces` pieces and keeps, per piece, the
   // candidates whose key is not below a threshold that a sample of the whole row puts safely
-  // under the kk-th largest key: positions (of the whole row) and keys go to cand_idx /
-  // cand_key [unit][piece][cap] in position order, and the piece's header {number found,
+  // under the kk-th largest key: pairs (score bits, position in the whole row) go to cand
+  // [unit][piece][cap] in position order, and the piece's header {number found,
   // b_lo, b_hi, 0} to piece_hdr[unit][piece].  Stage B selects the kk largest among the kept
   // ones, read as one row through the table of the pieces' counts; if the pieces hold fewer
   // than kk keys together or more than stage B has registers for -- the sample misled -- it
@@ -60,8 +62,7 @@ struct SelectArgs {
   int64_t piece_len;
   int64_t cap;
   int64_t units;  // rows of the launch (stage A maps its workgroups to rows and pieces itself)
-  int32_t* cand_idx;
-  uint32_t* cand_key;
+  uint2* cand;
   uint32_t* piece_hdr;
 };
 
@@ -108,12 +109,6 @@ __device__ inline uint32_t wave_entries_scan(const uint32_t* s_w, uint32_t& tota
   return __builtin_amdgcn_readlane(incl - v, wave_id());
 }
 
-// Number of set bits of a lane mask below this lane, added to acc; number of set bits.
-__device__ inline uint32_t mbcnt64(unsigned long long m, uint32_t acc) {
-  return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), acc));
-}
-__device__ inline uint32_t popc64(unsigned long long m) { return static_cast<uint32_t>(__popcll(m)); }
-
 // A wave-uniform bound as a value of its own, so that a second pass over the scores compares again: the masks of the
 // first pass would otherwise be kept for it, two scalar registers per score, most of them spilled.
 __device__ inline float compared_anew(float bound) {
@@ -128,11 +123,6 @@ __device__ inline void settle(uint32_t& count) {
   asm volatile("" : "+s"(count));
 }
 
-// Smallest score whose key is `key` (a key that a real score produces).
-__device__ inline float score_of_key(uint32_t key) {
-  return __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key);
-}
-constexpr uint32_t kKeyOfMinusInf = 0x007FFFFFu;
 constexpr uint32_t kNoScore = 0x7FC00000u;  // a NaN, in the place of what is no candidate: no compare holds for it
 
 // Result of a histogram walk, published in LDS for the whole workgroup.
@@ -392,9 +382,8 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
   if constexpr (kStageB) {
     // where position n (a multiple of 4) of the row lies in the [piece][cap] arrays, and how
     // many of the four entries from there on are real (the rest is padding)
-    const uint32_t* ckeys = a.cand_key + static_cast<int64_t>(u) * a.pieces * a.cap;
-    const int32_t* cpos = a.cand_idx + static_cast<int64_t>(u) * a.pieces * a.cap;
-    uint4 rk[NT], ri[NT];
+    const uint2* cand = a.cand + static_cast<int64_t>(u) * a.pieces * a.cap;
+    uint4 r01[NT], r23[NT];  // (score bits, position) of entries 0 and 1, 2 and 3
     int valid[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
@@ -410,14 +399,15 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
         valid[j] = static_cast<int>(tab->n[c]) - off;
         phys = c * a.cap + off;
       }
-      rk[j] = *reinterpret_cast<const uint4*>(ckeys + phys);
-      ri[j] = *reinterpret_cast<const uint4*>(cpos + phys);
+      const uint4* src = reinterpret_cast<const uint4*>(cand + phys);
+      r01[j] = src[0];
+      r23[j] = src[1];
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-      const uint32_t kv[4] = {rk[j].x, rk[j].y, rk[j].z, rk[j].w};
-      const uint32_t iv[4] = {ri[j].x, ri[j].y, ri[j].z, ri[j].w};
+      const uint32_t kv[4] = {r01[j].x, r01[j].z, r23[j].x, r23[j].z};
+      const uint32_t iv[4] = {r01[j].y, r01[j].w, r23[j].y, r23[j].w};
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         s4[j][c] = __uint_as_float(c < valid[j] ? kv[c] : kNoScore);
@@ -1191,6 +1181,106 @@ __global__ __launch_bounds__(kSelThreads) void bracket_kernel(SelectArgs a) {
   if (tid < 3) a.piece_hdr[static_cast<int64_t>(u) * a.pieces * 4 + 1 + tid] = tid == 0 ? b_lo : (tid == 1 ? b_hi : t_lo);
 }
 
+// The bracket of a row whose scores are not there yet: the workgroup scores a sample of its candidates itself (SAMPLE rows,
+// four adjacent ones at each of SAMPLE / 4 places, so that a place is one or two cache lines), and leaves b_lo, b_hi and the cut
+// in the header of the row's first piece for the scoring kernel that follows.  A heuristic, as every bracket: the sums
+// need not round as that kernel's do.  Bound by its chain: the trips to memory, the histogram, its walk: 6.4 us for 256 rows
+// and 2048 scored, 12.8 us for 32 rows and 8192 (with 4096 9.0, but the second stage then takes 20.8 us instead of 13.8).
+// The heads of a KV group read the same rows; they are placed on one XCD (workgroups go to the eight round-robin).
+struct SampleArgs {
+  const void* q_imp;
+  const void* Kimp;
+  int64_t ki_stride_b, ki_stride_h, ki_stride_n;
+  int32_t Hkv, g, n_groups;
+  float scale;
+};
+template <typename T, int DIMP, int SAMPLE>
+__global__ __launch_bounds__(kSelThreads) void score_bracket_kernel(SelectArgs a, SampleArgs s) {
+  constexpr int EPL = Pack16<T>::kElts;
+  constexpr int LPR = DIMP / EPL;             // lanes per projected row
+  constexpr int RPP = kSelThreads / LPR;      // rows per pass of the workgroup
+  constexpr int PASSES = SAMPLE / RPP;
+  constexpr int BATCH = PASSES < 8 ? PASSES : 8;  // loads in flight per lane (two batches are, while one is used)
+  constexpr int OWN = SAMPLE / kSelThreads;   // scores that a lane takes over
+  static_assert(PASSES % BATCH == 0 && BATCH % LPR == 0 && OWN >= 1, "every lane of a row takes over whole passes");
+  __shared__ SampleLds<kSelWaves> sl;
+  const int tid = threadIdx.x;
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int kvg = xcd + 8 * (slot / s.g);
+  if (kvg >= s.n_groups) return;  // (the launch is padded to a multiple of eight groups)
+  const int b = kvg / s.Hkv, hkv = kvg % s.Hkv;
+  const int u = kvg * s.g + slot % s.g;  // row b*Hq + h
+  const int N = static_cast<int>(a.N);
+  const int part = tid % LPR, rsub = tid / LPR;
+  const T* kbase = static_cast<const T*>(s.Kimp) + b * s.ki_stride_b + hkv * s.ki_stride_h + part * EPL;
+  const uint32_t span = static_cast<uint32_t>(a.hi - a.lo);
+  static_assert(kSelectMaxN * (SAMPLE / 4) <= (int64_t{1} << 32), "place times span fits 32 bits");
+  auto pos_of = [&](int r) -> int {  // row r of the sample
+    return ((a.lo + static_cast<int>(static_cast<uint32_t>(r >> 2) * span / (SAMPLE / 4))) & ~3) + (r & 3);
+  };
+  typename Pack16<T>::Raw kraw[BATCH];
+  auto load = [&](int p0) {
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const int n = pos_of((p0 + i) * RPP + rsub);
+      kraw[i] = Pack16<T>::load_raw(kbase + (n < N ? n : N - 1) * s.ki_stride_n);
+    }
+  };
+  load(0);
+  float qv[EPL];
+  Pack16<T>::load(static_cast<const T*>(s.q_imp) + static_cast<int64_t>(u) * DIMP + part * EPL, qv);
+  __builtin_amdgcn_sched_barrier(0);
+  uint4* z = reinterpret_cast<uint4*>(sl.hist);
+  for (int i = tid; i < kHistBins / 4; i += kSelThreads) z[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (tid < kFoundWords) reinterpret_cast<uint32_t*>(&sl.found)[tid] = 0;
+  __syncthreads();
+  uint32_t n_valid = 0;
+#pragma nounroll
+  for (int p0 = 0; p0 < PASSES; p0 += BATCH) {
+    float own[BATCH / LPR];
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      float kf[EPL], x = 0.f;
+      Pack16<T>::unpack(kraw[i], kf);
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) x = fmaf(qv[e], kf[e], x);
+      x = group_allreduce_sum<LPR>(x);
+      if (i % LPR == part) own[i / LPR] = x * s.scale;
+    }
+    if (p0 + BATCH < PASSES) load(p0 + BATCH);
+#pragma unroll
+    for (int o = 0; o < BATCH / LPR; ++o) {
+      const int n = pos_of((p0 + o * LPR + part) * RPP + rsub);
+      const bool valid = n >= a.lo && n < a.hi;  // (the four may straddle an end of the candidate range)
+      if (valid) atomicAdd(&sl.hist[score_key(own[o]) >> kTopShift], 1u);
+      n_valid += popc64(ballot64(valid));
+    }
+  }
+  uint32_t b_lo, b_hi, t_lo;
+  sample_bracket<kSelWaves>(sl.hist, n_valid, sl.part, sl.wsum, &sl.found, a.kk, span, b_lo, b_hi, &t_lo);
+  if (tid < 3) a.piece_hdr[static_cast<int64_t>(u) * a.pieces * 4 + 1 + tid] = tid == 0 ? b_lo : (tid == 1 ? b_hi : t_lo);
+}
+
+template <typename T, int DIMP>
+tb_status launch_score_bracket_d(const SelectArgs& a, const SampleArgs& s, int sample, hipStream_t st) {
+  const dim3 grid(static_cast<unsigned>((s.n_groups + 7) / 8 * 8 * s.g)), block(kSelThreads);
+  if (sample <= kScoredSample)
+    hipLaunchKernelGGL((score_bracket_kernel<T, DIMP, kScoredSample>), grid, block, 0, st, a, s);
+  else
+    hipLaunchKernelGGL((score_bracket_kernel<T, DIMP, kScoredSampleLarge>), grid, block, 0, st, a, s);
+  return hip_status(hipGetLastError());
+}
+template <typename T>
+tb_status launch_score_bracket(const ScoreLaunch& S, const SelectArgs& a, const SelectPlan& plan, hipStream_t st) {
+  const tb_cache_desc& d = *S.desc;
+  const SampleArgs s{S.q_imp, S.Kimp, d.ki_stride_b, d.ki_stride_h, d.ki_stride_n, d.Hkv, d.Hq / d.Hkv, d.B * d.Hkv, S.scale};
+  const int sample = plan.row_sample ? kScoredSampleLarge : kScoredSample;
+  if (d.Dimp == 16) return launch_score_bracket_d<T, 16>(a, s, sample, st);
+  if constexpr (sizeof(T) == 2)
+    if (d.Dimp == 32) return launch_score_bracket_d<T, 32>(a, s, sample, st);
+  return TB_ERR_UNSUPPORTED;
+}
+
 // ---- selection of a row by pieces, stage A.  The piece's scores are in registers (NT tiles per
 // wave).  Every piece of a row takes the same sample of the row's candidates (one 128-bit load
 // per thread at positions spread evenly over [lo, hi)) and so arrives at the same bracket as its
@@ -1218,8 +1308,7 @@ __device__ __forceinline__ void piece_body(const SelectArgs& a, const int u, con
   const float* s = row + base;
   const int last4 = n_c > 0 ? static_cast<int>((n_c - 1) & ~int64_t{3}) : 0;
   const int wspan0 = wave * NT * kWaveTile;  // the wave's span, as positions inside the piece
-  int32_t* out_idx = a.cand_idx + (static_cast<int64_t>(u) * a.pieces + c) * a.cap;
-  uint32_t* out_key = a.cand_key + (static_cast<int64_t>(u) * a.pieces + c) * a.cap;
+  uint2* out = a.cand + (static_cast<int64_t>(u) * a.pieces + c) * a.cap;
   uint32_t* row_hdr = a.piece_hdr + static_cast<int64_t>(u) * a.pieces * 4;
   uint32_t* hdr = row_hdr + c * 4;
   float4 raw[NT];
@@ -1261,10 +1350,7 @@ __device__ __forceinline__ void piece_body(const SelectArgs& a, const int u, con
     const int32_t* lpos = pl.reg.pos + wave * kCap;
     for (uint32_t e = lane; e < run; e += kWave) {
       const uint32_t at = wave_base + e;
-      if (at < static_cast<uint32_t>(a.cap)) {
-        out_idx[at] = lpos[e];
-        out_key[at] = lkey[e];
-      }
+      if (at < static_cast<uint32_t>(a.cap)) out[at] = make_uint2(lkey[e], static_cast<uint32_t>(lpos[e]));
     }
     return;
   }
@@ -1290,10 +1376,7 @@ __device__ __forceinline__ void piece_body(const SelectArgs& a, const int u, con
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       if (t[e]) {
-        if (o < static_cast<uint32_t>(a.cap)) {
-          out_idx[o] = p0 + e;
-          out_key[o] = __float_as_uint(v[e]);
-        }
+        if (o < static_cast<uint32_t>(a.cap)) out[o] = make_uint2(__float_as_uint(v[e]), static_cast<uint32_t>(p0 + e));
         ++o;
       }
     }
@@ -1311,17 +1394,25 @@ __global__ __launch_bounds__(kSelThreads, 4) void stage_b_kernel(SelectArgs a) {
   __shared__ SelLds<W> sl;
   __shared__ ListLds<W> ll;
   __shared__ PieceTab tab;
-  __shared__ uint32_t s_scan[2][W + 1];
+  __shared__ uint32_t s_part[3][W];
   const int tid = threadIdx.x;
   const int u = blockIdx.x;
   const uint32_t* hdr = a.piece_hdr + static_cast<int64_t>(u) * a.pieces * 4;
   uint32_t n = 0;
   if (tid < a.pieces) n = hdr[tid * 4];
   const uint32_t padded = (n + 3u) & ~3u;
-  uint32_t len, kept;
-  const uint32_t start = block_excl_scan<W>(padded, s_scan[0], len);
-  block_excl_scan<W>(n, s_scan[1], kept);
-  const int over = __syncthreads_or(n > static_cast<uint32_t>(a.cap));
+  const uint32_t incl = wave_incl_scan_u32(padded), incl_n = wave_incl_scan_u32(n);
+  if (lane_id() == kWave - 1) {
+    s_part[0][wave_id()] = incl;
+    s_part[1][wave_id()] = incl_n;
+  }
+  const bool over = ballot64(n > static_cast<uint32_t>(a.cap)) != 0ull;
+  if (lane_id() == 0) s_part[2][wave_id()] = over ? 1u : 0u;
+  __syncthreads();
+  uint32_t len, kept, overs;
+  const uint32_t start = wave_entries_scan<W>(s_part[0], len) + incl - padded;
+  wave_entries_scan<W>(s_part[1], kept);
+  wave_entries_scan<W>(s_part[2], overs);
   if (tid < kMaxPieces) {
     tab.start[tid] = start;
     tab.n[tid] = n;
@@ -1330,7 +1421,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void stage_b_kernel(SelectArgs a) {
     tab.len = len;
     tab.b_lo = hdr[1];
     tab.b_hi = hdr[2];
-    tab.ok = (!over && len <= static_cast<uint32_t>(NT * W * kWaveTile) && kept >= static_cast<uint32_t>(a.kk)) ? 1u : 0u;
+    tab.ok = (overs == 0u && len <= static_cast<uint32_t>(NT * W * kWaveTile) && kept >= static_cast<uint32_t>(a.kk)) ? 1u : 0u;
   }
   __syncthreads();
   if (tab.ok) {
@@ -1406,8 +1497,8 @@ tb_status launch_whole(const SelectArgs& a, int64_t units, hipStream_t st) {
   return hip_status(hipGetLastError());
 }
 
-// Second stage over kept keys that are in place (layout of SelectArgs::cand_*).
-tb_status launch_stage_b(const SelectLaunch& L, const SelectPlan& plan, hipStream_t st) {
+// Arguments of a selection; with a plan of several pieces, its scratch is [units][pieces][cap] pairs, then the pieces' headers.
+SelectArgs select_args(const SelectLaunch& L, const SelectPlan* plan) {
   SelectArgs a;
   a.scores = L.scores;
   a.score_stride = L.score_stride;
@@ -1418,16 +1509,19 @@ tb_status launch_stage_b(const SelectLaunch& L, const SelectPlan& plan, hipStrea
   a.idx = L.idx;
   a.count = L.count;
   a.idx_cap = L.idx_cap;
-  const int64_t per_unit = static_cast<int64_t>(plan.pieces) * plan.cap;
-  a.pieces = plan.pieces;
-  a.piece_len = plan.piece_len;
-  a.cap = plan.cap;
+  a.tiles_per_wave = static_cast<int32_t>((L.N + kSelWaves * kWaveTile - 1) / (kSelWaves * kWaveTile));  // of a workgroup on the whole row
+  a.pieces = plan ? plan->pieces : 1;
+  a.piece_len = plan ? plan->piece_len : 0;
+  a.cap = plan ? plan->cap : 0;
   a.units = L.units;
-  a.cand_idx = static_cast<int32_t*>(L.scratch);
-  a.cand_key = reinterpret_cast<uint32_t*>(a.cand_idx + L.units * per_unit);
-  a.piece_hdr = a.cand_key + L.units * per_unit;
-  a.tiles_per_wave = static_cast<int32_t>((L.N + kSelWaves * kWaveTile - 1) / (kSelWaves * kWaveTile));  // fall-back on the whole row
-  const dim3 grid(static_cast<unsigned>(L.units)), block(kSelThreads);
+  a.cand = plan ? static_cast<uint2*>(L.scratch) : nullptr;
+  a.piece_hdr = plan ? reinterpret_cast<uint32_t*>(a.cand + L.units * plan->pieces * plan->cap) : nullptr;
+  return a;
+}
+
+// Second stage over kept keys that are in place.
+tb_status launch_stage_b(const SelectArgs& a, const SelectPlan& plan, hipStream_t st) {
+  const dim3 grid(static_cast<unsigned>(a.units)), block(kSelThreads);
   if (plan.stage_b_tiles <= 2)
     hipLaunchKernelGGL(stage_b_kernel<2>, grid, block, 0, st, a);
   else if (plan.stage_b_tiles <= 4)
@@ -1443,37 +1537,11 @@ tb_status launch_stage_b(const SelectLaunch& L, const SelectPlan& plan, hipStrea
 
 tb_status launch_select(const SelectLaunch& L, hipStream_t st) {
   if (L.units == 0) return TB_OK;
-  SelectArgs a;
-  a.scores = L.scores;
-  a.score_stride = L.score_stride;
-  a.N = L.N;
-  a.kk = L.kk;
-  a.lo = L.lo;
-  a.hi = L.hi;
-  a.idx = L.idx;
-  a.count = L.count;
-  a.idx_cap = L.idx_cap;
-  a.tiles_per_wave = 0;
-  a.pieces = 1;
-  a.piece_len = 0;
-  a.cap = 0;
-  a.units = L.units;
-  a.cand_idx = nullptr;
-  a.cand_key = nullptr;
-  a.piece_hdr = nullptr;
-  const SelectPlan plan = L.plan ? *L.plan : select_plan(L.units, L.hi - L.lo, L.N, L.kk);
+  const SelectPlan plan = select_plan(L.units, L.hi - L.lo, L.N, L.kk);
   if (plan.pieces <= 1 || !L.scratch || L.scratch_bytes < select_scratch_bytes(L.units, plan))
-    return launch_whole(a, L.units, st);
+    return launch_whole(select_args(L, nullptr), L.units, st);
 
-  // scratch: kept positions, kept keys ([units][pieces][cap] each), then the pieces' headers
-  const int64_t per_unit = static_cast<int64_t>(plan.pieces) * plan.cap;
-  a.pieces = plan.pieces;
-  a.piece_len = plan.piece_len;
-  a.cap = plan.cap;
-  a.cand_idx = static_cast<int32_t*>(L.scratch);
-  a.cand_key = reinterpret_cast<uint32_t*>(a.cand_idx + L.units * per_unit);
-  a.piece_hdr = a.cand_key + L.units * per_unit;
-  a.units = L.units;
+  const SelectArgs a = select_args(L, &plan);
   const dim3 grid(static_cast<unsigned>((L.units + 7) / 8 * 8 * plan.pieces));
   const bool own = !plan.row_sample;
   if (!own) {
@@ -1486,7 +1554,16 @@ tb_status launch_select(const SelectLaunch& L, hipStream_t st) {
   else
     rc = own ? launch_prefilter_w<8, true>(a, plan.piece_tiles, grid, st) : launch_prefilter_w<8, false>(a, plan.piece_tiles, grid, st);
   if (rc != TB_OK) return rc;
-  return launch_stage_b(L, plan, st);
+  return launch_stage_b(a, plan, st);
+}
+
+tb_status launch_score_select(const ScoreLaunch& S, const SelectLaunch& L, const SelectPlan& plan, hipStream_t st) {
+  const SelectArgs a = select_args(L, &plan);
+  tb_status rc = S.desc->dtype == TB_F32 ? launch_score_bracket<float>(S, a, plan, st) : launch_score_bracket<bf16_t>(S, a, plan, st);
+  if (rc != TB_OK) return rc;
+  rc = launch_score_filter(S, FilterOut{a.cand, a.piece_hdr, plan.pieces, plan.piece_len, plan.cap, L.lo, L.hi}, st);
+  if (rc != TB_OK) return rc;
+  return launch_stage_b(a, plan, st);
 }
 
 }  // namespace tb

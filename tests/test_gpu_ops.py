@@ -11,6 +11,7 @@ import torch
 
 pytestmark = pytest.mark.gpu
 
+from paper_2503_07518_amd import binding as tb
 from gpu_util import (ATTN_TOL, DEV, assert_attention, assert_projection, assert_scores, dtype_name, gpu_attn,
                       gpu_decode_step, gpu_expand, gpu_project, gpu_score, gpu_select, np_of, projection_magnitude,
                       score_magnitude)
@@ -651,6 +652,54 @@ def test_decode_step_matches_separate_calls_and_oracle(oracle, dtype, B, Hq, Hkv
     assert np.array_equal(np_of(idx)[..., : ridx.shape[-1]], ridx)
     ro, rl = oracle.sparse_decode_attn(np_of(q), np_of(K), np_of(V), np_of(idx), np_of(cnt), dn, sm)
     assert_attention(np_of(out), ro, dn, np_of(lse), rl)
+
+
+@pytest.mark.parametrize("dtype,g,Hkv,B,Dimp,N", [
+    (torch.bfloat16, 1, 3, 1, 16, 65537),     # one row past the separate calls, a last piece of one row
+    (torch.float32, 2, 1, 2, 16, 70003),      # two of four waves have a head
+    (torch.bfloat16, 2, 3, 1, 32, 66001),
+    (torch.bfloat16, 4, 1, 1, 32, 131072),
+    (torch.float32, 8, 1, 1, 16, 131073),     # two heads a wave
+    (torch.bfloat16, 8, 3, 1, 32, 100001),    # a number of KV groups that is no multiple of eight
+    (torch.bfloat16, 4, 2, 1, 16, (1 << 20) - 5),  # the larger sample, pieces of sixteen blocks
+    (torch.float32, 4, 1, 1, 16, 1 << 20),
+    (torch.bfloat16, 1, 2, 1, 32, 66001),     # either side of the rule: scores and selection stay apart
+    (torch.float32, 8, 1, 1, 32, 66001),
+])
+def test_decode_step_long_rows(oracle, dtype, g, Hkv, B, Dimp, N):
+    """Rows of more than 65536 scores: the scoring kernel keeps the scores that a sampled bracket does not rule out.  The
+    scores must be those of the scoring call, bit for bit, and the lists the oracle's on them, with thresholds
+    above and below zero, ties, NaN, ascending rows (all that is kept crowds into the last pieces) and a sample that misleads; a
+    workspace too small for the lists of the pieces gives the same results."""
+    say(f"decode_step long rows dtype={dtype} g={g} Hkv={Hkv} B={B} Dimp={Dimp} N={N}")
+    Hq = g * Hkv
+    cap = N + 3
+    K = torch.zeros((B, Hkv, cap, 64), dtype=dtype, device=DEV)  # (the attention is not what is tested)
+    Kimp = randn((B, Hkv, cap, Dimp), dtype, 31)
+    q_imp, q = randn((B, Hq, Dimp), dtype, 32), randn((B, Hq, 64), dtype, 33)
+    inf, nan = float("inf"), float("nan")
+    ramp = torch.zeros_like(Kimp)
+    ramp[..., 0] = (torch.arange(cap, device=DEV) // 256).to(dtype)  # (256 equal scores a block: ties at every threshold)
+    odd = Kimp.clone()
+    odd[:, :, ::5, 0], odd[:, :, 1::5, 1], odd[:, :, 2::997, 2] = nan, -inf, inf
+    lie, low = Kimp.clone(), Kimp.clone()
+    pos = sample_positions(N).to(DEV)
+    lie[:, :, pos], low[:, :, pos] = 30 * q_imp[:, ::g, None], -30 * q_imp[:, ::g, None]
+    d = tb.make_desc(N, Hq, K=K, V=K, Kimp=Kimp)
+    some = min(N // 8, 5000)
+    for name, keys, scale, k, sink, window in (
+            ("random", Kimp, 0.5, some, 0, 0), ("random", Kimp, -1.0, N // 100, 128, 257), ("random", Kimp, 1.0, 1, 3, 0),
+            ("ramp", ramp, 1.0, some, 4, 64), ("ramp", ramp, -1.0, some, 0, 0), ("odd", odd, 1.0, some, 0, 5),
+            ("constant", torch.zeros_like(Kimp), 1.0, some, 1, 1), ("misled high", lie, 1.0, some, 0, 0), ("misled low", low, 1.0, some, 0, 0)):
+        separate = gpu_score(q_imp, keys, N, scale)
+        ridx, rcnt = oracle.select_topk(np_of(separate)[:, :, :N], k, sink, window)
+        need = tb.policy_count(N, k, sink, window)
+        small = tb.new_workspace(tb.TB_OP_ATTN, d, need)
+        for ws in (None, small):
+            scores, idx, cnt, out, lse = gpu_decode_step(q, q_imp, K, K, keys, N, k, sink, window, 1.0, scale=scale, ws=ws)
+            assert np.array_equal(np_of(scores)[:, :, :N].view(np.uint32), np_of(separate)[:, :, :N].view(np.uint32)), name
+            assert np.array_equal(np_of(cnt), rcnt), name
+            assert np.array_equal(np_of(idx)[..., :need], ridx[..., :need]), name
 
 
 def test_read_stream_probe_reads_and_writes_nothing():
