@@ -108,37 +108,54 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _stream(stream=None) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    # (the current stream's handle without a Stream object around it, which cost 3 us a call: more than the rest of one)
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
-def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
+def _dtype_code(dtype: torch.dtype) -> int:
+    if dtype == torch.float32:
         return TB_F32
-    if t.dtype == torch.bfloat16:
+    if dtype == torch.bfloat16:
         return TB_BF16
-    raise TypeError(f"unsupported element type {t.dtype}")
+    raise TypeError(f"unsupported element type {dtype}")
 
 
-def _strides3(t: Optional[torch.Tensor], inner: int) -> Tuple[int, int, int]:
-    if t is None:
-        return (0, 0, inner)
-    st = t.stride()
-    assert len(st) == 4 and st[3] == 1, "cache tensors are [B, Hkv, N, D] with D contiguous"
-    return st[:3]
+def _strides3(t: torch.Tensor) -> Tuple[int, int, int]:
+    sb, sh, sn, inner = t.stride()
+    assert inner == 1, "cache tensors are [B, Hkv, N, D] with D contiguous"
+    return sb, sh, sn
 
 
 def make_desc(N: int, Hq: int, K: Optional[torch.Tensor] = None, V: Optional[torch.Tensor] = None,
               Kimp: Optional[torch.Tensor] = None, D: Optional[int] = None, Dimp: Optional[int] = None) -> tb_cache_desc:
     """Describe one layer's cache from the tensors at hand.  Missing tensors get neutral
     strides; D / Dimp may be given explicitly when the tensor that carries them is absent."""
-    ref = K if K is not None else (Kimp if Kimp is not None else V)
-    assert ref is not None
-    B, Hkv = ref.shape[0], ref.shape[1]
-    D = D if D is not None else (K.shape[3] if K is not None else (V.shape[3] if V is not None else 128))
-    Dimp = Dimp if Dimp is not None else (Kimp.shape[3] if Kimp is not None else 32)
-    return tb_cache_desc(B, Hq, Hkv, D, Dimp, _dtype_code(ref), N, *_strides3(K, D), *_strides3(V if V is not None else K, D),
-                         *_strides3(Kimp, Dimp))
+    if K is not None:
+        B, Hkv, _, inner = K.shape
+        k = _strides3(K)
+        dtype = K.dtype
+    else:
+        ref = Kimp if Kimp is not None else V
+        assert ref is not None
+        B, Hkv = ref.shape[0], ref.shape[1]
+        inner = 128 if V is None else V.shape[3]
+        k = None
+        dtype = ref.dtype
+    if D is None:
+        D = inner
+    k = k or (0, 0, D)
+    v = k if V is None else _strides3(V)
+    if Kimp is not None:
+        if Dimp is None:
+            Dimp = Kimp.shape[3]
+        ki = _strides3(Kimp)
+    else:
+        if Dimp is None:
+            Dimp = 32
+        ki = (0, 0, Dimp)
+    return tb_cache_desc(B, Hq, Hkv, D, Dimp, _dtype_code(dtype), N, *k, *v, *ki)
 
 
 def tb_version() -> int:
@@ -229,7 +246,7 @@ def tb_predict_queries(h, gamma, beta, W1, b1, W2, b2, G: int, Hq: int, Dimp: in
     assert hidden_act.dtype == torch.float32 and hidden_act.shape == (B, hidden)
     assert ln_act.dtype == torch.float32 and ln_act.shape == (B, E)
     assert q_imp.shape == (G, B, Hq, Dimp) and q_imp.dtype == h.dtype
-    p = tb_predictor_desc(E, hidden, G, Hq, Dimp, _dtype_code(h), ln_eps)
+    p = tb_predictor_desc(E, hidden, G, Hq, Dimp, _dtype_code(h.dtype), ln_eps)
     _check(load_library().tb_predict_queries(ctypes.byref(p), B, _ptr(h), _ptr(gamma), _ptr(beta), _ptr(W1), _ptr(b1),
                                              _ptr(W2), _ptr(b2), _ptr(hidden_act), _ptr(ln_act), _ptr(q_imp), _stream(stream)),
            "tb_predict_queries")

@@ -165,10 +165,11 @@ class RingLayoutDecoder:
     def step(self, t: int, N_t: int, q: torch.Tensor, q_imp: torch.Tensor):
         """Step t sees the first N_t = N0 + t rows of the cache.  Returns (out, lse) views."""
         S, R = self.sink, self.ring
+        aux = tb.make_desc(S + R, self.Hq, K=self.aux_K, V=self.aux_V)
         if t > 0:  # the token appended before this step arrives in the ring
             slot = (t - 1) % R
             tb.tb_append_kv(tb.make_desc(self.Ncap, self.Hq, K=self.K, V=self.V), self.K, self.V, N_t - 1,
-                            tb.make_desc(S + R, self.Hq, K=self.aux_K, V=self.aux_V), self.aux_K, self.aux_V, S + slot)
+                            aux, self.aux_K, self.aux_V, S + slot)
             if t % R == 0:
                 # the head is back at slot 0: slot i holds token N_t - R + i; project the R keys of
                 # the ring in one batch and append them to the projected-key cache
@@ -186,7 +187,7 @@ class RingLayoutDecoder:
             # migration into the Important Buffer: the widened list without its sink and window entries
             tb.tb_gather_important(desc, self.K, self.V, self.exp_idx, self.exp_cnt, self.exp_cap, min(S, N_t), W_t,
                                    self.Kbuf, self.Vbuf, self.imp_cnt)
-        aux = tb.make_desc(S + W_t, self.Hq, K=self.aux_K, V=self.aux_V)
+        aux.N = S + W_t
         tb.tb_buffered_decode_attn(aux, q, self.Kbuf, self.Vbuf, self.imp_cnt, self.exp_cap, self.aux_K, self.aux_V,
                                    self.sm_scale, self.out, self.lse, self.ws, tail_begin=0, tail_end=S + W_t)
         return self.out, self.lse
