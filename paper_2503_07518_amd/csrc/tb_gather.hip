@@ -105,20 +105,20 @@ tb_status launch_td(const GatherLaunch& L, hipStream_t st) {
 }
 
 // Arrival of new rows: one 16-byte piece of K and one of V per thread, all KV heads of the batch in one
-// launch.  Bound by its launch (two elementwise copies of one row of 16 heads each: 2 x 3.0 us and the gap
-// between them; this: 4.4 us, the row cold).
+// launch.  Bound by its launch and one trip to memory (two elementwise copies of one row of 16 heads each: 2 x 3.0 us and the
+// gap between them; this: 4.2 us, the row cold; 4.4 with the row found by 64-bit divisions).
 struct AppendArgs {
   const char* src[2];
   char* dst[2];
   int64_t src_b[2], src_h[2], src_n[2], dst_b[2], dst_h[2], dst_n[2];  // strides in bytes
-  int64_t rows;
-  int32_t pieces;  // of 16 bytes per row
+  int32_t total, shift;  // 16-byte pieces of all rows; log2 of the pieces per row
 };
 
 __global__ __launch_bounds__(kGatherThreads) void append_kernel(AppendArgs a) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * kGatherThreads + threadIdx.x;
-  if (i >= a.rows * a.pieces) return;
-  const int64_t row = i / a.pieces, at = i % a.pieces * 16;
+  const int i = blockIdx.x * kGatherThreads + threadIdx.x;
+  if (i >= a.total) return;
+  const int64_t row = i >> a.shift;
+  const int at = (i & ((1 << a.shift) - 1)) * 16;
   const int h = blockIdx.y, b = blockIdx.z;
   uint4 v[2];
 #pragma unroll
@@ -161,10 +161,11 @@ tb_status launch_append(const tb_cache_desc& src, const void* K, const void* V, 
     a.src[t] = static_cast<const char*>(in[t]) + src_row * a.src_n[t];
     a.dst[t] = static_cast<char*>(out[t]) + dst_row * a.dst_n[t];
   }
-  a.rows = rows;
-  a.pieces = static_cast<int32_t>(src.D * elt / 16);
-  const dim3 grid(static_cast<unsigned>((rows * a.pieces + kGatherThreads - 1) / kGatherThreads), src.Hkv, src.B);
-  const int threads = rows * a.pieces <= kWave ? kWave : kGatherThreads;
+  const int pieces = static_cast<int>(src.D * elt / 16);  // per row: 8, 16 or 32
+  a.shift = 31 - __builtin_clz(pieces);
+  a.total = static_cast<int32_t>(rows * pieces);  // (at most 2^20 rows)
+  const dim3 grid(static_cast<unsigned>((a.total + kGatherThreads - 1) / kGatherThreads), src.Hkv, src.B);
+  const int threads = a.total <= kWave ? kWave : kGatherThreads;
   hipLaunchKernelGGL(append_kernel, grid, dim3(threads), 0, st, a);
   return hip_status(hipGetLastError());
 }
