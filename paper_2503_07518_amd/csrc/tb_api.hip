@@ -160,6 +160,18 @@ SelectPlan score_select_plan(const tb_cache_desc* d, int64_t candidates, int64_t
   return p;
 }
 
+// One launch for a whole step, a workgroup per head, against three: no more heads than compute units, a row that a workgroup
+// scores and a list that it attends to in little more than the two launches saved (a compute unit takes about 60 bytes a
+// nanosecond).  Separate and in one, us: 8 heads, 1024 rows of d' = 16, 128 kept, D = 64, fp32 12.7 and 9.0; D = 128, bf16,
+// d' = 32: 32 heads, 2048 rows, 200 kept (230 KB) 14.1 and 11.7, 4096 rows, 400 kept (460 KB) 16.2 and 15.0, 800 kept (660 KB) 16.5
+// and 16.6; 256 heads, 1024 rows, 100 kept 14.1 and 10.9, 4000 rows, 400 kept 24.7 and 23.5; 64 heads, 3000 rows, 684 kept (540
+// KB) 17.1 and 17.3; d' = 64, 4096 rows, 600 kept (810 KB) 16.9 and 18.5.
+bool step_in_one(const tb_cache_desc* d, int64_t rows, int nsplit) {
+  const int64_t elt = d->dtype == TB_F32 ? 4 : 2;
+  return d->N > 0 && d->N <= kStepMaxN && static_cast<int64_t>(d->B) * d->Hq <= 256 && nsplit <= kStepMaxSplits &&
+         (d->N * d->Dimp + rows * 2 * d->D) * elt <= 480 * 1024;
+}
+
 WsLayout ws_layout(int64_t units, int D, int nsplit) {
   WsLayout w;
   w.part_off = align_up(static_cast<size_t>(units) * kCounterStrideWords * sizeof(uint32_t), 256);
@@ -549,6 +561,12 @@ tb_status tb_decode_step(const tb_cache_desc* d, const void* q_imp, const void* 
   L.idx_cap = idx_cap;
   L.scratch = static_cast<char*>(ws) + w.part_off;
   L.scratch_bytes = ws_bytes - w.part_off;
+  AttnLaunch A{d,   q,   K,   V,
+               idx, count, idx_cap, p.count, 0, 0,
+               sm_scale, out, lse,
+               reinterpret_cast<float*>(static_cast<char*>(ws) + w.part_off),
+               reinterpret_cast<uint32_t*>(ws), plan};
+  if (step_in_one(d, p.count, plan.nsplit)) return launch_step(S, L, A, st);
   const SelectPlan both = score_select_plan(d, p.hi - p.lo, p.kk);
   if (both.pieces > 1 && L.scratch_bytes >= select_scratch_bytes(units, both)) {
     TB_TRY(launch_score_select(S, L, both, st));
@@ -556,12 +574,6 @@ tb_status tb_decode_step(const tb_cache_desc* d, const void* q_imp, const void* 
     TB_TRY(launch_score(S, st));
     TB_TRY(launch_select(L, st));
   }
-
-  AttnLaunch A{d,   q,   K,   V,
-               idx, count, idx_cap, p.count, 0, 0,
-               sm_scale, out, lse,
-               reinterpret_cast<float*>(static_cast<char*>(ws) + w.part_off),
-               reinterpret_cast<uint32_t*>(ws), plan};
   return launch_attn(A, st);
 }
 

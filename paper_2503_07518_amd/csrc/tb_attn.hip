@@ -34,22 +34,16 @@
 // the list shared, or, when there are enough KV groups to fill the chip, through
 // attn_group_kernel: one workgroup per (b, kv head, split) that serves all query heads of the
 // KV head, so that every listed row is loaded once.
-#include "tb_device.h"
-#include "tb_internal.h"
+#include "tb_attn_rows.h"
 
 namespace tb {
 namespace {
 
-constexpr int kAttnThreads = 256;
 constexpr int kXcds = 8;  // accelerator complex dies of the chip, each with its own L2
-constexpr int kAttnWaves = kAttnThreads / kWave;
 constexpr int kGroupWaves = kAttnGroupWaves;  // of a workgroup that serves a KV group on the matrix cores
-constexpr int kLoadsPerTile = kAttnLoadsPerTile;
 // occupancy the register allocation is held to: 4 waves per SIMD = 4 workgroups per CU, so that a
 // launch of up to 1024 workgroups is resident at once (no second round of workgroups)
 constexpr int kAttnWavesPerSimd = 4;
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
 
 struct AttnArgs {
   const void* q;
@@ -77,8 +71,6 @@ struct AttnArgs {
 
 constexpr int32_t kTailFlag = 0x40000000;  // buffered form: the row number refers to the cache, not the buffer
 
-__device__ inline float exp2_safe(float d) { return __builtin_amdgcn_exp2f(d); }
-
 // Waits until every vector-memory operation this wave has issued, stores included, has been
 // acknowledged (s_waitcnt with all counters at zero).
 __device__ inline void publish_fence() { __builtin_amdgcn_s_waitcnt(0); }
@@ -89,104 +81,23 @@ __device__ inline void store_pair(float* p, float m, float l) {
   __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Adds up the splits of GH heads (partials `po`, pairs `pp` of the first of them) and writes their outputs: the
-// work of the last workgroup to arrive, whose time is added to the whole launch.  A quad of outputs per
-// thread, 128 bits of an accumulator and its pair per load, the splits dealt round the J thread groups that
-// cover the outputs.  All loads of a thread are in flight together: a chain of device-scope loads would cost
-// a memory round trip per split, and such a load is paid per instruction even when its result is not needed,
-// so the chunk is sized to the split count.  With a scalar load each for value, max and sum (24 instructions
-// a thread for 16 splits instead of 4) the kernel took 15.0 us instead of 14.6 (32 heads, 3277 of 32768 rows, cold);
-// of these the ticket costs 0.7 and the combination 1.1.  The order of combination is fixed.
 constexpr int kAgentScope = 16;  // cache policy of a buffer load that agent-scope stores are visible to (sc1)
+// The splits of GH heads where the workgroups have left them (partials `po`, pairs `pp` of the first of them): 128
+// bits of an accumulator and its pair per load.  With a scalar load each for value, max and sum (24 instructions
+// a thread for 16 splits instead of 4) the kernel took 15.0 us instead of 14.6 (32 heads, 3277 of 32768 rows, cold);
+// of these the ticket costs 0.7 and the combination 1.1.
 template <int D, int GH, int NW>
-__device__ __forceinline__ void combine_splits(const float* po, const float* pp, const int nsplit, float* out, float* lse,
-                                               float (&s_m)[NW][GH], float (&s_l)[NW][GH], float (&s_acc)[NW][GH][D]) {
-  constexpr int kThreads = NW * kWave;
-  constexpr int QUADS = GH * D / 4;       // threads that cover the outputs
-  constexpr int J = kThreads / QUADS;     // thread groups, each taking every J-th split
-  constexpr int ROWS = QUADS < kWave ? NW : J;  // partial sums left for LDS
-  static_assert(QUADS <= kThreads && ROWS <= NW, "every output has a thread, the sums fit the waves' LDS");
+__device__ __forceinline__ void combine_published(const float* po, const float* pp, const int nsplit, float* out, float* lse,
+                                                  float (&s_m)[NW][GH], float (&s_l)[NW][GH], float (&s_acc)[NW][GH][D]) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  const int tid = threadIdx.x;
-  const int quad = tid % QUADS, j = tid / QUADS;
-  const int hh = quad / (D / 4), d = quad % (D / 4) * 4;
   const __amdgpu_buffer_rsrc_t rsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(po), 0, GH * nsplit * D * static_cast<int>(sizeof(float)), 0x00027000);
-  float M = -INFINITY, L = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
-  auto add = [&](const float m_o, const float l_o, const float (&o_o)[4]) {
-    const float m_n = fmaxf(M, m_o);
-    if (m_n > -INFINITY) {
-      const float wa = exp2_safe(M - m_n), wb = exp2_safe(m_o - m_n);
-      L = L * wa + l_o * wb;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = o[e] * wa + o_o[e] * wb;
-      M = m_n;
-    }
-  };
-  auto walk = [&](auto ch_tag) {
-    constexpr int CH = decltype(ch_tag)::value;
-    for (int s0 = j; s0 < nsplit; s0 += J * CH) {
-      u32x4 ov[CH];
-      unsigned long long pv[CH];
-#pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const int sp = s0 + c * J < nsplit ? s0 + c * J : nsplit - 1;
-        pv[c] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(pp) + hh * nsplit + sp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ov[c] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, ((hh * nsplit + sp) * D + d) * static_cast<int>(sizeof(float)), 0, kAgentScope);
-      }
-#pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const bool real = s0 + c * J < nsplit;  // (a repeated last split weighs nothing)
-        const float oc[4] = {__uint_as_float(ov[c].x), __uint_as_float(ov[c].y), __uint_as_float(ov[c].z), __uint_as_float(ov[c].w)};
-        add(real ? __uint_as_float(static_cast<uint32_t>(pv[c])) : -INFINITY, __uint_as_float(static_cast<uint32_t>(pv[c] >> 32)), oc);
-      }
-    }
-  };
-  if (nsplit <= J)
-    walk(std::integral_constant<int, 1>{});
-  else if (nsplit <= 2 * J)
-    walk(std::integral_constant<int, 2>{});
-  else if (nsplit <= 4 * J)
-    walk(std::integral_constant<int, 4>{});
-  else
-    walk(std::integral_constant<int, 8>{});
-#pragma unroll
-  for (int off = QUADS; off < kWave; off <<= 1) {
-    const float m_o = __shfl_xor(M, off, kWave), l_o = __shfl_xor(L, off, kWave);
-    float o_o[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o_o[e] = __shfl_xor(o[e], off, kWave);
-    add(m_o, l_o, o_o);
-  }
-  // (the LDS arrays were last read before the partial was published)
-  const int row = QUADS < kWave ? tid / kWave : j;
-  if (QUADS >= kWave || tid % kWave < QUADS) {
-    *reinterpret_cast<float4*>(&s_acc[row][hh][d]) = make_float4(o[0], o[1], o[2], o[3]);
-    if (d == 0) {
-      s_m[row][hh] = M;
-      s_l[row][hh] = L;
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int e0 = 0; e0 < GH * D; e0 += kThreads) {
-    const int e = e0 + tid, eh = e / D, ed = e % D;
-    if (e < GH * D) {
-      float Mt = -INFINITY, Lt = 0.f, ot = 0.f;
-#pragma unroll
-      for (int r = 0; r < ROWS; ++r) Mt = fmaxf(Mt, s_m[r][eh]);
-      if (Mt > -INFINITY) {
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-          const float wgt = exp2_safe(s_m[r][eh] - Mt);
-          Lt += s_l[r][eh] * wgt;
-          ot += s_acc[r][eh][ed] * wgt;
-        }
-      }
-      out[e] = (Lt > 0.f) ? ot / Lt : 0.f;
-      if (ed == 0 && lse) lse[eh] = (Lt > 0.f) ? Mt * kLn2 + logf(Lt) : -INFINITY;
-    }
-  }
+  combine_splits<D, GH, NW>(
+      nsplit, out, lse, s_m, s_l, s_acc,
+      [&](int at) { return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(pp) + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
+      [&](int at, int d) -> u32x4 {
+        return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (at * D + d) * static_cast<int>(sizeof(float)), 0, kAgentScope);
+      });
 }
 
 // SHARES: the list is cut into one share per XCD (nsplit divides by their number)
@@ -251,15 +162,8 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
     vbuf = reinterpret_cast<const char*>(static_cast<const T*>(a.Vbuf) + u * a.buf_cap * D) + sub * 16;
   }
 
-  float qv[EPL];
-  Pack16<T>::load(static_cast<const T*>(a.q) + u * D + sub * EPL, qv);
-#pragma unroll
-  for (int e = 0; e < EPL; ++e) qv[e] *= a.sm_scale_log2;
-
-  float m = -INFINITY, l = 0.f;
-  float acc[EPL];
-#pragma unroll
-  for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+  RowSoftmax<T, D> rows;
+  rows.init(static_cast<const T*>(a.q) + u * D + sub * EPL, a.sm_scale_log2);
 
   // row numbers of a tile: lanes 0..TILE-1 fetch one entry each (selected list, then the
   // dense tail); -1 marks a slot past the end.  The next tile's entries are fetched while the
@@ -331,77 +235,22 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
     n_next = fetch_rows(t0 + stride);
     // every gather of the tile is in flight before the first one is consumed
     __builtin_amdgcn_sched_barrier(0);
-    float sc[kLoadsPerTile];
-    float tmax = -INFINITY;
-#pragma unroll
-    for (int t = 0; t < kLoadsPerTile; ++t) {
-      float kf[EPL];
-      Pack16<T>::unpack(kraw[t], kf);
-      float s = 0.f;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) s = fmaf(qv[e], kf[e], s);
-      s = group_allreduce_sum<LPR>(s);
-      sc[t] = valid[t] ? s : -INFINITY;
-      tmax = fmaxf(tmax, sc[t]);
-    }
-    const float m_new = fmaxf(m, tmax);
-    if (m_new > -INFINITY) {
-      const float alpha = exp2_safe(m - m_new);  // m = -inf -> 0
-      l *= alpha;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[e] *= alpha;
-#pragma unroll
-      for (int t = 0; t < kLoadsPerTile; ++t) {
-        const float p = exp2_safe(sc[t] - m_new);  // invalid -> 0
-        l += p;
-        float vf[EPL];
-        Pack16<T>::unpack(vraw[t], vf);
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] = fmaf(p, vf[e], acc[e]);
-      }
-      m = m_new;
-    }
+    rows.consume(kraw, vraw, valid);
   }
-  // merge the row groups of the wave
-#pragma unroll
-  for (int off = LPR; off < kWave; off <<= 1) {
-    const float m_o = __shfl_xor(m, off, kWave);
-    const float l_o = __shfl_xor(l, off, kWave);
-    const float m_n = fmaxf(m, m_o);
-    const float wa = (m_n > -INFINITY) ? exp2_safe(m - m_n) : 0.f;
-    const float wb = (m_n > -INFINITY) ? exp2_safe(m_o - m_n) : 0.f;
-    l = l * wa + l_o * wb;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      const float a_o = __shfl_xor(acc[e], off, kWave);
-      acc[e] = acc[e] * wa + a_o * wb;
-    }
-    m = m_n;
-  }
+  rows.merge_groups();
   if (grp == 0) {
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) s_acc[wave][0][sub * EPL + e] = acc[e];
+    for (int e = 0; e < EPL; ++e) s_acc[wave][0][sub * EPL + e] = rows.acc[e];
     if (sub == 0) {
-      s_m[wave][0] = m;
-      s_l[wave][0] = l;
+      s_m[wave][0] = rows.m;
+      s_l[wave][0] = rows.l;
     }
   }
   __syncthreads();
 
   // merge the waves of the workgroup: thread d < D owns output element d
   float M = -INFINITY, L = 0.f, o = 0.f;
-  if (tid < D) {
-#pragma unroll
-    for (int w = 0; w < kAttnWaves; ++w) M = fmaxf(M, s_m[w][0]);
-    if (M > -INFINITY) {
-#pragma unroll
-      for (int w = 0; w < kAttnWaves; ++w) {
-        const float wgt = exp2_safe(s_m[w][0] - M);
-        L += s_l[w][0] * wgt;
-        o += s_acc[w][0][tid] * wgt;
-      }
-    }
-  }
+  if (tid < D) merge_waves<D, kAttnWaves>(&s_m[0], &s_l[0], &s_acc[0], tid, M, L, o);
 
   if (a.nsplit == 1) {
     if (tid < D) a.out[u * D + tid] = (L > 0.f) ? o / L : 0.f;
@@ -429,7 +278,7 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   }
   __syncthreads();
   if (!s_last) return;
-  combine_splits<D, 1, kAttnWaves>(a.partials + u * a.nsplit * D, a.partials + a.pairs_off + u * a.nsplit * 2, a.nsplit, a.out + u * D,
+  combine_published<D, 1, kAttnWaves>(a.partials + u * a.nsplit * D, a.partials + a.pairs_off + u * a.nsplit * 2, a.nsplit, a.out + u * D,
                                    a.lse ? a.lse + u : nullptr, s_m, s_l, s_acc);
   if (tid == 0) __hip_atomic_store(&a.counters[u * kCounterStrideWords], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -508,7 +357,7 @@ __device__ __forceinline__ void group_finish(const AttnArgs& a, const int64_t u0
   }
   __syncthreads();
   if (!gl.last) return;
-  combine_splits<D, GH, NW>(a.partials + u0 * a.nsplit * D, a.partials + a.pairs_off + u0 * a.nsplit * 2, a.nsplit, a.out + u0 * D,
+  combine_published<D, GH, NW>(a.partials + u0 * a.nsplit * D, a.partials + a.pairs_off + u0 * a.nsplit * 2, a.nsplit, a.out + u0 * D,
                             a.lse ? a.lse + u0 : nullptr, gl.m, gl.l, gl.acc);
   if (tid == 0) __hip_atomic_store(&a.counters[u0 * kCounterStrideWords], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

@@ -123,6 +123,12 @@ struct AttnLaunch {
   bool grouped = false;  // shared list served by one workgroup per KV group (plan made for that)
 };
 
+// Scores, selection and attention in one launch (a workgroup per head), for what step_in_one allows.
+constexpr int kStepMaxN = 4096;
+constexpr int kStepMaxSplits = 4;
+bool step_in_one(const tb_cache_desc* d, int64_t rows, int nsplit);
+tb_status launch_step(const ScoreLaunch& S, const SelectLaunch& L, const AttnLaunch& A, hipStream_t st);
+
 // Copies the listed rows of K and V into per-query-head buffers [B][Hq][buf_cap][D].
 struct GatherLaunch {
   const tb_cache_desc* desc;

@@ -654,6 +654,48 @@ def test_decode_step_matches_separate_calls_and_oracle(oracle, dtype, B, Hq, Hkv
     assert_attention(np_of(out), ro, dn, np_of(lse), rl)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("g,Hkv,B,D,Dimp,N,k,sink,window", [
+    (1, 1, 1, 64, 16, 1, 1, 0, 0),
+    (2, 3, 1, 128, 32, 65, 9, 1, 2),
+    (4, 8, 4, 128, 32, 1023, 130, 4, 64),      # 128 heads, one and two splits of the attention
+    (8, 8, 4, 64, 16, 4095, 400, 128, 256),    # 256 heads: the most
+    (8, 8, 4, 64, 64, 800, 90, 0, 0),
+    (1, 8, 1, 64, 16, 1024, 128, 0, 0),
+    (2, 2, 1, 128, 32, 2051, 500, 0, 0),       # bf16: three splits
+    (4, 1, 1, 128, 16, 4096, 511, 0, 0),       # the longest row
+    (4, 1, 1, 64, 16, 4096, 300, 0, 0),
+    (2, 1, 1, 128, 64, 1025, 200, 2, 0),
+    (4, 1, 1, 128, 64, 2051, 500, 0, 0),       # more bytes than one workgroup takes: separate kernels
+    (4, 2, 1, 64, 32, 700, 700, 0, 0),         # everything kept
+    (8, 1, 1, 128, 32, 300, 0, 0, 0),          # nothing kept
+    (4, 8, 9, 64, 32, 500, 50, 0, 0),          # 288 heads, and a row of 4097: separate kernels
+    (4, 1, 1, 64, 32, 4097, 100, 0, 0),
+])
+def test_decode_step_short_rows(oracle, dtype, g, Hkv, B, D, Dimp, N, k, sink, window):
+    """A short step is one launch: scores, lists, outputs must be those of the separate calls bit for bit (projected keys with
+    ties, NaN and infinities among them), in caches with strides of their own."""
+    say(f"decode_step short rows dtype={dtype} g={g} Hkv={Hkv} B={B} D={D} Dimp={Dimp} N={N} k={k}")
+    Hq, cap = g * Hkv, N + 5
+    K, V = randn((B, cap, Hkv, D + 8), dtype, 41).transpose(1, 2)[..., :D], randn((B, Hkv, cap, D), dtype, 42)
+    Kimp = randn((B, Hkv, cap, Dimp + 16), dtype, 43)[..., :Dimp]
+    q, q_imp = randn((B, Hq, D), dtype, 44), randn((B, Hq, Dimp), dtype, 45)
+    tied, odd = Kimp.clone(), Kimp.clone()
+    tied[:, :, 1::2] = tied[:, :, :1]
+    odd[:, :, ::5, 0], odd[:, :, 1::7, 1], odd[:, :, 2::9, 2] = float("nan"), -float("inf"), float("inf")
+    for name, keys, scale in (("random", Kimp, 1.0), ("negative", Kimp, -0.5), ("tied", tied, 1.0), ("odd", odd, 1.0)):
+        s, idx, cnt, out, lse = gpu_decode_step(q, q_imp, K, V, keys, N, k, sink, window, 0.1, scale=scale)
+        s2 = gpu_score(q_imp, keys, N, scale)
+        idx2, cnt2 = gpu_select(s2, N, k, sink, window, Hkv=Hkv)
+        out2, lse2 = gpu_attn(q, K, V, idx2, cnt2, N, 0.1, max_count=tb.policy_count(N, k, sink, window))
+        ridx, rcnt = oracle.select_topk(np_of(s2)[:, :, :N], k, sink, window)
+        need = tb.policy_count(N, k, sink, window)
+        assert np.array_equal(np_of(s)[:, :, :N].view(np.uint32), np_of(s2)[:, :, :N].view(np.uint32)), name
+        assert np.array_equal(np_of(cnt), rcnt) and np.array_equal(np_of(idx)[..., :need], ridx[..., :need]), name
+        assert torch.equal(cnt, cnt2) and torch.equal(idx, idx2), name
+        assert torch.equal(out, out2) and torch.equal(lse, lse2), name
+
+
 @pytest.mark.parametrize("dtype,g,Hkv,B,Dimp,N", [
     (torch.bfloat16, 1, 3, 1, 16, 65537),     # one row past the separate calls, a last piece of one row
     (torch.float32, 2, 1, 2, 16, 70003),      # two of four waves have a head
