@@ -123,9 +123,9 @@ def _dtype_code(dtype: torch.dtype) -> int:
 
 
 def _strides3(t: torch.Tensor) -> Tuple[int, int, int]:
-    sb, sh, sn, inner = t.stride()
-    assert inner == 1, "cache tensors are [B, Hkv, N, D] with D contiguous"
-    return sb, sh, sn
+    st = t.stride()
+    assert len(st) == 4 and st[3] == 1, "cache tensors are [B, Hkv, N, D] with D contiguous"
+    return st[:3]
 
 
 def make_desc(N: int, Hq: int, K: Optional[torch.Tensor] = None, V: Optional[torch.Tensor] = None,
@@ -133,8 +133,8 @@ def make_desc(N: int, Hq: int, K: Optional[torch.Tensor] = None, V: Optional[tor
     """Describe one layer's cache from the tensors at hand.  Missing tensors get neutral
     strides; D / Dimp may be given explicitly when the tensor that carries them is absent."""
     if K is not None:
-        B, Hkv, _, inner = K.shape
         k = _strides3(K)
+        B, Hkv, _, inner = K.shape
         dtype = K.dtype
     else:
         ref = Kimp if Kimp is not None else V
