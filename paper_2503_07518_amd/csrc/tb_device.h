@@ -121,18 +121,6 @@ __device__ inline float score_of_key(uint32_t key) {
 }
 constexpr uint32_t kKeyOfMinusInf = 0x007FFFFFu;
 
-// Inclusive prefix sum across the 64 lanes of a wave (generic: LDS-crossbar shuffles).
-template <typename T>
-__device__ inline T wave_incl_scan(T v) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    T o = __shfl_up(v, off, kWave);
-    if (lane >= off) v += o;
-  }
-  return v;
-}
-
 // 32-bit inclusive prefix sum with DPP moves (stays in the VALU, no LDS traffic): shifts by
 // 1, 2, 4, 8 inside each row of 16 lanes, then the last lane of row 0/2 is broadcast into row
 // 1/3 and the last lane of the lower half into the upper half.  Lanes whose source falls
@@ -166,32 +154,6 @@ __device__ inline float group_allreduce_sum(float s) {
   if (LANES >= 16) s += dpp(s, std::integral_constant<int, kRowMirror>{});
   if (LANES >= 32) s += __shfl_xor(s, 16, kWave);
   return s;
-}
-
-// Exclusive prefix sum over the threads of a block of NWAVES waves (thread order).
-// s_tmp needs NWAVES + 1 entries.  Ends with a barrier, so s_tmp may be reused right away
-// for another scan.  `total` receives the block-wide sum.
-template <int NWAVES, typename T>
-__device__ inline T block_excl_scan(T v, T* s_tmp, T& total) {
-  const int lane = lane_id();
-  const int wave = threadIdx.x / kWave;
-  const T incl = wave_incl_scan(v);
-  if (lane == kWave - 1) s_tmp[wave] = incl;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    T run = 0;
-    for (int w = 0; w < NWAVES; ++w) {
-      const T t = s_tmp[w];
-      s_tmp[w] = run;
-      run += t;
-    }
-    s_tmp[NWAVES] = run;
-  }
-  __syncthreads();
-  const T base = s_tmp[wave];
-  total = s_tmp[NWAVES];
-  __syncthreads();
-  return base + incl - v;
 }
 
 }  // namespace tb
