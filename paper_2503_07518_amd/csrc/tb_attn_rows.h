@@ -148,9 +148,13 @@ __device__ __forceinline__ void combine_splits(const int nsplit, float* out, flo
       }
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
-        const bool real = s0 + c * J < nsplit;  // (a repeated last split weighs nothing)
+        // (a repeated last split counts as an empty one: a weight of 0 alone would turn an infinite sum into NaN)
+        if (s0 + c * J >= nsplit) {
+          pv[c] = __float_as_uint(-INFINITY);
+          ov[c] = u32x4{0u, 0u, 0u, 0u};
+        }
         const float oc[4] = {__uint_as_float(ov[c].x), __uint_as_float(ov[c].y), __uint_as_float(ov[c].z), __uint_as_float(ov[c].w)};
-        add(real ? __uint_as_float(static_cast<uint32_t>(pv[c])) : -INFINITY, __uint_as_float(static_cast<uint32_t>(pv[c] >> 32)), oc);
+        add(__uint_as_float(static_cast<uint32_t>(pv[c])), __uint_as_float(static_cast<uint32_t>(pv[c] >> 32)), oc);
       }
     }
   };

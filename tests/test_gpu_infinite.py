@@ -1,0 +1,81 @@
+"""Infinite and NaN elements of V: a column of the output is infinite (or NaN) where an attended row makes it so and nowhere
+else, whatever the split of the list over workgroups and waves, and whatever lies in the slots past the list's end."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import DEV, assert_attention, gpu_attn, np_of
+from paper_2503_07518_amd import binding as tb
+
+pytestmark = pytest.mark.gpu
+
+INF = float("inf")
+
+
+def say(msg):
+    print(f"[case] {msg}", flush=True)
+
+
+def check(out, lse, ref, ref_lse, dn):
+    got = np_of(out)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)), "NaN elsewhere than in the oracle"
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    fin = np.isfinite(ref)
+    assert 0 < fin.sum() < fin.size
+    assert_attention(np.where(fin, got, 0.0), np.where(fin, ref, 0.0), dn, np_of(lse), ref_lse)
+
+
+def shared_attn(q, K, V, idx, cnt, N, sm, max_count):
+    B, Hq, D = q.shape
+    d = tb.make_desc(N, Hq, K=K, V=V)
+    ws = tb.new_workspace(tb.TB_OP_ATTN, d, max_count)
+    out = torch.full((B, Hq, D), float("nan"), dtype=torch.float32, device=DEV)
+    lse = torch.full((B, Hq), float("nan"), dtype=torch.float32, device=DEV)
+    tb.tb_sparse_decode_attn_shared(d, q, K, V, idx, cnt, max_count, sm, out, lse, ws)
+    return out, lse
+
+
+def tensors(dtype, B, Hq, Hkv, N, D, seed):
+    gen = torch.Generator().manual_seed(seed)
+    K, V = (torch.randn((B, Hkv, N, D), generator=gen).to(dtype) for _ in range(2))
+    return torch.randn((B, Hq, D), generator=gen).to(dtype), K, V, gen
+
+
+@pytest.mark.parametrize("dtype,D,B,Hkv,g,unit,splits,shared", [
+    # a list per head: `unit` rows are two tiles for each of a workgroup's four waves, so that `splits` of them make as
+    # many splits; either side of the numbers that fill the thread groups which add the splits up
+    *[(torch.bfloat16, 128, 1, 8, 1, 128, n, False) for n in (2, 8, 9, 15, 16, 17, 31, 33)],
+    *[(torch.float32, 128, 1, 4, 1, 64, n, False) for n in (7, 10, 21)],
+    *[(torch.bfloat16, 64, 1, 2, 4, 256, n, False) for n in (5, 16, 18)],
+    *[(torch.float32, 64, 1, 2, 2, 128, n, False) for n in (13, 30)],
+    # one list for all heads, a workgroup per KV group: matrix cores (steps of 256 rows), vector form
+    *[(torch.bfloat16, 128, 4, 8, 4, 256, n, True) for n in (4, 5, 7)],
+    *[(torch.bfloat16, 64, 2, 8, 8, 256, n, True) for n in (13, 15)],
+    *[(torch.float32, 128, 4, 8, 2, 64, n, True) for n in (4, 6, 13)],
+    *[(torch.float32, 128, 4, 8, 8, 64, n, True) for n in (3, 9)],
+    *[(torch.bfloat16, 64, 8, 8, 2, 256, n, True) for n in (3, 5)],
+])
+def test_infinite_values_of_every_split(oracle, dtype, D, B, Hkv, g, unit, splits, shared):
+    """Every split attends a row with an infinite element in a column of its own; the list ends with a whole tile."""
+    say(f"infinite values of every split dtype={dtype} D={D} B={B} Hkv={Hkv} g={g} splits={splits} shared={shared}")
+    Hq, rows = g * Hkv, unit * splits
+    N, dn = rows + 40, "f32" if dtype == torch.float32 else "bf16"
+    q, K, V, gen = tensors(dtype, B, Hq, Hkv, N, D, splits + D)
+    idx = torch.stack([torch.randperm(N, generator=gen)[:rows].sort().values for _ in range(B)]).to(torch.int32)
+    cnt = torch.full((B,), rows, dtype=torch.int32)
+    for b in range(B):
+        for j in range(2 * splits):  # (half a unit is the least that one split takes in a row)
+            V[b, :, int(idx[b, j * unit // 2 + j % 8]), j % (D - 4)] = INF if j % 3 else -INF
+        V[b, :, int(idx[b, rows - 1]), D - 1] = INF
+        V[b, :, int(idx[b, rows // 2]), D - 2] = float("nan")
+    sm = 1.0 / math.sqrt(D)
+    if shared:
+        out, lse = shared_attn(q.to(DEV), K.to(DEV), V.to(DEV), idx.to(DEV), cnt.to(DEV), N, sm, rows)
+        ref, ref_lse = oracle.sparse_decode_attn_shared(np_of(q), np_of(K), np_of(V), idx.numpy(), cnt.numpy(), dn, sm)
+    else:
+        lists, counts = idx[:, None].expand(B, Hq, rows).contiguous(), cnt[:, None].expand(B, Hq).contiguous()
+        out, lse = gpu_attn(q.to(DEV), K.to(DEV), V.to(DEV), lists.to(DEV), counts.to(DEV), N, sm)
+        ref, ref_lse = oracle.sparse_decode_attn(np_of(q), np_of(K), np_of(V), lists.numpy(), counts.numpy(), dn, sm)
+    check(out, lse, ref, ref_lse, dn)
