@@ -440,6 +440,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_group_kernel(AttnArgs a) {
     }
     n_next = fetch_rows(t0 + stride);
     __builtin_amdgcn_sched_barrier(0);  // every gather of the tile is in flight before the first is consumed
+    clear_past_end(vraw, valid);
     float sc[GH][kLoadsPerTile];
 #pragma unroll
     for (int t = 0; t < kLoadsPerTile; ++t) {

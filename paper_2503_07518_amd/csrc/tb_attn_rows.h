@@ -16,6 +16,20 @@ constexpr float kLn2 = 0.6931471805599453f;
 
 __device__ inline float exp2_safe(float d) { return __builtin_amdgcn_exp2f(d); }
 
+// A slot past the list's end adds nothing, whatever row it has loaded: its V counts as zeros (a weight of 0 is not enough:
+// 0 times an infinite element is NaN).  Only a wave's last tile has such slots; the others pay a branch (selects in
+// every tile: 32 heads, 3277 of 32768 rows 27.2 -> 27.6 us a step).
+template <typename Raw>
+__device__ __forceinline__ void clear_past_end(Raw (&vraw)[kLoadsPerTile], const bool (&valid)[kLoadsPerTile]) {
+  unsigned long long past = 0;
+#pragma unroll
+  for (int t = 0; t < kLoadsPerTile; ++t) past |= ballot64(!valid[t]);
+  if (past == 0) return;
+#pragma unroll
+  for (int t = 0; t < kLoadsPerTile; ++t)
+    if (!valid[t]) vraw[t].x = vraw[t].y = vraw[t].z = vraw[t].w = 0;
+}
+
 // The online softmax of a wave whose lane groups take one row each (lane: EPL elements of it), in the base-2 domain.
 template <typename T, int D>
 struct RowSoftmax {
@@ -35,7 +49,7 @@ struct RowSoftmax {
   }
 
   // kLoadsPerTile rows of every lane group
-  __device__ __forceinline__ void consume(const typename Pack16<T>::Raw (&kraw)[kLoadsPerTile], const typename Pack16<T>::Raw (&vraw)[kLoadsPerTile],
+  __device__ __forceinline__ void consume(const typename Pack16<T>::Raw (&kraw)[kLoadsPerTile], typename Pack16<T>::Raw (&vraw)[kLoadsPerTile],
                                           const bool (&valid)[kLoadsPerTile]) {
     float sc[kLoadsPerTile];
     float tmax = -INFINITY;
@@ -50,6 +64,7 @@ struct RowSoftmax {
       sc[t] = valid[t] ? s : -INFINITY;
       tmax = fmaxf(tmax, sc[t]);
     }
+    clear_past_end(vraw, valid);
     const float m_new = fmaxf(m, tmax);
     if (m_new > -INFINITY) {
       const float alpha = exp2_safe(m - m_new);  // m = -inf -> 0
