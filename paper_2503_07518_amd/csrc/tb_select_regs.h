@@ -58,10 +58,10 @@ __device__ inline uint32_t wave_entries_scan(const uint32_t* s_w, uint32_t& tota
 
 // A wave-uniform bound as a value of its own, so that a second pass over the scores compares again: the masks of the
 // first pass would otherwise be kept for it, two scalar registers per score, most of them spilled.
-__device__ inline float compared_anew(float bound) {
-  uint32_t b = __builtin_amdgcn_readfirstlane(__float_as_uint(bound));
+__device__ inline uint32_t compared_anew(uint32_t bound) {
+  uint32_t b = __builtin_amdgcn_readfirstlane(bound);
   asm volatile("" : "+s"(b));
-  return __uint_as_float(b);
+  return b;
 }
 
 // A count of lane masks, added up at this point (left alone, the compiler keeps the masks of a whole pass and counts at
@@ -270,13 +270,16 @@ __device__ inline void next_level(Level& v) {
 // One compute unit per row, so what counts is the instructions per score and what a phase waits for:
 //  * the sample is loaded first, and its histogram and walk run while the row itself is on its way;
 //  * where the bracket lies above zero (a budget below about half of the candidates) no keys are made: the scores' own
-//    bits are ordered there; what is no candidate is a NaN that no compare holds for;
+//    bits are ordered there; what is no candidate is a NaN that no compare holds for.  A threshold below that, or a cut
+//    through equal scores, turns the scores into keys once, in their registers (made again in every pass: 32 rows of 32768,
+//    half of the scores kept 18.9 us, now 16.5; 65536 negative scores, a tenth kept 20.8 and 17.7);
 //  * histogram adds of scores outside the bracket go to a spare word of the lane instead of being branched around (the
 //    exec-mask bookkeeping of a branch per score cost more than the adds: 10.4 -> 9.6 us on a row of 32768);
 //  * the output is one pass: a compare per score, the lane masks (scalar registers) give every kept score its place in
 //    the wave's LDS region, and after the one barrier that tells the waves where their parts begin the region is copied out 64
-//    entries a store (counting first and storing from the registers, 32 stores of a few lanes each: 10.6 -> 10.0);
-//  * nothing derived from a score is kept in registers for a later pass (lane_pos, compared_anew, settle): 59 registers
+//    entries a store (counting first and storing from the registers, 32 stores of a few lanes each: 10.6 -> 10.0).  A
+//    wave that keeps more than its region holds counts first after all, and so do all where the budget says so;
+//  * nothing derived from a score is kept in registers for a later pass (lane_pos, compared_anew, settle): 58 registers
 //    for 8 tiles, so that two workgroups share a compute unit, and none is spilled.
 // Selection alone, 32 rows, a tenth kept, us before and now: 1024 scores 6.4 and 4.2, 4096 5.3 and 4.9, 16384 7.7 and 6.9, 32768
 // 11.2 and 9.4, 65536 19.8 and 14.8; 512 rows of 16384 14.6 and 12.4, of 32768 27.4 and 19.3.  (1000 vector instructions a
@@ -394,12 +397,7 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
     if constexpr (kStageB) return cidx[kStageB ? j : 0][c] >= 0;
     return static_cast<uint32_t>(p + j * kWaveTile + c) < static_cast<uint32_t>(hi - lo);
   };
-  // (the same for the keys of the scores: `zero` is +0)
-  auto fresh_zero = []() -> float {
-    float z = 0.f;
-    asm volatile("" : "+v"(z));
-    return z;
-  };
+  const bool inside = wspan >= lo && wspan + NT * kWaveTile <= hi;  // every score of the wave is a candidate (not in stage B)
   if constexpr (kStageB) init_lds();
   auto for_each_tile = [&](auto&& body) {
 #pragma unroll
@@ -407,10 +405,38 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
       if (!kStageB || j < tpw) body(j, s4[j]);
   };
 
-  // The kept scores: all that are at least T (ties: scores equal to T are cut), or every candidate (all).
-  uint32_t T_key = 0;  // key of T
-  uint32_t r_eq = 0;   // with ties: how many scores equal to T are kept (lowest indices first)
-  bool all = true;
+  // The kept scores: all whose key is at least T_key (ties: of those equal to it the first r_eq), from 1 up every candidate.
+  uint32_t T_key = 1;
+  uint32_t r_eq = 0;
+  Level v{};
+  bool found = false, whole = false;  // whole: every score from lo_key up is kept, none is cut
+  int call = 1;
+  bool dense = true;
+  auto targets = [&](uint32_t c_above, uint32_t& na, uint32_t& nb) {
+    na = (c_above < v.need) ? v.need - c_above : 0u;
+    nb = 0u;
+  };
+  // A handful of scores share the chosen sub-bin (the usual case after the bracketed level: its
+  // sub-bins are a few thousand key values wide): instead of another histogram level,
+  // they have been gathered, one lane each (x: something that is ordered like them), and are ranked against each
+  // other in every wave.  Returns the threshold's x and reduces v.need to how many equal to it are needed.
+  auto rank_tiny = [&](uint32_t count, bool& whole) -> uint32_t {
+    __syncthreads();
+    const int n_tiny = static_cast<int>(count);
+    const uint32_t mine = lane < n_tiny ? sl.tiny[lane] : 0u;
+    uint32_t greater = 0, equal = 0;
+    for (int j = 0; j < n_tiny; ++j) {
+      const uint32_t other = __builtin_amdgcn_readlane(mine, j);
+      greater += other > mine ? 1u : 0u;
+      equal += other == mine ? 1u : 0u;
+    }
+    // the one whose ranks (greater, greater + equal] contain `need` is the threshold
+    const unsigned long long hit = ballot64(lane < n_tiny && greater < v.need && v.need <= greater + equal);
+    const int L = __ffsll(hit) - 1;  // (several lanes when the threshold value repeats: they agree)
+    v.need -= static_cast<uint32_t>(__builtin_amdgcn_readlane(greater, L));
+    whole = v.need == static_cast<uint32_t>(__builtin_amdgcn_readlane(equal, L));
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(mine, L));
+  };
   if (refine) {
     uint32_t b_lo, b_hi;
     if constexpr (kStageB) {
@@ -424,7 +450,7 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
     }
     __builtin_amdgcn_sched_barrier(0);  // (the row's scores are waited for from here on)
     if constexpr (!kStageB) {
-      if (!(wspan >= lo && wspan + NT * kWaveTile <= hi)) {  // (scalar)
+      if (!inside) {  // (scalar)
         const int p = lane_pos();
 #pragma unroll
         for (int j = 0; j < NT; ++j)
@@ -432,35 +458,7 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
           for (int c = 0; c < 4; ++c) s4[j][c] = candidate(p, j, c) ? s4[j][c] : __uint_as_float(kNoScore);
       }
     }
-    Level v = bracketed_level(b_lo, b_hi, kk);
-    auto targets = [&](uint32_t c_above, uint32_t& na, uint32_t& nb) {
-      na = (c_above < v.need) ? v.need - c_above : 0u;
-      nb = 0u;
-    };
-    // A handful of scores share the chosen sub-bin (the usual case after the bracketed level: its
-    // sub-bins are a few thousand key values wide): instead of another histogram level,
-    // they have been gathered, one lane each (x: something that is ordered like them), and are ranked against each
-    // other in every wave.  Returns the threshold's x and reduces v.need to how many equal to it are needed.
-    auto rank_tiny = [&](uint32_t count, bool& whole) -> uint32_t {
-      __syncthreads();
-      const int n_tiny = static_cast<int>(count);
-      const uint32_t mine = lane < n_tiny ? sl.tiny[lane] : 0u;
-      uint32_t greater = 0, equal = 0;
-      for (int j = 0; j < n_tiny; ++j) {
-        const uint32_t other = __builtin_amdgcn_readlane(mine, j);
-        greater += other > mine ? 1u : 0u;
-        equal += other == mine ? 1u : 0u;
-      }
-      // the one whose ranks (greater, greater + equal] contain `need` is the threshold
-      const unsigned long long hit = ballot64(lane < n_tiny && greater < v.need && v.need <= greater + equal);
-      const int L = __ffsll(hit) - 1;  // (several lanes when the threshold value repeats: they agree)
-      v.need -= static_cast<uint32_t>(__builtin_amdgcn_readlane(greater, L));
-      whole = v.need == static_cast<uint32_t>(__builtin_amdgcn_readlane(equal, L));
-      return static_cast<uint32_t>(__builtin_amdgcn_readlane(mine, L));
-    };
-    bool found = false, whole = false;  // whole: every score from lo_key up is kept, none is cut
-    int call = 1;
-    bool dense = true;
+    v = bracketed_level(b_lo, b_hi, kk);
     constexpr uint32_t kSign = 0x80000000u, kPastInf = 0x7F800001u;
     if (v.lo_key > kSign) {
       // The bracket lies above zero (a budget below about half of the candidates): the bits of the scores
@@ -515,11 +513,33 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
         widen_level(v);
       }
     }
-    if (!found) {
-      // the general form, over keys (0: not a candidate; no real score has a key below 0x007FFFFF)
-      auto key4 = [&](int p, float zero, int j, const float(&f4)[4], uint32_t(&k4)[4]) {
+  }
+  // Unless the threshold is known and a positive score that cuts no ties, what follows is over keys (0: not a candidate; no
+  // real score has a key below 0x007FFFFF), which take the scores' registers.
+  const bool keyed = __builtin_amdgcn_readfirstlane(!(found && whole)) != 0;
+  if (keyed) {
+    const int p = lane_pos();
+    // (one score after the other, in place: left alone, the compiler keeps scores beside their keys, and spills)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) k4[c] = candidate(p, j, c) ? score_key(f4[c] + zero) : 0u;
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        asm volatile("" : "+v"(s4[j][c]));
+        s4[j][c] = __uint_as_float(!kStageB || candidate(p, j, c) ? score_key(s4[j][c]) : 0u);
+        asm volatile("" : "+v"(s4[j][c]));
+      }
+    if (!kStageB && !inside) {  // (scalar)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s4[j][c] = candidate(p, j, c) ? s4[j][c] : 0.f;
+    }
+  }
+  if (refine) {
+    if (!found) {
+      auto key4 = [](const float(&f4)[4], uint32_t(&k4)[4]) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) k4[c] = __float_as_uint(f4[c]);
       };
 #pragma nounroll
       for (; call <= kMaxLevels; ++call) {
@@ -530,14 +550,12 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
           __syncthreads();
         }
         uint32_t n_above = 0;
-        const int p = lane_pos();
-        const float zero = fresh_zero();
         if (dense) {
           // a sizeable share of the keys falls into the range: test every key on its own.
           // (key > above_key implies key - lo_key >= span, so the two cases are disjoint.)
-          for_each_tile([&](int j, const float(&f4)[4]) {
+          for_each_tile([&](int, const float(&f4)[4]) {
             uint32_t k4[4];
-            key4(p, zero, j, f4, k4);
+            key4(f4, k4);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
               const uint32_t d = k4[c] - v.lo_key;  // wraps to a large value for keys below lo_key
@@ -548,9 +566,9 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
           });
         } else {
           // only the keys of one sub-bin take part: skip wave-uniformly
-          for_each_tile([&](int j, const float(&f4)[4]) {
+          for_each_tile([&](int, const float(&f4)[4]) {
             uint32_t k4[4];
-            key4(p, zero, j, f4, k4);
+            key4(f4, k4);
             const uint32_t d0 = k4[0] - v.lo_key, d1 = k4[1] - v.lo_key, d2 = k4[2] - v.lo_key, d3 = k4[3] - v.lo_key;
             const uint32_t dmin = min(min(d0, d1), min(d2, d3));
             if (ballot64(dmin < v.span) != 0ull) {
@@ -572,11 +590,9 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
           if (v.shift == 0) break;
           if (f.count_a <= static_cast<uint32_t>(kWave)) {
             const uint32_t sub = 1u << v.shift;
-            const int p = lane_pos();
-            const float zero = fresh_zero();
-            for_each_tile([&](int j, const float(&f4)[4]) {
+            for_each_tile([&](int, const float(&f4)[4]) {
               uint32_t k4[4];
-              key4(p, zero, j, f4, k4);
+              key4(f4, k4);
 #pragma unroll
               for (int c = 0; c < 4; ++c) {
                 const uint32_t d = k4[c] - v.lo_key;
@@ -596,31 +612,23 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
     }
     T_key = v.lo_key;
     r_eq = whole ? 0u : v.need;
-    all = whole && T_key <= kKeyOfMinusInf;
   }
 
   auto value = [&](int p, int j, int c) -> int32_t {  // what the list holds for score c of tile j (p: lane_pos() + lo)
     return kStageB ? cidx[kStageB ? j : 0][c] : p + j * kWaveTile + c;
   };
-  if (r_eq == 0u) {
-    // ---- ordered output, no score equal to T to cut (the usual case)
-    float T = score_of_key(T_key);
-    if (all) {  // every candidate, NaN included
-      T = 0.f;
-      const int p = lane_pos();
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) s4[j][c] = candidate(p, j, c) ? 0.f : __uint_as_float(kNoScore);
-    }
+  // ---- ordered output, no score equal to T to cut (the usual case).  bound: the bits of T, or T_key; kept(f, bound): the test.
+  // Where the budget alone is more than the regions hold, the first pass only counts.
+  const uint32_t room = kk > W * CAP ? 0u : static_cast<uint32_t>(CAP);
+  auto emit = [&](const uint32_t bound, auto&& kept) {
     uint32_t* const part = region + wave * CAP;
     const int p = lane_pos() + lo;
     uint32_t run = 0;  // kept scores of the wave so far (the same in every lane)
     for_each_tile([&](int j, const float(&f4)[4]) {
-      const bool t0 = f4[0] >= T, t1 = f4[1] >= T, t2 = f4[2] >= T, t3 = f4[3] >= T;
+      const bool t0 = kept(f4[0], bound), t1 = kept(f4[1], bound), t2 = kept(f4[2], bound), t3 = kept(f4[3], bound);
       const unsigned long long m0 = ballot64(t0), m1 = ballot64(t1), m2 = ballot64(t2), m3 = ballot64(t3);
       const uint32_t tot = popc64(m0) + popc64(m1) + popc64(m2) + popc64(m3);
-      if (run + tot <= static_cast<uint32_t>(CAP)) {
+      if (run + tot <= room) {
         uint32_t* w = part + run + mbcnt64(m3, mbcnt64(m2, mbcnt64(m1, mbcnt64(m0, 0u))));  // after the entries of lower lanes and earlier tiles
         if (t0) *w++ = static_cast<uint32_t>(value(p, j, 0));
         if (t1) *w++ = static_cast<uint32_t>(value(p, j, 1));
@@ -634,37 +642,46 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
     __syncthreads();
     uint32_t total;
     uint32_t at = wave_entries_scan<W>(sl.wgt, total);  // kept scores of the waves before
-    if (run <= static_cast<uint32_t>(CAP)) {
+    if (run <= room) {
       if (at + run <= static_cast<uint32_t>(kk))  // (always, when the counts add up)
         for (uint32_t e = lane; e < run; e += kWave) put(a.lo + at + e, static_cast<int32_t>(part[e]));
     } else {
       // more than the wave's region holds (large scores crowded into its span): from the registers
-      const float T2 = compared_anew(T);
+      const uint32_t again = compared_anew(bound);
       const int p = lane_pos() + lo;
       for_each_tile([&](int j, const float(&f4)[4]) {
-        const unsigned long long m0 = ballot64(f4[0] >= T2), m1 = ballot64(f4[1] >= T2), m2 = ballot64(f4[2] >= T2), m3 = ballot64(f4[3] >= T2);
-        uint32_t o = mbcnt64(m3, mbcnt64(m2, mbcnt64(m1, mbcnt64(m0, at))));
+        bool t[4];
+        unsigned long long m[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-          if (f4[c] >= T2) {
+          t[c] = kept(f4[c], again);
+          m[c] = ballot64(t[c]);
+        }
+        uint32_t o = mbcnt64(m[3], mbcnt64(m[2], mbcnt64(m[1], mbcnt64(m[0], at))));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          if (t[c]) {
             if (o < static_cast<uint32_t>(kk)) put(a.lo + o, value(p, j, c));
             ++o;
           }
         }
-        at += popc64(m0) + popc64(m1) + popc64(m2) + popc64(m3);
+        at += popc64(m[0]) + popc64(m[1]) + popc64(m[2]) + popc64(m[3]);
       });
     }
+  };
+  if (r_eq == 0u) {
+    if (keyed)  // (scalar)
+      emit(T_key, [](float f, uint32_t bound) { return __float_as_uint(f) >= bound; });
+    else
+      emit(__float_as_uint(score_of_key(T_key)), [](float f, uint32_t bound) { return f >= __uint_as_float(bound); });
   } else {
     // ---- ordered output with ties at the threshold: {key > T} and the first r_eq of {key == T}.
     // Pass A: the wave's totals of both.
-    auto key = [&](int p, float zero, int j, int c) { return candidate(p, j, c) ? score_key(s4[j][c] + zero) : 0u; };
-    const int p_a = lane_pos();
-    const float zero_a = fresh_zero();
     uint32_t run_gt = 0, run_eq = 0;
-    for_each_tile([&](int j, const float(&)[4]) {
+    for_each_tile([&](int, const float(&f4)[4]) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        const uint32_t k = key(p_a, zero_a, j, c);
+        const uint32_t k = __float_as_uint(f4[c]);
         run_gt += popc64(ballot64(k > T_key));
         run_eq += popc64(ballot64(k == T_key));
       }
@@ -680,14 +697,13 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
     uint32_t base_gt = wave_entries_scan<W>(sl.wgt, unused);
     uint32_t base_eq = wave_entries_scan<W>(sl.weq, unused);
     // Pass B: position of a kept score = (#greater before it) + min(#equal before it, r_eq)
-    const uint32_t T2 = __float_as_uint(compared_anew(__uint_as_float(T_key)));
-    const int p_b = lane_pos(), p = p_b + lo;
-    const float zero_b = fresh_zero();
-    for_each_tile([&](int j, const float(&)[4]) {
+    const uint32_t T2 = compared_anew(T_key);
+    const int p = lane_pos() + lo;
+    for_each_tile([&](int j, const float(&f4)[4]) {
       uint32_t gt = base_gt, eq = base_eq, k4[4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        k4[c] = key(p_b, zero_b, j, c);
+        k4[c] = __float_as_uint(f4[c]);
         const unsigned long long mg = ballot64(k4[c] > T2), me = ballot64(k4[c] == T2);
         gt = mbcnt64(mg, gt);
         eq = mbcnt64(me, eq);
