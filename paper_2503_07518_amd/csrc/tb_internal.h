@@ -97,6 +97,7 @@ struct FilterOut {
   int32_t pieces;
   int64_t piece_len, cap;
   int32_t lo, hi;
+  int32_t turn;  // pieces by which a KV group begins later than the one before (over all groups at most `pieces`)
 };
 tb_status launch_score_filter(const ScoreLaunch& S, const FilterOut& f, hipStream_t st);
 

@@ -868,7 +868,7 @@ tb_status launch_score_select(const ScoreLaunch& S, const SelectLaunch& L, const
   const SelectArgs a = select_args(L, &plan);
   tb_status rc = S.desc->dtype == TB_F32 ? launch_score_bracket<float>(S, a, plan, st) : launch_score_bracket<bf16_t>(S, a, plan, st);
   if (rc != TB_OK) return rc;
-  rc = launch_score_filter(S, FilterOut{a.cand, a.piece_hdr, plan.pieces, plan.piece_len, plan.cap, L.lo, L.hi}, st);
+  rc = launch_score_filter(S, FilterOut{a.cand, a.piece_hdr, plan.pieces, plan.piece_len, plan.cap, L.lo, L.hi, plan.pieces / (S.desc->B * S.desc->Hkv)}, st);
   if (rc != TB_OK) return rc;
   return launch_stage_b(a, plan, st);
 }
