@@ -185,7 +185,12 @@ tb_status tb_buffered_decode_attn(const tb_cache_desc* desc, const void* q, cons
 /* One prediction step in a single enqueue: tb_score -> tb_select_topk -> tb_sparse_decode_attn
  * with one validation pass and one launch plan.  Results (scores, idx, count, out, lse) are
  * identical to calling the three entry points one after the other.
- * ws: tb_workspace_bytes(TB_OP_DECODE_STEP, ...). */
+ * ws: tb_workspace_bytes(TB_OP_DECODE_STEP, ...).  For N > 65536, projected rows of at most
+ * min(64, 32 Hq / Hkv) bytes and a budget of at most an eighth of the candidates this is about
+ * 8 B Hq N bytes whatever the budget (the scoring kernel keeps candidates in lists with room for
+ * whole pieces of a row): 547 MB for B*Hq = 512, N = 131072.  With less, down to what
+ * TB_OP_SELECT and TB_OP_ATTN ask for (there: 220 MB with a budget of 1311) or TB_OP_ATTN alone,
+ * the call takes the same arguments and gives the same results by a slower route. */
 tb_status tb_decode_step(const tb_cache_desc* desc, const void* q_imp, const void* Kimp, float score_scale,
                          const void* q, const void* K, const void* V, int32_t k, int32_t sink, int32_t window,
                          float sm_scale, float* scores, int64_t score_stride, int32_t* idx, int32_t* count,
@@ -217,7 +222,8 @@ tb_status tb_predict_queries(const tb_predictor_desc* p, int32_t B, const void* 
  * length the selection policy produces, lo + kk + N - hi (TB_OP_SELECT returns 0 for every
  * shape whose rows are selected by one workgroup each).  Returns 0 on invalid
  * input.  A workspace of the TB_OP_DECODE_STEP size serves all three operations on that
- * shape.  The workspace pointer must be 16-byte aligned. */
+ * shape, and a workspace of any of the sizes serves fewer rows and shorter lists as well: make it
+ * for a cache's capacity.  The workspace pointer must be 16-byte aligned. */
 size_t tb_workspace_bytes(int32_t op, const tb_cache_desc* desc, int64_t max_count);
 
 /* A workspace must be zero-filled once before its first use (this call enqueues that fill;

@@ -115,10 +115,10 @@ SelectPlan select_plan(int64_t units, int64_t candidates, int64_t N, int64_t kk)
   while (units * ((N + len_of() - 1) / len_of()) < 256 && (tiles > 2 || waves > 4)) {
     if (tiles > 2) tiles /= 2; else waves /= 2;
   }
-  while ((N + len_of() - 1) / len_of() > 256 && tiles < 16) tiles *= 2;  // the table of stage B has 256 entries
+  while ((N + len_of() - 1) / len_of() > kMaxPieces && tiles < 16) tiles *= 2;
   const int64_t len = len_of();
   const int64_t pieces = (N + len - 1) / len;
-  if (pieces < 2 || pieces > 256) return p;
+  if (pieces < 2 || pieces > kMaxPieces) return p;
   p.pieces = static_cast<int>(pieces);
   p.piece_len = len;
   p.piece_waves = waves;
@@ -151,13 +151,30 @@ SelectPlan score_select_plan(const tb_cache_desc* d, int64_t candidates, int64_t
     return p;
   }
   int64_t blocks = (groups * N + 256 * kScoreFilterWgs - 1) / (256 * kScoreFilterWgs);  // per piece
-  const int64_t fewest = (N + 256 * 256 - 1) / (256 * 256);  // (the table of the second stage has 256 entries)
+  const int64_t fewest = (N + 256 * kMaxPieces - 1) / (256 * kMaxPieces);  // (the table of the second stage)
   if (blocks < fewest) blocks = fewest;
   p.piece_len = blocks * 256;
   p.pieces = static_cast<int>((N + p.piece_len - 1) / p.piece_len);
   p.cap = p.piece_len;
   choose_sample(p, candidates, kk, kScoredSample, kScoredSampleLarge);
   return p;
+}
+
+// Scratch for every row of up to N scores and every budget of up to max_count, so that a workspace made for a cache's capacity
+// serves it while it fills: fewer rows can be cut into more pieces, or round up to more.  A plan holds between two
+// multiples of 2048 rows, of which every piece length is one; with the first stage inside the scoring kernel the pieces together
+// are less than a piece longer than the row, and a piece is no longer for fewer rows.
+static size_t select_scratch_upto(int64_t units, int64_t N, int64_t max_count) {
+  size_t most = 0;
+  for (int64_t n = std::min(N, kSelectMaxN); n > 65536; n = (n - 1) / 2048 * 2048)
+    most = std::max(most, select_scratch_bytes(units, select_plan(units, n, n, std::min(max_count, n / 8))));
+  return most;
+}
+static size_t score_select_scratch_upto(const tb_cache_desc* d, int64_t max_count) {
+  tb_cache_desc longest = *d;
+  longest.N = std::min(d->N, kSelectMaxN);
+  const SelectPlan p = score_select_plan(&longest, longest.N, std::min(max_count, longest.N / 8));
+  return p.pieces > 1 ? static_cast<size_t>(d->B) * d->Hq * ((longest.N + p.piece_len) * 8 + kMaxPieces * 16) : 0;
 }
 
 // One launch for a whole step, a workgroup per head, against three: no more heads than compute units, a row that a workgroup
@@ -581,9 +598,7 @@ size_t tb_workspace_bytes(int32_t op, const tb_cache_desc* d, int64_t max_count)
   if (check_desc(d) != TB_OK || max_count < 0) return 0;
   const int64_t units = static_cast<int64_t>(d->B) * d->Hq;
   // two-stage selection of long rows (none for most shapes): max_count bounds the budget
-  // (sized for the largest budget that still takes the two-stage path on this row length)
-  int64_t kk_bound = max_count < d->N / 8 ? max_count : d->N / 8;
-  const size_t sel = select_scratch_bytes(units, select_plan(units, d->N, d->N, kk_bound));
+  const size_t sel = select_scratch_upto(units, d->N, max_count);
   const size_t sel_total = sel ? ws_layout(units, d->D, 1).part_off + align_up(sel, 256) : 0;
   if (op == TB_OP_SELECT) return sel_total;
   if (op == TB_OP_ATTN || op == TB_OP_DECODE_STEP) {
@@ -597,7 +612,7 @@ size_t tb_workspace_bytes(int32_t op, const tb_cache_desc* d, int64_t max_count)
       if (g_att > att) att = g_att;
     }
     if (op == TB_OP_ATTN) return att;
-    const size_t both = select_scratch_bytes(units, score_select_plan(d, d->N, kk_bound));
+    const size_t both = score_select_scratch_upto(d, max_count);
     const size_t step = both ? ws_layout(units, d->D, 1).part_off + align_up(both, 256) : 0;
     return std::max(std::max(step, sel_total), att);
   }

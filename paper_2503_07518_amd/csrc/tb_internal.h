@@ -63,6 +63,7 @@ struct SelectPlan {
   int piece_tiles;    // 256-key tiles that each of them keeps in registers: 2, 4, 8 or 16
   bool row_sample;    // a kernel before stage A samples the row, once; otherwise every piece does
 };
+constexpr int kMaxPieces = 256;   // pieces of a row: entries of the second stage's table
 constexpr int kRowSample = 8192;  // scores of a row that the kernel before stage A looks at
 SelectPlan select_plan(int64_t units, int64_t candidates, int64_t N, int64_t kk);
 // The plan of a selection whose first stage is part of the scoring kernel: pieces of whole 256-row blocks with

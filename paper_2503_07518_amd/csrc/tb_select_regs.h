@@ -11,7 +11,6 @@ namespace {
 constexpr int kWaveTile = kWave * 4;  // scores per wave tile: one float4 per lane
 constexpr int kHistBins = 4096;       // LDS histogram size (12 bits per level)
 constexpr int kTopShift = 20;         // key >> 20 = top 12 bits
-constexpr int kMaxPieces = 256;       // pieces of a row (the table of the second stage)
 
 struct SelectArgs {
   const float* scores;

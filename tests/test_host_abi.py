@@ -75,6 +75,16 @@ def test_workspace_sizes(tb):
     assert tb.tb_workspace_bytes(tb.TB_OP_SELECT, long_row, 0) == 0
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,Dimp,k", [(14, 32, 8, 32, 2000), (1, 32, 8, 32, 2000), (1, 8, 8, 32, 1000), (3, 24, 3, 16, 5000), (16, 64, 8, 64, 8192),
+                                               (5, 1, 1, 32, 30000)])
+def test_workspace_of_a_capacity_serves_fewer_rows(tb, B, Hq, Hkv, Dimp, k):
+    """A workspace made for a cache's capacity is enough for every number of rows on the way there."""
+    rows = sorted({*range(1024, 1 << 20, 9973), *range(65535, 90000, 61), 74877, 74941, 1 << 17, (1 << 17) + 1, 1 << 20})
+    for op in (tb.TB_OP_SELECT, tb.TB_OP_ATTN, tb.TB_OP_DECODE_STEP):
+        sizes = [tb.tb_workspace_bytes(op, desc(tb, B=B, Hq=Hq, Hkv=Hkv, Dimp=Dimp, N=n), k) for n in rows]
+        assert sizes == sorted(sizes), (op, next((rows[i], sizes[i], rows[i + 1], sizes[i + 1]) for i in range(len(sizes) - 1) if sizes[i] > sizes[i + 1]))
+
+
 def test_rejects_bad_arguments_without_launching(tb):
     L = tb.load_library()
     d = desc(tb)
