@@ -107,11 +107,17 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# the current stream's handle without a Stream object around it, which cost 3 us a call: more than the rest of one (torch
+# does not promise this function: without it the object serves)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None) -> int:
-    # (the current stream's handle without a Stream object around it, which cost 3 us a call: more than the rest of one)
-    if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dtype_code(dtype: torch.dtype) -> int:

@@ -161,3 +161,17 @@ def test_missing_library_is_an_error(tb, monkeypatch, tmp_path):
     monkeypatch.setattr(tb, "LIB_PATH", str(tmp_path / "libtokenbutler.so"))
     with pytest.raises(ImportError):
         tb.tb_version()
+
+
+def test_current_stream_without_the_raw_handle(tb, monkeypatch):
+    """A torch that lacks the function that gives a stream's bare handle still gives the stream."""
+    import torch
+
+    class Stream:
+        cuda_stream = 77
+    monkeypatch.setattr(tb, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    assert tb._stream() == 77 and tb._stream(Stream) == 77
+    monkeypatch.setattr(tb, "_raw_stream", lambda device: 1000 + device)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    assert tb._stream() == 1003 and tb._stream(Stream) == 77
