@@ -363,7 +363,7 @@ tb_status launch_tdg(const ScoreLaunch& L, const FilterOut* f, hipStream_t st) {
   const ScoreArgs a = score_args(L);
   if (d.N == 0) return TB_OK;
   if (f) {
-    if constexpr (DIMP * sizeof(T) <= 64) {  // (score_select_plan's rule)
+    if constexpr (DIMP * sizeof(T) <= 64 && DIMP * sizeof(T) <= 32 * G) {  // (score_select_plan's rule)
       hipLaunchKernelGGL((score_filter_kernel<T, DIMP, G>), dim3(f->pieces, d.Hkv, d.B), dim3(kScoreThreads), 0, st, a, *f);
       return hip_status(hipGetLastError());
     }

@@ -618,6 +618,7 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
   };
   // ---- ordered output, no score equal to T to cut (the usual case).  bound: the bits of T, or T_key; kept(f, bound): the test.
   // Where the budget alone is more than the regions hold, the first pass only counts.
+  constexpr bool kFits = NT * kWaveTile <= CAP;  // a wave's region holds all of its scores
   const uint32_t room = kk > W * CAP ? 0u : static_cast<uint32_t>(CAP);
   auto emit = [&](const uint32_t bound, auto&& kept) {
     uint32_t* const part = region + wave * CAP;
@@ -627,7 +628,7 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
       const bool t0 = kept(f4[0], bound), t1 = kept(f4[1], bound), t2 = kept(f4[2], bound), t3 = kept(f4[3], bound);
       const unsigned long long m0 = ballot64(t0), m1 = ballot64(t1), m2 = ballot64(t2), m3 = ballot64(t3);
       const uint32_t tot = popc64(m0) + popc64(m1) + popc64(m2) + popc64(m3);
-      if (run + tot <= room) {
+      if (kFits || run + tot <= room) {
         uint32_t* w = part + run + mbcnt64(m3, mbcnt64(m2, mbcnt64(m1, mbcnt64(m0, 0u))));  // after the entries of lower lanes and earlier tiles
         if (t0) *w++ = static_cast<uint32_t>(value(p, j, 0));
         if (t1) *w++ = static_cast<uint32_t>(value(p, j, 1));
@@ -641,7 +642,7 @@ __device__ __forceinline__ void select_regs(const SelectArgs& a, const int u, co
     __syncthreads();
     uint32_t total;
     uint32_t at = wave_entries_scan<W>(sl.wgt, total);  // kept scores of the waves before
-    if (run <= room) {
+    if (kFits || run <= room) {
       if (at + run <= static_cast<uint32_t>(kk))  // (always, when the counts add up)
         for (uint32_t e = lane; e < run; e += kWave) put(a.lo + at + e, static_cast<int32_t>(part[e]));
     } else {

@@ -17,6 +17,9 @@ namespace {
 
 constexpr int kStepWaves = 16;
 constexpr int kStepThreads = kStepWaves * kWave;
+static_assert(kStepMaxN == 4 * kStepThreads, "a thread stores four scores of the longest row");
+static_assert(kStepMaxN <= kStepWaves * kWaveTile, "the selection holds the longest row in one tile a wave");
+static_assert(kStepMaxSplits * kAttnWaves <= kStepWaves, "every split of the attention has its waves");
 
 struct StepArgs {
   SelectArgs sel;
@@ -73,6 +76,7 @@ __global__ __launch_bounds__(kStepThreads, 4) void step_kernel(StepArgs a) {
     constexpr int LPR = DIMP / EPL;           // lanes per projected row
     constexpr int RPP = kStepThreads / LPR;   // rows per pass of the workgroup
     constexpr int BATCH = 8;                  // passes whose loads are in flight together
+    static_assert(kStepMaxN % RPP == 0 && (!kMfma || RPP == 16 * kStepWaves), "whole passes stay within the scores' LDS");
     const int i16 = lane & 15, kb = lane >> 4;
     const int part = kMfma ? kb : tid % LPR;
     const int rsub = kMfma ? wave * 16 + i16 : tid / LPR;
