@@ -50,6 +50,7 @@ def _step(cfg, b):
 
 @pytest.mark.parametrize("name,kw", [
     ("split attention, one selection workgroup per row", dict(B=1, N=8192, k=800)),
+    ("a short step in one launch", dict(B=1, N=1024, k=100, heavy_per_kv_head=10)),
     ("selection by pieces (workspace scratch in the graph)", dict(B=2, N=70001, k=4096, heavy_per_kv_head=64)),
 ])
 def test_decode_step_graph_replays_match_eager(name, kw):

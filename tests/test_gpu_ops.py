@@ -242,13 +242,13 @@ def test_select_streamed_rows(oracle, N, ks):
     check_select(oracle, low, N, ks[0], 0, 0)
 
 
-def sample_positions(N, lo=0, hi=None):
+def sample_positions(N, lo=0, hi=None, places=1024):
     """Positions that the first stage of a selection by pieces may sample: four adjacent scores at
     each of up to 1024 places spread evenly over the candidates (a workgroup of T threads looks at
-    the places t * span / T, T = 256, 512 or 1024: all on this grid)."""
+    the places t * span / T, T = 256, 512 or 1024: all on this grid; the larger samples look at 2048)."""
     hi = N if hi is None else hi
     span = hi - lo
-    start = torch.tensor([(lo + (t * span) // 1024) & ~3 for t in range(1024)])
+    start = torch.tensor([(lo + (t * span) // places) & ~3 for t in range(places)])
     pos = (start[:, None] + torch.arange(4)[None, :]).reshape(-1)
     return torch.unique(pos[pos < N])
 
@@ -693,6 +693,68 @@ def test_decode_step_short_rows(oracle, dtype, g, Hkv, B, D, Dimp, N, k, sink, w
         assert np.array_equal(np_of(s)[:, :, :N].view(np.uint32), np_of(s2)[:, :, :N].view(np.uint32)), name
         assert np.array_equal(np_of(cnt), rcnt) and np.array_equal(np_of(idx)[..., :need], ridx[..., :need]), name
         assert torch.equal(cnt, cnt2) and torch.equal(idx, idx2), name
+        assert torch.equal(out, out2) and torch.equal(lse, lse2), name
+
+
+@pytest.mark.parametrize("dtype,g,Hkv,D,Dimp,N,k,sink,window", [
+    (torch.bfloat16, 4, 1, 64, 16, 4096, 1200, 0, 0),   # the longest row, all four splits
+    (torch.bfloat16, 2, 2, 64, 32, 3001, 1100, 3, 21),
+    (torch.float32, 1, 2, 64, 16, 2051, 650, 0, 0),
+    (torch.float32, 2, 1, 64, 16, 2600, 600, 5, 0),
+])
+def test_decode_step_short_rows_misleading_sample(oracle, dtype, g, Hkv, D, Dimp, N, k, sink, window):
+    """One launch, with scores that are huge or tiny exactly where its selection takes a sample (four adjacent ones at each of
+    256 places): the bracket misses the threshold and is widened."""
+    say(f"decode_step short rows, misleading sample dtype={dtype} g={g} Hkv={Hkv} N={N} k={k}")
+    Hq, lo, span = g * Hkv, sink, N - window - sink
+    K, V, Kimp = randn((1, Hkv, N, D), dtype, 51), randn((1, Hkv, N, D), dtype, 52), randn((1, Hkv, N, Dimp), dtype, 53)
+    q = randn((1, Hq, D), dtype, 54)
+    q_imp = randn((1, Hkv, Dimp), dtype, 55).repeat_interleave(g, dim=1)  # (one direction a KV group: its heads agree on what is huge)
+    pos = torch.tensor([((lo + t * span // 256) & ~3) + c for t in range(256) for c in range(4)])
+    pos = torch.unique(pos[(pos >= lo) & (pos < lo + span)])
+    rank, share = k * len(pos) / span, k / span
+    past = rank + 6 * math.sqrt(rank * (1 - share)) + 4  # the sample's rank for the bracket's lower end
+    n_high = min(len(pos), int(past + k) // 2)
+    assert past + 2 < n_high < k, "the sample puts the threshold among the huge scores, the row does not"
+    high, low = Kimp.clone(), Kimp.clone()
+    high[:, :, pos[torch.randperm(len(pos), generator=torch.Generator().manual_seed(N))[:n_high]].to(DEV)] = 30 * q_imp[:, ::g, None]
+    low[:, :, pos.to(DEV)] = -30 * q_imp[:, ::g, None]
+    for name, keys, kk in (("misled high", high, k), ("misled low", low, min(k, (span - len(pos)) // 2)), ("misled high, negative", low, -(-k // 2))):
+        scale = -1.0 if "negative" in name else 1.0
+        s, idx, cnt, out, lse = gpu_decode_step(q, q_imp, K, V, keys, N, kk, sink, window, 0.1, scale=scale)
+        s2 = gpu_score(q_imp, keys, N, scale)
+        need = tb.policy_count(N, kk, sink, window)
+        ridx, rcnt = oracle.select_topk(np_of(s2)[:, :, :N], kk, sink, window)
+        assert np.array_equal(np_of(s)[:, :, :N].view(np.uint32), np_of(s2)[:, :, :N].view(np.uint32)), name
+        assert np.array_equal(np_of(cnt), rcnt) and np.array_equal(np_of(idx)[..., :need], ridx[..., :need]), name
+        idx2, cnt2 = gpu_select(s2, N, kk, sink, window, Hkv=Hkv)
+        out2, lse2 = gpu_attn(q, K, V, idx2, cnt2, N, 0.1, max_count=need)
+        assert torch.equal(out, out2) and torch.equal(lse, lse2), name
+
+
+@pytest.mark.parametrize("dtype,g,Hkv,Dimp,N,sink,window", [(torch.bfloat16, 4, 2, 16, (1 << 20) - 5, 0, 0), (torch.float32, 2, 1, 16, 1 << 20, 128, 257),
+                                                            (torch.bfloat16, 2, 1, 32, 900001, 4, 0)])
+def test_decode_step_long_rows_larger_sample(oracle, dtype, g, Hkv, Dimp, N, sink, window):
+    """A hundredth of a very long row kept: the bracket comes from 8192 scored rows.  Scores in no order, huge ones exactly at
+    the sampled places (too little is kept) and tiny ones there (too much is): the second stage then selects on the whole row.
+    Outputs are those of the separate calls: the attention's partial sums take the place of the kept scores."""
+    say(f"decode_step long rows, larger sample dtype={dtype} g={g} Hkv={Hkv} Dimp={Dimp} N={N}")
+    Hq, k, D = g * Hkv, N // 100, 64
+    K, V, Kimp = randn((1, Hkv, N, D), dtype, 61), randn((1, Hkv, N, D), dtype, 62), randn((1, Hkv, N, Dimp), dtype, 63)
+    q = randn((1, Hq, D), dtype, 64)
+    q_imp = randn((1, Hkv, Dimp), dtype, 65).repeat_interleave(g, dim=1)
+    pos = sample_positions(N, sink, N - window, places=2048).to(DEV)
+    assert len(pos) < k
+    high, low = Kimp.clone(), Kimp.clone()
+    high[:, :, pos], low[:, :, pos] = 30 * q_imp[:, ::g, None], -30 * q_imp[:, ::g, None]
+    need = tb.policy_count(N, k, sink, window)
+    for name, keys in (("random", Kimp), ("misled high", high), ("misled low", low)):
+        scores, idx, cnt, out, lse = gpu_decode_step(q, q_imp, K, V, keys, N, k, sink, window, 0.125)
+        separate = gpu_score(q_imp, keys, N)
+        ridx, rcnt = oracle.select_topk(np_of(separate)[:, :, :N], k, sink, window)
+        assert np.array_equal(np_of(scores)[:, :, :N].view(np.uint32), np_of(separate)[:, :, :N].view(np.uint32)), name
+        assert np.array_equal(np_of(cnt), rcnt) and np.array_equal(np_of(idx)[..., :need], ridx[..., :need]), name
+        out2, lse2 = gpu_attn(q, K, V, idx, cnt, N, 0.125, max_count=need)
         assert torch.equal(out, out2) and torch.equal(lse, lse2), name
 
 
