@@ -179,10 +179,10 @@ static size_t score_select_scratch_upto(const tb_cache_desc* d, int64_t max_coun
 
 // One launch for a whole step, a workgroup per head, against three: no more heads than compute units, a row that a workgroup
 // scores and a list that it attends to in little more than the two launches saved (a compute unit takes about 60 bytes a
-// nanosecond).  Separate and in one, us: 8 heads, 1024 rows of d' = 16, 128 kept, D = 64, fp32 12.7 and 9.0; D = 128, bf16,
-// d' = 32: 32 heads, 2048 rows, 200 kept (230 KB) 14.1 and 11.7, 4096 rows, 400 kept (460 KB) 16.2 and 15.0, 800 kept (660 KB) 16.5
-// and 16.6; 256 heads, 1024 rows, 100 kept 14.1 and 10.9, 4000 rows, 400 kept 24.7 and 23.5; 64 heads, 3000 rows, 684 kept (540
-// KB) 17.1 and 17.3; d' = 64, 4096 rows, 600 kept (810 KB) 16.9 and 18.5.
+// nanosecond).  Separate and in one, us a step in a graph of steps: 8 heads, 1024 rows of d' = 16, 128 kept, D = 64, fp32 10.8 and
+// 8.8; D = 128, bf16, d' = 32: 32 heads, 2048 rows, 200 kept (230 KB) 14.4 and 11.7, 4096 rows, 400 kept (460 KB) 15.9 and 15.5, 800
+// kept (660 KB) 17.1 and 17.2; 256 heads, 1024 rows, 100 kept 14.7 and 11.6, 4000 rows, 400 kept 23.9 and 20.4; 64 heads, 3000
+// rows, 684 kept (540 KB) 18.4 and 18.4; d' = 64, 4096 rows, 600 kept (810 KB) 18.1 and 20.4.
 bool step_in_one(const tb_cache_desc* d, int64_t rows, int nsplit) {
   const int64_t elt = d->dtype == TB_F32 ? 4 : 2;
   return d->N > 0 && d->N <= kStepMaxN && static_cast<int64_t>(d->B) * d->Hq <= 256 && nsplit <= kStepMaxSplits &&

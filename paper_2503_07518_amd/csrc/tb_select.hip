@@ -2,14 +2,17 @@
 // index wins ties; emit ascending".
 //
 // The selection of one row (b,h) by one workgroup of W waves: wave w owns the contiguous span
-// [w*span, (w+1)*span) of the row's scores and keeps their order-preserving 32-bit keys in
-// registers (up to 64 per thread; longer rows are streamed again in every phase).  The exact
-// threshold key T (the kk-th largest) and the number r of keys equal to T that are still
-// needed are found by an MSB-first radix descent over LDS histograms:
+// [w*span, (w+1)*span) of the row's scores and keeps them in registers (up to 64 per thread;
+// longer rows are streamed again in every phase).  They are compared through order-preserving
+// 32-bit keys: positive scores by their own bits, which are ordered alike, others by keys that take
+// their place in the registers.  The exact threshold key T (the kk-th largest) and the number r
+// of keys equal to T that are still needed are found by an MSB-first radix descent over LDS
+// histograms:
 //
-//   bracket   a 12-bit histogram of a strided SAMPLE of the keys (one per thread) gives a range
-//             of top-12-bit bins [b_lo, b_hi] that contains T unless the sample is wildly
-//             unrepresentative (the rank of T in the sample, +- 6 standard deviations);
+//   bracket   a 12-bit histogram of a SAMPLE (one score per thread, four adjacent ones at each
+//             of as many places spread evenly over the candidates) gives a range of top-12-bit
+//             bins [b_lo, b_hi] that contains T unless the sample is wildly unrepresentative
+//             (the rank of T in the sample, +- 6 standard deviations);
 //   level 1   exact: every key above the bracket is counted, every key inside it goes into a
 //             histogram of up to 4096 sub-bins; if the exact counts show that T is NOT inside
 //             the bracket, the level is repeated with the bracket widened to all bins (slow
@@ -17,12 +20,12 @@
 //   level 2+  the remaining low bits, 12 at a time, over the few keys of the chosen sub-bin.
 //
 // Output: {key > T} U {first r keys == T by index} in ascending order.  Positions come from
-// prefix sums (DPP scans inside a 256-key wave tile, running totals along the wave's span, the
-// wave totals across the workgroup) -- no atomic slot grabbing, so the result is ordered and
-// reproducible.
+// counts (lane masks inside a 256-score wave tile, DPP scans where a row is streamed, running totals along
+// the wave's span, the wave totals across the workgroup) -- no atomic slot grabbing, so the result
+// is ordered and reproducible.
 //
 // Launch forms:
-//   select_kernel                      one 1024-thread workgroup per row, no global scratch;
+//   select_kernel                      one workgroup per row (1024 threads, 512 up to 4096 scores), no global scratch;
 //   prefilter_kernel + stage_b_kernel  long rows: the row is cut into pieces, one workgroup per
 //                                      piece keeps the keys at or above the lower end of a bracket
 //                                      that every piece derives from the same sample of the row

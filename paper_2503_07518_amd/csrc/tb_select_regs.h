@@ -24,8 +24,9 @@ struct SelectArgs {
   // Selection by pieces.  Stage A cuts the row into `pieces` pieces and keeps, per piece, the
   // candidates whose key is not below a threshold that a sample of the whole row puts safely
   // under the kk-th largest key: pairs (score bits, position in the whole row) go to cand
-  // [unit][piece][cap] in position order, and the piece's header {number found,
-  // b_lo, b_hi, 0} to piece_hdr[unit][piece].  Stage B selects the kk largest among the kept
+  // [unit][piece][cap] in position order, and the piece's header {number found, b_lo, b_hi, cut}
+  // to piece_hdr[unit][piece] (the cut in a row's first piece only, and only where a kernel before
+  // stage A has found the bracket; stage B reads the bracket there).  Stage B selects the kk largest among the kept
   // ones, read as one row through the table of the pieces' counts; if the pieces hold fewer
   // than kk keys together or more than stage B has registers for -- the sample misled -- it
   // selects on the original row instead.
@@ -271,7 +272,7 @@ __device__ inline void next_level(Level& v) {
 //  * where the bracket lies above zero (a budget below about half of the candidates) no keys are made: the scores' own
 //    bits are ordered there; what is no candidate is a NaN that no compare holds for.  A threshold below that, or a cut
 //    through equal scores, turns the scores into keys once, in their registers (made again in every pass: 32 rows of 32768,
-//    half of the scores kept 18.9 us, now 16.5; 65536 negative scores, a tenth kept 20.8 and 17.7);
+//    half of the scores kept 18.9 us, now 16.5; 65536 negative scores, a tenth kept 20.8 and 16.5);
 //  * histogram adds of scores outside the bracket go to a spare word of the lane instead of being branched around (the
 //    exec-mask bookkeeping of a branch per score cost more than the adds: 10.4 -> 9.6 us on a row of 32768);
 //  * the output is one pass: a compare per score, the lane masks (scalar registers) give every kept score its place in

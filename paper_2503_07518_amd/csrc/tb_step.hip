@@ -8,7 +8,7 @@
 // Scores, lists and outputs are those of the separate kernels, bit for bit: a score is the same sum, and the splits of the
 // attention that the separate kernel would give to workgroups of four waves are groups of four waves here.
 // Bound by its chain (a trip to memory for the projected keys, the selection's phases, another trip for the rows, the merges):
-// 8 heads, 1024 rows, d' = 16, D = 64, fp32 8.7 us, where the three kernels take 2.7, 4.8 and 4.8.
+// 8 heads, 1024 rows, d' = 16, D = 64, fp32 8.8 us a step in a graph of steps (8.9 traced), in three launches 10.8.
 #include "tb_attn_rows.h"
 #include "tb_select_regs.h"
 

@@ -765,7 +765,7 @@ def test_decode_step_long_rows_larger_sample(oracle, dtype, g, Hkv, Dimp, N, sin
     (torch.bfloat16, 4, 1, 1, 32, 131072),
     (torch.float32, 8, 1, 1, 16, 131073),     # two heads a wave
     (torch.bfloat16, 8, 3, 1, 32, 100001),    # a number of KV groups that is no multiple of eight
-    (torch.bfloat16, 4, 2, 1, 16, (1 << 20) - 5),  # the larger sample, pieces of sixteen blocks
+    (torch.bfloat16, 4, 2, 1, 16, (1 << 20) - 5),  # pieces of sixteen blocks; the larger sample where a hundredth is kept
     (torch.float32, 4, 1, 1, 16, 1 << 20),
     (torch.bfloat16, 1, 2, 1, 32, 66001),     # either side of the rule: scores and selection stay apart
     (torch.float32, 8, 1, 1, 32, 66001),
