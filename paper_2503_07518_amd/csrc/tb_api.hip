@@ -583,6 +583,7 @@ tb_status tb_decode_step(const tb_cache_desc* d, const void* q_imp, const void* 
                sm_scale, out, lse,
                reinterpret_cast<float*>(static_cast<char*>(ws) + w.part_off),
                reinterpret_cast<uint32_t*>(ws), plan};
+  A.fresh_lists = true;
   if (step_in_one(d, p.count, plan.nsplit)) return launch_step(S, L, A, st);
   const SelectPlan both = score_select_plan(d, p.hi - p.lo, p.kk);
   if (both.pieces > 1 && L.scratch_bytes >= select_scratch_bytes(units, both)) {

@@ -30,6 +30,11 @@
 // 2839 of 11356 rows: 15.5 us without shares, 13.2 with them, 6000 of 18000 rows: 24.3 and 18.7; 4 groups of four,
 // bf16, 6000 of 18000 rows: 11.7 and 10.9.
 //
+// Non-temporal gathers: a load that allocates in the last-level cache (256 MB) pays for what it displaces there.  Where a
+// launch reads more than that cache keeps for the next one, and heads seldom pick each other's rows (whose lines such a load
+// lets go of early), rows are read without.  streams_rows has the rule; 16 x 32 heads on 8, 2048 of 16384 rows 81.5 -> 76.5 us, 16 x 8 heads
+// on 8, 8000 rows 97.7 -> 84.5 (537 and 524 MB listed; rows read and folded, nothing else, 76 and 92 us, non-temporally 70 and 78).
+//
 // Head-less lists (one list per batch element for all heads) go through the same kernel with
 // the list shared, or, when there are enough KV groups to fill the chip, through
 // attn_group_kernel: one workgroup per (b, kv head, split) that serves all query heads of the
@@ -100,8 +105,8 @@ __device__ __forceinline__ void combine_published(const float* po, const float* 
       });
 }
 
-// SHARES: the list is cut into one share per XCD (nsplit divides by their number)
-template <typename T, int D, bool BUF, bool SHARES>
+// SHARES: the list is cut into one share per XCD (nsplit divides by their number).  NT: rows are read non-temporally
+template <typename T, int D, bool BUF, bool SHARES, bool NT>
 __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(AttnArgs a) {
   constexpr int EPL = Pack16<T>::kElts;    // elements per lane
   constexpr int LPR = D / EPL;             // lanes per row
@@ -224,12 +229,12 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
         const uint32_t row = valid[t] ? static_cast<uint32_t>(n & (kTailFlag - 1)) : 0u;
         const char* kp = tail ? kbase + row * k_row_bytes : kbuf + row * static_cast<uint32_t>(D * sizeof(T));
         const char* vp = tail ? vbase + row * v_row_bytes : vbuf + row * static_cast<uint32_t>(D * sizeof(T));
-        kraw[t] = Pack16<T>::load_raw(kp);
-        vraw[t] = Pack16<T>::load_raw(vp);
+        kraw[t] = Pack16<T>::template load_raw<NT>(kp);
+        vraw[t] = Pack16<T>::template load_raw<NT>(vp);
       } else {
         const uint32_t row = valid[t] ? static_cast<uint32_t>(n) : 0u;
-        kraw[t] = Pack16<T>::load_raw(kbase + row * k_row_bytes);
-        vraw[t] = Pack16<T>::load_raw(vbase + row * v_row_bytes);
+        kraw[t] = Pack16<T>::template load_raw<NT>(kbase + row * k_row_bytes);
+        vraw[t] = Pack16<T>::template load_raw<NT>(vbase + row * v_row_bytes);
       }
     }
     n_next = fetch_rows(t0 + stride);
@@ -765,6 +770,29 @@ tb_status launch_group(const AttnArgs& a, const AttnLaunch& L, hipStream_t st) {
   return hip_status(hipGetLastError());
 }
 
+// Non-temporal gathers of lists of up to `rows` rows.  With lists that do not depend on each other the g heads of a group read
+// `distinct` rows of N and come back to each of them g * rows / distinct times.  A step that has just selected its lists finds little in the
+// last-level cache from 100 MB of different rows on; beyond 1.3 readers a row, and for groups of eight, whose lists share more than
+// that where the scores favour the same rows, the lines are wanted again.  Attention alone in us, plain and non-temporal
+// (D = 128, bf16; B x heads on KV heads, listed of N): 4 x 32 on 8, 1638 of 16384 (92 MB) 19.6 and 20.2; 4 x 8 on 8, 6554 of 32768
+// (107 MB) 22.2 and 21.5; 4 x 16 on 8, 4096 of 32768 (126 MB) 27.2 and 24.9; 8 x 32 on 8, 1638 of 16384 (184 MB, 1.16) 37.7 and 33.5; 4 x 32
+// on 8, widened lists of 11600 of 65536 (1.33) 98.4 and 100.6; 16 x 64 on 8, 1638 of 16384 (1.4) 112.6 and 119; 4 x 64 on 8, 4096 of 131072,
+// the same rows in many lists (1.11 if they were not) 56.1 and 63.5.  Lists that are handed in may be those of the step before, whose rows
+// that cache still holds unless they are far more than it has room for: intervals of 8 steps that reuse lists of 220 MB 339 and
+// 349 us, of 295 MB 405 and 411, of 393 MB 508 and 495, of 430 MB 596 and 565.
+bool streams_rows(const AttnLaunch& L) {
+  const tb_cache_desc& d = *L.desc;
+  const int g = d.Hq / d.Hkv;
+  const double N = static_cast<double>(d.N), rows = static_cast<double>(L.max_count + (L.tail_end - L.tail_begin));
+  if (L.shared_list || rows <= 0.0 || g > 4) return false;
+  const double p = rows < N ? rows / N : 1.0;
+  double none = 1.0;  // share of the rows that no head of the group lists
+  for (int j = 0; j < g; ++j) none *= 1.0 - p;
+  const double distinct = N * (1.0 - none);
+  const double bytes = static_cast<double>(d.B) * d.Hkv * distinct * 2 * d.D * (d.dtype == TB_F32 ? 4 : 2);
+  return bytes >= (L.fresh_lists ? 100e6 : 375e6) && g * p * N <= 1.3 * distinct;
+}
+
 template <typename T, int D>
 tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
   const tb_cache_desc& d = *L.desc;
@@ -811,13 +839,15 @@ tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
   if (a.xcd_map) grid = dim3(static_cast<unsigned>(kXcds * ((a.n_kv_groups + kXcds - 1) / kXcds) * a.g * a.nsplit));
   const bool shares = a.g > 1 && !a.xcd_map && a.nsplit % kXcds == 0;
   if (L.Kbuf && shares)
-    hipLaunchKernelGGL((attn_kernel<T, D, true, true>), grid, dim3(kAttnThreads), 0, st, a);
+    hipLaunchKernelGGL((attn_kernel<T, D, true, true, false>), grid, dim3(kAttnThreads), 0, st, a);
   else if (L.Kbuf)
-    hipLaunchKernelGGL((attn_kernel<T, D, true, false>), grid, dim3(kAttnThreads), 0, st, a);
+    hipLaunchKernelGGL((attn_kernel<T, D, true, false, false>), grid, dim3(kAttnThreads), 0, st, a);
   else if (shares)
-    hipLaunchKernelGGL((attn_kernel<T, D, false, true>), grid, dim3(kAttnThreads), 0, st, a);
+    hipLaunchKernelGGL((attn_kernel<T, D, false, true, false>), grid, dim3(kAttnThreads), 0, st, a);
+  else if (streams_rows(L))
+    hipLaunchKernelGGL((attn_kernel<T, D, false, false, true>), grid, dim3(kAttnThreads), 0, st, a);
   else
-    hipLaunchKernelGGL((attn_kernel<T, D, false, false>), grid, dim3(kAttnThreads), 0, st, a);
+    hipLaunchKernelGGL((attn_kernel<T, D, false, false, false>), grid, dim3(kAttnThreads), 0, st, a);
   return hip_status(hipGetLastError());
 }
 

@@ -19,11 +19,26 @@ struct bf16_t {
 template <typename T>
 struct Pack16;  // one 16-byte vector of T, unpacked to fp32
 
+// 128 bits, past the caches that keep what is read again (NT) or through them.
+template <bool NT, typename Raw>
+__device__ inline Raw load_128(const void* p) {
+  if constexpr (NT) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    Raw r;
+    __builtin_memcpy(&r, &v, 16);
+    return r;
+  } else {
+    return *reinterpret_cast<const Raw*>(p);
+  }
+}
+
 template <>
 struct Pack16<float> {
   static constexpr int kElts = 4;
   using Raw = float4;
-  __device__ static inline Raw load_raw(const void* p) { return *reinterpret_cast<const float4*>(p); }
+  template <bool NT = false>
+  __device__ static inline Raw load_raw(const void* p) { return load_128<NT, Raw>(p); }
   __device__ static inline void unpack(const Raw& v, float (&f)[4]) {
     f[0] = v.x;
     f[1] = v.y;
@@ -43,7 +58,8 @@ template <>
 struct Pack16<bf16_t> {
   static constexpr int kElts = 8;
   using Raw = uint4;
-  __device__ static inline Raw load_raw(const void* p) { return *reinterpret_cast<const uint4*>(p); }
+  template <bool NT = false>
+  __device__ static inline Raw load_raw(const void* p) { return load_128<NT, Raw>(p); }
   __device__ static inline void unpack(const Raw& v, float (&f)[8]) {
     f[0] = __uint_as_float(v.x << 16);
     f[1] = __uint_as_float(v.x & 0xFFFF0000u);

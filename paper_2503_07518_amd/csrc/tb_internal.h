@@ -123,6 +123,7 @@ struct AttnLaunch {
   // head-less form: idx is [B][idx_cap] and count [B], one list for all heads of a batch element
   bool shared_list = false;
   bool grouped = false;  // shared list served by one workgroup per KV group (plan made for that)
+  bool fresh_lists = false;  // the lists have been selected by this call
 };
 
 // Scores, selection and attention in one launch (a workgroup per head), for what step_in_one allows.

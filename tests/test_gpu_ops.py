@@ -654,6 +654,32 @@ def test_decode_step_matches_separate_calls_and_oracle(oracle, dtype, B, Hq, Hkv
     assert_attention(np_of(out), ro, dn, np_of(lse), rl)
 
 
+@pytest.mark.parametrize("dtype,B,g,Hkv,D,N,k,sink,window", [
+    (torch.float32, 4, 1, 8, 128, 5003, 3000, 37, 101),
+    (torch.bfloat16, 8, 2, 8, 64, 9601, 3700, 0, 160),
+    (torch.bfloat16, 16, 4, 8, 128, 4001, 483, 5, 0),
+])
+def test_decode_step_large_lists(oracle, dtype, B, g, Hkv, D, N, k, sink, window):
+    """Lists of more than 100 MB of rows, just selected, are gathered non-temporally; handed in, like any others: the same
+    bits, with an infinite row among those that a tile's empty slots and nobody's list may load.  One unit against the oracle."""
+    say(f"decode_step large lists dtype={dtype} B={B} g={g} Hkv={Hkv} D={D} N={N} k={k} S={sink} W={window}")
+    Hq, Dimp, sm = g * Hkv, 16, 1 / math.sqrt(D)
+    q, q_imp = randn((B, Hq, D), dtype, 36), randn((B, Hq, Dimp), dtype, 37)
+    gen = torch.Generator(device=DEV).manual_seed(38)
+    K, V = (torch.randn((B, Hkv, N, D), generator=gen, device=DEV).to(dtype) for _ in range(2))
+    Kimp = torch.randn((B, Hkv, N, Dimp), generator=gen, device=DEV).to(dtype)
+    low = sink + 1  # (never selected: the only row with a score that is not finite)
+    Kimp[:, :, low], V[:, :, low] = float("nan"), float("inf")
+    s, idx, cnt, out, lse = gpu_decode_step(q, q_imp, K, V, Kimp, N, k, sink, window, sm)
+    out2, lse2 = gpu_attn(q, K, V, idx, cnt, N, sm, max_count=idx.shape[-1])
+    torch.cuda.synchronize()
+    assert torch.equal(out, out2) and torch.equal(lse, lse2) and bool(torch.isfinite(out).all())
+    b, h = B - 1, Hq - 1
+    ro, rl = oracle.sparse_decode_attn(np_of(q[b:b + 1, h:h + 1]), np_of(K[b:b + 1, h // g:h // g + 1]), np_of(V[b:b + 1, h // g:h // g + 1]),
+                                       np_of(idx[b:b + 1, h:h + 1]), np_of(cnt[b:b + 1, h:h + 1]), dtype_name(K), sm)
+    assert_attention(np_of(out[b, h]), ro[0, 0], dtype_name(K), np_of(lse[b, h]), rl[0, 0])
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("g,Hkv,B,D,Dimp,N,k,sink,window", [
     (1, 1, 1, 64, 16, 1, 1, 0, 0),
