@@ -182,6 +182,15 @@ tb_status tb_buffered_decode_attn(const tb_cache_desc* desc, const void* q, cons
                                   const void* V, int64_t tail_begin, int64_t tail_end, float sm_scale,
                                   float* out, float* lse, void* ws, size_t ws_bytes, void* stream);
 
+/* tb_append_kv of one row (src_row of the cache src, K_src, V_src) into row dst_row of the cache desc, K, V, then
+ * tb_buffered_decode_attn over that cache, in one launch: the attention takes the new row from where it comes
+ * from while it is copied.  Arguments and results are those of the two calls; src and desc as in tb_append_kv. */
+tb_status tb_append_buffered_decode_attn(const tb_cache_desc* src, const void* K_src, const void* V_src, int64_t src_row,
+                                         const tb_cache_desc* desc, const void* q, const void* Kbuf, const void* Vbuf,
+                                         int64_t buf_cap, const int32_t* count, int64_t max_count, void* K, void* V,
+                                         int64_t dst_row, int64_t tail_begin, int64_t tail_end, float sm_scale,
+                                         float* out, float* lse, void* ws, size_t ws_bytes, void* stream);
+
 /* One prediction step in a single enqueue: tb_score -> tb_select_topk -> tb_sparse_decode_attn
  * with one validation pass and one launch plan.  Results (scores, idx, count, out, lse) are
  * identical to calling the three entry points one after the other.

@@ -487,8 +487,9 @@ tb_status tb_gather_important(const tb_cache_desc* d, const void* K, const void*
   return launch_gather(L, static_cast<hipStream_t>(stream));
 }
 
-tb_status tb_append_kv(const tb_cache_desc* src, const void* K, const void* V, int64_t src_row, const tb_cache_desc* dst,
-                       void* Kdst, void* Vdst, int64_t dst_row, int64_t rows, void* stream) {
+namespace {
+tb_status check_append(const tb_cache_desc* src, const void* K, const void* V, int64_t src_row, const tb_cache_desc* dst, const void* Kdst,
+                       const void* Vdst, int64_t dst_row, int64_t rows) {
   TB_TRY(check_desc(src));
   TB_TRY(check_desc(dst));
   if (!K || !V || !Kdst || !Vdst || rows < 0 || src_row < 0 || dst_row < 0) return TB_ERR_INVALID_ARG;
@@ -500,13 +501,12 @@ tb_status tb_append_kv(const tb_cache_desc* src, const void* K, const void* V, i
   }
   if (!aligned16(K) || !aligned16(V) || !aligned16(Kdst) || !aligned16(Vdst)) return TB_ERR_UNSUPPORTED;
   if (rows > (int64_t{1} << 20)) return TB_ERR_UNSUPPORTED;
-  return launch_append(*src, K, V, src_row, *dst, Kdst, Vdst, dst_row, rows, static_cast<hipStream_t>(stream));
+  return TB_OK;
 }
 
-tb_status tb_buffered_decode_attn(const tb_cache_desc* d, const void* q, const void* Kbuf, const void* Vbuf,
-                                  int64_t buf_cap, const int32_t* count, int64_t max_count, const void* K,
-                                  const void* V, int64_t tail_begin, int64_t tail_end, float sm_scale, float* out,
-                                  float* lse, void* ws, size_t ws_bytes, void* stream) {
+tb_status buffered_attn(const tb_cache_desc* d, const void* q, const void* Kbuf, const void* Vbuf, int64_t buf_cap, const int32_t* count,
+                        int64_t max_count, const void* K, const void* V, int64_t tail_begin, int64_t tail_end, float sm_scale, float* out,
+                        float* lse, void* ws, size_t ws_bytes, void* stream, const NewRow* append) {
   if (!Kbuf || !Vbuf || buf_cap < 0 || max_count > buf_cap) return TB_ERR_INVALID_ARG;
   // the list itself is not read: its place in the argument check is taken by the count array
   TB_TRY(check_attn_args(d, q, K, V, count, count, buf_cap, max_count, tail_begin, tail_end, out));
@@ -514,7 +514,11 @@ tb_status tb_buffered_decode_attn(const tb_cache_desc* d, const void* q, const v
   const int64_t elt = d->dtype == TB_F32 ? 4 : 2;
   if (buf_cap * d->D * elt >= (int64_t{1} << 32)) return TB_ERR_UNSUPPORTED;  // 32-bit offsets inside a head's buffer
   const int64_t units = static_cast<int64_t>(d->B) * d->Hq;
-  if (units == 0) return TB_OK;
+  if (units == 0) {
+    if (!append) return TB_OK;
+    return launch_append(*append->src, append->K, append->V, append->src_row, *d, append->Kdst, append->Vdst, append->dst_row, 1,
+                         static_cast<hipStream_t>(stream));
+  }
   const int64_t rows = max_count + (tail_end - tail_begin);
   const AttnPlan plan = attn_plan(units, rows, attn_tile_rows_per_wg(d->dtype, d->D));
   const WsLayout w = ws_layout(units, d->D, plan.nsplit);
@@ -527,7 +531,32 @@ tb_status tb_buffered_decode_attn(const tb_cache_desc* d, const void* q, const v
   L.Kbuf = Kbuf;
   L.Vbuf = Vbuf;
   L.buf_cap = buf_cap;
+  L.append = append;
   return launch_attn(L, static_cast<hipStream_t>(stream));
+}
+}  // namespace
+
+tb_status tb_append_kv(const tb_cache_desc* src, const void* K, const void* V, int64_t src_row, const tb_cache_desc* dst,
+                       void* Kdst, void* Vdst, int64_t dst_row, int64_t rows, void* stream) {
+  TB_TRY(check_append(src, K, V, src_row, dst, Kdst, Vdst, dst_row, rows));
+  return launch_append(*src, K, V, src_row, *dst, Kdst, Vdst, dst_row, rows, static_cast<hipStream_t>(stream));
+}
+
+tb_status tb_buffered_decode_attn(const tb_cache_desc* d, const void* q, const void* Kbuf, const void* Vbuf,
+                                  int64_t buf_cap, const int32_t* count, int64_t max_count, const void* K,
+                                  const void* V, int64_t tail_begin, int64_t tail_end, float sm_scale, float* out,
+                                  float* lse, void* ws, size_t ws_bytes, void* stream) {
+  return buffered_attn(d, q, Kbuf, Vbuf, buf_cap, count, max_count, K, V, tail_begin, tail_end, sm_scale, out, lse, ws, ws_bytes, stream,
+                       nullptr);
+}
+
+tb_status tb_append_buffered_decode_attn(const tb_cache_desc* src, const void* K_src, const void* V_src, int64_t src_row,
+                                         const tb_cache_desc* d, const void* q, const void* Kbuf, const void* Vbuf, int64_t buf_cap,
+                                         const int32_t* count, int64_t max_count, void* K, void* V, int64_t dst_row, int64_t tail_begin,
+                                         int64_t tail_end, float sm_scale, float* out, float* lse, void* ws, size_t ws_bytes, void* stream) {
+  TB_TRY(check_append(src, K_src, V_src, src_row, d, K, V, dst_row, 1));
+  const NewRow row{src, K_src, V_src, src_row, dst_row, K, V};
+  return buffered_attn(d, q, Kbuf, Vbuf, buf_cap, count, max_count, K, V, tail_begin, tail_end, sm_scale, out, lse, ws, ws_bytes, stream, &row);
 }
 
 tb_status tb_predict_queries(const tb_predictor_desc* p, int32_t B, const void* h, const void* gamma,

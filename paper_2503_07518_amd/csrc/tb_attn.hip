@@ -35,6 +35,9 @@
 // lets go of early), rows are read without.  streams_rows has the rule; 16 x 32 heads on 8, 2048 of 16384 rows 81.5 -> 76.5 us, 16 x 8 heads
 // on 8, 8000 rows 97.7 -> 84.5 (537 and 524 MB listed; rows read and folded, nothing else, 76 and 92 us, non-temporally 70 and 78).
 //
+// A row that arrives in the three-buffer layout's ring comes with the attention of its step: as a launch of its own the copy took
+// 4.2 us, all of them launch and one trip to memory.  Interval of 16 steps and a wrap, 2 x 32 heads, 2816 rows a head: 480 -> 418 us.
+//
 // Head-less lists (one list per batch element for all heads) go through the same kernel with
 // the list shared, or, when there are enough KV groups to fill the chip, through
 // attn_group_kernel: one workgroup per (b, kv head, split) that serves all query heads of the
@@ -72,6 +75,12 @@ struct AttnArgs {
   const void* Kbuf;
   const void* Vbuf;
   int64_t buf_cap;
+  // buffered form: row new_row of the cache is on its way there (-1: none).  The workgroup of a KV head's first split copies
+  // it from new_from, and everybody reads it from there, so nobody depends on the copy.
+  const char* new_from[2];  // K and V: the row of the first KV head
+  char* new_to[2];
+  int64_t new_from_b[2], new_from_h[2], new_to_b[2], new_to_h[2];  // strides in bytes
+  int32_t new_row;
 };
 
 constexpr int32_t kTailFlag = 0x40000000;  // buffered form: the row number refers to the cache, not the buffer
@@ -166,6 +175,19 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
     kbuf = reinterpret_cast<const char*>(static_cast<const T*>(a.Kbuf) + u * a.buf_cap * D) + sub * 16;
     vbuf = reinterpret_cast<const char*>(static_cast<const T*>(a.Vbuf) + u * a.buf_cap * D) + sub * 16;
   }
+  const char* knew = nullptr;
+  const char* vnew = nullptr;
+  int32_t n_new = INT32_MIN;  // the new row as fetch_rows names it (this value: nobody's name)
+  if (BUF && a.new_row >= 0) {
+    n_new = a.new_row | kTailFlag;
+    knew = a.new_from[0] + b * a.new_from_b[0] + hkv * a.new_from_h[0] + sub * 16;
+    vnew = a.new_from[1] + b * a.new_from_b[1] + hkv * a.new_from_h[1] + sub * 16;
+    if (split == 0 && h % a.g == 0 && tid < LPR) {  // (sub == tid)
+      const uint4 kr = *reinterpret_cast<const uint4*>(knew), vr = *reinterpret_cast<const uint4*>(vnew);
+      *reinterpret_cast<uint4*>(a.new_to[0] + b * a.new_to_b[0] + hkv * a.new_to_h[0] + sub * 16) = kr;
+      *reinterpret_cast<uint4*>(a.new_to[1] + b * a.new_to_b[1] + hkv * a.new_to_h[1] + sub * 16) = vr;
+    }
+  }
 
   RowSoftmax<T, D> rows;
   rows.init(static_cast<const T*>(a.q) + u * D + sub * EPL, a.sm_scale_log2);
@@ -229,6 +251,10 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
         const uint32_t row = valid[t] ? static_cast<uint32_t>(n & (kTailFlag - 1)) : 0u;
         const char* kp = tail ? kbase + row * k_row_bytes : kbuf + row * static_cast<uint32_t>(D * sizeof(T));
         const char* vp = tail ? vbase + row * v_row_bytes : vbuf + row * static_cast<uint32_t>(D * sizeof(T));
+        if (n == n_new) {
+          kp = knew;
+          vp = vnew;
+        }
         kraw[t] = Pack16<T>::template load_raw<NT>(kp);
         vraw[t] = Pack16<T>::template load_raw<NT>(vp);
       } else {
@@ -825,6 +851,24 @@ tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
   a.Kbuf = L.Kbuf;
   a.Vbuf = L.Vbuf;
   a.buf_cap = L.buf_cap;
+  a.new_row = -1;
+  if (L.append) {
+    const NewRow& r = *L.append;
+    const int64_t elt = sizeof(T);
+    const int64_t from[2][3] = {{r.src->k_stride_b, r.src->k_stride_h, r.src->k_stride_n}, {r.src->v_stride_b, r.src->v_stride_h, r.src->v_stride_n}};
+    const int64_t to[2][3] = {{d.k_stride_b, d.k_stride_h, d.k_stride_n}, {d.v_stride_b, d.v_stride_h, d.v_stride_n}};
+    const void* in[2] = {r.K, r.V};
+    void* out[2] = {r.Kdst, r.Vdst};
+    for (int t = 0; t < 2; ++t) {
+      a.new_from[t] = static_cast<const char*>(in[t]) + r.src_row * from[t][2] * elt;
+      a.new_to[t] = static_cast<char*>(out[t]) + r.dst_row * to[t][2] * elt;
+      a.new_from_b[t] = from[t][0] * elt;
+      a.new_from_h[t] = from[t][1] * elt;
+      a.new_to_b[t] = to[t][0] * elt;
+      a.new_to_h[t] = to[t][1] * elt;
+    }
+    a.new_row = static_cast<int32_t>(r.dst_row);  // (below 2^30: launch conditions)
+  }
   a.shared_list = L.shared_list ? 1 : 0;
   a.n_kv_groups = d.B * d.Hkv;
   // per-XCD placement pays when heads share KV rows and the KV groups spread evenly over the XCDs

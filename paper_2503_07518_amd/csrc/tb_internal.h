@@ -102,6 +102,16 @@ struct FilterOut {
 };
 tb_status launch_score_filter(const ScoreLaunch& S, const FilterOut& f, hipStream_t st);
 
+// A row that reaches the cache with the attention over it: row src_row of src is copied to row dst_row.
+struct NewRow {
+  const tb_cache_desc* src;
+  const void* K;
+  const void* V;
+  int64_t src_row, dst_row;
+  void* Kdst;
+  void* Vdst;
+};
+
 struct AttnLaunch {
   const tb_cache_desc* desc;
   const void* q;
@@ -120,6 +130,7 @@ struct AttnLaunch {
   const void* Kbuf = nullptr;
   const void* Vbuf = nullptr;
   int64_t buf_cap = 0;
+  const NewRow* append = nullptr;  // (buffered form)
   // head-less form: idx is [B][idx_cap] and count [B], one list for all heads of a batch element
   bool shared_list = false;
   bool grouped = false;  // shared list served by one workgroup per KV group (plan made for that)

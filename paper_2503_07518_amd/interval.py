@@ -129,7 +129,8 @@ class RingLayoutDecoder:
     so the selection never needs a projected key that does not exist yet.
 
     Moving the first ``sink`` rows into the Sink Buffer is data arrival, done here with a plain device
-    copy; the model's new K/V row reaches the ring through ``tb_append_kv`` (one launch for both).
+    copy; the model's new K/V row reaches the ring with the step's attention (``tb_append_buffered_decode_attn``), at a
+    wrap through ``tb_append_kv`` ahead of the projection.
     """
 
     def __init__(self, K, V, W, Kimp, Hq: int, k: int, P: int, radius: int, ring: int, sink: int = 0,
@@ -166,17 +167,17 @@ class RingLayoutDecoder:
         """Step t sees the first N_t = N0 + t rows of the cache.  Returns (out, lse) views."""
         S, R = self.sink, self.ring
         aux = tb.make_desc(S + R, self.Hq, K=self.aux_K, V=self.aux_V)
-        if t > 0:  # the token appended before this step arrives in the ring
-            slot = (t - 1) % R
+        slot = (t - 1) % R  # of the token appended before this step, which arrives in the ring
+        wraps = t > 0 and t % R == 0
+        if wraps:
             tb.tb_append_kv(tb.make_desc(self.Ncap, self.Hq, K=self.K, V=self.V), self.K, self.V, N_t - 1,
                             aux, self.aux_K, self.aux_V, S + slot)
-            if t % R == 0:
-                # the head is back at slot 0: slot i holds token N_t - R + i; project the R keys of
-                # the ring in one batch and append them to the projected-key cache
-                ring_K = self.aux_K[:, :, S:S + R]
-                kimp_rows = self.Kimp[:, :, N_t - R:N_t]
-                tb.tb_project_keys(tb.make_desc(R, self.Hq, K=ring_K, Kimp=kimp_rows), ring_K, self.W, kimp_rows, 0, R)
-                self.projections += 1
+            # the head is back at slot 0: slot i holds token N_t - R + i; project the R keys of
+            # the ring in one batch and append them to the projected-key cache
+            ring_K = self.aux_K[:, :, S:S + R]
+            kimp_rows = self.Kimp[:, :, N_t - R:N_t]
+            tb.tb_project_keys(tb.make_desc(R, self.Hq, K=ring_K, Kimp=kimp_rows), ring_K, self.W, kimp_rows, 0, R)
+            self.projections += 1
         W_t = min(R, t)  # tokens in the ring
         if t % self.P == 0:
             desc = tb.make_desc(N_t, self.Hq, K=self.K, V=self.V, Kimp=self.Kimp)
@@ -188,6 +189,11 @@ class RingLayoutDecoder:
             tb.tb_gather_important(desc, self.K, self.V, self.exp_idx, self.exp_cnt, self.exp_cap, min(S, N_t), W_t,
                                    self.Kbuf, self.Vbuf, self.imp_cnt)
         aux.N = S + W_t
-        tb.tb_buffered_decode_attn(aux, q, self.Kbuf, self.Vbuf, self.imp_cnt, self.exp_cap, self.aux_K, self.aux_V,
-                                   self.sm_scale, self.out, self.lse, self.ws, tail_begin=0, tail_end=S + W_t)
+        if t > 0 and not wraps:  # nothing else reads the ring in this step: the new token arrives with the attention
+            tb.tb_append_buffered_decode_attn(tb.make_desc(self.Ncap, self.Hq, K=self.K, V=self.V), self.K, self.V, N_t - 1,
+                                              aux, q, self.Kbuf, self.Vbuf, self.imp_cnt, self.exp_cap, self.aux_K, self.aux_V, S + slot,
+                                              self.sm_scale, self.out, self.lse, self.ws, tail_begin=0, tail_end=S + W_t)
+        else:
+            tb.tb_buffered_decode_attn(aux, q, self.Kbuf, self.Vbuf, self.imp_cnt, self.exp_cap, self.aux_K, self.aux_V,
+                                       self.sm_scale, self.out, self.lse, self.ws, tail_begin=0, tail_end=S + W_t)
         return self.out, self.lse

@@ -193,3 +193,42 @@ def test_append_kv(dtype, D, rows):
     for bad in ((N - rows + 1, 0), (0, R - rows + 1), (-1, 0)):
         with pytest.raises(tb.TbError):
             tb.tb_append_kv(src, K, V, bad[0], dst, dK, dV, bad[1], rows)
+
+
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,D,cap,counts,tail,slot", [
+    (torch.bfloat16, 2, 8, 2, 128, 300, (300, 0, 17), (0, 96), 95),    # splits of a head, the row in the last tile
+    (torch.bfloat16, 1, 8, 1, 128, 3000, (3000, 129), (0, 64), 0),     # the list in shares, one per XCD
+    (torch.float32, 3, 4, 4, 64, 40, (40, 1, 0), (5, 60), 33),
+    (torch.float32, 1, 16, 2, 128, 1, (1, 0), (10, 20), 3),            # the row outside the attended range
+    (torch.bfloat16, 9, 16, 8, 64, 700, (700, 64, 1), (0, 128), 77),
+])
+def test_append_with_buffered_attention(dtype, B, Hq, Hkv, D, cap, counts, tail, slot):
+    """The row that arrives with the attention: the same bytes in the buffer and the same bits as the two calls, where the
+    place it goes to holds what must not be seen."""
+    say(f"append with attention dtype={dtype} B={B} Hq={Hq} Hkv={Hkv} D={D} cap={cap} tail={tail} slot={slot}")
+    g = torch.Generator().manual_seed(81)
+    N, R = 50, 128
+    K, V = (torch.randn((B, N, Hkv, D), generator=g).to(dtype).to(DEV).transpose(1, 2) for _ in range(2))  # strides of their own
+    aK, aV = (torch.randn((B, Hkv, R, D), generator=g).to(dtype).to(DEV) for _ in range(2))
+    aK[:, :, slot], aV[:, :, slot] = float("nan"), float("inf")
+    Kb, Vb = (torch.randn((B, Hq, cap, D), generator=g).to(dtype).to(DEV) for _ in range(2))
+    q = torch.randn((B, Hq, D), generator=g).to(dtype).to(DEV)
+    cnt = torch.tensor([counts[i % len(counts)] for i in range(B * Hq)], dtype=torch.int32, device=DEV).view(B, Hq)
+    src, dst = tb.make_desc(N, Hq, K=K, V=V), tb.make_desc(R, Hq, K=aK, V=aV)
+    ws = tb.new_workspace(tb.TB_OP_ATTN, dst, cap + R)
+    res = []
+    for fused in (True, False):
+        k, v = aK.clone(), aV.clone()
+        out, lse = (torch.full(s, float("nan"), device=DEV) for s in ((B, Hq, D), (B, Hq)))
+        if fused:
+            tb.tb_append_buffered_decode_attn(src, K, V, 41, dst, q, Kb, Vb, cnt, cap, k, v, slot, 0.1, out, lse, ws, *tail)
+        else:
+            tb.tb_append_kv(src, K, V, 41, dst, k, v, slot)
+            tb.tb_buffered_decode_attn(dst, q, Kb, Vb, cnt, cap, k, v, 0.1, out, lse, ws, *tail)
+        torch.cuda.synchronize()
+        res.append((k, v, out, lse))
+    assert all(torch.equal(a, b) for a, b in zip(*res)) and bool(torch.isfinite(res[0][2]).all())
+    assert torch.equal(res[0][0][:, :, slot], K[:, :, 41]) and torch.equal(res[0][1][:, :, slot], V[:, :, 41])
+    for bad in ((N, slot), (41, R), (-1, slot)):
+        with pytest.raises(tb.TbError):
+            tb.tb_append_buffered_decode_attn(src, K, V, bad[0], dst, q, Kb, Vb, cnt, cap, aK, aV, bad[1], 0.1, out, lse, ws, *tail)
