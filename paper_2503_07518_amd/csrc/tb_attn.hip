@@ -809,14 +809,10 @@ tb_status launch_group(const AttnArgs& a, const AttnLaunch& L, hipStream_t st) {
 bool streams_rows(const AttnLaunch& L) {
   const tb_cache_desc& d = *L.desc;
   const int g = d.Hq / d.Hkv;
-  const double N = static_cast<double>(d.N), rows = static_cast<double>(L.max_count + (L.tail_end - L.tail_begin));
-  if (L.shared_list || rows <= 0.0 || g > 4) return false;
-  const double p = rows < N ? rows / N : 1.0;
-  double none = 1.0;  // share of the rows that no head of the group lists
-  for (int j = 0; j < g; ++j) none *= 1.0 - p;
-  const double distinct = N * (1.0 - none);
-  const double bytes = static_cast<double>(d.B) * d.Hkv * distinct * 2 * d.D * (d.dtype == TB_F32 ? 4 : 2);
-  return bytes >= (L.fresh_lists ? 100e6 : 375e6) && g * p * N <= 1.3 * distinct;
+  if (L.shared_list || g > 4) return false;
+  const ListedRows r = listed_rows(g, static_cast<double>(L.max_count + (L.tail_end - L.tail_begin)), static_cast<double>(d.N));
+  const double bytes = static_cast<double>(d.B) * d.Hkv * r.distinct * 2 * d.D * (d.dtype == TB_F32 ? 4 : 2);
+  return bytes >= (L.fresh_lists ? 100e6 : 375e6) && r.reuse <= kStreamedReuse;
 }
 
 template <typename T, int D>
@@ -882,10 +878,12 @@ tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
   dim3 grid(L.plan.nsplit, d.Hq, d.B);
   if (a.xcd_map) grid = dim3(static_cast<unsigned>(kXcds * ((a.n_kv_groups + kXcds - 1) / kXcds) * a.g * a.nsplit));
   const bool shares = a.g > 1 && !a.xcd_map && a.nsplit % kXcds == 0;
+  // (per-head buffers share no rows: non-temporal whatever the size; against loads that the caches keep, an interval of 2 x 32 heads,
+  // 2816 rows a head, 418 and 407 us, of 4 x 32 heads, 9400 rows 1340 and 1209, of 8 heads, 1000 rows no difference)
   if (L.Kbuf && shares)
-    hipLaunchKernelGGL((attn_kernel<T, D, true, true, false>), grid, dim3(kAttnThreads), 0, st, a);
+    hipLaunchKernelGGL((attn_kernel<T, D, true, true, true>), grid, dim3(kAttnThreads), 0, st, a);
   else if (L.Kbuf)
-    hipLaunchKernelGGL((attn_kernel<T, D, true, false, false>), grid, dim3(kAttnThreads), 0, st, a);
+    hipLaunchKernelGGL((attn_kernel<T, D, true, false, true>), grid, dim3(kAttnThreads), 0, st, a);
   else if (shares)
     hipLaunchKernelGGL((attn_kernel<T, D, false, true, false>), grid, dim3(kAttnThreads), 0, st, a);
   else if (streams_rows(L))

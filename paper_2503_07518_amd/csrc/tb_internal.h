@@ -39,6 +39,21 @@ WsLayout ws_layout(int64_t units, int D, int nsplit);
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Lists of `rows` of N rows, one for each of the g heads of a KV group, that do not depend on each other: how many different
+// rows the group reads, and how often each of them.
+struct ListedRows {
+  double distinct, reuse;
+};
+inline ListedRows listed_rows(int g, double rows, double N) {
+  const double p = rows < N ? rows / N : 1.0;
+  double none = 1.0;  // share of the rows that no head lists
+  for (int j = 0; j < g; ++j) none *= 1.0 - p;
+  const double distinct = N * (1.0 - none);
+  return ListedRows{distinct, distinct > 0.0 ? g * p * N / distinct : 1.0};
+}
+// Readers a row up to which its line is not kept for the next one (non-temporal loads)
+constexpr double kStreamedReuse = 1.3;
+
 struct ScoreLaunch {
   const tb_cache_desc* desc;
   const void* q_imp;
