@@ -8,7 +8,8 @@
 
 namespace tb {
 
-constexpr int64_t kAttnTargetWgs = 512;   // workgroups a launch of the split attention aims at
+constexpr int64_t kAttnCus = 256;         // compute units
+constexpr int64_t kAttnMostWgs = 2560;    // workgroups of a launch whose heads are split
 constexpr int64_t kAttnGroupTargetWgs = 256;
 // Workgroups that the scoring kernel that filters aims at: several rounds of short ones follow the plain kernel's order
 // through the cache (4 x 8 KV heads, 131072 rows: 2048 workgroups 72.5 us, 4096 69.7, 8192 67.2, one block each 71.9), but
@@ -18,29 +19,64 @@ constexpr int64_t kAttnMinTiles = 2;      // a workgroup is worth its hand-over 
 
 // `want` splits or a few less: as many as equal shares of whole granules make
 static AttnPlan split_plan(int64_t max_rows, int64_t want, int granule) {
-  AttnPlan p{1, static_cast<int>(want)};
+  AttnPlan p{1, static_cast<int>(want), 1};
   int64_t rows = (max_rows + want - 1) / want;
   rows = (rows + granule - 1) / granule * granule;
   p.nsplit = static_cast<int>((max_rows + rows - 1) / rows);
   return p;
 }
 
-AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg) {
-  if (max_rows <= 0 || units <= 0) return AttnPlan{1, 1};
-  // Aim for two workgroups per compute unit (256 CUs): the gathers of the whole chip are in
-  // flight together, and fewer, longer workgroups mean fewer partials to hand over (measured
-  // best across the five configurations; 1024 was 1 µs slower on the smallest and 2 µs on the
-  // largest).
-  int64_t want = (kAttnTargetWgs + units - 1) / units;
-  const int64_t most = max_rows / (kAttnMinTiles * tile_rows_per_wg);
-  if (want > most) want = most;
-  if (want < 1) want = 1;
-  return split_plan(max_rows, want, tile_rows_per_wg / kAttnLoadsPerTile);
+// Splits per head.  A launch lasts as long as the compute unit with the most workgroups, each costing its rows and a start that
+// is worth kStart tiles, so that many splits pay where they even out the last round; every split costs the head's last
+// workgroup kHandOver tiles; one workgroup a compute unit does not keep enough gathers in flight (kAlone), and splits in shares, one
+// per XCD, read a fifth less from beyond their L2 (kShares).  bf16, D = 128, us with 512 / units splits rounded up, and now:
+// 3 x 32 heads on 8, 2433 rows 23.6 and 21.1 (6 splits put a third workgroup on a quarter of the compute units); 5 x 32, 3000 rows
+// 46.1 and 41.2; 14 x 32, 700 rows 27.9 and 24.0; 10 x 64, 3000 rows 119 and 108 (two instead of one); 22 x 8 on 1 50.6 and 37.7 (8
+// instead of 3: shares); fp32 3 x 32, 2400 rows 44.5 and 38.4.  Over 179 shapes of 8 to 960 heads, 200 to 12000 rows, both types
+// and sizes of head, the choice is 0.7% off the best of the numbers tried on average (512 / units: 6.4%), and at most 3.5% behind it.
+AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool shares) {
+  constexpr double kStart = 1.6, kHandOver = 0.1, kAlone = 1.6, kShares = 0.8;
+  if (max_rows <= 0 || units <= 0) return AttnPlan{1, 1, 1};
+  const int64_t most = std::max<int64_t>(1, std::min(max_rows / (kAttnMinTiles * tile_rows_per_wg), kAttnMostWgs / units));
+  int64_t want = 1;
+  double least = INFINITY;
+  auto consider = [&](int64_t n) {
+    const int64_t rounds = (units * n + kAttnCus - 1) / kAttnCus;
+    double cost = static_cast<double>(rounds) * (static_cast<double>(max_rows) / static_cast<double>(n) + kStart * tile_rows_per_wg);
+    if (rounds == 1) cost *= kAlone;
+    if (shares && n % kXcds == 0) cost *= kShares;
+    cost += kHandOver * static_cast<double>(n * tile_rows_per_wg);
+    if (cost < least) {
+      least = cost;
+      want = n;
+    }
+  };
+  consider(1);
+  for (int64_t rounds = 1; rounds * kAttnCus <= kAttnMostWgs; ++rounds) {  // as many splits as these rounds hold
+    const int64_t n = std::min(rounds * kAttnCus / units, most);
+    if (n > 1) consider(n);
+    if (shares && n > kXcds) consider(n / kXcds * kXcds);
+  }
+  AttnPlan p = split_plan(max_rows, want, tile_rows_per_wg / kAttnLoadsPerTile);
+  p.max_split = static_cast<int>(most);
+  p.least = std::min(p.nsplit, static_cast<int>((2 * kAttnCus + units - 1) / units));
+  return p;
+}
+// A workspace that was made for a list of some rows and is used for a few more (a dense tail) may have room for fewer splits than
+// these would get: it serves with those, down to the two workgroups a compute unit that every such workspace holds.
+static bool fit_splits(const tb_cache_desc* d, AttnPlan& p, size_t ws_bytes) {
+  const int64_t units = static_cast<int64_t>(d->B) * d->Hq;
+  while (p.nsplit > p.least && ws_bytes < ws_layout(units, d->D, p.nsplit).total) --p.nsplit;
+  return ws_bytes >= ws_layout(units, d->D, p.nsplit).total;
+}
+// (the buffered form is planned alike, so that it adds up in the same order)
+static AttnPlan attn_plan(const tb_cache_desc* d, int64_t max_rows) {
+  return attn_plan(static_cast<int64_t>(d->B) * d->Hq, max_rows, attn_tile_rows_per_wg(d->dtype, d->D), attn_in_shares(d));
 }
 
 AttnPlan attn_group_plan(const tb_cache_desc* d, int64_t max_rows) {
   const int64_t groups = static_cast<int64_t>(d->B) * d->Hkv;
-  if (max_rows <= 0 || groups <= 0 || !attn_group_mfma(d)) return attn_plan(groups, max_rows, attn_tile_rows_per_wg(d->dtype, d->D));
+  if (max_rows <= 0 || groups <= 0 || !attn_group_mfma(d)) return attn_plan(groups, max_rows, attn_tile_rows_per_wg(d->dtype, d->D), false);
   // On the matrix cores: 8 waves of 32 rows a step, up to one such workgroup per compute unit (the same
   // rows in flight as two of 4 waves, half the partials to combine).  A compute unit holds one of them at D = 128,
   // so a few more than compute units would take a second round (g = 4, D = 128, 3300 rows, attention alone:
@@ -388,18 +424,18 @@ tb_status sparse_attn(const tb_cache_desc* d, const void* q, const void* K, cons
   if (units == 0) return TB_OK;
   const int64_t rows = max_count + (tail_end - tail_begin);
   const bool grouped = shared_list && attn_shared_list_grouped(d, rows);
-  const AttnPlan by_head = attn_plan(units, rows, attn_tile_rows_per_wg(d->dtype, d->D));
+  const AttnPlan by_head = attn_plan(d, rows);
   AttnPlan plan = grouped ? attn_group_plan(d, rows) : by_head;
   if (!ws || !aligned16(ws)) return TB_ERR_WORKSPACE;
   if (grouped && attn_group_mfma(d)) {
     // where a workgroup per KV group splits finer than the forms that such a shape asked room for before it
     // (per head, or one split a group), a workspace of that size still serves, with fewer splits
     const int64_t groups = static_cast<int64_t>(d->B) * d->Hkv;
-    const int least = groups > kAttnGroupTargetWgs ? 1 : (groups < 32 ? by_head.nsplit : plan.nsplit);
-    while (plan.nsplit > least && ws_bytes < ws_layout(units, d->D, plan.nsplit).total) --plan.nsplit;
+    const int least = groups > kAttnGroupTargetWgs ? 1 : (groups < 32 ? by_head.least : plan.nsplit);
+    plan.least = std::min(plan.nsplit, least);
   }
+  if (!fit_splits(d, plan, ws_bytes)) return TB_ERR_WORKSPACE;
   const WsLayout w = ws_layout(units, d->D, plan.nsplit);
-  if (ws_bytes < w.total) return TB_ERR_WORKSPACE;
   AttnLaunch L{d,   q,   K,   V,
                idx, count, idx_cap, max_count, tail_begin, tail_end,
                sm_scale, out, lse,
@@ -434,9 +470,9 @@ tb_status tb_sparse_decode_attn_static(const tb_cache_desc* d, const void* q, co
   TB_TRY(check_attn_args(d, q, K, V, idx, count, idx_cap, max_count, tail_begin, tail_end, out));
   const int64_t units = static_cast<int64_t>(d->B) * d->Hq;
   if (units == 0) return TB_OK;
-  const AttnPlan plan = attn_plan(units, max_count + (tail_end - tail_begin), attn_tile_rows_per_wg(d->dtype, d->D));
+  AttnPlan plan = attn_plan(d, max_count + (tail_end - tail_begin));
+  if (!fit_splits(d, plan, kStaticScratchBytes)) return TB_ERR_WORKSPACE;  // beyond the library's own scratch
   const WsLayout w = ws_layout(units, d->D, plan.nsplit);
-  if (w.total > kStaticScratchBytes) return TB_ERR_WORKSPACE;  // beyond the library's own scratch
   void* ws = nullptr;
   TB_TRY(static_scratch(&ws));
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -520,9 +556,9 @@ tb_status buffered_attn(const tb_cache_desc* d, const void* q, const void* Kbuf,
                          static_cast<hipStream_t>(stream));
   }
   const int64_t rows = max_count + (tail_end - tail_begin);
-  const AttnPlan plan = attn_plan(units, rows, attn_tile_rows_per_wg(d->dtype, d->D));
+  AttnPlan plan = attn_plan(d, rows);
+  if (!ws || !aligned16(ws) || !fit_splits(d, plan, ws_bytes)) return TB_ERR_WORKSPACE;
   const WsLayout w = ws_layout(units, d->D, plan.nsplit);
-  if (!ws || !aligned16(ws) || ws_bytes < w.total) return TB_ERR_WORKSPACE;
   AttnLaunch L{d,   q,   K,   V,
                nullptr, count, buf_cap, max_count, tail_begin, tail_end,
                sm_scale, out, lse,
@@ -588,9 +624,9 @@ tb_status tb_decode_step(const tb_cache_desc* d, const void* q_imp, const void* 
   TB_TRY(check_attn_args(d, q, K, V, idx, count, idx_cap, p.count, 0, 0, out));
   const int64_t units = static_cast<int64_t>(d->B) * d->Hq;
   if (units == 0) return TB_OK;
-  const AttnPlan plan = attn_plan(units, p.count, attn_tile_rows_per_wg(d->dtype, d->D));
+  AttnPlan plan = attn_plan(d, p.count);
+  if (!ws || !aligned16(ws) || !fit_splits(d, plan, ws_bytes)) return TB_ERR_WORKSPACE;
   const WsLayout w = ws_layout(units, d->D, plan.nsplit);
-  if (!ws || !aligned16(ws) || ws_bytes < w.total) return TB_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   ScoreLaunch S{d, q_imp, Kimp, score_scale, scores, score_stride};
 
@@ -632,7 +668,7 @@ size_t tb_workspace_bytes(int32_t op, const tb_cache_desc* d, int64_t max_count)
   const size_t sel_total = sel ? ws_layout(units, d->D, 1).part_off + align_up(sel, 256) : 0;
   if (op == TB_OP_SELECT) return sel_total;
   if (op == TB_OP_ATTN || op == TB_OP_DECODE_STEP) {
-    const AttnPlan plan = attn_plan(units, max_count, attn_tile_rows_per_wg(d->dtype, d->D));
+    const AttnPlan plan = attn_plan(d, max_count);
     // sized for the largest split count a shorter list could get, so that one workspace serves
     // every call whose list is no longer than max_count
     size_t att = ws_layout(units, d->D, plan.max_split).total;

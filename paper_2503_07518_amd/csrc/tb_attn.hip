@@ -47,7 +47,6 @@
 namespace tb {
 namespace {
 
-constexpr int kXcds = 8;  // accelerator complex dies of the chip, each with its own L2
 constexpr int kGroupWaves = kAttnGroupWaves;  // of a workgroup that serves a KV group on the matrix cores
 // occupancy the register allocation is held to: 4 waves per SIMD = 4 workgroups per CU, so that a
 // launch of up to 1024 workgroups is resident at once (no second round of workgroups)
@@ -868,7 +867,7 @@ tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
   a.shared_list = L.shared_list ? 1 : 0;
   a.n_kv_groups = d.B * d.Hkv;
   // per-XCD placement pays when heads share KV rows and the KV groups spread evenly over the XCDs
-  a.xcd_map = (a.g > 1 && (a.n_kv_groups % kXcds == 0 || a.n_kv_groups >= 8 * kXcds)) ? 1 : 0;
+  a.xcd_map = attn_on_one_xcd(&d) ? 1 : 0;
   if (L.grouped) {  // the plan was made for one workgroup per KV group
     if (a.g == 2) return launch_group<T, D, 2>(a, L, st);
     if (a.g == 4) return launch_group<T, D, 4>(a, L, st);
@@ -877,7 +876,7 @@ tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
   }
   dim3 grid(L.plan.nsplit, d.Hq, d.B);
   if (a.xcd_map) grid = dim3(static_cast<unsigned>(kXcds * ((a.n_kv_groups + kXcds - 1) / kXcds) * a.g * a.nsplit));
-  const bool shares = a.g > 1 && !a.xcd_map && a.nsplit % kXcds == 0;
+  const bool shares = attn_in_shares(&d) && a.nsplit % kXcds == 0;
   // (per-head buffers share no rows: non-temporal whatever the size; against loads that the caches keep, an interval of 2 x 32 heads,
   // 2816 rows a head, 418 and 407 us, of 4 x 32 heads, 9400 rows 1340 and 1209, of 8 heads, 1000 rows no difference)
   if (L.Kbuf && shares)

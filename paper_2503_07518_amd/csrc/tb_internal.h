@@ -28,9 +28,20 @@ struct WsLayout {
 struct AttnPlan {
   int nsplit;     // workgroups per (b,h): the tiles of its list go round them
   int max_split;  // upper bound of nsplit for any list no longer than the one planned for
+  int least;      // splits that a smaller workspace may bring it down to
 };
 
-AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg);
+constexpr int kXcds = 8;  // accelerator complex dies of the chip, each with its own L2
+// With grouped queries the heads of a KV group are placed on one XCD where the groups spread evenly over the XCDs; elsewhere their
+// lists are cut into one share per XCD, if there are enough splits.
+inline bool attn_on_one_xcd(const tb_cache_desc* d) {
+  const int64_t groups = static_cast<int64_t>(d->B) * d->Hkv;
+  return d->Hq > d->Hkv && (groups % kXcds == 0 || groups >= 8 * kXcds);
+}
+inline bool attn_in_shares(const tb_cache_desc* d) { return d->Hq > d->Hkv && !attn_on_one_xcd(d); }
+
+// `shares`: splits in multiples of the number of XCDs are one share of the list each
+AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool shares);
 // A shared list's KV groups of four heads and more, bf16, are served on the matrix cores.
 inline bool attn_group_mfma(const tb_cache_desc* d) { return d->dtype == TB_BF16 && d->Hq >= 4 * d->Hkv; }
 AttnPlan attn_group_plan(const tb_cache_desc* d, int64_t max_rows);

@@ -579,6 +579,36 @@ def test_attn_strided_cache_and_max_count_truncation(oracle):
     assert_attention(np_of(out), ro, "bf16", np_of(lse), rl)
 
 
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,D,N,rows", [
+    (torch.bfloat16, 3, 32, 8, 128, 3000, 1100),   # 5 splits, 480 workgroups
+    (torch.bfloat16, 22, 8, 1, 128, 1500, 1030),   # shares of a list on more heads than half the compute units
+    (torch.bfloat16, 9, 32, 8, 64, 2500, 2049),    # more heads than compute units, split
+    (torch.float32, 20, 16, 4, 128, 700, 640),
+    (torch.float32, 1, 4, 4, 64, 400, 385),
+    (torch.bfloat16, 41, 64, 8, 64, 300, 257),     # one split a head, several rounds
+])
+def test_attn_split_counts(oracle, dtype, B, Hq, Hkv, D, N, rows):
+    """Numbers of heads either side of the compute units and of whole rounds of them: full lists, a list that ends before most
+    splits begin, one entry, an empty one; one workspace for every length."""
+    say(f"attn split counts dtype={dtype} B={B} Hq={Hq} Hkv={Hkv} D={D} N={N} rows={rows}")
+    dn, sm, g = "f32" if dtype == torch.float32 else "bf16", 1 / math.sqrt(D), Hq // Hkv
+    q, K, V = randn((B, Hq, D), dtype, 51), randn((B, Hkv, N, D), dtype, 52), randn((B, Hkv, N, D), dtype, 53)
+    gen = torch.Generator().manual_seed(54)
+    idx = torch.rand((B, Hq, N), generator=gen).topk(rows, dim=-1).indices.sort(-1).values.to(torch.int32)
+    from paper_2503_07518_amd import binding as tb
+    ws = tb.new_workspace(tb.TB_OP_ATTN, tb.make_desc(N, Hq, K=K, V=V), rows)
+    for most in (rows, rows // 3, 70):
+        cnt = torch.full((B, Hq), most, dtype=torch.int32)
+        cnt[0, 0], cnt[0, 1], cnt[-1, -1] = 0, 1, min(65, most)
+        out, lse = gpu_attn(q, K, V, idx.to(DEV), cnt.to(DEV), N, sm, max_count=most, ws=ws)
+        torch.cuda.synchronize()
+        for b, h in {(0, 0), (0, 1), (0, Hq - 1), (B // 2, Hq // 2), (B - 1, 0), (B - 1, Hq - 1)}:
+            ro, rl = oracle.sparse_decode_attn(np_of(q[b:b + 1, h:h + 1]), np_of(K[b:b + 1, h // g:h // g + 1]), np_of(V[b:b + 1, h // g:h // g + 1]),
+                                               idx[b:b + 1, h:h + 1].numpy(), cnt[b:b + 1, h:h + 1].numpy(), dn, sm)
+            assert_attention(np_of(out[b, h]), ro[0, 0], dn, np_of(lse[b, h]), rl[0, 0])
+        assert bool(torch.isfinite(out).all())
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,N,k", [(1, 32, 8, 32768, 3277), (16, 32, 8, 16384, 2048)])
 def test_attn_split_handover_repeatable(oracle, B, Hq, Hkv, N, k):
     """The split attention hands partial results from workgroup to workgroup (last arriver
