@@ -67,7 +67,7 @@ struct AttnArgs {
   float* partials;  // of the splits: accumulators [units][nsplit][D], then (max, sum) pairs [units][nsplit]
   int64_t pairs_off;  // floats before the pairs
   uint32_t* counters;
-  int32_t Hq, g, nsplit, n_kv_groups, xcd_map;
+  int32_t Hq, Hkv, g, nsplit, n_kv_groups, xcd_map;
   int32_t shared_list;  // one list and count per batch element, read by all of its heads
   // buffered form: the listed rows have been copied to per-query-head buffers
   // [B][Hq][buf_cap][D] in list order (slot i of the list is buffer row i); idx is unused
@@ -81,6 +81,12 @@ struct AttnArgs {
   int64_t new_from_b[2], new_from_h[2], new_to_b[2], new_to_h[2];  // strides in bytes
   int32_t new_row;
 };
+
+// Asks for the lines of the kernel's arguments together.  A line is a trip to memory the first time that a compute unit
+// reads it, and left alone the compiler reads each where it is first used, one trip behind the other.
+__device__ __forceinline__ void fetch_args(const AttnArgs& a) {
+  asm volatile("" ::"s"(a.q), "s"(a.tail_end), "s"(a.out), "s"(a.g), "s"(a.xcd_map));
+}
 
 constexpr int32_t kTailFlag = 0x40000000;  // buffered form: the row number refers to the cache, not the buffer
 
@@ -126,6 +132,7 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   __shared__ __attribute__((aligned(16))) float s_acc[kAttnWaves][1][D];
   __shared__ uint32_t s_last;
 
+  fetch_args(a);
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = wave_id();
@@ -137,16 +144,13 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   // k lives on XCD k % 8; slot s of an XCD is (its k-th group, head of the group, split).  (If
   // the hardware places workgroups differently, the mapping is just another order of the work.)
   int split, h, b, hkv;
-  if (a.xcd_map) {
-    const int per_group = a.g * a.nsplit;
-    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    const int kvg = xcd + kXcds * (slot / per_group);
+  if (a.xcd_map) {  // (XCD, split, its k-th group's heads)
+    const int k = blockIdx.z / a.g, kvg = blockIdx.x + kXcds * k;
     if (kvg >= a.n_kv_groups) return;  // the last round of groups does not fill all XCDs
-    const int within = slot % per_group;
-    split = within % a.nsplit;
-    hkv = kvg % (a.Hq / a.g);
-    b = kvg / (a.Hq / a.g);
-    h = hkv * a.g + within / a.nsplit;
+    split = blockIdx.y;
+    b = kvg / a.Hkv;
+    hkv = kvg - b * a.Hkv;
+    h = hkv * a.g + (blockIdx.z - k * a.g);
   } else {
     split = blockIdx.x;
     h = blockIdx.y;
@@ -167,7 +171,6 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   const uint32_t k_row_bytes = static_cast<uint32_t>(a.k_stride_n * sizeof(T));
   const uint32_t v_row_bytes = static_cast<uint32_t>(a.v_stride_n * sizeof(T));
   const int64_t lu = (!BUF && a.shared_list) ? b : u;  // which list this head reads
-  const int32_t* list = BUF ? nullptr : a.idx + lu * a.idx_cap;
   const char* kbuf = nullptr;
   const char* vbuf = nullptr;
   if (BUF) {
@@ -191,52 +194,44 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   RowSoftmax<T, D> rows;
   rows.init(static_cast<const T*>(a.q) + u * D + sub * EPL, a.sm_scale_log2);
 
-  // row numbers of a tile: lanes 0..TILE-1 fetch one entry each (selected list, then the
-  // dense tail); -1 marks a slot past the end.  The next tile's entries are fetched while the
-  // current tile is being processed.
-  auto fetch_rows = [&](int64_t t0) -> int32_t {
-    const int64_t i = t0 + lane;
-    if (lane < TILE && i < total) {
-      if (BUF) {  // slot i of the list is row i of the buffer; the tail is read from the cache
-        if (i < cnt) return static_cast<int32_t>(i);
-        const int64_t n = a.tail_begin + (i - cnt);
-        return static_cast<int32_t>(n < 0 ? 0 : (n >= a.N ? a.N - 1 : n)) | kTailFlag;
-      }
-      int64_t n = (i < cnt) ? static_cast<int64_t>(list[i]) : a.tail_begin + (i - cnt);
-      n = n < 0 ? 0 : (n >= a.N ? a.N - 1 : n);  // keep the gather inside the cache whatever the list holds
-      return static_cast<int32_t>(n);
-    }
-    return -1;
+  // Row numbers of a tile: lane i (modulo the tile) has slot i, an entry of the selected list, then of the dense tail; -1
+  // marks a slot past the end.  An entry is read without waiting for the count or asking whether there is one (clamped into the
+  // list's capacity), ahead of the gathers of the tile before, and looked at when its own tile begins: read under a condition it
+  // was waited for on the spot, and with it every gather of the tile before.  With the arguments and the first entries fetched
+  // together: steps of 32 heads on 8, 3277 of 32768 rows 27.9 -> 27.2 us, 16 x 32, 2048 of 16384 118.1 -> 116.1, 3 x 32, 2433 of 20011
+  // 35.9 -> 34.6; an interval of 8 steps of 4 x 32 heads, 65536 rows 823 -> 814.
+  const int64_t last_slot = a.idx_cap > 0 ? a.idx_cap - 1 : 0;
+  const int32_t* entries = BUF ? nullptr : (a.idx_cap > 0 ? a.idx + lu * a.idx_cap : a.count);
+  auto fetch_entry = [&](int64_t t0) -> int32_t {
+    if (BUF) return 0;  // slot i of the list is row i of the buffer
+    const int64_t i = t0 + (lane & (TILE - 1));
+    return entries[i < last_slot ? i : last_slot];
   };
-  int32_t n_next;
-  if (BUF || SHARES) {
-    int64_t cnt_now = a.count[lu];
-    cnt_now = cnt_now < 0 ? 0 : (cnt_now > a.max_count ? a.max_count : cnt_now);
-    cnt = cnt_now;
-    total = cnt + (a.tail_end - a.tail_begin);
-    if (SHARES) {  // whole tiles per XCD
-      const int64_t share = (total + kXcds * TILE - 1) / (kXcds * TILE) * TILE, beg = (split % kXcds) * share;
-      w_beg = beg + static_cast<int64_t>(split / kXcds * kAttnWaves + wave) * TILE;
-      stride = static_cast<int64_t>(a.nsplit / kXcds) * kAttnWaves * TILE;
-      total = min(total, beg + share);
-    }
-    n_next = fetch_rows(w_beg);
-  } else {
-    // first tile: the list entry is read without waiting for the count (the slot is inside
-    // the list's capacity whatever the count is) and sorted out afterwards
-    const int64_t i = w_beg + lane;
-    const int64_t i_safe = (i < a.idx_cap) ? i : (a.idx_cap > 0 ? a.idx_cap - 1 : 0);
-    const int32_t raw = (lane < TILE && a.idx_cap > 0) ? list[i_safe] : 0;
-    int64_t cnt_now = a.count[lu];
-    cnt_now = cnt_now < 0 ? 0 : (cnt_now > a.max_count ? a.max_count : cnt_now);
-    cnt = cnt_now;
-    total = cnt + (a.tail_end - a.tail_begin);
-    int64_t n = (i < cnt) ? static_cast<int64_t>(raw) : a.tail_begin + (i - cnt);
-    n = n < 0 ? 0 : (n >= a.N ? a.N - 1 : n);
-    n_next = (lane < TILE && i < total) ? static_cast<int32_t>(n) : -1;
+  auto row_at = [&](int64_t t0, int32_t entry) -> int32_t {
+    const int64_t i = t0 + (lane & (TILE - 1));
+    int64_t n = i < cnt ? static_cast<int64_t>(entry) : a.tail_begin + (i - cnt);
+    n = n < 0 ? 0 : (n >= a.N ? a.N - 1 : n);  // keep the gather inside the cache whatever the list holds
+    int32_t row = static_cast<int32_t>(n);
+    if (BUF) row = i < cnt ? static_cast<int32_t>(i) : row | kTailFlag;  // (the tail is read from the cache)
+    return i < total ? row : -1;
+  };
+  int32_t entry = 0;
+  const int32_t cnt_read = a.count[lu];
+  if (!SHARES) entry = fetch_entry(w_beg);
+  __builtin_amdgcn_sched_barrier(0);  // query, count and entries come in one trip to memory
+  cnt = cnt_read < 0 ? 0 : (cnt_read > a.max_count ? a.max_count : cnt_read);
+  total = cnt + (a.tail_end - a.tail_begin);
+  if (SHARES) {  // whole tiles per XCD
+    const int64_t share = (total + kXcds * TILE - 1) / (kXcds * TILE) * TILE, beg = (split % kXcds) * share;
+    w_beg = beg + static_cast<int64_t>(split / kXcds * kAttnWaves + wave) * TILE;
+    stride = static_cast<int64_t>(a.nsplit / kXcds) * kAttnWaves * TILE;
+    total = min(total, beg + share);
+    entry = fetch_entry(w_beg);
   }
   for (int64_t t0 = w_beg; t0 < total; t0 += stride) {
-    const int32_t n_mine = n_next;
+    const int32_t n_mine = row_at(t0, entry);
+    entry = fetch_entry(t0 + stride);
+    __builtin_amdgcn_sched_barrier(0);
     typename Pack16<T>::Raw kraw[kLoadsPerTile], vraw[kLoadsPerTile];  // kept packed until used
     bool valid[kLoadsPerTile];
 #pragma unroll
@@ -262,7 +257,6 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
         vraw[t] = Pack16<T>::template load_raw<NT>(vbase + row * v_row_bytes);
       }
     }
-    n_next = fetch_rows(t0 + stride);
     // every gather of the tile is in flight before the first one is consumed
     __builtin_amdgcn_sched_barrier(0);
     rows.consume(kraw, vraw, valid);
@@ -841,6 +835,7 @@ tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
   a.pairs_off = static_cast<int64_t>(d.B) * d.Hq * L.plan.nsplit * D;
   a.counters = L.counters;
   a.Hq = d.Hq;
+  a.Hkv = d.Hkv;
   a.g = d.Hq / d.Hkv;
   a.nsplit = L.plan.nsplit;
   a.Kbuf = L.Kbuf;
@@ -867,7 +862,8 @@ tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
   a.shared_list = L.shared_list ? 1 : 0;
   a.n_kv_groups = d.B * d.Hkv;
   // per-XCD placement pays when heads share KV rows and the KV groups spread evenly over the XCDs
-  a.xcd_map = attn_on_one_xcd(&d) ? 1 : 0;
+  const int64_t heads_per_xcd = (static_cast<int64_t>(a.n_kv_groups) + kXcds - 1) / kXcds * a.g;
+  a.xcd_map = attn_on_one_xcd(&d) && heads_per_xcd <= 65535 ? 1 : 0;  // (of a grid's third number)
   if (L.grouped) {  // the plan was made for one workgroup per KV group
     if (a.g == 2) return launch_group<T, D, 2>(a, L, st);
     if (a.g == 4) return launch_group<T, D, 4>(a, L, st);
@@ -875,7 +871,7 @@ tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
     return TB_ERR_UNSUPPORTED;
   }
   dim3 grid(L.plan.nsplit, d.Hq, d.B);
-  if (a.xcd_map) grid = dim3(static_cast<unsigned>(kXcds * ((a.n_kv_groups + kXcds - 1) / kXcds) * a.g * a.nsplit));
+  if (a.xcd_map) grid = dim3(kXcds, a.nsplit, static_cast<unsigned>(heads_per_xcd));
   const bool shares = attn_in_shares(&d) && a.nsplit % kXcds == 0;
   // (per-head buffers share no rows: non-temporal whatever the size; against loads that the caches keep, an interval of 2 x 32 heads,
   // 2816 rows a head, 418 and 407 us, of 4 x 32 heads, 9400 rows 1340 and 1209, of 8 heads, 1000 rows no difference)
