@@ -191,6 +191,17 @@ tb_status tb_append_buffered_decode_attn(const tb_cache_desc* src, const void* K
                                          int64_t dst_row, int64_t tail_begin, int64_t tail_end, float sm_scale,
                                          float* out, float* lse, void* ws, size_t ws_bytes, void* stream);
 
+/* tb_gather_important of the lists, from the cache src, K_src, V_src into the buffers, then (src_row >= 0) tb_append_kv of one row
+ * into row dst_row of the cache desc, K, V, then tb_buffered_decode_attn over buffers (max_count: the lists', no more than
+ * buf_cap) and cache, in one launch: a listed row is attended to on its way into its buffer.  Arguments and results are those of
+ * the calls; src and desc agree in all but N and strides. */
+tb_status tb_migrate_buffered_decode_attn(const tb_cache_desc* src, const void* K_src, const void* V_src, const int32_t* idx,
+                                          const int32_t* count, int64_t idx_cap, int64_t max_count, int32_t skip_front, int32_t skip_back,
+                                          int32_t* count_out, int64_t src_row, const tb_cache_desc* desc, const void* q, void* Kbuf,
+                                          void* Vbuf, int64_t buf_cap, void* K, void* V, int64_t dst_row, int64_t tail_begin,
+                                          int64_t tail_end, float sm_scale, float* out, float* lse, void* ws, size_t ws_bytes,
+                                          void* stream);
+
 /* One prediction step in a single enqueue: tb_score -> tb_select_topk -> tb_sparse_decode_attn
  * with one validation pass and one launch plan.  Results (scores, idx, count, out, lse) are
  * identical to calling the three entry points one after the other.

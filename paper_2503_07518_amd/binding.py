@@ -23,7 +23,7 @@ TB_OP_SELECT, TB_OP_ATTN, TB_OP_DECODE_STEP = 1, 2, 3
 EXPORTS = (
     "tb_project_keys", "tb_score", "tb_select_topk", "tb_expand_neighbors", "tb_sparse_decode_attn",
     "tb_sparse_decode_attn_shared", "tb_sparse_decode_attn_static",
-    "tb_gather_kv", "tb_gather_important", "tb_append_kv", "tb_buffered_decode_attn", "tb_append_buffered_decode_attn", "tb_predict_queries", "tb_decode_step", "tb_workspace_bytes", "tb_workspace_init", "tb_read_stream_probe", "tb_status_string", "tb_version",
+    "tb_gather_kv", "tb_gather_important", "tb_append_kv", "tb_buffered_decode_attn", "tb_append_buffered_decode_attn", "tb_migrate_buffered_decode_attn", "tb_predict_queries", "tb_decode_step", "tb_workspace_bytes", "tb_workspace_init", "tb_read_stream_probe", "tb_status_string", "tb_version",
 )
 
 
@@ -79,6 +79,8 @@ def load_library() -> ctypes.CDLL:
     L.tb_append_kv.argtypes = [dp, vp, vp, i64, dp, vp, vp, i64, i64, vp]
     L.tb_buffered_decode_attn.argtypes = [dp, vp, vp, vp, i64, vp, i64, vp, vp, i64, i64, f32, vp, vp, vp, sz, vp]
     L.tb_append_buffered_decode_attn.argtypes = [dp, vp, vp, i64, dp, vp, vp, vp, i64, vp, i64, vp, vp, i64, i64, i64, f32, vp, vp, vp, sz, vp]
+    L.tb_migrate_buffered_decode_attn.argtypes = [dp, vp, vp, vp, vp, i64, i64, i32, i32, vp, i64, dp, vp, vp, vp, i64, vp, vp, i64, i64, i64, f32, vp, vp, vp,
+                                                  sz, vp]
     L.tb_predict_queries.argtypes = [ctypes.POINTER(tb_predictor_desc), i32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
     L.tb_workspace_bytes.argtypes = [i32, dp, i64]
     L.tb_workspace_bytes.restype = sz
@@ -251,6 +253,18 @@ def tb_append_buffered_decode_attn(src, K_src, V_src, src_row: int, desc, q, Kbu
                                                          dst_row, tail_begin, tail_end, sm_scale, _ptr(out), _ptr(lse), _ptr(ws),
                                                          ws.numel() * ws.element_size(), _stream(stream)),
            "tb_append_buffered_decode_attn")
+
+
+def tb_migrate_buffered_decode_attn(src, K_src, V_src, idx, count, max_count: int, skip_front: int, skip_back: int, count_out, src_row: int, desc, q,
+                                    Kbuf, Vbuf, K, V, dst_row: int, sm_scale: float, out, lse, ws, tail_begin: int = 0, tail_end: int = 0,
+                                    stream=None) -> None:
+    """tb_gather_important of the lists into the buffers, (src_row >= 0) tb_append_kv of one row into row dst_row of the cache K, V, and
+    tb_buffered_decode_attn over both, in one launch."""
+    assert Kbuf.is_contiguous() and Vbuf.is_contiguous() and Kbuf.shape == Vbuf.shape
+    _check(load_library().tb_migrate_buffered_decode_attn(
+        ctypes.byref(src), _ptr(K_src), _ptr(V_src), _ptr(idx), _ptr(count), idx.stride(-2), max_count, skip_front, skip_back, _ptr(count_out), src_row,
+        ctypes.byref(desc), _ptr(q), _ptr(Kbuf), _ptr(Vbuf), Kbuf.shape[2], _ptr(K), _ptr(V), dst_row, tail_begin, tail_end, sm_scale, _ptr(out),
+        _ptr(lse), _ptr(ws), ws.numel() * ws.element_size(), _stream(stream)), "tb_migrate_buffered_decode_attn")
 
 
 def tb_predict_queries(h, gamma, beta, W1, b1, W2, b2, G: int, Hq: int, Dimp: int, hidden_act, ln_act, q_imp,

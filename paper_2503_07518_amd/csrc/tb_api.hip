@@ -502,10 +502,10 @@ tb_status tb_gather_kv(const tb_cache_desc* d, const void* K, const void* V, con
   return launch_gather(L, static_cast<hipStream_t>(stream));
 }
 
-tb_status tb_gather_important(const tb_cache_desc* d, const void* K, const void* V, const int32_t* idx,
-                              const int32_t* count, int64_t idx_cap, int64_t max_count, int32_t skip_front,
-                              int32_t skip_back, void* Kbuf, void* Vbuf, int64_t buf_cap, int32_t* count_out,
-                              void* stream) {
+namespace {
+tb_status check_gather(const tb_cache_desc* d, const void* K, const void* V, const int32_t* idx, const int32_t* count, int64_t idx_cap,
+                       int64_t max_count, int32_t skip_front, int32_t skip_back, void* Kbuf, void* Vbuf, int64_t buf_cap, int32_t* count_out,
+                       GatherLaunch& L) {
   TB_TRY(check_desc(d));
   if (!K || !V || !idx || !count || !Kbuf || !Vbuf || !count_out) return TB_ERR_INVALID_ARG;
   if (idx_cap < 0 || max_count < 0 || max_count > idx_cap || skip_front < 0 || skip_back < 0) return TB_ERR_INVALID_ARG;
@@ -516,10 +516,17 @@ tb_status tb_gather_important(const tb_cache_desc* d, const void* K, const void*
   TB_TRY(check_strides(d, d->v_stride_b, d->v_stride_h, d->v_stride_n, d->D));
   if (!aligned16(K) || !aligned16(V) || !aligned16(Kbuf) || !aligned16(Vbuf)) return TB_ERR_UNSUPPORTED;
   if (max_count > (int64_t{1} << 30)) return TB_ERR_UNSUPPORTED;
-  GatherLaunch L{d, K, V, idx, count, idx_cap, max_count, Kbuf, Vbuf, buf_cap};
-  L.skip_front = skip_front;
-  L.skip_back = skip_back;
-  L.count_out = count_out;
+  L = GatherLaunch{d, K, V, idx, count, idx_cap, max_count, Kbuf, Vbuf, buf_cap, skip_front, skip_back, count_out};
+  return TB_OK;
+}
+}  // namespace
+
+tb_status tb_gather_important(const tb_cache_desc* d, const void* K, const void* V, const int32_t* idx,
+                              const int32_t* count, int64_t idx_cap, int64_t max_count, int32_t skip_front,
+                              int32_t skip_back, void* Kbuf, void* Vbuf, int64_t buf_cap, int32_t* count_out,
+                              void* stream) {
+  GatherLaunch L;
+  TB_TRY(check_gather(d, K, V, idx, count, idx_cap, max_count, skip_front, skip_back, Kbuf, Vbuf, buf_cap, count_out, L));
   return launch_gather(L, static_cast<hipStream_t>(stream));
 }
 
@@ -542,7 +549,7 @@ tb_status check_append(const tb_cache_desc* src, const void* K, const void* V, i
 
 tb_status buffered_attn(const tb_cache_desc* d, const void* q, const void* Kbuf, const void* Vbuf, int64_t buf_cap, const int32_t* count,
                         int64_t max_count, const void* K, const void* V, int64_t tail_begin, int64_t tail_end, float sm_scale, float* out,
-                        float* lse, void* ws, size_t ws_bytes, void* stream, const NewRow* append) {
+                        float* lse, void* ws, size_t ws_bytes, void* stream, const NewRow* append, const GatherLaunch* migrate = nullptr) {
   if (!Kbuf || !Vbuf || buf_cap < 0 || max_count > buf_cap) return TB_ERR_INVALID_ARG;
   // the list itself is not read: its place in the argument check is taken by the count array
   TB_TRY(check_attn_args(d, q, K, V, count, count, buf_cap, max_count, tail_begin, tail_end, out));
@@ -568,6 +575,7 @@ tb_status buffered_attn(const tb_cache_desc* d, const void* q, const void* Kbuf,
   L.Vbuf = Vbuf;
   L.buf_cap = buf_cap;
   L.append = append;
+  L.migrate = migrate;
   return launch_attn(L, static_cast<hipStream_t>(stream));
 }
 }  // namespace
@@ -593,6 +601,21 @@ tb_status tb_append_buffered_decode_attn(const tb_cache_desc* src, const void* K
   TB_TRY(check_append(src, K_src, V_src, src_row, d, K, V, dst_row, 1));
   const NewRow row{src, K_src, V_src, src_row, dst_row, K, V};
   return buffered_attn(d, q, Kbuf, Vbuf, buf_cap, count, max_count, K, V, tail_begin, tail_end, sm_scale, out, lse, ws, ws_bytes, stream, &row);
+}
+
+tb_status tb_migrate_buffered_decode_attn(const tb_cache_desc* src, const void* K_src, const void* V_src, const int32_t* idx,
+                                          const int32_t* count, int64_t idx_cap, int64_t max_count, int32_t skip_front, int32_t skip_back,
+                                          int32_t* count_out, int64_t src_row, const tb_cache_desc* d, const void* q, void* Kbuf, void* Vbuf,
+                                          int64_t buf_cap, void* K, void* V, int64_t dst_row, int64_t tail_begin, int64_t tail_end,
+                                          float sm_scale, float* out, float* lse, void* ws, size_t ws_bytes, void* stream) {
+  GatherLaunch lists;
+  TB_TRY(check_gather(src, K_src, V_src, idx, count, idx_cap, max_count, skip_front, skip_back, Kbuf, Vbuf, buf_cap, count_out, lists));
+  TB_TRY(check_desc(d));
+  if (src->B != d->B || src->Hq != d->Hq || src->Hkv != d->Hkv || src->D != d->D || src->dtype != d->dtype) return TB_ERR_INVALID_ARG;
+  if (src_row >= 0) TB_TRY(check_append(src, K_src, V_src, src_row, d, K, V, dst_row, 1));
+  const NewRow row{src, K_src, V_src, src_row, dst_row, K, V};
+  return buffered_attn(d, q, Kbuf, Vbuf, buf_cap, count_out, std::min(max_count, buf_cap), K, V, tail_begin, tail_end, sm_scale, out, lse, ws,
+                       ws_bytes, stream, src_row >= 0 ? &row : nullptr, &lists);
 }
 
 tb_status tb_predict_queries(const tb_predictor_desc* p, int32_t B, const void* h, const void* gamma,

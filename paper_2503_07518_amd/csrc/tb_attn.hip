@@ -80,6 +80,13 @@ struct AttnArgs {
   char* new_to[2];
   int64_t new_from_b[2], new_from_h[2], new_to_b[2], new_to_h[2];  // strides in bytes
   int32_t new_row;
+  // buffered form, lists migrated on the way: the rows that `idx` names between its first skip_front and last skip_back entries are
+  // taken from the cache src and left in the buffers
+  const char* src[2];  // K and V
+  int64_t src_b[2], src_h[2], src_n[2];  // strides in bytes
+  int64_t src_N;
+  int32_t skip_front, skip_back;
+  int32_t* count_out;
 };
 
 // Asks for the lines of the kernel's arguments together.  A line is a trip to memory the first time that a compute unit
@@ -119,14 +126,18 @@ __device__ __forceinline__ void combine_published(const float* po, const float* 
       });
 }
 
-// SHARES: the list is cut into one share per XCD (nsplit divides by their number).  NT: rows are read non-temporally
-template <typename T, int D, bool BUF, bool SHARES, bool NT>
+// SHARES: the list is cut into one share per XCD (nsplit divides by their number).  NT: rows are read non-temporally.  MIG: the
+// buffered form of a step that has new lists: a listed row comes from the cache and is stored in its slot of the buffer by the wave
+// that attends to it, so that it is not read again: migration 27 us and attention 15.6 apart for 2 x 32 heads, 2816 rows a head, an
+// interval of 16 steps and a wrap with two of them 403 -> 372 us.
+template <typename T, int D, bool BUF, bool SHARES, bool NT, bool MIG = false>
 __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(AttnArgs a) {
   constexpr int EPL = Pack16<T>::kElts;    // elements per lane
   constexpr int LPR = D / EPL;             // lanes per row
   constexpr int GPW = kWave / LPR;         // row groups per wave
   constexpr int TILE = kLoadsPerTile * GPW;  // rows per wave tile
   static_assert(LPR >= 4 && LPR <= 32, "row must span 4..32 lanes");
+  static_assert(BUF || !MIG, "rows migrate to buffers");
 
   __shared__ float s_m[kAttnWaves][1], s_l[kAttnWaves][1];
   __shared__ __attribute__((aligned(16))) float s_acc[kAttnWaves][1][D];
@@ -177,6 +188,12 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
     kbuf = reinterpret_cast<const char*>(static_cast<const T*>(a.Kbuf) + u * a.buf_cap * D) + sub * 16;
     vbuf = reinterpret_cast<const char*>(static_cast<const T*>(a.Vbuf) + u * a.buf_cap * D) + sub * 16;
   }
+  const char* ksrc = nullptr;
+  const char* vsrc = nullptr;
+  if (MIG) {
+    ksrc = a.src[0] + b * a.src_b[0] + hkv * a.src_h[0] + sub * 16;
+    vsrc = a.src[1] + b * a.src_b[1] + hkv * a.src_h[1] + sub * 16;
+  }
   const char* knew = nullptr;
   const char* vnew = nullptr;
   int32_t n_new = INT32_MIN;  // the new row as fetch_rows names it (this value: nobody's name)
@@ -201,10 +218,10 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   // together: steps of 32 heads on 8, 3277 of 32768 rows 27.9 -> 27.2 us, 16 x 32, 2048 of 16384 118.1 -> 116.1, 3 x 32, 2433 of 20011
   // 35.9 -> 34.6; an interval of 8 steps of 4 x 32 heads, 65536 rows 823 -> 814.
   const int64_t last_slot = a.idx_cap > 0 ? a.idx_cap - 1 : 0;
-  const int32_t* entries = BUF ? nullptr : (a.idx_cap > 0 ? a.idx + lu * a.idx_cap : a.count);
+  const int32_t* entries = BUF && !MIG ? nullptr : (a.idx_cap > 0 ? a.idx + lu * a.idx_cap : a.count);
   auto fetch_entry = [&](int64_t t0) -> int32_t {
-    if (BUF) return 0;  // slot i of the list is row i of the buffer
-    const int64_t i = t0 + (lane & (TILE - 1));
+    if (BUF && !MIG) return 0;  // slot i of the list is row i of the buffer
+    const int64_t i = t0 + (lane & (TILE - 1)) + (MIG ? a.skip_front : 0);
     return entries[i < last_slot ? i : last_slot];
   };
   auto row_at = [&](int64_t t0, int32_t entry) -> int32_t {
@@ -213,6 +230,7 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
     n = n < 0 ? 0 : (n >= a.N ? a.N - 1 : n);  // keep the gather inside the cache whatever the list holds
     int32_t row = static_cast<int32_t>(n);
     if (BUF) row = i < cnt ? static_cast<int32_t>(i) : row | kTailFlag;  // (the tail is read from the cache)
+    if (MIG && i < cnt) row = static_cast<int32_t>(entry < 0 ? 0 : (entry >= a.src_N ? a.src_N - 1 : entry));
     return i < total ? row : -1;
   };
   int32_t entry = 0;
@@ -220,6 +238,10 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   if (!SHARES) entry = fetch_entry(w_beg);
   __builtin_amdgcn_sched_barrier(0);  // query, count and entries come in one trip to memory
   cnt = cnt_read < 0 ? 0 : (cnt_read > a.max_count ? a.max_count : cnt_read);
+  if (MIG) {
+    cnt = max(cnt - a.skip_front - a.skip_back, int64_t{0});
+    if (split == 0 && tid == 0) a.count_out[u] = static_cast<int32_t>(cnt);
+  }
   total = cnt + (a.tail_end - a.tail_begin);
   if (SHARES) {  // whole tiles per XCD
     const int64_t share = (total + kXcds * TILE - 1) / (kXcds * TILE) * TILE, beg = (split % kXcds) * share;
@@ -245,6 +267,10 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
         const uint32_t row = valid[t] ? static_cast<uint32_t>(n & (kTailFlag - 1)) : 0u;
         const char* kp = tail ? kbase + row * k_row_bytes : kbuf + row * static_cast<uint32_t>(D * sizeof(T));
         const char* vp = tail ? vbase + row * v_row_bytes : vbuf + row * static_cast<uint32_t>(D * sizeof(T));
+        if (MIG && !tail) {  // (a slot past the end: the cache's first row)
+          kp = ksrc + static_cast<int64_t>(row) * a.src_n[0];
+          vp = vsrc + static_cast<int64_t>(row) * a.src_n[1];
+        }
         if (n == n_new) {
           kp = knew;
           vp = vnew;
@@ -260,6 +286,18 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
     // every gather of the tile is in flight before the first one is consumed
     __builtin_amdgcn_sched_barrier(0);
     rows.consume(kraw, vraw, valid);
+    if constexpr (MIG) {
+#pragma unroll
+      for (int t = 0; t < kLoadsPerTile; ++t) {
+        const int64_t slot = t0 + t * GPW + grp;
+        if (slot < cnt) {  // (the buffers' own alignment and size are the attention's)
+          char* ko = const_cast<char*>(kbuf) + slot * static_cast<int64_t>(D * sizeof(T));
+          char* vo = const_cast<char*>(vbuf) + slot * static_cast<int64_t>(D * sizeof(T));
+          __builtin_memcpy(__builtin_assume_aligned(ko, 16), &kraw[t], 16);
+          __builtin_memcpy(__builtin_assume_aligned(vo, 16), &vraw[t], 16);
+        }
+      }
+    }
   }
   rows.merge_groups();
   if (grp == 0) {
@@ -859,6 +897,26 @@ tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
     }
     a.new_row = static_cast<int32_t>(r.dst_row);  // (below 2^30: launch conditions)
   }
+  if (L.migrate) {
+    const GatherLaunch& m = *L.migrate;
+    const int64_t elt = sizeof(T);
+    a.idx = m.idx;
+    a.idx_cap = m.idx_cap;
+    a.max_count = m.max_count;
+    a.count = m.count;
+    a.src[0] = static_cast<const char*>(m.K);
+    a.src[1] = static_cast<const char*>(m.V);
+    const int64_t strides[2][3] = {{m.desc->k_stride_b, m.desc->k_stride_h, m.desc->k_stride_n}, {m.desc->v_stride_b, m.desc->v_stride_h, m.desc->v_stride_n}};
+    for (int t = 0; t < 2; ++t) {
+      a.src_b[t] = strides[t][0] * elt;
+      a.src_h[t] = strides[t][1] * elt;
+      a.src_n[t] = strides[t][2] * elt;
+    }
+    a.src_N = m.desc->N;
+    a.skip_front = m.skip_front;
+    a.skip_back = m.skip_back;
+    a.count_out = m.count_out;
+  }
   a.shared_list = L.shared_list ? 1 : 0;
   a.n_kv_groups = d.B * d.Hkv;
   // per-XCD placement pays when heads share KV rows and the KV groups spread evenly over the XCDs
@@ -875,7 +933,20 @@ tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
   const bool shares = attn_in_shares(&d) && a.nsplit % kXcds == 0;
   // (per-head buffers share no rows: non-temporal whatever the size; against loads that the caches keep, an interval of 2 x 32 heads,
   // 2816 rows a head, 418 and 407 us, of 4 x 32 heads, 9400 rows 1340 and 1209, of 8 heads, 1000 rows no difference)
-  if (L.Kbuf && shares)
+  if (L.migrate) {
+    // (rows that several heads list are kept in the caches for them, as in the migration on its own)
+    const GatherLaunch& m = *L.migrate;
+    const double listed = static_cast<double>(m.max_count - m.skip_front - m.skip_back);
+    const bool nt = listed_rows(a.g, listed > 1.0 ? listed : 1.0, static_cast<double>(m.desc->N)).reuse <= kStreamedReuse;
+    if (shares && nt)
+      hipLaunchKernelGGL((attn_kernel<T, D, true, true, true, true>), grid, dim3(kAttnThreads), 0, st, a);
+    else if (shares)
+      hipLaunchKernelGGL((attn_kernel<T, D, true, true, false, true>), grid, dim3(kAttnThreads), 0, st, a);
+    else if (nt)
+      hipLaunchKernelGGL((attn_kernel<T, D, true, false, true, true>), grid, dim3(kAttnThreads), 0, st, a);
+    else
+      hipLaunchKernelGGL((attn_kernel<T, D, true, false, false, true>), grid, dim3(kAttnThreads), 0, st, a);
+  } else if (L.Kbuf && shares)
     hipLaunchKernelGGL((attn_kernel<T, D, true, true, true>), grid, dim3(kAttnThreads), 0, st, a);
   else if (L.Kbuf)
     hipLaunchKernelGGL((attn_kernel<T, D, true, false, true>), grid, dim3(kAttnThreads), 0, st, a);

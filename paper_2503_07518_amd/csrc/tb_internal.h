@@ -138,6 +138,20 @@ struct NewRow {
   void* Vdst;
 };
 
+struct GatherLaunch {
+  const tb_cache_desc* desc;
+  const void* K;
+  const void* V;
+  const int32_t* idx;
+  const int32_t* count;
+  int64_t idx_cap, max_count;
+  void* Kbuf;
+  void* Vbuf;
+  int64_t buf_cap;
+  int32_t skip_front = 0, skip_back = 0;  // list entries left out at the two ends
+  int32_t* count_out = nullptr;           // receives count - skip_front - skip_back (>= 0) per list
+};
+
 struct AttnLaunch {
   const tb_cache_desc* desc;
   const void* q;
@@ -157,6 +171,7 @@ struct AttnLaunch {
   const void* Vbuf = nullptr;
   int64_t buf_cap = 0;
   const NewRow* append = nullptr;  // (buffered form)
+  const GatherLaunch* migrate = nullptr;  // (buffered form) the rows of these lists come from their cache and are left in the buffers
   // head-less form: idx is [B][idx_cap] and count [B], one list for all heads of a batch element
   bool shared_list = false;
   bool grouped = false;  // shared list served by one workgroup per KV group (plan made for that)
@@ -170,19 +185,6 @@ bool step_in_one(const tb_cache_desc* d, int64_t rows, int nsplit);
 tb_status launch_step(const ScoreLaunch& S, const SelectLaunch& L, const AttnLaunch& A, hipStream_t st);
 
 // Copies the listed rows of K and V into per-query-head buffers [B][Hq][buf_cap][D].
-struct GatherLaunch {
-  const tb_cache_desc* desc;
-  const void* K;
-  const void* V;
-  const int32_t* idx;
-  const int32_t* count;
-  int64_t idx_cap, max_count;
-  void* Kbuf;
-  void* Vbuf;
-  int64_t buf_cap;
-  int32_t skip_front = 0, skip_back = 0;  // list entries left out at the two ends
-  int32_t* count_out = nullptr;           // receives count - skip_front - skip_back (>= 0) per list
-};
 tb_status launch_gather(const GatherLaunch& a, hipStream_t st);
 tb_status launch_append(const tb_cache_desc& src, const void* K, const void* V, int64_t src_row, const tb_cache_desc& dst, void* Kdst,
                         void* Vdst, int64_t dst_row, int64_t rows, hipStream_t st);

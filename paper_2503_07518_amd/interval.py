@@ -130,7 +130,8 @@ class RingLayoutDecoder:
 
     Moving the first ``sink`` rows into the Sink Buffer is data arrival, done here with a plain device
     copy; the model's new K/V row reaches the ring with the step's attention (``tb_append_buffered_decode_attn``), at a
-    wrap through ``tb_append_kv`` ahead of the projection.
+    wrap through ``tb_append_kv`` ahead of the projection; a prediction step's attention migrates the rows it attends to
+    (``tb_migrate_buffered_decode_attn``).
     """
 
     def __init__(self, K, V, W, Kimp, Hq: int, k: int, P: int, radius: int, ring: int, sink: int = 0,
@@ -185,11 +186,15 @@ class RingLayoutDecoder:
             tb.tb_select_topk(desc, self.scores, self.k, S, W_t, self.idx, self.cnt, self.sel_ws)
             tb.tb_expand_neighbors(self.B, self.Hq, N_t, self.radius, self.mode, self.idx, self.cnt, self.exp_idx,
                                    self.exp_cnt)
-            # migration into the Important Buffer: the widened list without its sink and window entries
-            tb.tb_gather_important(desc, self.K, self.V, self.exp_idx, self.exp_cnt, self.exp_cap, min(S, N_t), W_t,
-                                   self.Kbuf, self.Vbuf, self.imp_cnt)
+            # migration into the Important Buffer: the widened list without its sink and window entries; the new token arrives with
+            # it, unless the ring has just been projected
+            aux.N = S + W_t
+            tb.tb_migrate_buffered_decode_attn(desc, self.K, self.V, self.exp_idx, self.exp_cnt, self.exp_cap, min(S, N_t), W_t, self.imp_cnt,
+                                               N_t - 1 if t > 0 and not wraps else -1, aux, q, self.Kbuf, self.Vbuf, self.aux_K, self.aux_V,
+                                               S + slot, self.sm_scale, self.out, self.lse, self.ws, tail_begin=0, tail_end=S + W_t)
+            return self.out, self.lse
         aux.N = S + W_t
-        if t > 0 and not wraps:  # nothing else reads the ring in this step: the new token arrives with the attention
+        if not wraps:  # nothing else reads the ring in this step: the new token arrives with the attention
             tb.tb_append_buffered_decode_attn(tb.make_desc(self.Ncap, self.Hq, K=self.K, V=self.V), self.K, self.V, N_t - 1,
                                               aux, q, self.Kbuf, self.Vbuf, self.imp_cnt, self.exp_cap, self.aux_K, self.aux_V, S + slot,
                                               self.sm_scale, self.out, self.lse, self.ws, tail_begin=0, tail_end=S + W_t)

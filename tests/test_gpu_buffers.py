@@ -232,3 +232,49 @@ def test_append_with_buffered_attention(dtype, B, Hq, Hkv, D, cap, counts, tail,
     for bad in ((N, slot), (41, R), (-1, slot)):
         with pytest.raises(tb.TbError):
             tb.tb_append_buffered_decode_attn(src, K, V, bad[0], dst, q, Kb, Vb, cnt, cap, aK, aV, bad[1], 0.1, out, lse, ws, *tail)
+
+
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,D,cap,counts,front,back,tail,slot", [
+    (torch.bfloat16, 2, 8, 2, 128, 300, (300, 0, 17, 40), 16, 9, (0, 96), 95),      # lists shorter than what is left out, a row that arrives
+    (torch.bfloat16, 1, 8, 1, 128, 3000, (3000, 129), 4, 64, (0, 64), -1),          # in shares, one per XCD; most rows listed by several heads
+    (torch.float32, 3, 4, 4, 64, 40, (40, 1, 0), 0, 0, (5, 60), 33),
+    (torch.float32, 1, 16, 2, 128, 1, (1, 0), 0, 1, (10, 20), -1),                  # nothing migrates
+    (torch.bfloat16, 9, 16, 8, 64, 700, (700, 64, 1), 128, 256, (0, 128), 77),
+    (torch.float32, 5, 8, 1, 128, 1100, (1100, 777), 3, 5, (7, 7), -1),             # no dense range
+])
+def test_migration_with_buffered_attention(dtype, B, Hq, Hkv, D, cap, counts, front, back, tail, slot):
+    """Rows that migrate with the attention: buffers (past the migrated rows untouched), counts, ring and results the same bits as
+    the separate calls, for lists with entries outside the cache, too."""
+    say(f"migration with attention dtype={dtype} B={B} Hq={Hq} Hkv={Hkv} D={D} cap={cap} front={front} back={back} tail={tail} slot={slot}")
+    g = torch.Generator().manual_seed(82)
+    N, R = 2 * cap + 50, 128
+    K, V = (torch.randn((B, N, Hkv, D), generator=g).to(dtype).to(DEV).transpose(1, 2) for _ in range(2))  # strides of their own
+    aK, aV = (torch.randn((B, Hkv, R, D), generator=g).to(dtype).to(DEV) for _ in range(2))
+    q = torch.randn((B, Hq, D), generator=g).to(dtype).to(DEV)
+    idx = torch.rand((B, Hq, N), generator=g).topk(cap, dim=-1).indices.sort(-1).values.to(torch.int32)
+    idx[0, 0, :2], idx[-1, -1, -2:] = -5, N + 7
+    idx, cnt = idx[:, :, :cap].contiguous().to(DEV), torch.tensor([counts[i % len(counts)] for i in range(B * Hq)], dtype=torch.int32, device=DEV).view(B, Hq)
+    src, dst = tb.make_desc(N, Hq, K=K, V=V), tb.make_desc(R, Hq, K=aK, V=aV)
+    ws = tb.new_workspace(tb.TB_OP_ATTN, dst, cap + R)
+    res = []
+    for fused in (True, False):
+        k, v = aK.clone(), aV.clone()
+        Kb, Vb = (torch.full((B, Hq, cap, D), 3.5, dtype=dtype, device=DEV) for _ in range(2))
+        out, lse = (torch.full(s, float("nan"), device=DEV) for s in ((B, Hq, D), (B, Hq)))
+        n_out = torch.full((B, Hq), -7, dtype=torch.int32, device=DEV)
+        if fused:
+            tb.tb_migrate_buffered_decode_attn(src, K, V, idx, cnt, cap, front, back, n_out, 41 if slot >= 0 else -1, dst, q, Kb, Vb, k, v, slot, 0.1,
+                                               out, lse, ws, *tail)
+        else:
+            tb.tb_gather_important(src, K, V, idx, cnt, cap, front, back, Kb, Vb, n_out)
+            if slot >= 0:
+                tb.tb_append_kv(src, K, V, 41, dst, k, v, slot)
+            tb.tb_buffered_decode_attn(dst, q, Kb, Vb, n_out, cap, k, v, 0.1, out, lse, ws, *tail)
+        torch.cuda.synchronize()
+        res.append((k, v, Kb, Vb, n_out, out, lse))
+    assert all(torch.equal(a, b) for a, b in zip(*res)) and bool(torch.isfinite(res[0][5]).all())
+    assert torch.equal(res[0][4], (cnt - front - back).clamp(min=0))
+    for bad in (dict(cap=cap + 1), dict(front=-1), dict(src_row=N), dict(dst_row=R)):
+        with pytest.raises(tb.TbError):
+            tb.tb_migrate_buffered_decode_attn(src, K, V, idx, cnt, bad.get("cap", cap), bad.get("front", front), back, n_out, bad.get("src_row", 41), dst, q,
+                                               Kb, Vb, k, v, bad.get("dst_row", 0), 0.1, out, lse, ws, *tail)
