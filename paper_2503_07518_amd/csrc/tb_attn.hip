@@ -829,11 +829,12 @@ tb_status launch_group(const AttnArgs& a, const AttnLaunch& L, hipStream_t st) {
 
 // Non-temporal gathers of lists of up to `rows` rows.  With lists that do not depend on each other the g heads of a group read
 // `distinct` rows of N and come back to each of them g * rows / distinct times.  A step that has just selected its lists finds little in the
-// last-level cache from 100 MB of different rows on; beyond 1.3 readers a row, and for groups of eight, whose lists share more than
-// that where the scores favour the same rows, the lines are wanted again.  Attention alone in us, plain and non-temporal
+// last-level cache from 100 MB of different rows on; beyond 1.3 readers a row (1.4 where the rows are far more than that cache), and
+// for groups of eight, whose lists share more than that where the scores favour the same rows, the lines are wanted again.  Attention alone in us, plain and non-temporal
 // (D = 128, bf16; B x heads on KV heads, listed of N): 4 x 32 on 8, 1638 of 16384 (92 MB) 19.6 and 20.2; 4 x 8 on 8, 6554 of 32768
 // (107 MB) 22.2 and 21.5; 4 x 16 on 8, 4096 of 32768 (126 MB) 27.2 and 24.9; 8 x 32 on 8, 1638 of 16384 (184 MB, 1.16) 37.7 and 33.5; 4 x 32
-// on 8, widened lists of 11600 of 65536 (1.33) 98.4 and 100.6; 16 x 64 on 8, 1638 of 16384 (1.4) 112.6 and 119; 4 x 64 on 8, 4096 of 131072,
+// on 8, 12450 of 65536 (612 MB, 1.33) 104.1 and 102.0, an interval of 8 steps that reuse such lists 814 and 800; 4 x 32 on 8, 18350 of 65536
+// (785 MB, 1.53) 130.8 and 139.3; 16 x 64 on 8, 1638 of 16384 (1.4) 112.6 and 119; 4 x 64 on 8, 4096 of 131072,
 // the same rows in many lists (1.11 if they were not) 56.1 and 63.5.  Lists that are handed in may be those of the step before, whose rows
 // that cache still holds unless they are far more than it has room for: intervals of 8 steps that reuse lists of 220 MB 339 and
 // 349 us, of 295 MB 405 and 411, of 393 MB 508 and 495, of 430 MB 596 and 565.
@@ -843,7 +844,7 @@ bool streams_rows(const AttnLaunch& L) {
   if (L.shared_list || g > 4) return false;
   const ListedRows r = listed_rows(g, static_cast<double>(L.max_count + (L.tail_end - L.tail_begin)), static_cast<double>(d.N));
   const double bytes = static_cast<double>(d.B) * d.Hkv * r.distinct * 2 * d.D * (d.dtype == TB_F32 ? 4 : 2);
-  return bytes >= (L.fresh_lists ? 100e6 : 375e6) && r.reuse <= kStreamedReuse;
+  return (L.fresh_lists && bytes >= 100e6 && r.reuse <= kStreamedReuse) || (bytes >= 375e6 && r.reuse <= 1.4);
 }
 
 template <typename T, int D>
