@@ -218,7 +218,8 @@ static size_t score_select_scratch_upto(const tb_cache_desc* d, int64_t max_coun
 // nanosecond).  Separate and in one, us a step in a graph of steps: 8 heads, 1024 rows of d' = 16, 128 kept, D = 64, fp32 10.8 and
 // 8.8; D = 128, bf16, d' = 32: 32 heads, 2048 rows, 200 kept (230 KB) 14.4 and 11.7, 4096 rows, 400 kept (460 KB) 15.9 and 15.5, 800
 // kept (660 KB) 17.1 and 17.2; 256 heads, 1024 rows, 100 kept 14.7 and 11.6, 4000 rows, 400 kept 23.9 and 20.4; 64 heads, 3000
-// rows, 684 kept (540 KB) 18.4 and 18.4; d' = 64, 4096 rows, 600 kept (810 KB) 18.1 and 20.4.
+// rows, 684 kept (540 KB) 18.4 and 18.4; d' = 64, 4096 rows, 600 kept (810 KB) 18.1 and 20.4.  112 heads on 28, 2300 rows of d' = 16, 760
+// kept (as many splits as there are waves for since attn_plan evens out the rounds) 23.2 and 16.1.
 bool step_in_one(const tb_cache_desc* d, int64_t rows, int nsplit) {
   const int64_t elt = d->dtype == TB_F32 ? 4 : 2;
   return d->N > 0 && d->N <= kStepMaxN && static_cast<int64_t>(d->B) * d->Hq <= 256 && nsplit <= kStepMaxSplits &&

@@ -830,7 +830,8 @@ tb_status launch_group(const AttnArgs& a, const AttnLaunch& L, hipStream_t st) {
 // Non-temporal gathers of lists of up to `rows` rows.  With lists that do not depend on each other the g heads of a group read
 // `distinct` rows of N and come back to each of them g * rows / distinct times.  A step that has just selected its lists finds little in the
 // last-level cache from 100 MB of different rows on; beyond 1.3 readers a row (1.4 where the rows are far more than that cache), and
-// for groups of eight, whose lists share more than that where the scores favour the same rows, the lines are wanted again.  Attention alone in us, plain and non-temporal
+// for groups of eight, whose lists share more than that where the scores favour the same rows, the lines are wanted again.
+// Attention alone in us, plain and non-temporal
 // (D = 128, bf16; B x heads on KV heads, listed of N): 4 x 32 on 8, 1638 of 16384 (92 MB) 19.6 and 20.2; 4 x 8 on 8, 6554 of 32768
 // (107 MB) 22.2 and 21.5; 4 x 16 on 8, 4096 of 32768 (126 MB) 27.2 and 24.9; 8 x 32 on 8, 1638 of 16384 (184 MB, 1.16) 37.7 and 33.5; 4 x 32
 // on 8, 12450 of 65536 (612 MB, 1.33) 104.1 and 102.0, an interval of 8 steps that reuse such lists 814 and 800; 4 x 32 on 8, 18350 of 65536
