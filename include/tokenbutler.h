@@ -194,7 +194,7 @@ tb_status tb_append_buffered_decode_attn(const tb_cache_desc* src, const void* K
 /* tb_gather_important of the lists, from the cache src, K_src, V_src into the buffers, then (src_row >= 0) tb_append_kv of one row
  * into row dst_row of the cache desc, K, V, then tb_buffered_decode_attn over buffers (max_count: the lists', no more than
  * buf_cap) and cache, in one launch: a listed row is attended to on its way into its buffer.  Arguments and results are those of
- * the calls; src and desc agree in all but N and strides. */
+ * the calls; src and desc agree in all but N and strides, do not overlap, and src->N <= 2^30 (else TB_ERR_UNSUPPORTED). */
 tb_status tb_migrate_buffered_decode_attn(const tb_cache_desc* src, const void* K_src, const void* V_src, const int32_t* idx,
                                           const int32_t* count, int64_t idx_cap, int64_t max_count, int32_t skip_front, int32_t skip_back,
                                           int32_t* count_out, int64_t src_row, const tb_cache_desc* desc, const void* q, void* Kbuf,

@@ -613,6 +613,7 @@ tb_status tb_migrate_buffered_decode_attn(const tb_cache_desc* src, const void* 
   TB_TRY(check_gather(src, K_src, V_src, idx, count, idx_cap, max_count, skip_front, skip_back, Kbuf, Vbuf, buf_cap, count_out, lists));
   TB_TRY(check_desc(d));
   if (src->B != d->B || src->Hq != d->Hq || src->Hkv != d->Hkv || src->D != d->D || src->dtype != d->dtype) return TB_ERR_INVALID_ARG;
+  if (src->N > (int64_t{1} << 30)) return TB_ERR_UNSUPPORTED;  // the next bit of a row number names the cache of the dense range
   if (src_row >= 0) TB_TRY(check_append(src, K_src, V_src, src_row, d, K, V, dst_row, 1));
   const NewRow row{src, K_src, V_src, src_row, dst_row, K, V};
   return buffered_attn(d, q, Kbuf, Vbuf, buf_cap, count_out, std::min(max_count, buf_cap), K, V, tail_begin, tail_end, sm_scale, out, lse, ws,

@@ -155,6 +155,20 @@ def test_rejects_bad_arguments_without_launching(tb):
     assert L.tb_workspace_init(P, 6, None) == tb.TB_ERR_INVALID_ARG
 
 
+def migrate(tb, src, dst, idx_cap=100, max_count=100, front=0, back=0, src_row=-1, dst_row=0, buf_cap=100, tail=(0, 0), ws_bytes=64):
+    """tb_migrate_buffered_decode_attn with a workspace that is too small: a call that gets so far has passed every other check."""
+    r = ctypes.byref
+    return tb.load_library().tb_migrate_buffered_decode_attn(r(src), P, P, P, P, idx_cap, max_count, front, back, P, src_row, r(dst), P, P, P, buf_cap, P, P,
+                                                             dst_row, *tail, 1.0, P, NULL, P, ws_bytes, None)
+
+
+@pytest.mark.parametrize("rows,want", [(1 << 30, "TB_ERR_WORKSPACE"), ((1 << 30) + 1, "TB_ERR_UNSUPPORTED"), (1 << 33, "TB_ERR_UNSUPPORTED")])
+def test_migration_refuses_rows_that_its_numbers_cannot_name(tb, rows, want):
+    """Bit 30 of a row number says which cache the row is in: a source of more rows than that is refused."""
+    strides = dict(k_stride_b=0, k_stride_h=0, v_stride_b=0, v_stride_h=0)
+    assert migrate(tb, desc(tb, N=rows, **strides), desc(tb)) == getattr(tb, want)
+
+
 def test_missing_library_is_an_error(tb, monkeypatch, tmp_path):
     """The product path has no fallback: without the HIP library the ops raise."""
     monkeypatch.setattr(tb, "_lib", None)
