@@ -112,7 +112,7 @@ tb_status tb_expand_neighbors(int32_t B, int32_t Hq, int64_t N, int32_t radius, 
  * reused across a prediction interval; pass tail_begin == tail_end for none).
  * q: [B][Hq][D] contiguous.  idx entries must lie in [0, desc->N); tail_end <= desc->N.
  * max_count: host-side upper bound on count[b,h] (<= idx_cap) used to size the launch; a list
- * longer than max_count is truncated to it.  out: fp32 [B][Hq][D]; lse: fp32 [B][Hq] or NULL.
+ * longer than max_count is truncated to it, and entries from max_count on are not read.  out: fp32 [B][Hq][D]; lse: fp32 [B][Hq] or NULL.
  * An empty list gives out = 0 and lse = -inf.  ws: tb_workspace_bytes(TB_OP_ATTN, ...). */
 tb_status tb_sparse_decode_attn(const tb_cache_desc* desc, const void* q, const void* K, const void* V,
                                 const int32_t* idx, const int32_t* count, int64_t idx_cap, int64_t max_count,

@@ -196,7 +196,7 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
   }
   const char* knew = nullptr;
   const char* vnew = nullptr;
-  int32_t n_new = INT32_MIN;  // the new row as fetch_rows names it (this value: nobody's name)
+  int32_t n_new = INT32_MIN;  // the new row as row_at names it (this value: nobody's name)
   if (BUF && a.new_row >= 0) {
     n_new = a.new_row | kTailFlag;
     knew = a.new_from[0] + b * a.new_from_b[0] + hkv * a.new_from_h[0] + sub * 16;
@@ -213,12 +213,12 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWavesPerSimd) void attn_kernel(A
 
   // Row numbers of a tile: lane i (modulo the tile) has slot i, an entry of the selected list, then of the dense tail; -1
   // marks a slot past the end.  An entry is read without waiting for the count or asking whether there is one (clamped into the
-  // list's capacity), ahead of the gathers of the tile before, and looked at when its own tile begins: read under a condition it
-  // was waited for on the spot, and with it every gather of the tile before.  With the arguments and the first entries fetched
+  // max_count entries that the call names: the list may end with them), ahead of the gathers of the tile before, and looked at when
+  // its own tile begins: read under a condition it was waited for on the spot, and with it every gather of the tile before.  With the arguments and the first entries fetched
   // together: steps of 32 heads on 8, 3277 of 32768 rows 27.9 -> 27.2 us, 16 x 32, 2048 of 16384 118.1 -> 116.1, 3 x 32, 2433 of 20011
   // 35.9 -> 34.6; an interval of 8 steps of 4 x 32 heads, 65536 rows 823 -> 814.
-  const int64_t last_slot = a.idx_cap > 0 ? a.idx_cap - 1 : 0;
-  const int32_t* entries = BUF && !MIG ? nullptr : (a.idx_cap > 0 ? a.idx + lu * a.idx_cap : a.count);
+  const int64_t last_slot = a.max_count > 0 ? a.max_count - 1 : 0;
+  const int32_t* entries = BUF && !MIG ? nullptr : (a.max_count > 0 ? a.idx + lu * a.idx_cap : a.count);
   auto fetch_entry = [&](int64_t t0) -> int32_t {
     if (BUF && !MIG) return 0;  // slot i of the list is row i of the buffer
     const int64_t i = t0 + (lane & (TILE - 1)) + (MIG ? a.skip_front : 0);
@@ -650,13 +650,13 @@ __global__ __launch_bounds__(kGroupWaves * kWave, 2) void attn_group_mfma_kernel
     return static_cast<int32_t>(n);
   };
   // lane r (and r + 32) of a step: the row of its slot r.  The first step's entries are read without
-  // waiting for the count (the slots are inside the list's capacity whatever the count is).
+  // waiting for the count (clamped into the entries that the call names, whatever the count is).
   int32_t n_next;
   {
     const int64_t i0 = w_beg + (lane & 31);
-    const int64_t cap1 = a.idx_cap > 0 ? a.idx_cap - 1 : 0;
-    const int32_t raw = a.idx_cap > 0 ? list[i0 < cap1 ? i0 : cap1] : 0;
-    const int32_t raw_first = a.idx_cap > 0 ? list[w_beg < cap1 ? w_beg : cap1] : 0;
+    const int64_t last = a.max_count - 1;
+    const int32_t raw = a.max_count > 0 ? list[i0 < last ? i0 : last] : 0;
+    const int32_t raw_first = a.max_count > 0 ? list[w_beg < last ? w_beg : last] : 0;
     const int64_t c = a.count[b];
     cnt = c < 0 ? 0 : (c > a.max_count ? a.max_count : c);
     total = cnt + (a.tail_end - a.tail_begin);

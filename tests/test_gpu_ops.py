@@ -579,6 +579,38 @@ def test_attn_strided_cache_and_max_count_truncation(oracle):
     assert_attention(np_of(out), ro, "bf16", np_of(lse), rl)
 
 
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,D,rows", [
+    (torch.bfloat16, 2, 8, 8, 128, 300),    # lists of their own, several splits
+    (torch.float32, 1, 8, 1, 64, 2100),     # in shares, one per XCD
+    (torch.float32, 1, 2, 2, 128, 1),
+    (torch.bfloat16, 4, 32, 8, 128, 0),     # nothing is named: only the dense range
+    (torch.bfloat16, 4, 32, 8, 128, 3300),  # one list for all heads: a workgroup per KV group, on the matrix cores
+    (torch.float32, 4, 32, 8, 128, 400),
+])
+def test_attn_lists_that_are_columns_of_an_array(dtype, B, Hq, Hkv, D, rows):
+    """Lists that are the last columns of a wider array: the last of them ends with the array, and nothing behind the entries
+    that the call names is read (what lies in front of the next list is a row number outside the cache).  The same bits as for
+    lists of their own."""
+    say(f"attn lists in columns dtype={dtype} B={B} Hq={Hq} Hkv={Hkv} D={D} rows={rows}")
+    N, before, tail = rows + 90, 700, (rows + 80, rows + 90)
+    q, K, V = randn((B, Hq, D), dtype, 55), randn((B, Hkv, N, D), dtype, 56), randn((B, Hkv, N, D), dtype, 57)
+    gen = torch.Generator().manual_seed(58)
+    wide = torch.full((B, Hq, before + rows), 1 << 30, dtype=torch.int32)
+    wide[:, :, before:] = torch.rand((B, Hq, N), generator=gen).topk(rows, dim=-1).indices.sort(-1).values.to(torch.int32)
+    wide = wide.to(DEV)
+    idx, cnt = wide[:, :, before:] if rows else wide, torch.full((B, Hq), rows, dtype=torch.int32, device=DEV)
+    ws = tb.new_workspace(tb.TB_OP_ATTN, tb.make_desc(N, Hq, K=K, V=V), rows + 10)
+    res = [gpu_attn(q, K, V, lists, cnt, N, 0.1, max_count=rows, tail=tail, ws=ws) for lists in (idx, idx.contiguous())]
+    shared = []
+    for lists in (idx[:, -1], idx[:, -1].contiguous()):  # (one list per batch element, Hq lists of the array apart)
+        out, lse = torch.full((B, Hq, D), float("nan"), device=DEV), torch.full((B, Hq), float("nan"), device=DEV)
+        tb.tb_sparse_decode_attn_shared(tb.make_desc(N, Hq, K=K, V=V), q, K, V, lists, cnt[:, 0].contiguous(), rows, 0.1, out, lse, ws, *tail)
+        shared.append((out, lse))
+    torch.cuda.synchronize()
+    for a, b in (res, shared):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and bool(torch.isfinite(a[0]).all())
+
+
 @pytest.mark.parametrize("dtype,B,Hq,Hkv,D,N,rows", [
     (torch.bfloat16, 3, 32, 8, 128, 3000, 1100),   # 5 splits, 480 workgroups
     (torch.bfloat16, 22, 8, 1, 128, 1500, 1030),   # shares of a list on more heads than half the compute units
