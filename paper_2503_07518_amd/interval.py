@@ -167,7 +167,7 @@ class RingLayoutDecoder:
     def step(self, t: int, N_t: int, q: torch.Tensor, q_imp: torch.Tensor):
         """Step t sees the first N_t = N0 + t rows of the cache.  Returns (out, lse) views."""
         S, R = self.sink, self.ring
-        aux = tb.make_desc(S + R, self.Hq, K=self.aux_K, V=self.aux_V)
+        aux = tb.make_desc(S + R, self.Hq, K=self.aux_K, V=self.aux_V)  # (all its rows: at t = 0 without a sink none is attended to)
         slot = (t - 1) % R  # of the token appended before this step, which arrives in the ring
         wraps = t > 0 and t % R == 0
         if wraps:
@@ -188,12 +188,10 @@ class RingLayoutDecoder:
                                    self.exp_cnt)
             # migration into the Important Buffer: the widened list without its sink and window entries; the new token arrives with
             # it, unless the ring has just been projected
-            aux.N = S + W_t
             tb.tb_migrate_buffered_decode_attn(desc, self.K, self.V, self.exp_idx, self.exp_cnt, self.exp_cap, min(S, N_t), W_t, self.imp_cnt,
                                                N_t - 1 if t > 0 and not wraps else -1, aux, q, self.Kbuf, self.Vbuf, self.aux_K, self.aux_V,
                                                S + slot, self.sm_scale, self.out, self.lse, self.ws, tail_begin=0, tail_end=S + W_t)
             return self.out, self.lse
-        aux.N = S + W_t
         if not wraps:  # nothing else reads the ring in this step: the new token arrives with the attention
             tb.tb_append_buffered_decode_attn(tb.make_desc(self.Ncap, self.Hq, K=self.K, V=self.V), self.K, self.V, N_t - 1,
                                               aux, q, self.Kbuf, self.Vbuf, self.imp_cnt, self.exp_cap, self.aux_K, self.aux_V, S + slot,

@@ -125,7 +125,16 @@ def test_ring_layout_interval_loop(oracle, mode):
     wraps of the ring (Sec. 3.3 "Inference Setup"), over more than two wraps, every step against
     the oracle's driver in ring mode: selection, widened list and migrated row counts bit-exact,
     attention to the bar.  The projected-key cache starts with the post-prefill rows only."""
-    ring, sink = 8, 16
+    check_ring_layout(oracle, mode, sink=16)
+
+
+def test_ring_layout_without_sink(oracle):
+    """No sink rows, the decoder's default: the first step attends to nothing but the Important Buffer."""
+    check_ring_layout(oracle, mode=0, sink=0)
+
+
+def check_ring_layout(oracle, mode, sink):
+    ring = 8
     cfg = workloads.C4.scaled(name="C4_small_ring", B=2, N=4096, k=256, steps=21, P=4, heavy_per_kv_head=8)
     say(f"ring layout: ring={ring} sink={sink} P={cfg.P} steps={cfg.steps} neighbour rule {mode}")
     data = workloads.make_layer(cfg, device=DEV)
