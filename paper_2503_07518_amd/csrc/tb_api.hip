@@ -19,7 +19,7 @@ constexpr int64_t kAttnMinTiles = 2;      // a workgroup is worth its hand-over 
 
 // `want` splits or a few less: as many as equal shares of whole granules make
 static AttnPlan split_plan(int64_t max_rows, int64_t want, int granule) {
-  AttnPlan p{1, static_cast<int>(want), 1};
+  AttnPlan p{1, static_cast<int>(want), 1, 1};
   int64_t rows = (max_rows + want - 1) / want;
   rows = (rows + granule - 1) / granule * granule;
   p.nsplit = static_cast<int>((max_rows + rows - 1) / rows);
@@ -36,7 +36,7 @@ static AttnPlan split_plan(int64_t max_rows, int64_t want, int granule) {
 // and sizes of head, the choice is 0.7% off the best of the numbers tried on average (512 / units: 6.4%), and at most 3.5% behind it.
 AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool shares) {
   constexpr double kStart = 1.6, kHandOver = 0.1, kAlone = 1.6, kShares = 0.8;
-  if (max_rows <= 0 || units <= 0) return AttnPlan{1, 1, 1};
+  if (max_rows <= 0 || units <= 0) return AttnPlan{1, 1, 1, 1};
   const int64_t most = std::max<int64_t>(1, std::min(max_rows / (kAttnMinTiles * tile_rows_per_wg), kAttnMostWgs / units));
   int64_t want = 1;
   double least = INFINITY;
@@ -57,17 +57,26 @@ AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool s
     if (n > 1) consider(n);
     if (shares && n > kXcds) consider(n / kXcds * kXcds);
   }
-  AttnPlan p = split_plan(max_rows, want, tile_rows_per_wg / kAttnLoadsPerTile);
+  const int granule = tile_rows_per_wg / kAttnLoadsPerTile;
+  AttnPlan p = split_plan(max_rows, want, granule);
+  // (rounded down, it would not be a number that cuts the list into shares: 8 heads on 1, fp32, 8196 rows 15.2 us with 61 splits,
+  // 13.6 with 64; 32 on 4, bf16, 3100 rows 13.5 with 15, 12.4 with 16; 8 on 1, 2050 rows 8.1 and 7.9)
+  if (shares && want % kXcds == 0) {
+    p.nsplit = static_cast<int>(want);
+    p.multiple = kXcds;
+  }
   p.max_split = static_cast<int>(most);
-  p.least = std::min(p.nsplit, static_cast<int>((2 * kAttnCus + units - 1) / units));
+  p.least = std::min(p.nsplit, split_plan(max_rows, std::min(most, (2 * kAttnCus + units - 1) / units), granule).nsplit);
   return p;
 }
-// A workspace that was made for a list of some rows and is used for a few more (a dense tail) may have room for fewer splits than
-// these would get: it serves with those, down to the two workgroups a compute unit that every such workspace holds.
+// A workspace with room for fewer splits than the plan's serves with those, down to `least`: two workgroups a compute unit, or two
+// tiles a wave where that is fewer, which is what a workspace made for a list as long as this one always has.
 static bool fit_splits(const tb_cache_desc* d, AttnPlan& p, size_t ws_bytes) {
   const int64_t units = static_cast<int64_t>(d->B) * d->Hq;
+  const int planned = p.nsplit;
   while (p.nsplit > p.least && ws_bytes < ws_layout(units, d->D, p.nsplit).total) --p.nsplit;
-  return ws_bytes >= ws_layout(units, d->D, p.nsplit).total;
+  if (p.nsplit < planned && p.nsplit > p.multiple) p.nsplit -= p.nsplit % p.multiple;
+  return ws_bytes >= ws_layout(units, d->D, p.least).total;
 }
 // (the buffered form is planned alike, so that it adds up in the same order)
 static AttnPlan attn_plan(const tb_cache_desc* d, int64_t max_rows) {

@@ -28,7 +28,8 @@ struct WsLayout {
 struct AttnPlan {
   int nsplit;     // workgroups per (b,h): the tiles of its list go round them
   int max_split;  // upper bound of nsplit for any list no longer than the one planned for
-  int least;      // splits that a smaller workspace may bring it down to
+  int least;      // splits that a workspace has to have room for
+  int multiple;   // of which a smaller workspace leaves a multiple (shares of the list: one per XCD)
 };
 
 constexpr int kXcds = 8;  // accelerator complex dies of the chip, each with its own L2

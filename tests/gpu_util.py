@@ -2,6 +2,8 @@
 C ABI through the binding and hand results to the oracle as numpy arrays."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -93,6 +95,33 @@ def gpu_decode_step(q, q_imp, K, V, Kimp, N, k, sink, window, sm_scale, scale=1.
         ws = tb.new_workspace(tb.TB_OP_DECODE_STEP, d, need)
     tb.tb_decode_step(d, q_imp, Kimp, scale, q, K, V, k, sink, window, sm_scale, scores, idx, cnt, out, lse, ws)
     return scores, idx, cnt, out, lse
+
+
+class AttnPlan(ctypes.Structure):
+    """The library's own type (tb_internal.h): the workgroups per head that a launch of the attention gets."""
+    _fields_ = [(f, ctypes.c_int) for f in ("nsplit", "max_split", "least", "multiple")]
+
+
+def attn_plan(dtype, B, Hq, Hkv, D, rows):
+    """The library's plan of the attention over up to `rows` rows a head, and whether it cuts the lists into one share per XCD."""
+    lib = tb.load_library()
+    plan = lib._ZN2tb9attn_planEllib
+    plan.restype, plan.argtypes = AttnPlan, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_bool]
+    groups, f32 = B * Hkv, dtype == torch.float32
+    in_shares = Hq > Hkv and groups % 8 and groups < 64
+    p = plan(B * Hq, rows, lib._ZN2tb21attn_tile_rows_per_wgEii(tb.TB_F32 if f32 else tb.TB_BF16, D), bool(in_shares))
+    return p, bool(in_shares) and p.nsplit % 8 == 0
+
+
+def group_plan(dtype, B, Hq, Hkv, D, rows):
+    """The same for one list for all heads that a workgroup per KV group attends to; None where the lists go head by head."""
+    lib = tb.load_library()
+    d = tb.tb_cache_desc()
+    d.B, d.Hq, d.Hkv, d.D, d.dtype = B, Hq, Hkv, D, tb.TB_F32 if dtype == torch.float32 else tb.TB_BF16
+    grouped, plan = lib._ZN2tb24attn_shared_list_groupedEPK13tb_cache_descl, lib._ZN2tb15attn_group_planEPK13tb_cache_descl
+    grouped.restype, grouped.argtypes = ctypes.c_bool, [ctypes.POINTER(tb.tb_cache_desc), ctypes.c_int64]
+    plan.restype, plan.argtypes = AttnPlan, grouped.argtypes
+    return plan(ctypes.byref(d), rows) if grouped(ctypes.byref(d), rows) else None
 
 
 # --------------------------------------------------------------------------- the parity bars

@@ -12,7 +12,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 from paper_2503_07518_amd import binding as tb
-from gpu_util import (ATTN_TOL, DEV, assert_attention, assert_projection, assert_scores, dtype_name, gpu_attn,
+from gpu_util import (ATTN_TOL, DEV, assert_attention, assert_projection, assert_scores, attn_plan, dtype_name, gpu_attn,
                       gpu_decode_step, gpu_expand, gpu_project, gpu_score, gpu_select, np_of, projection_magnitude,
                       score_magnitude)
 
@@ -639,6 +639,39 @@ def test_attn_split_counts(oracle, dtype, B, Hq, Hkv, D, N, rows):
                                                idx[b:b + 1, h:h + 1].numpy(), cnt[b:b + 1, h:h + 1].numpy(), dn, sm)
             assert_attention(np_of(out[b, h]), ro[0, 0], dn, np_of(lse[b, h]), rl[0, 0])
         assert bool(torch.isfinite(out).all())
+
+
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,rows,rooms", [
+    (torch.bfloat16, 3, 32, 8, 5000, (7, 6, 5)),         # eight splits planned, six asked for
+    (torch.float32, 5, 8, 1, 4000, (20, 16, 14, 13, 12)),  # 24 in shares, one per XCD; thirteen asked for
+])
+def test_attn_workspace_with_room_for_fewer_splits(oracle, dtype, B, Hq, Hkv, rows, rooms):
+    """A workspace made for a shorter list serves with fewer splits as long as it holds what is asked for at least."""
+    D, N = 128, rows + 70
+    q, K, V = randn((B, Hq, D), dtype, 61), randn((B, Hkv, N, D), dtype, 62), randn((B, Hkv, N, D), dtype, 63)
+    plan, _ = attn_plan(dtype, B, Hq, Hkv, D, rows)
+    gen = torch.Generator().manual_seed(64)
+    idx = torch.rand((B, Hq, N), generator=gen).topk(rows, dim=-1).indices.sort(-1).values.to(torch.int32).to(DEV)
+    cnt = torch.full((B, Hq), rows, dtype=torch.int32, device=DEV)
+    d, dn = tb.make_desc(N, Hq, K=K, V=V), dtype_name(K)
+    ref = None
+    for room in (plan.nsplit, *rooms):
+        say(f"attn workspace dtype={dtype} B={B} Hq={Hq} Hkv={Hkv} rows={rows}: room for {room} of {plan.nsplit} splits, least {plan.least}")
+        shorter = next(r for r in range(1, rows + 1) if attn_plan(dtype, B, Hq, Hkv, D, r)[0].max_split >= room)
+        assert attn_plan(dtype, B, Hq, Hkv, D, shorter)[0].max_split == room
+        ws = tb.new_workspace(tb.TB_OP_ATTN, d, shorter)
+        if room < plan.least:
+            with pytest.raises(tb.TbError):
+                gpu_attn(q, K, V, idx, cnt, N, 0.1, ws=ws)
+            continue
+        out, lse = gpu_attn(q, K, V, idx, cnt, N, 0.1, ws=ws)
+        torch.cuda.synchronize()
+        if ref is None:
+            b, h, ref = B - 1, Hq - 1, (out, lse)
+            ro, rl = oracle.sparse_decode_attn(np_of(q[b:, h:]), np_of(K[b:, Hkv - 1:]), np_of(V[b:, Hkv - 1:]), np_of(idx[b:, h:]), np_of(cnt[b:, h:]), dn, 0.1)
+            assert_attention(np_of(out[b:, h:]), ro, dn, np_of(lse[b:, h:]), rl)
+        # fp32 sums in another order: 4000 terms err by a few 1e-6 of the largest at most
+        assert float((out - ref[0]).abs().max()) <= 1e-5 and float((lse - ref[1]).abs().max()) <= 1e-5 * float(ref[1].abs().max())
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,N,k", [(1, 32, 8, 32768, 3277), (16, 32, 8, 16384, 2048)])

@@ -85,6 +85,43 @@ def test_workspace_of_a_capacity_serves_fewer_rows(tb, B, Hq, Hkv, Dimp, k):
         assert sizes == sorted(sizes), (op, next((rows[i], sizes[i], rows[i + 1], sizes[i + 1]) for i in range(len(sizes) - 1) if sizes[i] > sizes[i + 1]))
 
 
+def rounded(rows, want, granule):
+    """`want` splits or a few less: as many as equal shares of whole granules make."""
+    share = -(-rows // want)
+    return -(-rows // (-(-share // granule) * granule))
+
+
+@pytest.mark.parametrize("f32,B,Hq,Hkv,rows,splits", [
+    (False, 1, 8, 2, 3277, 24), (False, 1, 16, 4, 8384, 32), (True, 1, 8, 1, 8196, 64), (False, 1, 16, 4, 3350, 16), (False, 2, 4, 2, 6890, 32),
+    (False, 1, 8, 1, 2050, 16), (False, 1, 8, 1, 3100, 24), (False, 1, 32, 4, 3100, 16)])
+def test_attention_plan_in_shares(tb, f32, B, Hq, Hkv, rows, splits):
+    """Where the plan counts on the list being cut into one share per XCD, the number of splits is a multiple of them."""
+    import torch
+    from gpu_util import attn_plan
+    p, in_shares = attn_plan(torch.float32 if f32 else torch.bfloat16, B, Hq, Hkv, 128, rows)
+    assert (p.nsplit, in_shares) == (splits, True)
+
+
+def test_attention_plan_and_workspace(tb):
+    """For every length: no more splits than a workspace made for that length has room for, no more asked for than two
+    workgroups a compute unit (which every workspace held that was made for as many rows), and from 32 splits on in shares."""
+    import torch
+    from gpu_util import attn_plan
+    for dtype, D in ((torch.bfloat16, 128), (torch.bfloat16, 64), (torch.float32, 128)):
+        tile = {(torch.bfloat16, 128): 64, (torch.bfloat16, 64): 128, (torch.float32, 128): 32}[dtype, D]
+        for B, Hq, Hkv in ((1, 1, 1), (1, 8, 1), (1, 8, 8), (1, 16, 2), (3, 8, 1), (1, 32, 4), (1, 32, 8), (3, 32, 8), (5, 40, 5), (2, 256, 256), (20, 64, 8)):
+            units, longest = B * Hq, 0
+            for rows in range(1, 12000, 41):
+                p, in_shares = attn_plan(dtype, B, Hq, Hkv, D, rows)
+                before = rounded(rows, max(1, min(-(-512 // units), rows // (2 * tile))), tile // 4)
+                assert 1 <= p.least <= min(p.nsplit, before) and p.nsplit <= p.max_split, (units, rows, tile)
+                assert longest <= p.max_split
+                longest = p.max_split
+                assert p.multiple in (1, 8) and p.nsplit % p.multiple == 0
+                if Hq > Hkv and B * Hkv % 8 and p.nsplit >= 32:
+                    assert in_shares, (units, rows, tile)
+
+
 def test_rejects_bad_arguments_without_launching(tb):
     L = tb.load_library()
     d = desc(tb)
