@@ -249,6 +249,7 @@ namespace {
 // array's name to a kernel (on the host it is only a stand-in for the symbol): the device
 // address is looked up once per device and kept.
 constexpr size_t kStaticScratchBytes = size_t{4} << 20;
+static_assert(kAttnMostWgs * (kCounterStrideWords + 128 + 2) * sizeof(float) + 512 <= kStaticScratchBytes, "heads that are split fit the scratch");
 constexpr int kMaxDevices = 64;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 std::mutex g_scratch_mutex;
@@ -480,9 +481,9 @@ tb_status tb_sparse_decode_attn_static(const tb_cache_desc* d, const void* q, co
   TB_TRY(check_attn_args(d, q, K, V, idx, count, idx_cap, max_count, tail_begin, tail_end, out));
   const int64_t units = static_cast<int64_t>(d->B) * d->Hq;
   if (units == 0) return TB_OK;
-  AttnPlan plan = attn_plan(d, max_count + (tail_end - tail_begin));
-  if (!fit_splits(d, plan, kStaticScratchBytes)) return TB_ERR_WORKSPACE;  // beyond the library's own scratch
+  const AttnPlan plan = attn_plan(d, max_count + (tail_end - tail_begin));
   const WsLayout w = ws_layout(units, d->D, plan.nsplit);
+  if (w.total > kStaticScratchBytes) return TB_ERR_WORKSPACE;  // beyond the library's own scratch
   void* ws = nullptr;
   TB_TRY(static_scratch(&ws));
   hipStream_t st = static_cast<hipStream_t>(stream);
