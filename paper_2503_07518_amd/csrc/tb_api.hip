@@ -425,11 +425,10 @@ tb_status tb_expand_neighbors(int32_t B, int32_t Hq, int64_t N, int32_t radius, 
                        cap_out, static_cast<hipStream_t>(stream));
 }
 
-namespace {
-tb_status sparse_attn(const tb_cache_desc* d, const void* q, const void* K, const void* V, const int32_t* idx,
-                      const int32_t* count, int64_t idx_cap, int64_t max_count, int64_t tail_begin,
-                      int64_t tail_end, float sm_scale, float* out, float* lse, void* ws, size_t ws_bytes,
-                      void* stream, bool shared_list) {
+static tb_status sparse_attn(const tb_cache_desc* d, const void* q, const void* K, const void* V, const int32_t* idx,
+                             const int32_t* count, int64_t idx_cap, int64_t max_count, int64_t tail_begin,
+                             int64_t tail_end, float sm_scale, float* out, float* lse, void* ws, size_t ws_bytes,
+                             void* stream, bool shared_list) {
   TB_TRY(check_attn_args(d, q, K, V, idx, count, idx_cap, max_count, tail_begin, tail_end, out));
   const int64_t units = static_cast<int64_t>(d->B) * d->Hq;
   if (units == 0) return TB_OK;
@@ -456,7 +455,6 @@ tb_status sparse_attn(const tb_cache_desc* d, const void* q, const void* K, cons
   L.grouped = grouped;
   return launch_attn(L, static_cast<hipStream_t>(stream));
 }
-}  // namespace
 
 tb_status tb_sparse_decode_attn(const tb_cache_desc* d, const void* q, const void* K, const void* V,
                                 const int32_t* idx, const int32_t* count, int64_t idx_cap, int64_t max_count,
@@ -513,10 +511,9 @@ tb_status tb_gather_kv(const tb_cache_desc* d, const void* K, const void* V, con
   return launch_gather(L, static_cast<hipStream_t>(stream));
 }
 
-namespace {
-tb_status check_gather(const tb_cache_desc* d, const void* K, const void* V, const int32_t* idx, const int32_t* count, int64_t idx_cap,
-                       int64_t max_count, int32_t skip_front, int32_t skip_back, void* Kbuf, void* Vbuf, int64_t buf_cap, int32_t* count_out,
-                       GatherLaunch& L) {
+static tb_status check_gather(const tb_cache_desc* d, const void* K, const void* V, const int32_t* idx, const int32_t* count, int64_t idx_cap,
+                              int64_t max_count, int32_t skip_front, int32_t skip_back, void* Kbuf, void* Vbuf, int64_t buf_cap, int32_t* count_out,
+                              GatherLaunch& L) {
   TB_TRY(check_desc(d));
   if (!K || !V || !idx || !count || !Kbuf || !Vbuf || !count_out) return TB_ERR_INVALID_ARG;
   if (idx_cap < 0 || max_count < 0 || max_count > idx_cap || skip_front < 0 || skip_back < 0) return TB_ERR_INVALID_ARG;
@@ -530,7 +527,6 @@ tb_status check_gather(const tb_cache_desc* d, const void* K, const void* V, con
   L = GatherLaunch{d, K, V, idx, count, idx_cap, max_count, Kbuf, Vbuf, buf_cap, skip_front, skip_back, count_out};
   return TB_OK;
 }
-}  // namespace
 
 tb_status tb_gather_important(const tb_cache_desc* d, const void* K, const void* V, const int32_t* idx,
                               const int32_t* count, int64_t idx_cap, int64_t max_count, int32_t skip_front,
@@ -541,9 +537,8 @@ tb_status tb_gather_important(const tb_cache_desc* d, const void* K, const void*
   return launch_gather(L, static_cast<hipStream_t>(stream));
 }
 
-namespace {
-tb_status check_append(const tb_cache_desc* src, const void* K, const void* V, int64_t src_row, const tb_cache_desc* dst, const void* Kdst,
-                       const void* Vdst, int64_t dst_row, int64_t rows) {
+static tb_status check_append(const tb_cache_desc* src, const void* K, const void* V, int64_t src_row, const tb_cache_desc* dst, const void* Kdst,
+                              const void* Vdst, int64_t dst_row, int64_t rows) {
   TB_TRY(check_desc(src));
   TB_TRY(check_desc(dst));
   if (!K || !V || !Kdst || !Vdst || rows < 0 || src_row < 0 || dst_row < 0) return TB_ERR_INVALID_ARG;
@@ -558,9 +553,9 @@ tb_status check_append(const tb_cache_desc* src, const void* K, const void* V, i
   return TB_OK;
 }
 
-tb_status buffered_attn(const tb_cache_desc* d, const void* q, const void* Kbuf, const void* Vbuf, int64_t buf_cap, const int32_t* count,
-                        int64_t max_count, const void* K, const void* V, int64_t tail_begin, int64_t tail_end, float sm_scale, float* out,
-                        float* lse, void* ws, size_t ws_bytes, void* stream, const NewRow* append, const GatherLaunch* migrate = nullptr) {
+static tb_status buffered_attn(const tb_cache_desc* d, const void* q, const void* Kbuf, const void* Vbuf, int64_t buf_cap, const int32_t* count,
+                               int64_t max_count, const void* K, const void* V, int64_t tail_begin, int64_t tail_end, float sm_scale, float* out,
+                               float* lse, void* ws, size_t ws_bytes, void* stream, const NewRow* append, const GatherLaunch* migrate = nullptr) {
   if (!Kbuf || !Vbuf || buf_cap < 0 || max_count > buf_cap) return TB_ERR_INVALID_ARG;
   // the list itself is not read: its place in the argument check is taken by the count array
   TB_TRY(check_attn_args(d, q, K, V, count, count, buf_cap, max_count, tail_begin, tail_end, out));
@@ -589,7 +584,6 @@ tb_status buffered_attn(const tb_cache_desc* d, const void* q, const void* Kbuf,
   L.migrate = migrate;
   return launch_attn(L, static_cast<hipStream_t>(stream));
 }
-}  // namespace
 
 tb_status tb_append_kv(const tb_cache_desc* src, const void* K, const void* V, int64_t src_row, const tb_cache_desc* dst,
                        void* Kdst, void* Vdst, int64_t dst_row, int64_t rows, void* stream) {

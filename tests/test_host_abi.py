@@ -33,6 +33,9 @@ def test_header_symbols_are_exported(tb):
     lib = tb.load_library()
     for n in names:
         assert getattr(lib, n) is not None
+    # nothing else takes up a name without a namespace, which a program's own function of that name would stand in for
+    for n in ("sparse_attn", "buffered_attn", "check_gather", "check_append"):
+        assert not hasattr(lib, n), n
 
 
 def test_version_and_status_strings(tb):
