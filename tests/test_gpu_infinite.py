@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import DEV, assert_attention, gpu_attn, gpu_decode_step, np_of
+from gpu_util import DEV, assert_attention, attn_plan, gpu_attn, gpu_decode_step, group_plan, np_of
 from paper_2503_07518_amd import binding as tb
 
 pytestmark = pytest.mark.gpu
@@ -44,29 +44,33 @@ def tensors(dtype, B, Hq, Hkv, N, D, seed):
 
 
 @pytest.mark.parametrize("dtype,D,B,Hkv,g,unit,splits,shared", [
-    # a list per head: `unit` rows are two tiles for each of a workgroup's four waves, so that `splits` of them make as
-    # many splits; either side of the numbers that fill the thread groups which add the splits up
-    *[(torch.bfloat16, 128, 1, 8, 1, 128, n, False) for n in (2, 8, 9, 15, 16, 17, 31, 33)],
-    *[(torch.float32, 128, 1, 4, 1, 64, n, False) for n in (7, 10, 21)],
-    *[(torch.bfloat16, 64, 1, 2, 4, 256, n, False) for n in (5, 16, 18)],
-    *[(torch.float32, 64, 1, 2, 2, 128, n, False) for n in (13, 30)],
+    # a list per head: `unit` rows are two tiles for each of a workgroup's four waves; either side of the numbers of splits that
+    # fill the thread groups which add them up (8, 16, 32 with D = 128, 16, 32, 64 with D = 64), where the plan has such numbers
+    *[(torch.bfloat16, 128, 1, 8, 1, 128, n, False) for n in (2, 8, 9, 15, 16, 17, 31)],
+    *[(torch.bfloat16, 128, 1, 4, 1, 128, n, False) for n in (32, 33, 47)],
+    *[(torch.float32, 128, 1, 4, 1, 64, n, False) for n in (7, 10, 21, 33)],
+    *[(torch.bfloat16, 64, 1, 2, 4, 256, n, False) for n in (5, 16, 24)],
+    *[(torch.float32, 64, 1, 2, 2, 128, n, False) for n in (13, 32, 40)],
     # one list for all heads, a workgroup per KV group: matrix cores (steps of 256 rows), vector form
     *[(torch.bfloat16, 128, 4, 8, 4, 256, n, True) for n in (4, 5, 7)],
     *[(torch.bfloat16, 64, 2, 8, 8, 256, n, True) for n in (13, 15)],
     *[(torch.float32, 128, 4, 8, 2, 64, n, True) for n in (4, 6, 13)],
-    *[(torch.float32, 128, 4, 8, 8, 64, n, True) for n in (3, 9)],
-    *[(torch.bfloat16, 64, 8, 8, 2, 256, n, True) for n in (3, 5)],
+    *[(torch.float32, 128, 4, 8, 8, 64, n, True) for n in (3, 12)],
+    *[(torch.bfloat16, 64, 8, 8, 2, 256, n, True) for n in (3, 6)],
 ])
 def test_infinite_values_of_every_split(oracle, dtype, D, B, Hkv, g, unit, splits, shared):
     """Every split attends a row with an infinite element in a column of its own; the list ends with a whole tile."""
     say(f"infinite values of every split dtype={dtype} D={D} B={B} Hkv={Hkv} g={g} splits={splits} shared={shared}")
-    Hq, rows = g * Hkv, unit * splits
+    Hq = g * Hkv
+    plan = (lambda rows: group_plan(dtype, B, Hq, Hkv, D, rows)) if shared else (lambda rows: attn_plan(dtype, B, Hq, Hkv, D, rows)[0])
+    rows = next((r for r in range(unit // 2, 100 * unit, unit // 2) if (p := plan(r)) and p.nsplit == splits), None)
+    assert rows, "the plan has no such number of splits"
     N, dn = rows + 40, "f32" if dtype == torch.float32 else "bf16"
     q, K, V, gen = tensors(dtype, B, Hq, Hkv, N, D, splits + D)
     idx = torch.stack([torch.randperm(N, generator=gen)[:rows].sort().values for _ in range(B)]).to(torch.int32)
     cnt = torch.full((B,), rows, dtype=torch.int32)
     for b in range(B):
-        for j in range(2 * splits):  # (half a unit is the least that one split takes in a row)
+        for j in range(2 * rows // unit):  # (half a unit is the least that one split takes in a row)
             V[b, :, int(idx[b, j * unit // 2 + j % 8]), j % (D - 4)] = INF if j % 3 else -INF
         V[b, :, int(idx[b, rows - 1]), D - 1] = INF
         V[b, :, int(idx[b, rows // 2]), D - 2] = float("nan")

@@ -611,13 +611,22 @@ def test_attn_lists_that_are_columns_of_an_array(dtype, B, Hq, Hkv, D, rows):
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and bool(torch.isfinite(a[0]).all())
 
 
+# splits a head for the full lists of the test below, and whether they are one share of the list per XCD
+SPLIT_COUNTS = {(3, 32, 8, 128, 1100): (5, False), (22, 8, 1, 128, 1030): (4, False), (9, 32, 8, 64, 2049): (3, False), (20, 16, 4, 128, 640): (3, False),
+                (1, 4, 4, 64, 385): (3, False), (41, 64, 8, 64, 257): (1, False), (22, 8, 1, 128, 2070): (8, True), (1, 16, 2, 64, 8200): (16, True),
+                (5, 8, 4, 128, 4000): (24, True)}
+
+
 @pytest.mark.parametrize("dtype,B,Hq,Hkv,D,N,rows", [
     (torch.bfloat16, 3, 32, 8, 128, 3000, 1100),   # 5 splits, 480 workgroups
-    (torch.bfloat16, 22, 8, 1, 128, 1500, 1030),   # shares of a list on more heads than half the compute units
+    (torch.bfloat16, 22, 8, 1, 128, 1500, 1030),   # more heads than half the compute units, four splits
     (torch.bfloat16, 9, 32, 8, 64, 2500, 2049),    # more heads than compute units, split
     (torch.float32, 20, 16, 4, 128, 700, 640),
     (torch.float32, 1, 4, 4, 64, 400, 385),
     (torch.bfloat16, 41, 64, 8, 64, 300, 257),     # one split a head, several rounds
+    (torch.bfloat16, 22, 8, 1, 128, 2500, 2070),   # eight splits: one share of the list per XCD
+    (torch.bfloat16, 1, 16, 2, 64, 9000, 8200),    # shares of two workgroups and more
+    (torch.float32, 5, 8, 4, 128, 4100, 4000),
 ])
 def test_attn_split_counts(oracle, dtype, B, Hq, Hkv, D, N, rows):
     """Numbers of heads either side of the compute units and of whole rounds of them: full lists, a list that ends before most
@@ -627,7 +636,8 @@ def test_attn_split_counts(oracle, dtype, B, Hq, Hkv, D, N, rows):
     q, K, V = randn((B, Hq, D), dtype, 51), randn((B, Hkv, N, D), dtype, 52), randn((B, Hkv, N, D), dtype, 53)
     gen = torch.Generator().manual_seed(54)
     idx = torch.rand((B, Hq, N), generator=gen).topk(rows, dim=-1).indices.sort(-1).values.to(torch.int32)
-    from paper_2503_07518_amd import binding as tb
+    plan, in_shares = attn_plan(dtype, B, Hq, Hkv, D, rows)
+    assert (plan.nsplit, in_shares) == SPLIT_COUNTS[B, Hq, Hkv, D, rows], "the plan has changed: these shapes were chosen for theirs"
     ws = tb.new_workspace(tb.TB_OP_ATTN, tb.make_desc(N, Hq, K=K, V=V), rows)
     for most in (rows, rows // 3, 70):
         cnt = torch.full((B, Hq), most, dtype=torch.int32)
@@ -756,14 +766,15 @@ def test_decode_step_matches_separate_calls_and_oracle(oracle, dtype, B, Hq, Hkv
 ])
 def test_decode_step_large_lists(oracle, dtype, B, g, Hkv, D, N, k, sink, window):
     """Lists of more than 100 MB of rows, just selected, are gathered non-temporally; handed in, like any others: the same
-    bits, with an infinite row among those that a tile's empty slots and nobody's list may load.  One unit against the oracle."""
+    bits, with an infinite row that is in nobody's list; without a sink it is the one that a tile's empty slots load.  One unit
+    against the oracle."""
     say(f"decode_step large lists dtype={dtype} B={B} g={g} Hkv={Hkv} D={D} N={N} k={k} S={sink} W={window}")
     Hq, Dimp, sm = g * Hkv, 16, 1 / math.sqrt(D)
     q, q_imp = randn((B, Hq, D), dtype, 36), randn((B, Hq, Dimp), dtype, 37)
     gen = torch.Generator(device=DEV).manual_seed(38)
     K, V = (torch.randn((B, Hkv, N, D), generator=gen, device=DEV).to(dtype) for _ in range(2))
     Kimp = torch.randn((B, Hkv, N, Dimp), generator=gen, device=DEV).to(dtype)
-    low = sink + 1  # (never selected: the only row with a score that is not finite)
+    low = sink + 1 if sink else 0  # (never selected: the only row with a score that is not finite; an empty slot loads row 0)
     Kimp[:, :, low], V[:, :, low] = float("nan"), float("inf")
     s, idx, cnt, out, lse = gpu_decode_step(q, q_imp, K, V, Kimp, N, k, sink, window, sm)
     out2, lse2 = gpu_attn(q, K, V, idx, cnt, N, sm, max_count=idx.shape[-1])
