@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import DEV, assert_attention, dtype_name, gpu_attn, np_of
+from gpu_util import DEV, assert_attention, attn_plan, dtype_name, gpu_attn, np_of
 from paper_2503_07518_amd import binding as tb, interval, workloads
 
 pytestmark = pytest.mark.gpu
@@ -254,14 +254,52 @@ def test_append_with_buffered_attention(dtype, B, Hq, Hkv, D, cap, counts, tail,
 def test_migration_with_buffered_attention(dtype, B, Hq, Hkv, D, cap, counts, front, back, tail, slot):
     """Rows that migrate with the attention: buffers (past the migrated rows untouched), counts, ring and results the same bits as
     the separate calls, for lists with entries outside the cache, too."""
-    say(f"migration with attention dtype={dtype} B={B} Hq={Hq} Hkv={Hkv} D={D} cap={cap} front={front} back={back} tail={tail} slot={slot}")
+    check_migration(dtype, B, Hq, Hkv, D, 2 * cap + 50, cap, counts, front, back, tail, slot)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("D,Hq,Hkv,sparse,slot", [(64, 8, 2, True, 77), (128, 8, 1, True, 0), (64, 16, 2, False, 127), (128, 4, 2, False, 5)])
+def test_migration_in_shares(dtype, D, Hq, Hkv, sparse, slot):
+    """Few KV groups: the lists go in shares, one per XCD.  Rows that few heads list (read non-temporally) and many, with a row that
+    arrives; infinite and NaN rows among those that are listed, and in row 0, which slots past the end load and no list holds."""
+    cap, front, back, tail = 3001, 16, 40, (3, 128)
+    _, in_shares = attn_plan(dtype, 1, Hq, Hkv, D, cap + tail[1] - tail[0])
+    assert in_shares, "the plan has changed: these shapes were chosen for theirs"
+    N, g = (40 if sparse else 2) * cap, Hq // Hkv
+    p = (cap - front - back) / N
+    assert (g * p / (1 - (1 - p) ** g) <= 1.3) == sparse  # (readers a row up to which rows are not kept in the caches)
+    check_migration(dtype, 1, Hq, Hkv, D, N, cap, (cap, 1999, 2 * cap // 3, 30), front, back, tail, slot, infinite=True)
+
+
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,D,cap,sparse", [(torch.bfloat16, 2, 8, 8, 128, 700, True), (torch.float32, 2, 16, 8, 64, 333, False)])
+def test_migration_of_infinite_rows(dtype, B, Hq, Hkv, D, cap, sparse):
+    """The same without shares."""
+    assert not attn_plan(dtype, B, Hq, Hkv, D, cap + 90)[1]
+    check_migration(dtype, B, Hq, Hkv, D, (20 if sparse else 2) * cap, cap, (cap, 3, cap // 2 + 1), 2, 1, (10, 100), 64, infinite=True)
+
+
+def same(a, b):
+    """Equal bits, one NaN being like another."""
+    nan = torch.isnan(a) if a.is_floating_point() else torch.zeros_like(a, dtype=torch.bool)
+    return torch.equal(nan, torch.isnan(b) if b.is_floating_point() else nan) and torch.equal(a.masked_fill(nan, 0), b.masked_fill(nan, 0))
+
+
+def check_migration(dtype, B, Hq, Hkv, D, N, cap, counts, front, back, tail, slot, infinite=False):
+    say(f"migration with attention dtype={dtype} B={B} Hq={Hq} Hkv={Hkv} D={D} N={N} cap={cap} front={front} back={back} tail={tail} slot={slot}")
     g = torch.Generator().manual_seed(82)
-    N, R = 2 * cap + 50, 128
+    R = 128
     K, V = (torch.randn((B, N, Hkv, D), generator=g).to(dtype).to(DEV).transpose(1, 2) for _ in range(2))  # strides of their own
     aK, aV = (torch.randn((B, Hkv, R, D), generator=g).to(dtype).to(DEV) for _ in range(2))
     q = torch.randn((B, Hq, D), generator=g).to(dtype).to(DEV)
-    idx = torch.rand((B, Hq, N), generator=g).topk(cap, dim=-1).indices.sort(-1).values.to(torch.int32)
+    idx = torch.rand((B, Hq, N), generator=g)
+    idx[:, :, 0] = 0.0 if infinite else idx[:, :, 0]
+    idx = idx.topk(cap, dim=-1).indices.sort(-1).values.to(torch.int32)
     idx[0, 0, :2], idx[-1, -1, -2:] = -5, N + 7
+    if infinite:
+        idx.clamp_(min=1)
+        V[:, :, 0, 1], V[:, :, 0, 2], V[:, :, 0, 3], K[:, :, 0, 5] = float("inf"), -float("inf"), float("nan"), float("inf")
+        V[0, 0, int(idx[0, 0, cap // 2]), 7], V[0, -1, int(idx[0, -1, front]), 9] = float("inf"), float("nan")
+        V[:, :, N - 1, 11] = -float("inf")
     idx, cnt = idx[:, :, :cap].contiguous().to(DEV), torch.tensor([counts[i % len(counts)] for i in range(B * Hq)], dtype=torch.int32, device=DEV).view(B, Hq)
     src, dst = tb.make_desc(N, Hq, K=K, V=V), tb.make_desc(R, Hq, K=aK, V=aV)
     ws = tb.new_workspace(tb.TB_OP_ATTN, dst, cap + R)
@@ -281,7 +319,12 @@ def test_migration_with_buffered_attention(dtype, B, Hq, Hkv, D, cap, counts, fr
             tb.tb_buffered_decode_attn(dst, q, Kb, Vb, n_out, cap, k, v, 0.1, out, lse, ws, *tail)
         torch.cuda.synchronize()
         res.append((k, v, Kb, Vb, n_out, out, lse))
-    assert all(torch.equal(a, b) for a, b in zip(*res)) and bool(torch.isfinite(res[0][5]).all())
+    assert all(same(a, b) for a, b in zip(*res))
+    finite = torch.isfinite(res[0][5])
+    if infinite:  # only where a listed row makes it so, never from row 0
+        assert bool(finite[:, :, (1, 2, 3, 5)].all()) and 0 < int((~finite).sum()) <= 3 * B * Hq and bool(torch.isfinite(res[0][6]).all())
+    else:
+        assert bool(finite.all())
     assert torch.equal(res[0][4], (cnt - front - back).clamp(min=0))
     for bad in (dict(cap=cap + 1), dict(front=-1), dict(src_row=N), dict(dst_row=R)):
         with pytest.raises(tb.TbError):

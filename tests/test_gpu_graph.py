@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 from gpu_util import DEV, np_of
 from paper_2503_07518_amd import binding as tb
-from paper_2503_07518_amd import workloads
+from paper_2503_07518_amd import interval, workloads
 
 
 def _capture(fn):
@@ -100,3 +100,44 @@ def test_static_scratch_attention_in_a_graph():
         call()                       # and an eager call on the same scratch in between
         torch.cuda.synchronize()
         assert torch.equal(a["out"], ref_out)
+
+
+def test_three_buffer_steps_in_a_graph():
+    """A prediction step, whose rows migrate on the way, and a reuse step of the three-buffer layout, each with a row that arrives."""
+    print("[case] graph replay: three-buffer layout, a prediction and a reuse step", flush=True)
+    cfg = workloads.C4.scaled(name="C4_graph_ring", B=2, N=4096, k=256, steps=6, P=4, heavy_per_kv_head=8)
+    data = workloads.make_layer(cfg, device=DEV)
+    K, V = data["K"], data["V"]
+    Kimp = torch.zeros((cfg.B, cfg.Hkv, K.shape[2], cfg.Dimp), dtype=K.dtype, device=DEV)
+    tb.tb_project_keys(tb.make_desc(cfg.N, cfg.Hq, K=K, V=V, Kimp=Kimp), K, data["W"], Kimp, 0, cfg.N)
+    dec = interval.RingLayoutDecoder(K, V, data["W"], Kimp, cfg.Hq, cfg.k, cfg.P, cfg.radius, 8, sink=16, sm_scale=cfg.sm_scale)
+    q, q_imp = [[t.contiguous() for t in data[n]] for n in ("q", "q_imp")]
+
+    def steps(which):
+        return [tuple(x.clone() for x in dec.step(t, cfg.N + t, q[t], q_imp[t])) for t in which]
+    first = steps(range(4))
+    ref = steps((4, 5))
+    kept = {name: getattr(dec, name).clone() for name in ("aux_K", "aux_V", "imp_cnt", "exp_cnt")}
+    mask = (torch.arange(dec.exp_cap, device=DEV) < kept["imp_cnt"][:, :, None])[..., None]
+    rows = [torch.where(mask, b, 0) for b in (dec.Kbuf, dec.Vbuf)]
+    got = [torch.empty_like(x) for pair in ref for x in pair]
+
+    def call():
+        for i, t in enumerate((4, 5)):
+            out, lse = dec.step(t, cfg.N + t, q[t], q_imp[t])
+            got[2 * i].copy_(out)
+            got[2 * i + 1].copy_(lse)
+    g = _capture(call)
+    for r in range(3):
+        assert all(torch.equal(a, b) for x, y in zip(steps(range(4)), first) for a, b in zip(x, y))  # eager steps between the replays
+        for x in got + [dec.Kbuf, dec.Vbuf]:
+            x.fill_(float("nan"))
+        dec.aux_K[:, :, 16 + 3:], dec.aux_V[:, :, 16 + 3:] = float("nan"), float("nan")  # the slots that the two steps fill, and those behind
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, [x for pair in ref for x in pair])), f"replay {r} differs"
+        for name in ("imp_cnt", "exp_cnt"):
+            assert torch.equal(getattr(dec, name), kept[name]), name
+        assert torch.equal(dec.aux_K[:, :, :16 + 5], kept["aux_K"][:, :, :16 + 5]) and torch.equal(dec.aux_V[:, :, :16 + 5], kept["aux_V"][:, :, :16 + 5])
+        assert all(torch.equal(torch.where(mask, b, 0), want) for b, want in zip((dec.Kbuf, dec.Vbuf), rows))
