@@ -29,13 +29,18 @@ static AttnPlan split_plan(int64_t max_rows, int64_t want, int granule) {
 // Splits per head.  A launch lasts as long as the compute unit with the most workgroups, each costing its rows and a start that
 // is worth kStart tiles, so that many splits pay where they even out the last round; every split costs the head's last
 // workgroup kHandOver tiles; one workgroup a compute unit does not keep enough gathers in flight (kAlone), and splits in shares, one
-// per XCD, read a fifth less from beyond their L2 (kShares).  bf16, D = 128, us with 512 / units splits rounded up, and now:
-// 3 x 32 heads on 8, 2433 rows 23.6 and 21.1 (6 splits put a third workgroup on a quarter of the compute units); 5 x 32, 3000 rows
-// 46.1 and 41.2; 14 x 32, 700 rows 27.9 and 24.0; 10 x 64, 3000 rows 119 and 108 (two instead of one); 22 x 8 on 1 50.6 and 37.7 (8
-// instead of 3: shares); fp32 3 x 32, 2400 rows 44.5 and 38.4.  Over 179 shapes of 8 to 960 heads, 200 to 12000 rows, both types
-// and sizes of head, the choice is 0.7% off the best of the numbers tried on average (512 / units: 6.4%), and at most 3.5% behind it.
+// per XCD, read a fifth less from beyond their L2 (kShares; in a launch of one round, which waits for trips more than for bytes,
+// kSharesAlone: 8 heads on 2, 1590 rows 9.0 us with 8 splits in shares and 7.8 with 12 without; 16 on 2, 4500 rows 11.2 with 16
+// and 10.5 with 24).  bf16, D = 128, us with 512 / units splits rounded up, and now: 3 x 32 heads on 8, 2433 rows 23.6 and 21.1 (6
+// splits put a third workgroup on a quarter of the compute units); 5 x 32, 3000 rows 46.1 and 41.2; 14 x 32, 700 rows 27.9 and 24.0;
+// 10 x 64, 3000 rows 119 and 108 (two instead of one); 22 x 8 on 1 50.6 and 37.7 (8 instead of 3: shares); fp32 3 x 32, 2400 rows
+// 44.5 and 38.4.  The constants were chosen on 179 shapes of 8 to 960 heads, 200 to 12000 rows, both types and sizes of head (the choice
+// 0.7% off the best of the numbers tried on average and 11% at most, 512 / units 6.4% on average; 18 of the numbers chosen had not
+// been tried, the nearest one stands for them), kSharesAlone on 216 of 4 to 40 heads on 1, 2 or 4 KV heads (0.8% and 7%).  On other
+// shapes, drawn at random: 86 of all kinds 1.0% off the best on average, 13% at most (before kSharesAlone), and against 512 / units 3%
+// faster on average, 4% slower at most without shares; 60 of few KV groups against 512 / units 9% faster on average, none slower.
 AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool shares) {
-  constexpr double kStart = 1.6, kHandOver = 0.1, kAlone = 1.6, kShares = 0.8;
+  constexpr double kStart = 1.6, kHandOver = 0.1, kAlone = 1.6, kShares = 0.8, kSharesAlone = 0.91;
   if (max_rows <= 0 || units <= 0) return AttnPlan{1, 1, 1, 1};
   const int64_t most = std::max<int64_t>(1, std::min(max_rows / (kAttnMinTiles * tile_rows_per_wg), kAttnMostWgs / units));
   int64_t want = 1;
@@ -44,7 +49,7 @@ AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool s
     const int64_t rounds = (units * n + kAttnCus - 1) / kAttnCus;
     double cost = static_cast<double>(rounds) * (static_cast<double>(max_rows) / static_cast<double>(n) + kStart * tile_rows_per_wg);
     if (rounds == 1) cost *= kAlone;
-    if (shares && n % kXcds == 0) cost *= kShares;
+    if (shares && n % kXcds == 0) cost *= rounds == 1 ? kSharesAlone : kShares;
     cost += kHandOver * static_cast<double>(n * tile_rows_per_wg);
     if (cost < least) {
       least = cost;

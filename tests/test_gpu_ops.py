@@ -532,11 +532,11 @@ def test_attn_full_budget_equals_dense_and_tail(oracle):
 
 
 @pytest.mark.parametrize("dtype,g,Hkv,D", [(torch.bfloat16, 8, 1, 128), (torch.bfloat16, 4, 2, 64), (torch.float32, 2, 4, 128)])
-@pytest.mark.parametrize("cap,counts", [(1500, (1500, 1, 127)), (3000, (129, 2999, 0)), (3000, (1023, 1025, 2048))])
+@pytest.mark.parametrize("cap,counts", [(1500, (1500, 1, 127)), (3000, (129, 2999, 0)), (3000, (1023, 1025, 2048)), (5000, (129, 4999, 0)), (5000, (1023, 1025, 5000))])
 def test_attn_few_groups_shares(oracle, dtype, g, Hkv, D, cap, counts):
-    """Few KV groups, whose lists are cut into one share per XCD: lists of every length below their
+    """Few KV groups, whose longer lists are cut into one share per XCD: lists of every length below their
     capacity, with a tail, and the buffered form the same bit for bit."""
-    from paper_2503_07518_amd import binding as tb
+    assert cap < 5000 or attn_plan(dtype, 1, g * Hkv, Hkv, D, cap + 7)[1], "the plan has changed: these shapes were chosen for theirs"
     say(f"attn shares dtype={dtype} g={g} Hkv={Hkv} D={D} counts={counts}")
     B, Hq, N = 1, g * Hkv, 2 * cap + 9
     q, K, V = randn((B, Hq, D), dtype, 26), randn((B, Hkv, N, D), dtype, 27), randn((B, Hkv, N, D), dtype, 28)
@@ -613,7 +613,7 @@ def test_attn_lists_that_are_columns_of_an_array(dtype, B, Hq, Hkv, D, rows):
 
 # splits a head for the full lists of the test below, and whether they are one share of the list per XCD
 SPLIT_COUNTS = {(3, 32, 8, 128, 1100): (5, False), (22, 8, 1, 128, 1030): (4, False), (9, 32, 8, 64, 2049): (3, False), (20, 16, 4, 128, 640): (3, False),
-                (1, 4, 4, 64, 385): (3, False), (41, 64, 8, 64, 257): (1, False), (22, 8, 1, 128, 2070): (8, True), (1, 16, 2, 64, 8200): (16, True),
+                (1, 4, 4, 64, 385): (3, False), (41, 64, 8, 64, 257): (1, False), (22, 8, 1, 128, 2070): (8, True), (1, 16, 2, 64, 8200): (32, True),
                 (5, 8, 4, 128, 4000): (24, True)}
 
 

@@ -95,7 +95,7 @@ def rounded(rows, want, granule):
 
 
 @pytest.mark.parametrize("f32,B,Hq,Hkv,rows,splits", [
-    (False, 1, 8, 2, 3277, 24), (False, 1, 16, 4, 8384, 32), (True, 1, 8, 1, 8196, 64), (False, 1, 16, 4, 3350, 16), (False, 2, 4, 2, 6890, 32),
+    (False, 1, 8, 2, 3277, 24), (False, 1, 16, 4, 8384, 32), (True, 1, 8, 1, 8196, 64), (False, 1, 16, 4, 3350, 24), (False, 2, 4, 2, 6890, 32),
     (False, 1, 8, 1, 2050, 16), (False, 1, 8, 1, 3100, 24), (False, 1, 32, 4, 3100, 16)])
 def test_attention_plan_in_shares(tb, f32, B, Hq, Hkv, rows, splits):
     """Where the plan counts on the list being cut into one share per XCD, the number of splits is a multiple of them."""
@@ -103,6 +103,16 @@ def test_attention_plan_in_shares(tb, f32, B, Hq, Hkv, rows, splits):
     from gpu_util import attn_plan
     p, in_shares = attn_plan(torch.float32 if f32 else torch.bfloat16, B, Hq, Hkv, 128, rows)
     assert (p.nsplit, in_shares) == (splits, True)
+
+
+@pytest.mark.parametrize("f32,B,Hq,Hkv,D,rows,splits", [(False, 1, 8, 2, 128, 1590, 12), (False, 1, 16, 4, 128, 1590, 12), (True, 1, 16, 2, 64, 1590, 12),
+                                                        (False, 2, 4, 1, 128, 1300, 10)])
+def test_attention_plan_of_few_short_lists(tb, f32, B, Hq, Hkv, D, rows, splits):
+    """In a launch of one round the shares' gain is small: eight of them do not take the place of half as many splits again."""
+    import torch
+    from gpu_util import attn_plan
+    p, in_shares = attn_plan(torch.float32 if f32 else torch.bfloat16, B, Hq, Hkv, D, rows)
+    assert (p.nsplit, in_shares) == (splits, False)
 
 
 def test_attention_plan_and_workspace(tb):
