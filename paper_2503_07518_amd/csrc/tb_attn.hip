@@ -829,14 +829,19 @@ tb_status launch_group(const AttnArgs& a, const AttnLaunch& L, hipStream_t st) {
 
 // Non-temporal gathers of lists of up to `rows` rows.  With lists that do not depend on each other the g heads of a group read
 // `distinct` rows of N and come back to each of them g * rows / distinct times.  A step that has just selected its lists finds little in the
-// last-level cache from 100 MB of different rows on; beyond 1.3 readers a row (1.4 where the rows are far more than that cache), and
-// for groups of eight, whose lists share more than that where the scores favour the same rows, the lines are wanted again.
-// Attention alone in us, plain and non-temporal
-// (D = 128, bf16; B x heads on KV heads, listed of N): 4 x 32 on 8, 1638 of 16384 (92 MB) 19.6 and 20.2; 4 x 8 on 8, 6554 of 32768
-// (107 MB) 22.2 and 21.5; 4 x 16 on 8, 4096 of 32768 (126 MB) 27.2 and 24.9; 8 x 32 on 8, 1638 of 16384 (184 MB, 1.16) 37.7 and 33.5; 4 x 32
-// on 8, 12450 of 65536 (612 MB, 1.33) 104.1 and 102.0, an interval of 8 steps that reuse such lists 814 and 800; 4 x 32 on 8, 18350 of 65536
-// (785 MB, 1.53) 130.8 and 139.3; 16 x 64 on 8, 1638 of 16384 (1.4) 112.6 and 119; 4 x 64 on 8, 4096 of 131072,
-// the same rows in many lists (1.11 if they were not) 56.1 and 63.5.  Lists that are handed in may be those of the step before, whose rows
+// last-level cache from 100 MB of different rows on; beyond 1.3 readers a row (1.4 where the rows are far more than that cache)
+// the lines are wanted again.  Whole steps in us over copies that no cache holds, plain and non-temporal (D = 128, bf16; B x heads on KV
+// heads, listed of N): 4 x 16 on 8, 3277 of 32768 (101 MB) 47.7 and 47.9; 3 x 32 on 8, 2600 of 32768 (111 MB) 51.8 and 47.5; 5 x 16 on
+// 8, 3277 of 32768 (126 MB) 58.3 and 55.4; 4 x 32 on 8, 3277 of 32768 (182 MB) 67.7 and 63.8; 4 x 32 on 8, 8192 of 131072 (480 MB) 175
+// and 161.  Attention alone: 4 x 32 on 8, 12450 of 65536 (612 MB, 1.33) 104.1 and 102.0, an interval of 8 steps that reuse such lists
+// 814 and 800; 4 x 32 on 8, 18350 of 65536 (785 MB, 1.53) 130.8 and 139.3; 16 x 64 on 8, 1638 of 16384 (1.4) 112.6 and 119.
+// Sizes do not say whether the heads of a group favour the same rows.  With projected keys of Zipf-scaled magnitude, steps: two heads a
+// group (1.28 readers a row instead of 1.06) 5 x 16 on 8, 3277 of 32768 53.1 and 52.4, 4 x 16 on 8, 8192 of 131072 118 and 113; four (1.9
+// instead of 1.2) 4 x 32 on 8, 3277 of 32768 57.7 and 58.3, 16 x 32 on 8, 1638 of 16384 96.1 and 98.6, 4 x 32 on 8, 8192 of 131072 152
+// and 141: 3% lost at most, where independent lists win 3 to 8%.  Eight lose more (attention alone, with an earlier loop, 4 x 64 on 8,
+// 4096 of 131072 56.1 and 63.5), and so do lists in shares: both are read plainly (shares, steps: 7 x 16 on 4, 3277 of 32768 66.8 and
+// 62.6, 13 x 8 on 4, 6000 of 40000 108 and 101, but Zipf-scaled 7 x 16 on 4 54.4 and 57.8, 9 x 16 on 4, 4000 of 40000 78.2 and 85.4).
+// Lists that are handed in may be those of the step before, whose rows
 // that cache still holds unless they are far more than it has room for: intervals of 8 steps that reuse lists of 220 MB 339 and
 // 349 us, of 295 MB 405 and 411, of 393 MB 508 and 495, of 430 MB 596 and 565.
 bool streams_rows(const AttnLaunch& L) {
