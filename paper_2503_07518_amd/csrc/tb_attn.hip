@@ -850,7 +850,8 @@ bool streams_rows(const AttnLaunch& L) {
   if (L.shared_list || g > 4) return false;
   const ListedRows r = listed_rows(g, static_cast<double>(L.max_count + (L.tail_end - L.tail_begin)), static_cast<double>(d.N));
   const double bytes = static_cast<double>(d.B) * d.Hkv * r.distinct * 2 * d.D * (d.dtype == TB_F32 ? 4 : 2);
-  return (L.fresh_lists && bytes >= 100e6 && r.reuse <= kStreamedReuse) || (bytes >= 375e6 && r.reuse <= 1.4);
+  return ((L.fresh_lists && bytes >= 100e6 && r.reuse <= kStreamedReuse) || (bytes >= 375e6 && r.reuse <= 1.4)) && in_device_memory(L.K) &&
+         in_device_memory(L.V);
 }
 
 template <typename T, int D>
@@ -944,7 +945,8 @@ tb_status launch_td(const AttnLaunch& L, hipStream_t st) {
     // (rows that several heads list are kept in the caches for them, as in the migration on its own)
     const GatherLaunch& m = *L.migrate;
     const double listed = static_cast<double>(m.max_count - m.skip_front - m.skip_back);
-    const bool nt = listed_rows(a.g, listed > 1.0 ? listed : 1.0, static_cast<double>(m.desc->N)).reuse <= kStreamedReuse;
+    const bool nt = listed_rows(a.g, listed > 1.0 ? listed : 1.0, static_cast<double>(m.desc->N)).reuse <= kStreamedReuse &&
+                    in_device_memory(m.K) && in_device_memory(m.V);
     if (shares && nt)
       hipLaunchKernelGGL((attn_kernel<T, D, true, true, true, true>), grid, dim3(kAttnThreads), 0, st, a);
     else if (shares)

@@ -103,7 +103,8 @@ tb_status launch_td(const GatherLaunch& L, hipStream_t st) {
   // (at least one workgroup per list, so that count_out is written for an empty one too)
   const int64_t rows = L.max_count > L.skip_front + L.skip_back ? L.max_count - L.skip_front - L.skip_back : 1;
   dim3 grid(static_cast<unsigned>((rows + rows_per_wg - 1) / rows_per_wg), d.Hq, d.B);
-  if (listed_rows(a.g, static_cast<double>(rows), static_cast<double>(d.N)).reuse <= kStreamedReuse)
+  if (listed_rows(a.g, static_cast<double>(rows), static_cast<double>(d.N)).reuse <= kStreamedReuse && in_device_memory(L.K) &&
+      in_device_memory(L.V))
     hipLaunchKernelGGL((gather_kernel<T, D, true>), grid, dim3(kGatherThreads), 0, st, a);
   else
     hipLaunchKernelGGL((gather_kernel<T, D, false>), grid, dim3(kGatherThreads), 0, st, a);

@@ -65,6 +65,10 @@ inline ListedRows listed_rows(int g, double rows, double N) {
 }
 // Readers a row up to which its line is not kept for the next one (non-temporal loads)
 constexpr double kStreamedReuse = 1.3;
+// Whether the rows of a cache are in the memory of a GPU: rows of an offloaded one come over the host link, which any second
+// reader a row is worth keeping lines for (steps of 4 x 32 heads on 8 over pinned host memory, plain and non-temporal loads: 3277 of
+// 32768 rows 3.34 and 3.73 ms, 12288 of 65536 11.1 and 13.7).  Asked at every launch that would read non-temporally, 0.1 us.
+bool in_device_memory(const void* p);
 
 struct ScoreLaunch {
   const tb_cache_desc* desc;

@@ -43,6 +43,15 @@ tb_status launch_read_stream(const void* src, size_t bytes, uint32_t* sink, hipS
   return hip_status(hipGetLastError());
 }
 
+bool in_device_memory(const void* p) {
+  hipPointerAttribute_t at{};
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();  // (not this call's error)
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice;
+}
+
 tb_status launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
   const size_t words = bytes / 4;
   if (words == 0) return TB_OK;

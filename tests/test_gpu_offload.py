@@ -51,3 +51,45 @@ def test_decode_step_with_kv_in_pinned_host_memory(oracle):
     assert np.array_equal(rcnt, np_of(cnt)) and np.array_equal(ridx, np_of(idx)[..., : ridx.shape[-1]])
     rout, rlse = oracle.sparse_decode_attn(np_of(q), Kn, Vn, np_of(idx), np_of(cnt), "bf16", 1.0 / math.sqrt(D))
     assert_attention(np_of(out), rout, "bf16", np_of(lse), rlse)
+
+
+def test_memory_kind_of_a_pointer():
+    """What decides whether rows may be read non-temporally: device memory is told from pinned host memory, and a pointer that the
+    runtime does not know leaves no error behind for the next launch."""
+    print("[case] memory kind of device, pinned and unknown pointers", flush=True)
+    kind = tb.load_library()._ZN2tb16in_device_memoryEPKv
+    kind.restype, kind.argtypes = ctypes.c_bool, [ctypes.c_void_p]
+    on_gpu, pinned, pageable = torch.zeros(1 << 20, device=DEV), torch.zeros(1 << 20, pin_memory=True), np.zeros(1 << 20)
+    assert kind(on_gpu.data_ptr()) and kind(on_gpu.data_ptr() + 4096) and not kind(pinned.data_ptr()) and not kind(pageable.ctypes.data)
+    ws = torch.ones(64, dtype=torch.int32, device=DEV)
+    tb.tb_workspace_init(ws)
+    torch.cuda.synchronize()
+    assert not ws.any()
+
+
+def test_large_lists_and_migration_of_an_offloaded_cache():
+    """Lists of more than 100 MB of rows, and rows that migrate, from pinned host memory and from the GPU's own: the same bits."""
+    B, Hq, Hkv, N, D, k = 4, 16, 8, 8192, 128, 3400
+    print(f"[case] offloaded K/V: large lists and migration B={B} Hq={Hq} Hkv={Hkv} N={N} k={k}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(6)
+    K, V = (torch.randn((B, Hkv, N, D), generator=gen, device=DEV).to(torch.bfloat16) for _ in range(2))
+    hosts = [torch.empty((B, Hkv, N, D), dtype=torch.bfloat16, pin_memory=True).copy_(t) for t in (K, V)]
+    if any(device_address(t) != t.data_ptr() for t in hosts):
+        pytest.skip("pinned host memory is not mapped at the same address for the device on this box")
+    Kimp = torch.randn((B, Hkv, N, 16), generator=gen, device=DEV).to(torch.bfloat16)
+    q, q_imp = (torch.randn((B, Hq, n), generator=gen, device=DEV).to(torch.bfloat16) for n in (D, 16))
+    aK, aV = (torch.randn((B, Hkv, 64, D), generator=gen, device=DEV).to(torch.bfloat16) for _ in range(2))
+    res = []
+    for k_rows, v_rows in ((K, V), hosts):
+        _, idx, cnt, out, lse = gpu_decode_step(q, q_imp, k_rows, v_rows, Kimp, N, k, 0, 0, 0.1)
+        few = torch.full_like(cnt, 1500)
+        src, dst = tb.make_desc(N, Hq, K=k_rows, V=v_rows), tb.make_desc(64, Hq, K=aK, V=aV)
+        bufs = [torch.zeros((B, Hq, 1500, D), dtype=torch.bfloat16, device=DEV) for _ in range(4)]
+        n_out, out2, lse2 = torch.zeros_like(cnt), torch.zeros_like(out), torch.zeros_like(lse)
+        ws = tb.new_workspace(tb.TB_OP_ATTN, dst, 1564)
+        tb.tb_gather_kv(src, k_rows, v_rows, idx, few, 1500, bufs[0], bufs[1])
+        tb.tb_migrate_buffered_decode_attn(src, k_rows, v_rows, idx, few, 1500, 0, 0, n_out, -1, dst, q, bufs[2], bufs[3], aK, aV, 0, 0.1, out2, lse2, ws, 0, 64)
+        torch.cuda.synchronize()
+        assert torch.equal(bufs[0], bufs[2]) and torch.equal(bufs[1], bufs[3])
+        res.append((idx, cnt, out, lse, *bufs[:2], n_out, out2, lse2))
+    assert all(torch.equal(a, b) for a, b in zip(*res))
