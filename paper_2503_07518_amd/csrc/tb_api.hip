@@ -39,7 +39,15 @@ static AttnPlan split_plan(int64_t max_rows, int64_t want, int granule) {
 // been tried, the nearest one stands for them), kSharesAlone on 216 of 4 to 40 heads on 1, 2 or 4 KV heads (0.8% and 7%).  On other
 // shapes, drawn at random: 86 of all kinds 1.0% off the best on average, 13% at most (before kSharesAlone), and against 512 / units 3%
 // faster on average, 4% slower at most without shares; 60 of few KV groups against 512 / units 9% faster on average, none slower.
-AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool shares) {
+// One list for all heads (one_list, for heads that are not on one XCD): split s of head h is on XCD (s + nsplit h) % 8, so that the
+// rows of a split go to one XCD's L2 with a multiple of eight splits, to two with another multiple of four, and to all
+// eight with an odd number.  Only launches of few workgroups (kFewWgs) take numbers that are no multiple of four.  fp32, 9 x 8 heads
+// on 2, D = 64, 5000 rows: 7 splits 35.0 us, 8 19.5; 9 x 16 on 2, 660 rows: 3 19.8, 4 and 8 11.8; bf16, 3 x 32 on 4, 1000 rows: 5 13.7, 4 9.9.
+// 162 such shapes 0.9% off the best number tried on average, 15% at most, kFewWgs chosen on them, 108 others 0.9% and 10%
+// (512 / units 16% on average and 134% at most, without this rule 3% and 89%).  70 shared lists drawn at random: 12% faster than
+// with 512 / units on average, none slower.
+AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool shares, bool one_list) {
+  constexpr int64_t kFewWgs = 144;
   constexpr double kStart = 1.6, kHandOver = 0.1, kAlone = 1.6, kShares = 0.8, kSharesAlone = 0.91;
   if (max_rows <= 0 || units <= 0) return AttnPlan{1, 1, 1, 1};
   const int64_t most = std::max<int64_t>(1, std::min(max_rows / (kAttnMinTiles * tile_rows_per_wg), kAttnMostWgs / units));
@@ -56,19 +64,22 @@ AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool s
       want = n;
     }
   };
-  consider(1);
+  const int64_t step = !one_list || most < 2 ? 1 : (most < 4 ? 2 : 4);
+  consider(step);
   for (int64_t rounds = 1; rounds * kAttnCus <= kAttnMostWgs; ++rounds) {  // as many splits as these rounds hold
     const int64_t n = std::min(rounds * kAttnCus / units, most);
-    if (n > 1) consider(n);
+    if (n > 1 && (step == 1 || units * n <= kFewWgs)) consider(n);
+    if (step > 1 && n > step) consider(n / step * step);
     if (shares && n > kXcds) consider(n / kXcds * kXcds);
   }
   const int granule = tile_rows_per_wg / kAttnLoadsPerTile;
   AttnPlan p = split_plan(max_rows, want, granule);
   // (rounded down, it would not be a number that cuts the list into shares: 8 heads on 1, fp32, 8196 rows 15.2 us with 61 splits,
   // 13.6 with 64; 32 on 4, bf16, 3100 rows 13.5 with 15, 12.4 with 16; 8 on 1, 2050 rows 8.1 and 7.9)
-  if (shares && want % kXcds == 0) {
+  const int64_t multiple = shares && want % kXcds == 0 ? kXcds : (want % step == 0 ? step : 1);
+  if (multiple > 1) {
     p.nsplit = static_cast<int>(want);
-    p.multiple = kXcds;
+    p.multiple = static_cast<int>(multiple);
   }
   p.max_split = static_cast<int>(most);
   p.least = std::min(p.nsplit, split_plan(max_rows, std::min(most, (2 * kAttnCus + units - 1) / units), granule).nsplit);
@@ -84,13 +95,14 @@ static bool fit_splits(const tb_cache_desc* d, AttnPlan& p, size_t ws_bytes) {
   return ws_bytes >= ws_layout(units, d->D, p.least).total;
 }
 // (the buffered form is planned alike, so that it adds up in the same order)
-static AttnPlan attn_plan(const tb_cache_desc* d, int64_t max_rows) {
-  return attn_plan(static_cast<int64_t>(d->B) * d->Hq, max_rows, attn_tile_rows_per_wg(d->dtype, d->D), attn_in_shares(d));
+static AttnPlan attn_plan(const tb_cache_desc* d, int64_t max_rows, bool shared_list = false) {
+  const bool shares = attn_in_shares(d);
+  return attn_plan(static_cast<int64_t>(d->B) * d->Hq, max_rows, attn_tile_rows_per_wg(d->dtype, d->D), shares, shares && shared_list);
 }
 
 AttnPlan attn_group_plan(const tb_cache_desc* d, int64_t max_rows) {
   const int64_t groups = static_cast<int64_t>(d->B) * d->Hkv;
-  if (max_rows <= 0 || groups <= 0 || !attn_group_mfma(d)) return attn_plan(groups, max_rows, attn_tile_rows_per_wg(d->dtype, d->D), false);
+  if (max_rows <= 0 || groups <= 0 || !attn_group_mfma(d)) return attn_plan(groups, max_rows, attn_tile_rows_per_wg(d->dtype, d->D), false, false);
   // On the matrix cores: 8 waves of 32 rows a step, up to one such workgroup per compute unit (the same
   // rows in flight as two of 4 waves, half the partials to combine).  A compute unit holds one of them at D = 128,
   // so a few more than compute units would take a second round (g = 4, D = 128, 3300 rows, attention alone:
@@ -439,7 +451,7 @@ static tb_status sparse_attn(const tb_cache_desc* d, const void* q, const void* 
   if (units == 0) return TB_OK;
   const int64_t rows = max_count + (tail_end - tail_begin);
   const bool grouped = shared_list && attn_shared_list_grouped(d, rows);
-  const AttnPlan by_head = attn_plan(d, rows);
+  const AttnPlan by_head = attn_plan(d, rows, shared_list);
   AttnPlan plan = grouped ? attn_group_plan(d, rows) : by_head;
   if (!ws || !aligned16(ws)) return TB_ERR_WORKSPACE;
   if (grouped && attn_group_mfma(d)) {

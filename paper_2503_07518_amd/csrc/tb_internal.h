@@ -29,7 +29,7 @@ struct AttnPlan {
   int nsplit;     // workgroups per (b,h): the tiles of its list go round them
   int max_split;  // upper bound of nsplit for any list no longer than the one planned for
   int least;      // splits that a workspace has to have room for
-  int multiple;   // of which a smaller workspace leaves a multiple (shares of the list: one per XCD)
+  int multiple;   // of which a smaller workspace leaves a multiple (shares of the list, heads that meet on an XCD)
 };
 
 constexpr int kXcds = 8;  // accelerator complex dies of the chip, each with its own L2
@@ -41,8 +41,8 @@ inline bool attn_on_one_xcd(const tb_cache_desc* d) {
 }
 inline bool attn_in_shares(const tb_cache_desc* d) { return d->Hq > d->Hkv && !attn_on_one_xcd(d); }
 
-// `shares`: splits in multiples of the number of XCDs are one share of the list each
-AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool shares);
+// `shares`: splits in multiples of the number of XCDs are one share of the list each; one_list: all heads read the same list
+AttnPlan attn_plan(int64_t units, int64_t max_rows, int tile_rows_per_wg, bool shares, bool one_list);
 // A shared list's KV groups of four heads and more, bf16, are served on the matrix cores.
 inline bool attn_group_mfma(const tb_cache_desc* d) { return d->dtype == TB_BF16 && d->Hq >= 4 * d->Hkv; }
 AttnPlan attn_group_plan(const tb_cache_desc* d, int64_t max_rows);

@@ -102,15 +102,15 @@ class AttnPlan(ctypes.Structure):
     _fields_ = [(f, ctypes.c_int) for f in ("nsplit", "max_split", "least", "multiple")]
 
 
-def attn_plan(dtype, B, Hq, Hkv, D, rows):
+def attn_plan(dtype, B, Hq, Hkv, D, rows, one_list=False):
     """The library's plan of the attention over up to `rows` rows a head, and whether it cuts the lists into one share per XCD."""
     lib = tb.load_library()
-    plan = lib._ZN2tb9attn_planEllib
-    plan.restype, plan.argtypes = AttnPlan, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_bool]
+    plan = lib._ZN2tb9attn_planEllibb
+    plan.restype, plan.argtypes = AttnPlan, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_bool, ctypes.c_bool]
     groups, f32 = B * Hkv, dtype == torch.float32
-    in_shares = Hq > Hkv and groups % 8 and groups < 64
-    p = plan(B * Hq, rows, lib._ZN2tb21attn_tile_rows_per_wgEii(tb.TB_F32 if f32 else tb.TB_BF16, D), bool(in_shares))
-    return p, bool(in_shares) and p.nsplit % 8 == 0
+    in_shares = bool(Hq > Hkv and groups % 8 and groups < 64)
+    p = plan(B * Hq, rows, lib._ZN2tb21attn_tile_rows_per_wgEii(tb.TB_F32 if f32 else tb.TB_BF16, D), in_shares, in_shares and one_list)
+    return p, in_shares and p.nsplit % 8 == 0
 
 
 def group_plan(dtype, B, Hq, Hkv, D, rows):

@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import (DEV, assert_attention, assert_scores, dtype_name, gpu_attn, gpu_score, gpu_select, np_of,
+from gpu_util import (DEV, assert_attention, assert_scores, attn_plan, dtype_name, gpu_attn, gpu_score, gpu_select, group_plan, np_of,
                       score_magnitude)
 from paper_2503_07518_amd import binding as tb
 
@@ -199,6 +199,25 @@ def test_headless_group_counts(oracle, B, Hkv, g, D, rows):
                                                           cnt[b:b + 1].numpy(), "bf16", sm)
             assert_attention(np_of(out[b:b + 1]), ref, "bf16", np_of(lse[b:b + 1]), r_lse)
         assert bool(torch.isfinite(out).all())
+
+
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,D,rows,splits", [
+    (torch.float32, 9, 16, 2, 128, 660, 8), (torch.bfloat16, 3, 32, 4, 128, 1000, 4), (torch.bfloat16, 9, 16, 2, 64, 1000, 2),
+    (torch.float32, 9, 8, 2, 64, 2990, 8), (torch.float32, 3, 8, 2, 64, 6001, 16), (torch.bfloat16, 1, 8, 4, 64, 1630, 6), (torch.float32, 3, 2, 1, 64, 70, 1)])
+def test_headless_split_counts(oracle, dtype, B, Hq, Hkv, D, rows, splits):
+    """Few KV groups, no workgroup per group: numbers of splits that let an XCD read a part of the list, or any for few workgroups."""
+    plan, _ = attn_plan(dtype, B, Hq, Hkv, D, rows, one_list=True)
+    assert group_plan(dtype, B, Hq, Hkv, D, rows) is None and plan.nsplit == splits, "the plan has changed: these shapes were chosen for theirs"
+    say(f"head-less split counts dtype={dtype} B={B} Hq={Hq} Hkv={Hkv} D={D} rows={rows} splits={splits}")
+    N, gen = rows + 50, torch.Generator().manual_seed(rows)
+    K, V = (torch.randn((B, Hkv, N, D), generator=gen).to(dtype).to(DEV) for _ in range(2))
+    q = torch.randn((B, Hq, D), generator=gen).to(dtype).to(DEV)
+    idx = torch.rand((B, N), generator=gen).topk(rows, dim=-1).indices.sort(-1).values.to(torch.int32).to(DEV)
+    for counts in ((rows,), (rows // 2 + 1, 0, 1), (67, rows - 1)):
+        cnt = torch.tensor([min(counts[b % len(counts)], rows) for b in range(B)], dtype=torch.int32, device=DEV)
+        out, lse = shared_attn(q, K, V, idx, cnt, N, 0.1, rows)
+        ro, rl = oracle.sparse_decode_attn_shared(np_of(q), np_of(K), np_of(V), np_of(idx), np_of(cnt), dtype_name(K), 0.1)
+        assert_attention(np_of(out), ro, dtype_name(K), np_of(lse), rl)
 
 
 @pytest.mark.parametrize("B,Hkv,D,rows,fits", [(38, 8, 64, 2100, 200), (2, 8, 64, 4200, None)])

@@ -115,6 +115,15 @@ def test_attention_plan_of_few_short_lists(tb, f32, B, Hq, Hkv, D, rows, splits)
     assert (p.nsplit, in_shares) == (splits, False)
 
 
+@pytest.mark.parametrize("f32,B,Hq,Hkv,D,rows,splits", [(True, 9, 8, 2, 64, 5000, 16), (True, 20, 8, 1, 64, 1000, 4), (True, 9, 16, 2, 128, 660, 8),
+                                                        (False, 9, 16, 2, 64, 2327, 8), (False, 3, 32, 4, 128, 1000, 4), (True, 3, 32, 4, 128, 400, 4)])
+def test_attention_plan_of_one_list_for_all_heads(tb, f32, B, Hq, Hkv, D, rows, splits):
+    """Heads that read the same list meet on an XCD with a multiple of four splits."""
+    import torch
+    from gpu_util import attn_plan
+    assert attn_plan(torch.float32 if f32 else torch.bfloat16, B, Hq, Hkv, D, rows, one_list=True)[0].nsplit == splits
+
+
 def test_attention_plan_and_workspace(tb):
     """For every length: no more splits than a workspace made for that length has room for, no more asked for than two
     workgroups a compute unit (which every workspace held that was made for as many rows), and from 32 splits on in shares."""
@@ -124,14 +133,14 @@ def test_attention_plan_and_workspace(tb):
         tile = {(torch.bfloat16, 128): 64, (torch.bfloat16, 64): 128, (torch.float32, 128): 32}[dtype, D]
         for B, Hq, Hkv in ((1, 1, 1), (1, 8, 1), (1, 8, 8), (1, 16, 2), (3, 8, 1), (1, 32, 4), (1, 32, 8), (3, 32, 8), (5, 40, 5), (2, 256, 256), (20, 64, 8)):
             units, longest = B * Hq, 0
-            for rows in range(1, 12000, 41):
-                p, in_shares = attn_plan(dtype, B, Hq, Hkv, D, rows)
+            for rows, one_list in ((r, one) for r in range(1, 12000, 41) for one in (False, True)):
+                p, in_shares = attn_plan(dtype, B, Hq, Hkv, D, rows, one_list)
                 before = rounded(rows, max(1, min(-(-512 // units), rows // (2 * tile))), tile // 4)
                 assert 1 <= p.least <= min(p.nsplit, before) and p.nsplit <= p.max_split, (units, rows, tile)
                 assert longest <= p.max_split
                 longest = p.max_split
-                assert p.multiple in (1, 8) and p.nsplit % p.multiple == 0
-                if Hq > Hkv and B * Hkv % 8 and p.nsplit >= 32:
+                assert p.multiple in ((1, 2, 4, 8) if one_list else (1, 8)) and p.nsplit % p.multiple == 0
+                if not one_list and Hq > Hkv and B * Hkv % 8 and p.nsplit >= 32:
                     assert in_shares, (units, rows, tile)
 
 
